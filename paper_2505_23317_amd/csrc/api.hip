@@ -49,13 +49,12 @@ struct cfdetr_ctx {
   int32_t* items = nullptr;   // attention work items, 8 * cap8 entries of four words
   int cap8 = 0;               // entries per queue (one queue per XCD)
   int32_t* queue_heads = nullptr;   // 8 fetch counters per layer, set by the plan kernel
-  int attn_grid = 0;                // workgroups of an attention launch
-  int32_t* m_seen = nullptr;        // pinned host: row totals of earlier runs (merged, fine only), copied back without a wait
+  int attn_grid[2] = {};            // workgroups of an attention launch, for items of 128 / 256 queries
+  int32_t* m_seen = nullptr;        // pinned host: row totals of earlier runs (merged, fine only), written by the plan kernel
   int32_t* n_roi = nullptr;         // regions per frame (scratch of the region proposal)
   int32_t* tok_pad = nullptr;       // padded token table, offsets and true lengths of the
   int32_t* cu_pad = nullptr;        // padded form of the fine pass
   int32_t* kv_len = nullptr;
-  int block_q = 0;
   int32_t* err_flag = nullptr;
   int32_t* vt_pos = nullptr;     // position of every row of the run in vt (first LayerNorm writes it)
   void* tail_packed = nullptr;   // w_o, w_ff1, w_ff2 of every layer in the fused kernel's order
@@ -80,7 +79,7 @@ struct cfdetr_ctx {
   int32_t* dpcu = nullptr;
   int32_t* ditems = nullptr;
   int dcap8 = 0;
-  int dgrid = 0;
+  int dgrid[2] = {};
   void* dmid_packed = nullptr;   // per layer: first out-projection and cross-attention query projection, packed
   void* dk_all = nullptr;     // keys of the tokens for every decoder layer, [L][max_tokens_total, d]
   void* dvt_all = nullptr;    // their values, feature-major, [L][d, vt_ld]
@@ -254,16 +253,39 @@ cfdetr_status embed_level(cfdetr_ctx* ctx, const void* images, int level,
   return CFDETR_OK;
 }
 
-// All layers + final LayerNorm over the tokens in ctx->x.  The sequences are
-// n_prefix coarse grids (n0 tokens each) followed by the B sequences of cu; the
-// plan kernel turns that into ctx->cu_all / ctx->m_all, which every kernel reads
-// on the device.  Output rows below split_row go to y0, the others to y1.
+// What the host knows of an encoder run when it enqueues it.  The launchers choose their
+// tiles, and the attention its items, by the rows they expect.  A coarse-only or padded run has
+// exactly its capacity; otherwise the count is on the device, and the count of the previous
+// run of the same kind (which its plan kernel wrote to pinned memory; nobody waits for it) is a
+// good guess in a stream of frames.
+struct RunShape {
+  int rows = 0;                // 0: nothing known yet
+  int32_t* m_seen = nullptr;   // where the plan kernel leaves the total for the next call
+  int block_q = 128, attn_grid = 0;
+};
+
+enum class RunKind { kMerged = 0, kFine = 1, kExact = 2 };
+
+RunShape run_shape(const cfdetr_ctx* ctx, RunKind kind, int m_cap) {
+  RunShape r;
+  if (kind == RunKind::kExact) {
+    r.rows = m_cap;
+  } else if (ctx->m_seen && ctx->bf16) {
+    r.m_seen = ctx->m_seen + (int)kind;
+    r.rows = *static_cast<volatile int32_t*>(r.m_seen);
+  }
+  const cfdetr_config& c = ctx->cfg;
+  r.block_q = attention_block_q(c.d_model / c.n_heads, ctx->bf16, r.rows, c.n_heads);
+  r.attn_grid = ctx->attn_grid[r.block_q == 256];
+  return r;
+}
+
 // The plan of an encoder run over n_prefix coarse grids followed by the caller's sequences.
-PlanArgs encoder_plan(const cfdetr_ctx* ctx, int n_prefix) {
+PlanArgs encoder_plan(const cfdetr_ctx* ctx, int n_prefix, const RunShape& shape) {
   PlanArgs p{};
   p.n_prefix = n_prefix;
   p.prefix_len = ctx->n0;
-  p.block_q = ctx->block_q;
+  p.block_q = shape.block_q;
   p.heads = ctx->cfg.n_heads;
   p.items = ctx->items;
   p.cap8 = ctx->cap8;
@@ -272,41 +294,26 @@ PlanArgs encoder_plan(const cfdetr_ctx* ctx, int n_prefix) {
   p.pcu = ctx->pcu;
   p.queue_heads = ctx->queue_heads;
   p.n_heads_q = 8 * ctx->cfg.n_layers;
-  p.queue_start = ctx->attn_grid / 8;
+  p.queue_start = shape.attn_grid / 8;
+  p.m_seen = shape.m_seen;
   return p;
 }
 
-cfdetr_status run_encoder(cfdetr_ctx* ctx, const int32_t* cu, int B, int n_prefix, int m_cap,
-                          float* y0, int split_row, float* y1, hipStream_t s,
-                          const int32_t* kv_len = nullptr, bool plan_done = false) {
+// All layers + final LayerNorm over the tokens in ctx->x.  The sequences are
+// n_prefix coarse grids (n0 tokens each) followed by B sequences of the caller's; the
+// plan kernel, launched before, has turned that into ctx->cu_all / ctx->m_all, which every
+// kernel reads on the device.  Output rows below split_row go to y0, the others to y1.
+cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int m_cap, float* y0,
+                          int split_row, float* y1, hipStream_t s, const int32_t* kv_len = nullptr) {
   const cfdetr_config& c = ctx->cfg;
   const cfdetr_weights& w = ctx->w;
   const int d = c.d_model, F = c.d_ffn;
   const size_t es = ctx->esz;
   const float eps = c.ln_eps;
   const bool bf = ctx->bf16;
-  const int nseq = n_prefix + B;
   const int32_t* cu_all = ctx->cu_all;
   const int32_t* m_ptr = ctx->m_all;
-  // The contraction launchers choose their tiles by the rows they expect.  The count of this
-  // run is on the device; the count of the previous run of the same kind (copied back
-  // without waiting for it) is a good guess in a stream of frames.  A coarse-only run has
-  // exactly its capacity.
-  int m_hint = 0;
-  int32_t* m_seen = nullptr;
-  if (cu == ctx->coarse_cu && n_prefix == 0) {
-    m_hint = m_cap;
-  } else if (ctx->m_seen && bf && !(gemm_residual_ln_supported(d, bf) && ctx->tail_packed_layer != 0)) {
-    m_seen = ctx->m_seen + (n_prefix > 0 ? 0 : kv_len ? 2 : 1);
-    m_hint = *static_cast<volatile int32_t*>(m_seen);
-  }
-  if (!plan_done)   // (the selection kernel of a merged run has made the plan already)
-    CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, encoder_plan(ctx, n_prefix), s,
-                                         m_cap - n_prefix * ctx->n0, 0, ctx->err_flag));
-  if (m_seen) {
-    hipError_t e = hipMemcpyAsync(m_seen, ctx->m_all, 4, hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return fail_hip(ctx, "copy of the row count", e);
-  }
+  const int m_hint = shape.rows;
   // Where a workgroup can own whole rows, the residual contractions also apply the
   // LayerNorm that follows them, and only the very first one is a launch of its own.
   const bool fused_ln = gemm_residual_ln_supported(d, bf);
@@ -345,7 +352,7 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, const int32_t* cu, int B, int n_prefi
                                           s));
     CF_LAUNCH(CFDETR_K_ATTN,
               launch_attention(ctx->qkv, ctx->vt, ctx->vt_ld, ctx->o, d, c.n_heads, ctx->items, ctx->cap8, ctx->queue_heads + 8 * l,
-                               ctx->attn_grid, ctx->block_q, bf, kv_len, s));
+                               shape.attn_grid, shape.block_q, bf, kv_len, s));
     if (fused_tail) {
       // out-projection, LayerNorm, feed-forward block and the LayerNorm after it (the next
       // layer's first one, or the final one) in one kernel
@@ -420,7 +427,9 @@ cfdetr_status coarse_impl(cfdetr_ctx* ctx, const void* images, int B, float* x0_
   cfdetr_status st = embed_level(ctx, images, 0, ctx->coarse_desc, ctx->coarse_cu, B, ctx->x,
                                  x0_out, nullptr, M, M, s);
   if (st != CFDETR_OK) return st;
-  return run_encoder(ctx, ctx->coarse_cu, B, 0, M, y_coarse, 0, nullptr, s);
+  const RunShape shape = run_shape(ctx, RunKind::kExact, M);
+  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(ctx->coarse_cu, B, encoder_plan(ctx, 0, shape), s, M, 0, ctx->err_flag));
+  return run_encoder(ctx, B, shape, M, y_coarse, 0, nullptr, s);
 }
 
 cfdetr_status select_impl(cfdetr_ctx* ctx, const int32_t* boxes, const uint8_t* tier,
@@ -465,10 +474,11 @@ cfdetr_status fine_impl(cfdetr_ctx* ctx, const void* images, int B, const int32_
   // the capacity empties the run and raises the error flag), and every kernel after it,
   // the embedding included, reads the checked copy.
   const int cap = ctx->cfg.max_tokens_total;
-  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, encoder_plan(ctx, 0), s, cap, 0, ctx->err_flag));
+  const RunShape shape = run_shape(ctx, RunKind::kFine, cap);
+  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, encoder_plan(ctx, 0, shape), s, cap, 0, ctx->err_flag));
   cfdetr_status st = fine_embed(ctx, images, B, tok_desc, ctx->cu_all, x0_cache, 0, s);
   if (st != CFDETR_OK) return st;
-  return run_encoder(ctx, ctx->cu_all, B, 0, cap, y_mixed, 0, nullptr, s, nullptr, true);
+  return run_encoder(ctx, B, shape, cap, y_mixed, 0, nullptr, s);
 }
 
 // A3 as the paper states it: every frame's token set brought to t_pad tokens (repeats of
@@ -478,13 +488,15 @@ cfdetr_status padded_impl(cfdetr_ctx* ctx, const void* images, int B, const int3
                           const int32_t* cu, const float* x0_cache, int t_pad, float* y_padded,
                           hipStream_t s) {
   // the caller's offsets are checked first (as in fine_impl); the padding reads the checked copy
-  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, encoder_plan(ctx, 0), s, ctx->cfg.max_tokens_total, 0,
-                                       ctx->err_flag));
+  const RunShape shape = run_shape(ctx, RunKind::kExact, B * t_pad);
+  const PlanArgs plan = encoder_plan(ctx, 0, shape);
+  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, plan, s, ctx->cfg.max_tokens_total, 0, ctx->err_flag));
   CF_LAUNCH(CFDETR_K_SELECT, launch_pad_tokens(tok_desc, ctx->cu_all, B, t_pad, ctx->tok_pad,
                                                ctx->cu_pad, ctx->kv_len, ctx->err_flag, s));
   cfdetr_status st = fine_embed(ctx, images, B, ctx->tok_pad, ctx->cu_pad, x0_cache, 0, s);
   if (st != CFDETR_OK) return st;
-  return run_encoder(ctx, ctx->cu_pad, B, 0, B * t_pad, y_padded, 0, nullptr, s, ctx->kv_len);
+  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(ctx->cu_pad, B, plan, s, B * t_pad, 0, ctx->err_flag));
+  return run_encoder(ctx, B, shape, B * t_pad, y_padded, 0, nullptr, s, ctx->kv_len);
 }
 
 // Decoder over the encoded tokens `memory` of B frames (Sec. II-A).  The token side (bf16
@@ -498,11 +510,13 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
   const int Mq = B * Q, cap_m = c.max_tokens_total;
   const float eps = c.ln_eps;
   const float qs = attention_q_scale(d / c.n_heads);
+  const int dblock_q = attention_block_q(d / c.n_heads, true, Mq, c.n_heads);
+  const int dgrid = ctx->dgrid[dblock_q == 256];
   // token sequences: offsets, total and padded offsets (the work list is not used).  The
   // offsets are the caller's: the plan checks them, and after an error the second plan
   // hands the attention kernels no work.
   {
-    PlanArgs p = encoder_plan(ctx, 0);
+    PlanArgs p = encoder_plan(ctx, 0, RunShape{});
     p.n_heads_q = 8;
     CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, p, s, cap_m, 1, ctx->err_flag, nullptr));
   }
@@ -510,7 +524,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
   // query sequences: B times Q rows, work list for both attentions of every layer
   {
     PlanArgs p{};
-    p.block_q = ctx->block_q;
+    p.block_q = dblock_q;
     p.heads = c.n_heads;
     p.items = ctx->ditems;
     p.cap8 = ctx->dcap8;
@@ -519,7 +533,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
     p.pcu = ctx->dpcu;
     p.queue_heads = ctx->dqueue;
     p.n_heads_q = 16 * L;
-    p.queue_start = ctx->dgrid / 8;
+    p.queue_start = dgrid / 8;
     CF_LAUNCH(CFDETR_K_PLAN, launch_plan(ctx->dcu, B, p, s, 0, 0, nullptr, ctx->err_flag));
   }
   CF_LAUNCH(CFDETR_K_DEC, launch_broadcast_rows(w.query_embed, ctx->dx, Q, d, B, s));
@@ -559,7 +573,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
     }
     CF_LAUNCH(CFDETR_K_ATTN,
               launch_attention(ctx->dqkv, ctx->dvt, ctx->dvt_ld, ctx->d_o, d, c.n_heads, ctx->ditems, ctx->dcap8, ctx->dqueue + 16 * l,
-                               ctx->dgrid, ctx->block_q, true, nullptr, s));
+                               dgrid, dblock_q, true, nullptr, s));
     // cross-attention: the queries read the tokens of their frame
     if (fused) {
       // first out-projection, LayerNorm and the query projection in one kernel
@@ -583,7 +597,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
                                      static_cast<const bf16_t*>(ctx->dvt_all) + l * v_stride,
                                      ctx->vt_ld, ctx->d_o,
                                      ctx->cu_all, ctx->pcu, d, c.n_heads, ctx->ditems,
-                                     ctx->dcap8, ctx->dqueue + 16 * l + 8, ctx->dgrid, s));
+                                     ctx->dcap8, ctx->dqueue + 16 * l + 8, dgrid, dblock_q, s));
     if (fused) {
       LayerTailArgs ta{};
       ta.O = ctx->d_o;
@@ -653,13 +667,13 @@ cfdetr_status merged_impl(cfdetr_ctx* ctx, const void* images, int B, const int3
                                  ctx->x0, nullptr, Mc, Mc, s);
   if (st != CFDETR_OK) return st;
   // the selection also plans the run over the B coarse grids and the B mixed sets
-  const PlanArgs plan = encoder_plan(ctx, B);
+  const RunShape shape = run_shape(ctx, RunKind::kMerged, Mc + ctx->cfg.max_tokens_total);
+  const PlanArgs plan = encoder_plan(ctx, B, shape);
   st = select_impl(ctx, boxes, tier, box_offsets, B, tok_desc, cu_seqlens, level_counts, s, &plan);
   if (st != CFDETR_OK) return st;
   st = fine_embed(ctx, images, B, tok_desc, cu_seqlens, ctx->x0, Mc, s);
   if (st != CFDETR_OK) return st;
-  return run_encoder(ctx, cu_seqlens, B, B, Mc + ctx->cfg.max_tokens_total, y_coarse, Mc,
-                     y_mixed, s, nullptr, true);
+  return run_encoder(ctx, 2 * B, shape, Mc + ctx->cfg.max_tokens_total, y_coarse, Mc, y_mixed, s);
 }
 
 }  // namespace
@@ -704,18 +718,19 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   c->n0 = p.rows[0] * p.cols[0];
   c->nonfinest = 0;
   for (int l = 0; l + 1 < cfg->n_levels; ++l) c->nonfinest += p.rows[l] * p.cols[l];
-  c->block_q = attention_block_q();
   // Activation buffers hold one merged run: max_batch coarse grids + the mixed sets.
   c->tok_cap = (uint64_t)cfg->max_tokens_total + (uint64_t)cfg->max_batch * c->n0;
   {
     // Query tiles of a whole run, and of its longest possible sequence; an XCD never
     // gets more than (all items)/8 + (tiles of the longest sequence) work items.
-    const int tiles_all = (int)((c->tok_cap + c->block_q - 1) / c->block_q) + 2 * cfg->max_batch;
+    const int bq = 128;   // the smallest items there are
+    const int tiles_all = (int)((c->tok_cap + bq - 1) / bq) + 2 * cfg->max_batch;
     const int longest = std::max(cfg->max_tokens_total, c->n0);
-    c->cap8 = (tiles_all * cfg->n_heads + 7) / 8 + (longest + c->block_q - 1) / c->block_q;
+    c->cap8 = (tiles_all * cfg->n_heads + 7) / 8 + (longest + bq - 1) / bq;
   }
-  c->attn_grid = attention_grid(cfg->d_model / cfg->n_heads, c->bf16, c->cap8);
-  if (c->attn_grid < 8) {
+  for (int i = 0; i < 2; ++i)
+    c->attn_grid[i] = attention_grid(cfg->d_model / cfg->n_heads, c->bf16, 128 << i, c->cap8);
+  if (c->attn_grid[0] < 8 || c->attn_grid[1] < 8) {
     delete c;
     return fail_create(CFDETR_EDEVICE, "cannot size the attention grid for this device");
   }
@@ -756,10 +771,10 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
     return fail_create(CFDETR_ENOMEM, std::string("hipMalloc of the work space: ") +
                                           hipGetErrorString(e));
   }
-  // three pinned words for row counts that come back from the device without a wait; the
+  // two pinned words for row counts that come back from the device without a wait; the
   // library works without them (tiles are then chosen for the capacity)
-  if (hipHostMalloc(reinterpret_cast<void**>(&c->m_seen), 3 * sizeof(int32_t), hipHostMallocDefault) == hipSuccess)
-    c->m_seen[0] = c->m_seen[1] = c->m_seen[2] = 0;
+  if (hipHostMalloc(reinterpret_cast<void**>(&c->m_seen), 2 * sizeof(int32_t), hipHostMallocDefault) == hipSuccess)
+    c->m_seen[0] = c->m_seen[1] = 0;
   else
     c->m_seen = nullptr;
   char* base = static_cast<char*>(c->arena);
@@ -1051,10 +1066,11 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
   const uint64_t Bm = c.max_batch, Q = w->n_queries, d = c.d_model, F = c.d_ffn;
   const uint64_t Mq = Bm * Q;
   // query tiles of a whole run; per queue at most all/8 + those of one sequence
-  const int tiles_seq = (int)((Q + ctx->block_q - 1) / ctx->block_q);
+  const int tiles_seq = (int)((Q + 127) / 128);
   ctx->dcap8 = (int)((Bm * tiles_seq * c.n_heads + 7) / 8) + tiles_seq;
-  ctx->dgrid = attention_grid(c.d_model / c.n_heads, true, ctx->dcap8);
-  if (ctx->dgrid < 8) return fail(ctx, CFDETR_EDEVICE, "cannot size the attention grid");
+  for (int i = 0; i < 2; ++i)
+    ctx->dgrid[i] = attention_grid(c.d_model / c.n_heads, true, 128 << i, ctx->dcap8);
+  if (ctx->dgrid[0] < 8 || ctx->dgrid[1] < 8) return fail(ctx, CFDETR_EDEVICE, "cannot size the attention grid");
   ctx->dvt_ld = (int)(Bm * ((Q + 63) & ~uint64_t(63)) + 64);
   Carver cv;
   const uint64_t o_x = cv.take(Mq * d * 4), o_a = cv.take(Mq * d * 2), o_qkv = cv.take(Mq * 3 * d * 2);

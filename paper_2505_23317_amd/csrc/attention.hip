@@ -2,10 +2,10 @@
 // every token of its own frame; A3, Sec. III-B: several frames in one batch).
 // Frames are addressed by offsets, so no padding token is ever computed.
 //
-// bf16 kernel, flash style.  A work item is 128 queries of one (frame, head); each of
-// the four wavefronts of a workgroup owns 32 of them.  Keys/values are walked in tiles
-// of 64 that go from global memory straight into LDS (global_load_lds,
-// double-buffered, one barrier per tile).  Everything is computed transposed so that
+// bf16 kernel, flash style.  A work item is 128 (or 256) queries of one (frame, head); each
+// of the four wavefronts of a workgroup owns 32 (or 64) of them.  Keys/values are walked in
+// tiles of 64 that go from global memory straight into LDS (global_load_lds, a ring of three
+// tiles, one wait and one barrier per tile).  Everything is computed transposed so that
 // a query is a LANE:
 //   S^T[key, q] = K . Q^T          (MFMA A = K rows from LDS, B = Q rows in registers)
 //   O^T[dh, q] += V^T . P^T        (MFMA A = V^T rows from LDS, B = P from registers)
@@ -23,6 +23,24 @@
 // unpadded; 16-byte chunks are XOR-swizzled by row so that operand reads of 16
 // consecutive rows hit disjoint banks.
 //
+// What bounds the loop is that its parts depend on each other: the logits of a tile, their
+// exponentials, the product with the values.  One after the other they leave the matrix unit
+// idle through the exponentials and the vector unit idle through the MFMAs, and neither
+// LDS nor occupancy makes up for it (the kernel that did so, with four wavefronts per SIMD,
+// had the matrix unit busy 43 % of a launch, and at one wavefront per SIMD a 64-key tile took
+// 0.93 us).  So the loop is a software pipeline over units of 32 keys: while the exponentials
+// of unit u are worked out, the MFMAs of two other units run, the values of unit u - 1 and the
+// logits of unit u + 1, in one fixed instruction order: an MFMA, then its share of two
+// exponentials, two additions and a convert (32 clocks of the one beside about 34 of the
+// others).  Measured, before -> after: one 4000-token frame of 6 heads of 64, 65.5 -> 43 us; 920
+// tokens 17.9 -> 13 us; 24 470 tokens in 8 frames 149 -> 135 us; 8 x (1600 + 6400) tokens 488 ->
+// 420 us (1.27 PFLOP/s, matrix unit busy 64 % at the 1.85 GHz that the load leaves).
+//
+// 64 queries per wavefront (head width 64 only) feed two MFMAs from every operand read, so LDS
+// traffic per FLOP halves, but take 256 registers (two wavefronts per SIMD) and make items of
+// 256 queries: the better form once there is far more work than the chip holds at once
+// (attention_block_q).  Every query's arithmetic is the same in both, to the bit.
+//
 // Softmax arithmetic per element is one exp2, one add and half a convert: q arrives
 // multiplied by log2(e)/sqrt(dh), so S is a base-2 logit, and the probabilities are taken as
 // 2^S, relative to the reference 0 and not to a running maximum: O / l is the same quotient
@@ -30,8 +48,8 @@
 // no maximum has to be tracked, compared or applied.  What a fixed reference cannot do is
 // stay inside the exponent range: when a query's sum of probabilities ends outside
 // [2^-64, 2^100] (or is no number), some probability that matters may have been flushed to
-// zero or have overflowed; the workgroup then walks the item's keys again, once for the
-// largest logit of every query and once with the probabilities relative to it, which is
+// zero or have overflowed; such queries are computed again (exact_queries), with a walk for
+// their largest logit and one with the probabilities relative to it, which is
 // exact for any logits.  Trained or randomly initialised weights do not get there (|S| of
 // a few tens); the parity tests force it.
 //
@@ -54,12 +72,12 @@ namespace cfdetr {
 namespace {
 
 constexpr int kBlockKV = 64;
+constexpr int kWavesPerGroup = 4;
 // sums of probabilities (relative to the reference 0) outside this range send an item
 // through the exact walk: below, probabilities that matter may have been flushed to zero
 // (normal numbers end at 2^-126; 2^24 flushed ones add up to less than 2^-100); above, one
 // may have overflowed
 constexpr float kSumLow = 0x1p-64f, kSumHigh = 0x1p+100f;
-constexpr int kFast = 0, kScan = 1, kExact = 2;
 
 __device__ __forceinline__ int swap_bits_2_3(int i) {
   return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1);
@@ -70,27 +88,6 @@ __device__ __forceinline__ int swap_bits_2_3(int i) {
 template <int ROWB>
 __device__ __forceinline__ int swz(int r) {
   return ROWB == 128 ? ((r >> 1) & 7) : ((r >> 2) & 3);
-}
-
-// p = 2^s for the 32 logits of a lane, packed to bf16 MFMA operands; returns their sum.
-__device__ __forceinline__ float exp_tile(const f32x16 (&s)[2], bf16x8 (&pf)[2][2]) {
-  float psum = 0.f;
-#pragma unroll
-  for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      uint32_t w[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float p0 = __builtin_amdgcn_exp2f(s[sub][8 * t + 2 * e]);
-        const float p1 = __builtin_amdgcn_exp2f(s[sub][8 * t + 2 * e + 1]);
-        psum += p0 + p1;
-        w[e] = pack_bf16x2(p0, p1);
-      }
-      uint4 packed = make_uint4(w[0], w[1], w[2], w[3]);
-      pf[sub][t] = *reinterpret_cast<bf16x8*>(&packed);
-    }
-  return psum;
 }
 
 // One 16-byte piece per lane from global memory straight into LDS (1 KB per wavefront at
@@ -109,7 +106,7 @@ __device__ __forceinline__ void attn_dma16(const void* sbase, uint32_t voff, uin
 // costs the kernel an occupancy step (the loop's register budget is what sets it).
 template <int DH>
 __device__ __attribute__((noinline)) void clear_v_padding(unsigned char* wV, int nvalid, int tid) {
-  for (int u = tid; u < DH * 8; u += 256) {
+  for (int u = tid; u < DH * 8; u += 64 * kWavesPerGroup) {
     const int rho = u >> 3, c = u & 7;   // row (feature), logical chunk of 8 keys
     const int n = nvalid - 8 * c;        // keys of this chunk inside the sequence
     if (n < 8) {
@@ -124,28 +121,128 @@ __device__ __attribute__((noinline)) void clear_v_padding(unsigned char* wV, int
   }
 }
 
+// The exact walk of 32 queries per wavefront (see above), for an item whose sums left the safe
+// range: the largest logit of every query, then the probabilities relative to it; only the
+// queries with `redo` set are written.  Everything is fetched again; this is the rare path and
+// it is a function of its own, so that the registers of the fast path are not its business.
 template <int DH>
-__global__ __launch_bounds__(256) void attention_bf16_kernel(
+__device__ __attribute__((noinline)) void exact_queries(
+    const bf16_t* q_row, const bf16_t* kbase, int k_ld, const bf16_t* vbase, int vt_ld, int TK,
+    bf16_t* orow, bool redo, unsigned char* smem) {
+  constexpr int KS = DH / 16, MO = DH / 32, KROWB = DH * 2, KCPR = KROWB / 16;
+  unsigned char* const sK = smem;
+  unsigned char* const sV = smem + kBlockKV * KROWB;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+  const int n_kv = (TK + kBlockKV - 1) / kBlockKV;
+  bf16x8 qf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(q_row + ks * 16 + g * 8);
+  f32x16 acc_o[MO];
+#pragma unroll
+  for (int i = 0; i < MO; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc_o[i][r] = 0.f;
+  float m_ref = -INFINITY, l_run = 0.f;
+#pragma nounroll
+  for (int pass = 0; pass < 2; ++pass) {
+#pragma nounroll
+    for (int it = 0; it < n_kv; ++it) {
+      const int kv0 = it * kBlockKV;
+      __syncthreads();
+      for (int u = tid; u < kBlockKV * KCPR; u += 64 * kWavesPerGroup) {
+        const int rho = u / KCPR, c = u % KCPR;
+        const int key = min(kv0 + ((rho & 32) | swap_bits_2_3(rho & 31)), TK - 1);
+        *reinterpret_cast<uint4*>(sK + rho * KROWB + ((c ^ swz<KROWB>(rho)) << 4)) =
+            *reinterpret_cast<const uint4*>(kbase + (size_t)key * k_ld + c * 8);
+      }
+      if (pass == 1)
+        for (int u = tid; u < DH * 8; u += 64 * kWavesPerGroup) {
+          const int rho = u >> 3, c = u & 7;
+          *reinterpret_cast<uint4*>(sV + rho * 128 + ((c ^ swz<128>(rho)) << 4)) =
+              *reinterpret_cast<const uint4*>(vbase + (size_t)rho * vt_ld + kv0 + c * 8);
+        }
+      __syncthreads();
+      if (pass == 1 && kv0 + kBlockKV > TK) {
+        clear_v_padding<DH>(sV, TK - kv0, tid);
+        __syncthreads();
+      }
+#pragma unroll
+      for (int sub = 0; sub < 2; ++sub) {
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        const int rho = sub * 32 + l32;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              *reinterpret_cast<const bf16x8*>(sK + rho * KROWB + (((2 * ks + g) ^ swz<KROWB>(rho)) << 4)),
+              qf[ks], s, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (kv0 + sub * 32 + 16 * (r >> 3) + 8 * g + (r & 7) >= TK) s[r] = -INFINITY;
+        if (pass == 0) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) m_ref = fmaxf(m_ref, s[r]);
+          continue;
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          uint32_t w[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float p0 = __builtin_amdgcn_exp2f(s[8 * t + 2 * e] - m_ref);
+            const float p1 = __builtin_amdgcn_exp2f(s[8 * t + 2 * e + 1] - m_ref);
+            l_run += p0 + p1;
+            w[e] = pack_bf16x2(p0, p1);
+          }
+          uint4 packed = make_uint4(w[0], w[1], w[2], w[3]);
+          const bf16x8 pf = *reinterpret_cast<bf16x8*>(&packed);
+#pragma unroll
+          for (int i = 0; i < MO; ++i) {
+            const int rv = i * 32 + l32;
+            acc_o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                *reinterpret_cast<const bf16x8*>(sV + rv * 128 + (((4 * sub + 2 * t + g) ^ swz<128>(rv)) << 4)),
+                pf, acc_o[i], 0, 0, 0);
+          }
+        }
+      }
+    }
+    if (pass == 0) m_ref = fmaxf(m_ref, __shfl_xor(m_ref, 32, kWave));
+  }
+  __syncthreads();
+  const float inv = 1.0f / (l_run + __shfl_xor(l_run, 32, kWave));
+  if (redo) {
+#pragma unroll
+    for (int i = 0; i < MO; ++i)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq)
+        *reinterpret_cast<uint2*>(orow + i * 32 + rq * 8 + g * 4) =
+            make_uint2(pack_bf16x2(acc_o[i][4 * rq] * inv, acc_o[i][4 * rq + 1] * inv),
+                       pack_bf16x2(acc_o[i][4 * rq + 2] * inv, acc_o[i][4 * rq + 3] * inv));
+  }
+}
+
+// QB: blocks of 32 queries per wavefront.  The second launch bound holds the compiler to the
+// registers of two (64 queries), three or (head width 32) four wavefronts per SIMD.
+template <int DH, int QB>
+__global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4) void attention_bf16_kernel(
     const bf16_t* __restrict__ qbuf, int q_ld, const bf16_t* __restrict__ kbuf, int k_ld,
     const bf16_t* __restrict__ vt, int vt_ld, bf16_t* __restrict__ out,
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ pcu_k, int d,
     const int4* __restrict__ items, int cap8, int32_t* __restrict__ queue_heads,
     const int32_t* __restrict__ kv_len) {
-  constexpr int BQ = 128;
+  constexpr int NW = kWavesPerGroup;
+  constexpr int BQ = 32 * QB * NW;
   constexpr int KS = DH / 16;          // k-steps of Q.K^T
   constexpr int MO = DH / 32;          // 32-row blocks of O^T
   constexpr int KROWB = DH * 2;        // bytes per K row in LDS
   constexpr int KCPR = KROWB / 16;     // chunks per K row
   constexpr int KRPI = 1024 / KROWB;   // K rows per wave load instruction
-  constexpr int KI = kBlockKV / KRPI / 4;   // K load instructions per wavefront
-  constexpr int VI = DH / 8 / 4;            // V^T load instructions per wavefront (8 rows each)
-  constexpr int KBYTES = kBlockKV * KROWB, VBYTES = DH * 128;
-  // One array per buffer and operand: the compiler then knows that a tile being
-  // filled is not the tile being read, and does not wait for the fill before the reads.
-  __shared__ __attribute__((aligned(1024))) unsigned char sK0[KBYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char sK1[KBYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char sV0[VBYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char sV1[VBYTES];
+  constexpr int KI = kBlockKV / KRPI / NW;   // K load instructions per wavefront
+  constexpr int VI = DH / 8 / NW;            // V^T load instructions per wavefront (8 rows each)
+  constexpr int KBYTES = kBlockKV * KROWB, VBYTES = DH * 128, TILE = KBYTES + VBYTES;
+  constexpr int NB = 3;                // ring of key tiles
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NB * TILE];
   __shared__ int32_t s_item;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -173,8 +270,13 @@ __global__ __launch_bounds__(256) void attention_bf16_kernel(
     const int rho = (wave * VI + j) * 8 + (lane >> 3);
     v_off[j] = ((uint32_t)rho * (uint32_t)vt_ld + (uint32_t)(((lane & 7) ^ swz<128>(rho)) * 8)) * 2u;
   }
-  const uint32_t lds_k0 = (uint32_t)(uintptr_t)sK0, lds_k1 = (uint32_t)(uintptr_t)sK1;
-  const uint32_t lds_v0 = (uint32_t)(uintptr_t)sV0, lds_v1 = (uint32_t)(uintptr_t)sV1;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+  // operand addresses inside a tile: row l32 of a 32-row block, chunk swizzled
+  uint32_t ka[KS], va[4];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) ka[ks] = l32 * KROWB + (((2 * ks + g) ^ swz<KROWB>(l32)) << 4);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) va[c] = KBYTES + l32 * 128 + (((2 * c + g) ^ swz<128>(l32)) << 4);
 
   for (;;) {
     // An entry is four words: the item, then offset, length and padded offset of its
@@ -195,171 +297,252 @@ __global__ __launch_bounds__(256) void attention_bf16_kernel(
     const int TK = kv_len ? min(kv_len[frame], TKall) : TKall;
     const bf16_t* qbase = qbuf + (size_t)seq0 * q_ld + head * DH;
     const bf16_t* kbase = kbuf + (size_t)kseq0 * k_ld + head * DH;
-
-    // Q operands: lane = query, 8 consecutive dh per k-step.
-    bf16x8 qf[KS];
-    {
-      const int q_load = min(qt * BQ + wave * 32 + l32, T - 1);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        qf[ks] = *reinterpret_cast<const bf16x8*>(qbase + (size_t)q_load * q_ld + ks * 16 + g * 8);
-    }
     const bf16_t* vbase = vt + (size_t)(head * DH) * vt_ld + kpad0;
-
-    // Fill of the tile that starts at key kv0_: inside the sequence the lane offsets are the
-    // constants above; the last, ragged tile clamps its keys to the sequence (the lanes that
-    // would read past it fetch the last key again; their logits are masked).
-#define CFDETR_ATTN_ISSUE(kv0_, buf_)                                                        \
-  do {                                                                                       \
-    const bf16_t* kb_ = kbase + (size_t)(kv0_) * k_ld;                                       \
-    const uint32_t lk_ = ((buf_) ? lds_k1 : lds_k0) + wave * (KI * 1024);                    \
-    if ((kv0_) + kBlockKV <= TK) {                                                           \
-      _Pragma("unroll") for (int j = 0; j < KI; ++j) attn_dma16(kb_, k_off[j], lk_ + j * 1024); \
-    } else {                                                                                 \
-      _Pragma("unroll") for (int j = 0; j < KI; ++j) {                                       \
-        const int rho = (wave * KI + j) * KRPI + lane / KCPR;                                \
-        const int key = min((rho & 32) | swap_bits_2_3(rho & 31), TK - 1 - (kv0_));          \
-        attn_dma16(kb_, (uint32_t)key * (uint32_t)(k_ld * 2) +                               \
-                            (uint32_t)(((lane % KCPR) ^ swz<KROWB>(rho)) * 16), lk_ + j * 1024); \
-      }                                                                                      \
-    }                                                                                        \
-    const bf16_t* vb_ = vbase + (kv0_);                                                      \
-    const uint32_t lv_ = ((buf_) ? lds_v1 : lds_v0) + wave * (VI * 1024);                    \
-    _Pragma("unroll") for (int j = 0; j < VI; ++j) attn_dma16(vb_, v_off[j], lv_ + j * 1024); \
-  } while (0)
-
-    // One walk over the key tiles of the item.  kFast: probabilities relative to the
-    // reference 0.  kScan: only the largest logit of every query.  kExact: probabilities
-    // relative to m_ref (that largest logit).  All wavefronts of the workgroup take the same
-    // walks (the tiles and the barriers are shared).
-    f32x16 acc_o[MO];
-    float l_run = 0.f;    // sum of the probabilities of this lane's keys
-    float m_ref = 0.f;
     const int n_kv = (TK + kBlockKV - 1) / kBlockKV;
-    auto walk = [&](auto mode_tag) {
-      constexpr int kMode = decltype(mode_tag)::value;
-      float smax = -INFINITY;
-      if (kMode != kScan) {
-        l_run = 0.f;
-#pragma unroll
-        for (int i = 0; i < MO; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc_o[i][r] = 0.f;
-      }
-      CFDETR_ATTN_ISSUE(0, 0);
-      for (int it0 = 0; it0 < n_kv; it0 += 2) {
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {   // buffer index: a constant after unrolling
-          const int it = it0 + b;
-          if (it >= n_kv) break;
-          const int kv0 = it * kBlockKV;
-          // vmcnt(0): this wavefront's part of tile `it` is in LDS; the barrier publishes
-          // every wavefront's part and retires all reads of the other buffer.
-          __builtin_amdgcn_s_waitcnt(0x0F70);
-          __syncthreads();
-          if (it + 1 < n_kv) CFDETR_ATTN_ISSUE(kv0 + kBlockKV, b ^ 1);
-          const unsigned char* cK = b ? sK1 : sK0;
-          const unsigned char* cV = b ? sV1 : sV0;
-          if (kMode != kScan && kv0 + kBlockKV > TK) {
-            // Last, ragged tile (no fill is in flight any more): the V^T positions past the
-            // end of the sequence are padding that nothing in this run wrote.  They only
-            // meet probabilities that are exactly 0, but 0 * NaN is NaN, so they are cleared
-            // here: whatever an earlier run left there cannot reach a result.
-            clear_v_padding<DH>(b ? sV1 : sV0, TK - kv0, tid);
-            __syncthreads();
-          }
 
-          // S^T for the two 32-key sub-tiles; keys past the end of the frame (last tile
-          // only) get -inf.
-          f32x16 s[2];
+    // Fill of tile j_: inside the sequence the lane offsets are the constants above; the
+    // last, ragged tile clamps its keys to the sequence (the lanes that would read past it
+    // fetch the last key again; their logits are masked).
+    auto issue = [&](int j_, int slot_) {
+      const int kv0_ = j_ * kBlockKV;
+      const bf16_t* kb_ = kbase + (size_t)kv0_ * k_ld;
+      const uint32_t lb_ = lds0 + slot_ * TILE;
+      const uint32_t lk_ = lb_ + wave * (KI * 1024), lv_ = lb_ + KBYTES + wave * (VI * 1024);
+      if (kv0_ + kBlockKV <= TK) {
 #pragma unroll
-          for (int sub = 0; sub < 2; ++sub) {
-            const int rho = sub * 32 + l32;
+        for (int j = 0; j < KI; ++j) attn_dma16(kb_, k_off[j], lk_ + j * 1024);
+      } else {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-              const bf16x8 kf = *reinterpret_cast<const bf16x8*>(
-                  cK + rho * KROWB + (((2 * ks + g) ^ swz<KROWB>(rho)) << 4));
-              s[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s[sub], 0, 0, 0);
-            }
-          }
-          if (kv0 + kBlockKV > TK) {
-            asm volatile("" ::: "memory");   // keeps this a branch: one tile per item comes here
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                const int key = kv0 + sub * 32 + 16 * (r >> 3) + 8 * g + (r & 7);
-                if (key >= TK) s[sub][r] = -INFINITY;
-              }
-          }
-          if (kMode == kScan) {
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) smax = fmaxf(smax, s[sub][r]);
-            continue;
-          }
-          if (kMode == kExact) {
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) s[sub][r] -= m_ref;
-          }
-          bf16x8 pf[2][2];
-          l_run += exp_tile(s, pf);
-          // O^T += V^T . P^T
-#pragma unroll
-          for (int i = 0; i < MO; ++i) {
-            const int rho = i * 32 + l32;
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-              for (int t = 0; t < 2; ++t) {
-                const bf16x8 vf = *reinterpret_cast<const bf16x8*>(
-                    cV + rho * 128 + (((4 * sub + 2 * t + g) ^ swz<128>(rho)) << 4));
-                acc_o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[sub][t], acc_o[i], 0, 0, 0);
-              }
-          }
+        for (int j = 0; j < KI; ++j) {
+          const int rho = (wave * KI + j) * KRPI + lane / KCPR;
+          const int key = min((rho & 32) | swap_bits_2_3(rho & 31), TK - 1 - kv0_);
+          attn_dma16(kb_, (uint32_t)key * (uint32_t)(k_ld * 2) +
+                              (uint32_t)(((lane % KCPR) ^ swz<KROWB>(rho)) * 16), lk_ + j * 1024);
         }
       }
-      return smax;
+      const bf16_t* vb_ = vbase + kv0_;
+#pragma unroll
+      for (int j = 0; j < VI; ++j) attn_dma16(vb_, v_off[j], lv_ + j * 1024);
     };
 
-    walk(std::integral_constant<int, kFast>{});
-    float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
-    // A sum that left the range in which every probability that matters is a normal number
-    // (some logit beyond +-100 or so in base 2; also inf and NaN): find every query's
-    // largest logit first and take the probabilities relative to it.
-    if (__syncthreads_or(!(l_tot >= kSumLow && l_tot <= kSumHigh))) {
-      const float smax = walk(std::integral_constant<int, kScan>{});
-      m_ref = fmaxf(smax, __shfl_xor(smax, 32, kWave));
-      __syncthreads();   // every wavefront is done with the last tile of the scan
-      walk(std::integral_constant<int, kExact>{});
-      l_tot = l_run + __shfl_xor(l_run, 32, kWave);
+    issue(0, 0);
+    // Q operands: lane = query, 8 consecutive dh per k-step.
+    bf16x8 qf[QB][KS];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const int q_load = min(qt * BQ + (wave * QB + qb) * 32 + l32, T - 1);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        qf[qb][ks] = *reinterpret_cast<const bf16x8*>(qbase + (size_t)q_load * q_ld + ks * 16 + g * 8);
     }
-#undef CFDETR_ATTN_ISSUE
-
-    const float inv = 1.0f / l_tot;
-    const int q_local = qt * BQ + wave * 32 + l32;
-    if (q_local < T) {
-      bf16_t* orow = out + (size_t)(seq0 + q_local) * d + head * DH;
+    f32x16 acc_o[QB][MO];
+    float l_run[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      l_run[qb] = 0.f;
 #pragma unroll
       for (int i = 0; i < MO; ++i)
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-          // registers 4*rq..4*rq+3 of lane group g are dh = 32*i + 8*rq + 4*g + 0..3
-          uint2 w;
-          w.x = pack_bf16x2(acc_o[i][4 * rq] * inv, acc_o[i][4 * rq + 1] * inv);
-          w.y = pack_bf16x2(acc_o[i][4 * rq + 2] * inv, acc_o[i][4 * rq + 3] * inv);
-          *reinterpret_cast<uint2*>(orow + i * 32 + rq * 8 + g * 4) = w;
-        }
+        for (int r = 0; r < 16; ++r) acc_o[qb][i][r] = 0.f;
     }
-    // the next entry; the barriers also keep the next item's first fill behind every
-    // wavefront's last reads of this one's tiles
-    if (drained) break;
+    bf16x8 kf[KS], vf[MO][2];
+    bf16x8 pA[QB][2], pB[QB][2];
+    f32x16 sA[QB], sB[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pB[qb][t][e] = (__bf16)0.f;
+
+    auto read_k = [&](const unsigned char* tile, int sub) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        kf[ks] = *reinterpret_cast<const bf16x8*>(tile + ka[ks] + sub * (32 * KROWB));
+    };
+    auto read_v = [&](const unsigned char* tile, int sub) {
+#pragma unroll
+      for (int i = 0; i < MO; ++i)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          vf[i][t] = *reinterpret_cast<const bf16x8*>(tile + va[2 * sub + t] + i * (32 * 128));
+    };
+    auto qk1 = [&](f32x16(&s)[QB], int m) {   // MFMA m of the first product
+      const int ks = m / QB, qb = m % QB;
+      if (ks == 0) {
+        f32x16 z;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z[r] = 0.f;
+        s[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[qb][ks], z, 0, 0, 0);
+      } else {
+        s[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[qb][ks], s[qb], 0, 0, 0);
+      }
+    };
+    auto pv1 = [&](bf16x8(&p)[QB][2], int m) {   // MFMA m of the second product
+      const int qb = m % QB, i = (m / QB) % MO, t = m / QB / MO;
+      acc_o[qb][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i][t], p[qb][t], acc_o[qb][i], 0, 0, 0);
+    };
+    auto mask = [&](f32x16(&s)[QB], int key0) {
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (key0 + 16 * (r >> 3) + 8 * g + (r & 7) >= TK) s[qb][r] = -INFINITY;
+    };
+    // One stage: on the matrix unit the values of unit u - 1 (operands in vf) and then the
+    // logits of unit u + 1 (keys read here, from ktile), between them the exponentials of
+    // unit u: behind every MFMA its share of that arithmetic and of the LDS reads, in an order
+    // the compiler is not to change.  The values of unit u are read behind the first product.
+    auto stage = [&](f32x16(&s)[QB], f32x16(&sn)[QB], bf16x8(&pc)[QB][2], bf16x8(&pp)[QB][2],
+                     const unsigned char* ktile, int ksub, const unsigned char* vtile, int vsub,
+                     auto more_tag) {
+      constexpr bool kMore = decltype(more_tag)::value;   // there is a unit u + 1
+      constexpr int NQK = QB * KS, NPV = QB * 2 * MO, NM = NQK + NPV;
+      constexpr int PAIRS = QB * 8, PPM = PAIRS / NM;
+      static_assert(PAIRS % NM == 0, "exponentials per MFMA");
+      uint32_t w[QB][8];
+      float e0 = 0.f, e1 = 0.f;
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        if (m < NPV) {
+          pv1(pp, m);
+          if (kMore && m < KS) kf[m] = *reinterpret_cast<const bf16x8*>(ktile + ka[m] + ksub * (32 * KROWB));
+        } else {
+          if (kMore) qk1(sn, m - NPV);
+          if (m - NPV < 2 * MO) {
+            const int t_ = (m - NPV) / MO, i_ = (m - NPV) % MO;
+            vf[i_][t_] = *reinterpret_cast<const bf16x8*>(vtile + va[2 * vsub + t_] + i_ * (32 * 128));
+          }
+        }
+#pragma unroll
+        for (int x = m * PPM; x < (m + 1) * PPM; ++x) {
+          const int qb = x / 8, e = x % 8;
+          // sum and conversion of the pair before: its exponentials have left the
+          // transcendental pipe by now
+          if (x > 0) {
+            const int qy = (x - 1) / 8;
+            l_run[qy] += e0 + e1;
+            w[qy][(x - 1) % 8] = pack_bf16x2(e0, e1);
+            asm volatile("" : "+v"(w[qy][(x - 1) % 8]), "+v"(l_run[qy]));
+          }
+          e0 = __builtin_amdgcn_exp2f(s[qb][2 * e]);
+          e1 = __builtin_amdgcn_exp2f(s[qb][2 * e + 1]);
+          asm volatile("" : "+v"(e0), "+v"(e1));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      l_run[QB - 1] += e0 + e1;
+      w[QB - 1][7] = pack_bf16x2(e0, e1);
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+        for (int t_ = 0; t_ < 2; ++t_) {
+          uint4 packed = make_uint4(w[qb][4 * t_], w[qb][4 * t_ + 1], w[qb][4 * t_ + 2], w[qb][4 * t_ + 3]);
+          pc[qb][t_] = *reinterpret_cast<bf16x8*>(&packed);
+        }
+    };
+
+    // Tile j sits in slot j % 3.  The fills are waited for once per tile, between its two
+    // units: tile j + 1 is then in LDS and every wavefront is past its last read of tile
+    // j - 1, whose slot tile j + 2 takes.
+    __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
+    if (n_kv > 1) issue(1, 1);
+    else if (TK < kBlockKV) {
+      clear_v_padding<DH>(smem + KBYTES, TK, tid);
+      __syncthreads();
+    }
+    read_k(smem, 0);
+#pragma unroll
+    for (int m = 0; m < QB * KS; ++m) qk1(sA, m);
+    read_v(smem, 0);   // (in front of the first unit: met with probabilities 0)
+    const unsigned char* tcur = smem;
+    int slot = 0;
+    const auto yes = std::integral_constant<bool, true>{};
+    const auto no = std::integral_constant<bool, false>{};
+    // Three tiles at a time have constant slots, which makes every LDS address a lane constant
+    // plus an immediate (with the slot in a register the additions are 8 % of a tile's vector
+    // instructions); what is left over, and a ragged tile's padding, take the general form.
+    auto tile_step = [&](int j, auto slot_tag) {
+      constexpr int kSlot = decltype(slot_tag)::value, kNext = (kSlot + 1) % NB;
+      const unsigned char* cur = smem + kSlot * TILE;
+      const unsigned char* next = smem + kNext * TILE;
+      stage(sA, sB, pA, pB, cur, 1, cur, 0, yes);    // unit 2j
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      __syncthreads();
+      issue(j + 2, (kSlot + 2) % NB);
+      stage(sB, sA, pB, pA, next, 0, cur, 1, yes);   // unit 2j + 1
+    };
+    int j = 0;
+    for (; j + 5 <= n_kv; j += 3) {
+      tile_step(j, std::integral_constant<int, 0>{});
+      tile_step(j + 1, std::integral_constant<int, 1>{});
+      tile_step(j + 2, std::integral_constant<int, 2>{});
+    }
+    for (; j < n_kv - 1; ++j) {
+      stage(sA, sB, pA, pB, tcur, 1, tcur, 0, yes);    // unit 2j
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      __syncthreads();
+      const int snext = slot == NB - 1 ? 0 : slot + 1;
+      const unsigned char* tnext = smem + snext * TILE;
+      if (j + 2 < n_kv) {
+        issue(j + 2, snext == NB - 1 ? 0 : snext + 1);
+      } else if (TK & (kBlockKV - 1)) {
+        clear_v_padding<DH>(smem + snext * TILE + KBYTES, TK - (j + 1) * kBlockKV, tid);
+        __syncthreads();
+      }
+      stage(sB, sA, pB, pA, tnext, 0, tcur, 1, yes);   // unit 2j + 1
+      tcur = tnext;
+      slot = snext;
+    }
+    {
+      // the last tile, ragged or not
+      const int kv0 = (n_kv - 1) * kBlockKV;
+      if (TK & (kBlockKV - 1)) mask(sA, kv0);
+      stage(sA, sB, pA, pB, tcur, 1, tcur, 0, yes);
+      if (TK & (kBlockKV - 1)) mask(sB, kv0 + 32);
+      stage(sB, sA, pB, pA, tcur, 0, tcur, 1, no);
+#pragma unroll
+      for (int m = 0; m < QB * 2 * MO; ++m) pv1(pB, m);
+    }
+
+    bool redo[QB], any = false;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const float l_tot = l_run[qb] + __shfl_xor(l_run[qb], 32, kWave);
+      redo[qb] = !(l_tot >= kSumLow && l_tot <= kSumHigh);
+      any |= redo[qb];
+      const float inv = 1.0f / l_tot;
+      const int q_local = qt * BQ + (wave * QB + qb) * 32 + l32;
+      if (q_local < T) {
+        bf16_t* orow = out + (size_t)(seq0 + q_local) * d + head * DH;
+#pragma unroll
+        for (int i = 0; i < MO; ++i)
+#pragma unroll
+          for (int rq = 0; rq < 4; ++rq) {
+            // registers 4*rq..4*rq+3 of lane group g are dh = 32*i + 8*rq + 4*g + 0..3
+            uint2 w;
+            w.x = pack_bf16x2(acc_o[qb][i][4 * rq] * inv, acc_o[qb][i][4 * rq + 1] * inv);
+            w.y = pack_bf16x2(acc_o[qb][i][4 * rq + 2] * inv, acc_o[qb][i][4 * rq + 3] * inv);
+            *reinterpret_cast<uint2*>(orow + i * 32 + rq * 8 + g * 4) = w;
+          }
+      }
+    }
+    // A sum that left the range in which every probability that matters is a normal number
+    // (some logit beyond +-100 or so in base 2; also inf and NaN): those queries are computed
+    // again relative to their largest logit.  The barrier keeps the next item's first fill
+    // behind every wavefront's last reads of this one's tiles.
+    if (__syncthreads_or(any)) {
+#pragma nounroll
+      for (int qb = 0; qb < QB; ++qb) {
+        const int q_local = qt * BQ + (wave * QB + qb) * 32 + l32;
+        const bool again = QB == 1 ? redo[0] : (qb == 0 ? redo[0] : redo[QB - 1]);
+        exact_queries<DH>(qbase + (size_t)min(q_local, T - 1) * q_ld, kbase, k_ld, vbase, vt_ld, TK,
+                              out + (size_t)(seq0 + min(q_local, T - 1)) * d + head * DH,
+                              again && q_local < T, smem);
+      }
+    }
+    if (drained) break;
     if (tid == 0) s_item = atomicAdd(&queue_heads[home], 1);
     __syncthreads();
     entry = __builtin_amdgcn_readfirstlane(s_item);
@@ -434,7 +617,15 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(
 
 }  // namespace
 
-int attention_block_q() { return 128; }
+
+// Queries per work item.  64 queries per wavefront win where the wavefronts of 32 would be
+// more than the chip works on at once, with room for the coarser items' uneven end: at 2500 to
+// 2800 of them 32 queries are 7 to 9 % faster (74 against 79 us, 32 against 35), at 4600 64
+// queries are 5 % and at 16000 8 % faster (141 -> 135, 454 -> 420).  At head width 32 the
+// exponentials bind whatever the LDS traffic is, and the small form is never slower.
+int attention_block_q(int d_head, bool use_bf16, int64_t rows, int heads) {
+  return use_bf16 && d_head == 64 && rows * heads > (int64_t)3500 * 32 ? 256 : 128;
+}
 
 float attention_q_scale(int d_head) {
   return 1.44269504088896340736f / sqrtf((float)d_head);
@@ -448,45 +639,63 @@ int resident_grid(K kern) {
   int dev = 0, cus = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, 0) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64 * kWavesPerGroup, 0) != hipSuccess) return 0;
   if (cus <= 0 || per_cu <= 0) return 0;
   return (cus * per_cu + 7) & ~7;
 }
 
 }  // namespace
 
-int attention_grid(int d_head, bool use_bf16, int cap8) {
+int attention_grid(int d_head, bool use_bf16, int block_q, int cap8) {
   const long all = 8L * cap8;
   if (!use_bf16) return (int)all;
   int resident = 0;
-  if (d_head == 64) resident = resident_grid(attention_bf16_kernel<64>);
-  else if (d_head == 32) resident = resident_grid(attention_bf16_kernel<32>);
+  if (d_head == 64 && block_q == 256) resident = resident_grid(attention_bf16_kernel<64, 2>);
+  else if (d_head == 64) resident = resident_grid(attention_bf16_kernel<64, 1>);
+  else if (d_head == 32) resident = resident_grid(attention_bf16_kernel<32, 1>);
   if (resident <= 0) return 0;
   return (int)(all < resident ? all : resident);
 }
 
+namespace {
+
+// The bf16 kernel for a head width and item size; false: there is none.
+bool launch_bf16(int dh, int block_q, int grid_size, hipStream_t s, const bf16_t* q, int q_ld,
+                 const bf16_t* k, int k_ld, const bf16_t* v, int vt_ld, bf16_t* out,
+                 const int32_t* cu_k, const int32_t* pcu_k, int d, const int4* recs, int cap8,
+                 int32_t* queue_heads, const int32_t* kv_len) {
+  const dim3 grid(grid_size), block(64 * kWavesPerGroup);
+  if (dh == 64 && block_q == 256)
+    hipLaunchKernelGGL((attention_bf16_kernel<64, 2>), grid, block, 0, s, q, q_ld, k, k_ld, v, vt_ld,
+                       out, cu_k, pcu_k, d, recs, cap8, queue_heads, kv_len);
+  else if (dh == 64 && block_q == 128)
+    hipLaunchKernelGGL((attention_bf16_kernel<64, 1>), grid, block, 0, s, q, q_ld, k, k_ld, v, vt_ld,
+                       out, cu_k, pcu_k, d, recs, cap8, queue_heads, kv_len);
+  else if (dh == 32 && block_q == 128)
+    hipLaunchKernelGGL((attention_bf16_kernel<32, 1>), grid, block, 0, s, q, q_ld, k, k_ld, v, vt_ld,
+                       out, cu_k, pcu_k, d, recs, cap8, queue_heads, kv_len);
+  else
+    return false;
+  return true;
+}
+
+}  // namespace
+
 hipError_t launch_attention(const void* qkv, const void* vt, int vt_ld, void* out, int d, int heads,
                             const int32_t* items, int cap8, int32_t* queue_heads, int grid_size,
                             int block_q, bool use_bf16, const int32_t* kv_len, hipStream_t s) {
-  if (block_q != 128 || grid_size < 8 || grid_size % 8 != 0 || grid_size > 8 * cap8)
-    return hipErrorInvalidValue;
+  if (grid_size < 8 || grid_size % 8 != 0 || grid_size > 8 * cap8) return hipErrorInvalidValue;
   const int dh = d / heads;
   const int4* recs = reinterpret_cast<const int4*>(items);
   if (use_bf16) {
+    // queries and keys are thirds of the same rows
     const bf16_t* in = static_cast<const bf16_t*>(qkv);
-    const bf16_t* v = static_cast<const bf16_t*>(vt);
-    bf16_t* o = static_cast<bf16_t*>(out);
-    dim3 grid(grid_size);
-    // self-attention: queries and keys are thirds of the same rows
-    if (dh == 64)
-      hipLaunchKernelGGL(attention_bf16_kernel<64>, grid, dim3(256), 0, s, in, 3 * d, in + d, 3 * d,
-                         v, vt_ld, o, nullptr, nullptr, d, recs, cap8, queue_heads, kv_len);
-    else if (dh == 32)
-      hipLaunchKernelGGL(attention_bf16_kernel<32>, grid, dim3(256), 0, s, in, 3 * d, in + d, 3 * d,
-                         v, vt_ld, o, nullptr, nullptr, d, recs, cap8, queue_heads, kv_len);
-    else
+    if (!launch_bf16(dh, block_q, grid_size, s, in, 3 * d, in + d, 3 * d, static_cast<const bf16_t*>(vt),
+                     vt_ld, static_cast<bf16_t*>(out), nullptr, nullptr, d, recs, cap8, queue_heads,
+                     kv_len))
       return hipErrorInvalidValue;
   } else {
+    if (block_q != 128) return hipErrorInvalidValue;
     const float scale = 1.0f / sqrtf((float)dh);
     dim3 grid(8 * cap8);
     const float* in = static_cast<const float*>(qkv);
@@ -506,22 +715,13 @@ hipError_t launch_attention(const void* qkv, const void* vt, int vt_ld, void* ou
 hipError_t launch_cross_attention(const void* q, const void* k, const void* vt, int vt_ld,
                                   void* out, const int32_t* cu_k,
                                   const int32_t* pcu_k, int d, int heads, const int32_t* items,
-                                  int cap8, int32_t* queue_heads, int grid_size, hipStream_t s) {
+                                  int cap8, int32_t* queue_heads, int grid_size, int block_q,
+                                  hipStream_t s) {
   if (grid_size < 8 || grid_size % 8 != 0 || grid_size > 8 * cap8) return hipErrorInvalidValue;
-  const int dh = d / heads;
-  const int4* recs = reinterpret_cast<const int4*>(items);
-  const bf16_t* qb = static_cast<const bf16_t*>(q);
-  const bf16_t* kb = static_cast<const bf16_t*>(k);
-  const bf16_t* v = static_cast<const bf16_t*>(vt);
-  bf16_t* o = static_cast<bf16_t*>(out);
-  dim3 grid(grid_size);
-  if (dh == 64)
-    hipLaunchKernelGGL(attention_bf16_kernel<64>, grid, dim3(256), 0, s, qb, d, kb, d, v, vt_ld, o,
-                       cu_k, pcu_k, d, recs, cap8, queue_heads, nullptr);
-  else if (dh == 32)
-    hipLaunchKernelGGL(attention_bf16_kernel<32>, grid, dim3(256), 0, s, qb, d, kb, d, v, vt_ld, o,
-                       cu_k, pcu_k, d, recs, cap8, queue_heads, nullptr);
-  else
+  if (!launch_bf16(d / heads, block_q, grid_size, s, static_cast<const bf16_t*>(q), d,
+                   static_cast<const bf16_t*>(k), d, static_cast<const bf16_t*>(vt), vt_ld,
+                   static_cast<bf16_t*>(out), cu_k, pcu_k, d, reinterpret_cast<const int4*>(items), cap8,
+                   queue_heads, nullptr))
     return hipErrorInvalidValue;
   return hipGetLastError();
 }

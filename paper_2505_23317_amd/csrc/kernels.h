@@ -18,6 +18,7 @@ struct PlanArgs {
   int32_t* pcu;
   int32_t* queue_heads;
   int n_heads_q, queue_start;
+  int32_t* m_seen;   // may be null: pinned host word that gets the total, for later calls
 };
 
 // ---- A2 selection (select.hip) -------------------------------------------
@@ -271,11 +272,13 @@ hipError_t launch_attention(const void* qkv, const void* vt, int vt_ld, void* ou
 hipError_t launch_cross_attention(const void* q, const void* k, const void* vt, int vt_ld,
                                   void* out, const int32_t* cu_k,
                                   const int32_t* pcu_k, int d, int heads, const int32_t* items,
-                                  int cap8, int32_t* queue_heads, int grid_size, hipStream_t s);
+                                  int cap8, int32_t* queue_heads, int grid_size, int block_q,
+                                  hipStream_t s);
+// Queries per work item (plan and kernels), for about that many query rows: 128 or 256.  A
+// query's result is the same, bit for bit, either way.
+int attention_block_q(int d_head, bool use_bf16, int64_t rows, int heads);
 // Grid of launch_attention on the current device: a multiple of 8, at most 8*cap8;
 // 0 if the device cannot be queried.
-int attention_grid(int d_head, bool use_bf16, int cap8);
-// Queries per work item of both attention kernels.
-int attention_block_q();
+int attention_grid(int d_head, bool use_bf16, int block_q, int cap8);
 
 }  // namespace cfdetr

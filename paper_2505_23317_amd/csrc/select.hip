@@ -113,6 +113,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& p, int nseq, const int
     p.cu_all[nseq] = pos;
     p.pcu[nseq] = ppos;
     *p.m_all = pos;
+    if (p.m_seen != nullptr) *p.m_seen = pos;
   }
   __syncthreads();
   for (int G = tid; G < ngroups; G += blockDim.x) {   // one thread per group
