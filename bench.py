@@ -99,9 +99,9 @@ def cpu_baseline(cfg, wl, cfg_id, single_thread=False, budget_s=10.0):
 
 # kernel family of the profile interface -> names it may have in the counter summary (the
 # fused kernels of width 256 first: where they run, the separate ones do not)
-TRAFFIC_FAMILY = {"attention": ["attention"], "qkv": ["layer_head", "gemm_qkv"],
+TRAFFIC_FAMILY = {"attention": ["attention"], "qkv": ["layer_head", "wide_head", "gemm_qkv"],
                   "ffn1": ["gemm_ffn1_gelu"], "out_proj": ["gemm_out_proj"],
-                  "ffn2": ["layer_tail", "gemm_ffn2"], "layernorm": ["layernorm"],
+                  "ffn2": ["layer_tail", "wide_layer", "gemm_ffn2"], "layernorm": ["layernorm"],
                   "embed": ["embed"], "gather": ["gather_coarse"]}
 
 
@@ -127,10 +127,10 @@ def hbm_traffic(cfg_id, family):
 # kernel family -> pattern of its kernel names in the rocprofv3 kernel statistics
 STATS_FAMILY = {
     "attention": r"attention_bf16_kernel",
-    "qkv": r"EpiQkv|layer_head_kernel",
+    "qkv": r"EpiQkv|layer_head_kernel|wide_layer_kernel<384, ., 0>",
     "ffn1": r"EpiAct<unsigned short, (true|1)>",
     "out_proj": r"EpiResidual",
-    "ffn2": r"layer_tail_kernel|EpiResidual",
+    "ffn2": r"layer_tail_kernel|wide_layer_kernel<384, ., [12]>|EpiResidual",
     "layernorm": r"layernorm",
     "embed": r"EpiEmbed|gemm_bf16_gather_kernel",
     "gather": r"gather_coarse_kernel",

@@ -60,6 +60,10 @@ struct cfdetr_ctx {
   void* tail_packed = nullptr;   // w_o, w_ff1, w_ff2 of every layer in the fused kernel's order
   uint64_t tail_packed_layer = 0;   // bytes per layer; 0: the shape has no fused kernel
   void* head_packed = nullptr;      // w_qkv of the first layer in the same layout
+  void* wide_packed = nullptr;      // the same for width 384 (layer.hip)
+  uint64_t wide_layer = 0;
+  void* wide_head = nullptr;
+  int cus = 256;                    // compute units of the device
 
   // decoder (cfdetr_decoder_attach): its own allocation
   bool has_dec = false;
@@ -318,6 +322,47 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
   // LayerNorm that follows them, and only the very first one is a launch of its own.
   const bool fused_ln = gemm_residual_ln_supported(d, bf);
   const bool fused_tail = fused_ln && ctx->tail_packed_layer != 0;
+  if (ctx->wide_layer) {
+    // width 384: one kernel ahead of the loop and one behind each attention
+    const int mt = wide_layer_tiles(shape.rows ? shape.rows : m_cap, ctx->cus);
+    WideLayerArgs wa{};
+    wa.packed = ctx->wide_head;
+    wa.resid = ctx->x;
+    wa.ln_g = w.ln1_g;
+    wa.ln_b = w.ln1_b;
+    wa.eps = eps;
+    wa.b_qkv = w.b_qkv;
+    wa.q_scale = attention_q_scale(d / c.n_heads);
+    wa.qk = ctx->qkv;
+    wa.vt = ctx->vt;
+    wa.vt_ld = ctx->vt_ld;
+    wa.vt_pos = ctx->vt_pos;
+    wa.cu = cu_all;
+    wa.pcu = ctx->pcu;
+    wa.B = nseq;
+    CF_LAUNCH(CFDETR_K_QKV, launch_wide_layer(wa, d, F, mt, m_ptr, 0, m_cap, s));
+    wa.O = ctx->o;
+    wa.out = y0;
+    wa.split_row = split_row;
+    wa.out2 = y1;
+    for (int l = 0; l < c.n_layers; ++l) {
+      CF_LAUNCH(CFDETR_K_ATTN,
+                launch_attention(ctx->qkv, ctx->vt, ctx->vt_ld, ctx->o, d, c.n_heads, ctx->items, ctx->cap8, ctx->queue_heads + 8 * l,
+                                 shape.attn_grid, shape.block_q, bf, kv_len, s));
+      wa.last = l + 1 == c.n_layers;
+      wa.packed = static_cast<const char*>(ctx->wide_packed) + (size_t)l * ctx->wide_layer;
+      wa.b_o = w.b_o + (size_t)l * d;
+      wa.ln2_g = w.ln2_g + (size_t)l * d;
+      wa.ln2_b = w.ln2_b + (size_t)l * d;
+      wa.b_ff1 = w.b_ff1 + (size_t)l * F;
+      wa.b_ff2 = w.b_ff2 + (size_t)l * d;
+      wa.ln_g = wa.last ? w.lnf_g : w.ln1_g + (size_t)(l + 1) * d;
+      wa.ln_b = wa.last ? w.lnf_b : w.ln1_b + (size_t)(l + 1) * d;
+      wa.b_qkv = wa.last ? nullptr : w.b_qkv + (size_t)(l + 1) * 3 * d;
+      CF_LAUNCH(CFDETR_K_FF2, launch_wide_layer(wa, d, F, mt, m_ptr, 0, m_cap, s));
+    }
+    return CFDETR_OK;
+  }
   for (int l = 0; l < c.n_layers; ++l) {
     const char* wqkv = static_cast<const char*>(w.w_qkv) + (size_t)l * 3 * d * d * es;
     const char* wo = static_cast<const char*>(w.w_o) + (size_t)l * d * d * es;
@@ -698,6 +743,11 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   cfdetr_ctx* c = new (std::nothrow) cfdetr_ctx();
   if (!c) return fail_create(CFDETR_ENOMEM, "host allocation failed");
   c->cfg = *cfg;
+  if (int dev = 0; hipGetDevice(&dev) != hipSuccess ||
+                   hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+    delete c;
+    return fail_create(CFDETR_EDEVICE, "cannot read the number of compute units");
+  }
   c->w = *w;
   c->bf16 = cfg->act_dtype == CFDETR_BF16;
   c->esz = c->bf16 ? 2 : 4;
@@ -764,6 +814,10 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
     c->tail_packed_layer = layer_tail_packed_bytes((int)d, (int)F);
   const uint64_t o_pack = cv.take(c->tail_packed_layer * cfg->n_layers);
   const uint64_t o_hpack = cv.take(c->tail_packed_layer ? 3 * d * d * 2 : 0);
+  if (wide_layer_supported((int)d, (int)F, c->bf16, Tm))
+    c->wide_layer = wide_layer_packed_bytes((int)d, (int)F, false);
+  const uint64_t o_wide = cv.take(c->wide_layer * cfg->n_layers);
+  const uint64_t o_whead = cv.take(c->wide_layer ? wide_layer_packed_bytes((int)d, (int)F, true) : 0);
   c->arena_bytes = cv.off;
   e = hipMalloc(&c->arena, c->arena_bytes);
   if (e != hipSuccess) {
@@ -806,6 +860,8 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   c->kv_len = reinterpret_cast<int32_t*>(base + o_kvlen);
   c->tail_packed = base + o_pack;
   c->head_packed = base + o_hpack;
+  c->wide_packed = base + o_wide;
+  c->wide_head = base + o_whead;
 
   // static tables: coarse grid descriptors, zeroed counters, position tables
   std::vector<int32_t> desc(Bm * c->n0), cu(Bm + 1);
@@ -837,6 +893,16 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
         nullptr);
   if (e == hipSuccess && c->tail_packed_layer)
     e = launch_layer_head_pack(w->w_qkv, (int)d, c->head_packed, nullptr);
+  for (int l = 0; l < cfg->n_layers && e == hipSuccess && c->wide_layer; ++l)
+    e = launch_wide_pack(
+        static_cast<const char*>(w->w_o) + (size_t)l * d * d * 2,
+        static_cast<const char*>(w->w_ff1) + (size_t)l * F * d * 2,
+        static_cast<const char*>(w->w_ff2) + (size_t)l * d * F * 2,
+        l + 1 < cfg->n_layers ? static_cast<const char*>(w->w_qkv) + (size_t)(l + 1) * 3 * d * d * 2
+                              : nullptr,
+        (int)d, (int)F, static_cast<char*>(c->wide_packed) + (size_t)l * c->wide_layer, nullptr);
+  if (e == hipSuccess && c->wide_layer)
+    e = launch_wide_pack(nullptr, nullptr, nullptr, w->w_qkv, (int)d, (int)F, c->wide_head, nullptr);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     if (c->m_seen) hipHostFree(c->m_seen);

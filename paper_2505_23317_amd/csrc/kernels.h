@@ -225,6 +225,40 @@ hipError_t launch_layer_head(const float* x, const void* packed, const float* ln
                              int B, int d, const int32_t* m_ptr, int m_host, int m_capacity,
                              hipStream_t s);
 
+// The same for width 384 (layer.hip), the first layer's LayerNorm and projection included:
+// LayerTailArgs' fields, with O null for that first launch.  It lists the rows' places in vt
+// (vt_pos), which the layers' launches read.  `mt`: 32-row tiles per workgroup (1 to 3, all
+// with the same results); wide_layer_tiles chooses it for the rows expected.
+struct WideLayerArgs {
+  const void* O;
+  const void* packed;   // launch_wide_pack's
+  const float *b_o, *ln2_g, *ln2_b, *b_ff1, *b_ff2;
+  float* resid;
+  const float *ln_g, *ln_b;
+  float eps;
+  bool last;
+  float* out;
+  int split_row;
+  float* out2;
+  const float* b_qkv;
+  float q_scale;
+  void* qk;
+  void* vt;
+  int vt_ld;
+  int32_t* vt_pos;
+  const int32_t* cu;
+  const int32_t* pcu;
+  int B;
+};
+bool wide_layer_supported(int d, int F, bool use_bf16, uint64_t rows);
+int wide_layer_tiles(int rows, int cus);
+uint64_t wide_layer_packed_bytes(int d, int F, bool head);
+// Wo, W1 and W2 null: the first launch's; Wqkv (the next layer's) null: the last layer's.
+hipError_t launch_wide_pack(const void* Wo, const void* W1, const void* W2, const void* Wqkv, int d,
+                            int F, void* packed, hipStream_t s);
+hipError_t launch_wide_layer(const WideLayerArgs& a, int d, int F, int mt, const int32_t* m_ptr,
+                             int m_host, int m_capacity, hipStream_t s);
+
 // Between the decoder's two attentions, in the same style (width 256, bf16): the output
 // projection of the first with its residual, the LayerNorm behind it and the query
 // projection of the second:  resid[M,d] += O . Wo^T + b_o;  q_out[M,d] (bf16) =

@@ -1,0 +1,700 @@
+// Width 384: everything of a layer after attention in one kernel (out-projection, residual,
+// LayerNorm, feed-forward block, residual, the next LayerNorm and the next layer's q/k/v
+// projection), as layer_tail_kernel (gemm.hip) is for width 256.
+#include "kernels.h"
+
+#include <type_traits>
+
+namespace cfdetr {
+
+namespace {
+
+constexpr int kRingMax = 24;    // most weight blocks of 1 KB a wavefront holds in registers
+constexpr int kFC = 128;        // hidden units of a chunk: one 32-wide tile per wavefront
+
+__device__ __forceinline__ int tile_order(int pid, int total) {
+  const int per = total >> 3;
+  return (pid < (per << 3)) ? (pid & 7) * per + (pid >> 3) : pid;
+}
+
+__device__ __forceinline__ float gelu_sig(float x) {
+  const float xc = __builtin_amdgcn_fmed3f(x, -8.0f, 8.0f);
+  const float x2 = xc * xc;
+  const float t = fmaf(fmaf(1.0142780e-03f, x2, -1.0677580e-01f), x2, -2.3011212e+00f) * xc;
+  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
+}
+
+struct WideArgs {
+  const bf16_t* O;
+  const unsigned char* packed;   // four weight streams, one per wavefront
+  uint32_t stream;               // bytes of one of them
+  const float *b_o, *ln2_g, *ln2_b, *b1, *b2;
+  int F;
+  float* x;
+  const float *ln_g, *ln_b;
+  float eps;
+  float* out;
+  int split_row;
+  float* out2;
+  const float* b_qkv;
+  float q_scale;
+  bf16_t* qk;
+  bf16_t* vt;
+  int vt_ld;
+  int32_t* vt_pos;
+  const int32_t* cu;
+  const int32_t* pcu;
+  int nseq;
+  const int32_t* m_ptr;
+  int m_host;
+};
+
+// LDS of a workgroup: operand rows, a hidden chunk (its place also serves the row sums and the
+// staging of outputs), and the vectors of the layer.
+template <int D, int MT>
+struct WideLds {
+  static constexpr int kA = MT * 32 * D * 2, kH = MT * 32 * kFC * 2, kStg = 4 * 16 * 208;
+  static constexpr int kHS = kH > kStg ? kH : kStg;
+  static constexpr int kVec = kA + kHS;                  // [b1 or b_qkv][ln2_g][ln2_b][b2][ln_g][ln_b]
+  static int bytes(int F) { return kVec + ((F > 3 * D ? F : 3 * D) + 5 * D) * 4; }
+};
+
+// What a launch does: the first layer's LayerNorm and projection only, a whole layer, or the
+// last layer (which ends in the final LayerNorm).
+constexpr int kHead = 0, kMid = 1, kLast = 2;
+
+// A workgroup of four wavefronts owns 32 MT complete rows; wavefront w owns columns
+// [w D/4, (w + 1) D/4) of them.  The rows' residuals stay in the accumulators from the first
+// product to the last: they start as x + b_o, the out-projection is added on top by its MFMAs,
+// LayerNorm reads them there, b2 and the second feed-forward matrix come on top again.  Per
+// row only O and x are read and x, q, k, v written; as separate kernels the same rows made
+// 30 KB of traffic more per layer (bf16 rows of both LayerNorms, hidden activations, x twice).
+// Weights: no wavefront shares one with another, so they skip the LDS.  They are packed in the
+// order of use, 1 KB per MFMA operand, and stream through a ring of registers that is refilled
+// right behind the MFMA that used a block.  Operand rows and hidden chunk lie in LDS with
+// 16-byte chunks XORed by the row (row lengths are multiples of 256 bytes, all 64 banks).
+// The feed-forward block goes in chunks of 128 hidden units; the activation of chunk c runs
+// between the MFMAs of the second matrix on chunk c - 1, laid out instruction by instruction
+// (the compiler puts it in front of them otherwise).  Vectors are in LDS because a global load
+// that is waited for waits for the whole ring behind which it was issued.
+//
+// Bounds: the matrix cores at the clock the power limit leaves (1.9 GHz with all CUs busy),
+// the activation's vector instructions (they exceed what its MFMAs hide: 60 clocks a value
+// pair against 32), and the CU's vector-memory path: 64 B/clk for 3.5 MB of weights per
+// workgroup, which is what taller tiles save.  Measured per layer at D = 384, F = 1536
+// against q/k/v, out-projection, two LayerNorms and the two feed-forward matrices as kernels
+// of their own: 22,400 rows 168 -> 111 us, 64,000 rows 430 -> 261 us, 3,520 rows 54 -> 45 us,
+// 920 rows 45 -> 43 us.
+template <int D, int MT, int kKind>
+__global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArgs p) {
+  constexpr int kRing = MT > 2 ? 24 : 12;   // what the registers of one or two workgroups per CU hold
+  constexpr int NT = D / 128, KS = D / 16, BM = 32 * MT, ROWB = D * 2, HROWB = kFC * 2;
+  using L = WideLds<D, MT>;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  unsigned char* const sA = smem;
+  unsigned char* const sH = smem + L::kA;
+  float* const s_red = reinterpret_cast<float*>(smem + L::kA);
+
+  const int M = p.m_ptr ? *p.m_ptr : p.m_host;
+  const int total = (M + BM - 1) / BM;
+  if ((int)blockIdx.x >= total) return;
+  const int m0 = tile_order(blockIdx.x, total) * BM;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, g = lane >> 5;
+  unsigned char* const stg = smem + L::kA + wave * (16 * 208);
+  float* const v_b1 = reinterpret_cast<float*>(smem + L::kVec);
+  float* const v_d = v_b1 + max(p.F, 3 * D);   // five vectors of D
+  const int c0 = wave * (D / 4);
+
+  int vpos[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const int m = min(m0 + i * 32 + l32, M - 1);
+    if (kKind == kHead) {
+      const int f = frame_of_token(p.cu, p.nseq, m);
+      vpos[i] = p.pcu[f] + (m - p.cu[f]);
+      if (wave == 0 && g == 0 && m0 + i * 32 + l32 < M) p.vt_pos[m] = vpos[i];
+    } else if (kKind == kMid) {
+      vpos[i] = p.vt_pos[m];
+    }
+  }
+
+  // the vectors of the layer
+  if (kKind != kHead) {
+    for (int i = tid * 4; i < p.F; i += 1024) *reinterpret_cast<float4*>(v_b1 + i) = *reinterpret_cast<const float4*>(p.b1 + i);
+  } else {
+    for (int i = tid * 4; i < 3 * D; i += 1024) *reinterpret_cast<float4*>(v_b1 + i) = *reinterpret_cast<const float4*>(p.b_qkv + i);
+  }
+  if (tid < D / 4) {
+    if (kKind != kHead) {
+      *reinterpret_cast<float4*>(v_d + tid * 4) = *reinterpret_cast<const float4*>(p.ln2_g + tid * 4);
+      *reinterpret_cast<float4*>(v_d + D + tid * 4) = *reinterpret_cast<const float4*>(p.ln2_b + tid * 4);
+      *reinterpret_cast<float4*>(v_d + 2 * D + tid * 4) = *reinterpret_cast<const float4*>(p.b2 + tid * 4);
+    }
+    *reinterpret_cast<float4*>(v_d + 3 * D + tid * 4) = *reinterpret_cast<const float4*>(p.ln_g + tid * 4);
+    *reinterpret_cast<float4*>(v_d + 4 * D + tid * 4) = *reinterpret_cast<const float4*>(p.ln_b + tid * 4);
+  }
+  // weight stream
+  const unsigned char* wp = p.packed + (size_t)wave * p.stream;
+  const uint32_t voff = lane * 16;
+  bf16x8 wr[kRing];
+  // block i of the ring's next round: the base of every fourth one in scalar registers, so
+  // that a load costs no vector arithmetic
+  typedef const __attribute__((address_space(1))) unsigned char* gptr;
+  gptr wq = (gptr)wp;
+  auto next_block = [&](int i) {
+    if (i % 4 == 0) {
+      wq = (gptr)wp + i * 1024;
+      asm volatile("" : "+s"(wq));
+    }
+    return *reinterpret_cast<const __attribute__((address_space(1))) bf16x8*>(wq + (i % 4) * 1024 + voff);
+  };
+#pragma unroll
+  for (int i = 0; i < kRing; ++i) wr[i] = *reinterpret_cast<const bf16x8*>(wp + i * 1024 + voff);
+
+  if (kKind != kHead) {
+    // rows of O into sA
+    constexpr int UNITS = BM * (ROWB / 16);
+#pragma unroll
+    for (int u0 = 0; u0 < UNITS; u0 += 256) {
+      const int u = u0 + tid;
+      const int row = u / (ROWB / 16), pos = u % (ROWB / 16);
+      const int c = (pos & ~15) | ((pos ^ row) & 15);
+      const bf16_t* src = p.O + (size_t)min(m0 + row, M - 1) * D + c * 8;
+      const uint32_t dst = (uint32_t)(uintptr_t)sA + (u0 + wave * 64) * 16;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                   : : "s"(dst), "v"(src) : "memory");
+    }
+  }
+  // residual rows (plus the bias of what is added to them) as start values
+  uint32_t xo[MT];   // byte offset of the lane's first column of its rows in x
+#pragma unroll
+  for (int i = 0; i < MT; ++i) xo[i] = ((uint32_t)min(m0 + i * 32 + l32, M - 1) * D + c0 + 4 * g) * 4u;
+  f32x16 acc[NT][MT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int col = c0 + j * 32 + 8 * q + 4 * g;
+      float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (kKind != kHead) b = *reinterpret_cast<const float4*>(p.b_o + col);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const float4 v = *reinterpret_cast<const float4*>(
+            reinterpret_cast<const unsigned char*>(p.x) + (xo[i] + (uint32_t)(j * 128 + q * 32)));
+        acc[j][i][4 * q] = v.x + b.x;
+        acc[j][i][4 * q + 1] = v.y + b.y;
+        acc[j][i][4 * q + 2] = v.z + b.z;
+        acc[j][i][4 * q + 3] = v.w + b.w;
+      }
+    }
+
+  // LDS operand addresses (chunk swizzled with the row), k-step modulo 4
+  uint32_t ao[8], ho[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    ao[k] = l32 * ROWB + (((2 * k + g) ^ (l32 & 15)) << 4);
+    ho[k] = l32 * HROWB + (((2 * k + g) ^ (l32 & 15)) << 4);
+  }
+
+  // One product over NK k-steps of the operand rows at `rows` (row length RB bytes), NTX column
+  // tiles per wavefront; `side(ks, mfma)` is work to put behind the MFMAs.
+#define WIDE_PRODUCT(ACC_, NTX_, NK_, ROWS_, RB_, OFF_)                                          \
+  do {                                                                                           \
+    constexpr int UN_ = kRing / (NTX_);   /* k-steps of a ring round */                          \
+    constexpr int BS_ = UN_ % 8 == 0 ? UN_ : UN_ == 4 ? 8 : 2 * UN_;                             \
+    static_assert(BS_ % 8 == 0 && (NK_) % BS_ == 0, "k-steps");                                  \
+    bf16x8 a_[2][MT];                                                                            \
+    _Pragma("unroll") for (int i = 0; i < MT; ++i)                                               \
+        a_[0][i] = *reinterpret_cast<const bf16x8*>((ROWS_) + OFF_[0] + i * (32 * (RB_)));       \
+    const unsigned char* rp_ = (ROWS_);                                                          \
+    _Pragma("nounroll") for (int k0_ = 0; k0_ < (NK_); k0_ += BS_) {                             \
+      _Pragma("unroll") for (int u = 0; u < BS_; ++u) {                                          \
+        if (u % UN_ == 0) wp += kRing * 1024;                                                    \
+        _Pragma("unroll") for (int i = 0; i < MT; ++i)                                           \
+            a_[(u + 1) & 1][i] = *reinterpret_cast<const bf16x8*>(                               \
+                rp_ + OFF_[(u + 1) & 7] + ((u + 1) / 8) * 256 + i * (32 * (RB_)));               \
+        _Pragma("unroll") for (int j = 0; j < (NTX_); ++j)                                       \
+            _Pragma("unroll") for (int i = 0; i < MT; ++i) ACC_[j][i] =                          \
+                __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[(u % UN_) * (NTX_) + j], a_[u & 1][i],        \
+                                                        ACC_[j][i], 0, 0, 0);                    \
+        _Pragma("unroll") for (int j = 0; j < (NTX_); ++j)                                       \
+            wr[(u % UN_) * (NTX_) + j] = next_block((u % UN_) * (NTX_) + j);                     \
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                       \
+        __builtin_amdgcn_sched_group_barrier(0x100, MT, 0);                                      \
+        __builtin_amdgcn_sched_group_barrier(0x008, MT - 1, 0);                                  \
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                       \
+        _Pragma("unroll") for (int j = 1; j < (NTX_); ++j) {                                     \
+          __builtin_amdgcn_sched_group_barrier(0x008, MT, 0);                                    \
+          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                     \
+        }                                                                                        \
+        __builtin_amdgcn_sched_barrier(0);                                                       \
+      }                                                                                          \
+      rp_ += (BS_ / 8) * 256;                                                                    \
+    }                                                                                            \
+  } while (0)
+
+  // mean and 1/sigma of the complete rows in acc (fused multiply-adds written out here and
+  // below: left to the compiler they would differ between instances, and so would the bits)
+  float mean[MT], rstd[MT];
+  auto stats = [&]() {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      float s = 0.f;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          s += (acc[j][i][4 * q] + acc[j][i][4 * q + 1]) + (acc[j][i][4 * q + 2] + acc[j][i][4 * q + 3]);
+      s += __shfl_xor(s, 32, kWave);
+      float v = 0.f;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float e = fmaf(s, -4.0f / D, acc[j][i][r]);
+          v = fmaf(e, e, v);
+        }
+      v += __shfl_xor(v, 32, kWave);
+      if (g == 0) {
+        s_red[(i * 32 + l32) * 8 + wave] = s;
+        s_red[(i * 32 + l32) * 8 + 4 + wave] = v;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const float4 s = *reinterpret_cast<const float4*>(s_red + (i * 32 + l32) * 8);
+      const float4 v = *reinterpret_cast<const float4*>(s_red + (i * 32 + l32) * 8 + 4);
+      mean[i] = ((s.x + s.y) + (s.z + s.w)) * (1.0f / D);
+      const float d0 = fmaf(mean[i], -(D / 4), s.x), d1 = fmaf(mean[i], -(D / 4), s.y);
+      const float d2 = fmaf(mean[i], -(D / 4), s.z), d3 = fmaf(mean[i], -(D / 4), s.w);
+      const float between = fmaf(d0, d0, d1 * d1) + fmaf(d2, d2, d3 * d3);
+      const float within = (v.x + v.y) + (v.z + v.w);
+      rstd[i] = rsqrtf(fmaf(fmaf(between, 4.0f / D, within), 1.0f / D, p.eps));
+    }
+  };
+  auto norm_to_lds = [&](const float* gain, const float* offs) {
+    float shift[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) shift[i] = -mean[i] * rstd[i];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int col = c0 + j * 32 + 8 * q + 4 * g;
+        const float4 ga = *reinterpret_cast<const float4*>(gain + col);
+        const float4 of = *reinterpret_cast<const float4*>(offs + col);
+        const int chunk = (c0 >> 3) + j * 4 + q;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          const float r0 = fmaf(fmaf(acc[j][i][4 * q], rstd[i], shift[i]), ga.x, of.x);
+          const float r1 = fmaf(fmaf(acc[j][i][4 * q + 1], rstd[i], shift[i]), ga.y, of.y);
+          const float r2 = fmaf(fmaf(acc[j][i][4 * q + 2], rstd[i], shift[i]), ga.z, of.z);
+          const float r3 = fmaf(fmaf(acc[j][i][4 * q + 3], rstd[i], shift[i]), ga.w, of.w);
+          *reinterpret_cast<uint2*>(sA + (i * 32 + l32) * ROWB + ((chunk ^ (l32 & 15)) << 4) + g * 8) =
+              make_uint2(pack_bf16x2(r0, r1), pack_bf16x2(r2, r3));
+        }
+      }
+    __syncthreads();
+  };
+
+  if (kKind != kHead) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    WIDE_PRODUCT(acc, NT, KS, sA, ROWB, ao);   // attention output times Wo
+    stats();
+    norm_to_lds(v_d, v_d + D);
+    // bias of the second FFN matrix
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 b = *reinterpret_cast<const float4*>(v_d + 2 * D + c0 + j * 32 + 8 * q + 4 * g);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          acc[j][i][4 * q] += b.x;
+          acc[j][i][4 * q + 1] += b.y;
+          acc[j][i][4 * q + 2] += b.z;
+          acc[j][i][4 * q + 3] += b.w;
+        }
+      }
+    f32x16 hid[1][MT];
+    uint2 pk[MT][4];
+    auto hid_bias = [&](int c) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 b = *reinterpret_cast<const float4*>(v_b1 + c * kFC + wave * 32 + 8 * q + 4 * g);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          hid[0][i][4 * q] = b.x;
+          hid[0][i][4 * q + 1] = b.y;
+          hid[0][i][4 * q + 2] = b.z;
+          hid[0][i][4 * q + 3] = b.w;
+        }
+      }
+    };
+    auto put_hidden = [&]() {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<uint2*>(sH + (i * 32 + l32) * HROWB + (((wave * 4 + q) ^ (l32 & 15)) << 4) + g * 8) = pk[i][q];
+    };
+    const int nc = p.F / kFC;
+    hid_bias(0);
+    WIDE_PRODUCT(hid, 1, KS, sA, ROWB, ao);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        pk[i][q] = make_uint2(pack_bf16x2(gelu_sig(hid[0][i][4 * q]), gelu_sig(hid[0][i][4 * q + 1])),
+                              pack_bf16x2(gelu_sig(hid[0][i][4 * q + 2]), gelu_sig(hid[0][i][4 * q + 3])));
+#pragma nounroll
+    for (int c = 1; c < nc; ++c) {
+      // chunk c - 1 is in pk (every wavefront has passed its reads of sH): into LDS
+      put_hidden();
+      hid_bias(c);
+      WIDE_PRODUCT(hid, 1, KS, sA, ROWB, ao);
+      __syncthreads();
+      // second matrix on chunk c - 1, the activation of chunk c between its MFMAs
+      {
+        constexpr int NM = NT * MT;
+        bf16x8 a_[2][MT];
+        float ge[MT][4];
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          a_[0][i] = *reinterpret_cast<const bf16x8*>(sH + ho[0] + i * (32 * HROWB));
+#pragma unroll
+        for (int t = 0; t < kFC / 16; ++t) {
+          constexpr int UN = kRing / NT;
+          if (t % UN == 0) wp += kRing * 1024;
+          // registers 2 t and 2 t + 1 of every hidden tile: V values, nine steps each, step by step
+          constexpr int V = 2 * MT, OPS = 9 * V, PER = (OPS + NM - 1) / NM;
+          float gx[V], gc[V], gt[V], g2[V];
+#pragma unroll
+          for (int m = 0; m < NM; ++m) {
+            const int j = m / MT, i = m % MT;
+            acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[(t % UN) * NT + j], a_[t & 1][i], acc[j][i], 0, 0, 0);
+            if (m < MT)
+              a_[(t + 1) & 1][m] = *reinterpret_cast<const bf16x8*>(sH + ho[(t + 1) & 7] + ((t + 1) / 8) * 256 + m * (32 * HROWB));
+            if (i == MT - 1) wr[(t % UN) * NT + j] = next_block((t % UN) * NT + j);
+#pragma unroll
+            for (int o = m * PER; o < (m + 1) * PER && o < OPS; ++o) {
+              const int s = o / V, v = o % V;
+              const int vi = v / 2, r = 2 * t + v % 2;
+              if (s == 0) {
+                gx[v] = hid[0][vi][r];
+                asm volatile("" : "+v"(gx[v]));
+                gc[v] = __builtin_amdgcn_fmed3f(gx[v], -8.0f, 8.0f);
+                asm volatile("" : "+v"(gc[v]));
+              } else if (s == 1) {
+                g2[v] = gc[v] * gc[v];
+                asm volatile("" : "+v"(g2[v]));
+              } else if (s == 2) {
+                gt[v] = fmaf(1.0142780e-03f, g2[v], -1.0677580e-01f);
+                asm volatile("" : "+v"(gt[v]));
+              } else if (s == 3) {
+                gt[v] = fmaf(gt[v], g2[v], -2.3011212e+00f);
+                asm volatile("" : "+v"(gt[v]));
+              } else if (s == 4) {
+                gt[v] = gt[v] * gc[v];
+                asm volatile("" : "+v"(gt[v]));
+              } else if (s == 5) {
+                gt[v] = __builtin_amdgcn_exp2f(gt[v]);
+                asm volatile("" : "+v"(gt[v]));
+              } else if (s == 6) {
+                gt[v] = 1.0f + gt[v];
+                asm volatile("" : "+v"(gt[v]));
+              } else if (s == 7) {
+                gt[v] = __builtin_amdgcn_rcpf(gt[v]);
+                asm volatile("" : "+v"(gt[v]));
+              } else {
+                ge[vi][r & 3] = gx[v] * gt[v];
+                asm volatile("" : "+v"(ge[vi][r & 3]));
+                if (r & 1) {
+                  uint32_t w = pack_bf16x2(ge[vi][(r & 3) - 1], ge[vi][r & 3]);
+                  asm volatile("" : "+v"(w));
+                  if ((r & 3) == 1) pk[vi][r >> 2].x = w;
+                  else pk[vi][r >> 2].y = w;
+                }
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
+      __syncthreads();
+    }
+    put_hidden();
+    __syncthreads();
+    float4 bq[2];
+    if (kKind == kMid) {
+      // the next projection's bias takes the place of b1 (everybody is done with that)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) bq[k] = *reinterpret_cast<const float4*>(p.b_qkv + min(tid * 4 + k * 1024, 3 * D - 4));
+    }
+    WIDE_PRODUCT(acc, NT, kFC / 16, sH, HROWB, ho);
+    if (kKind == kMid) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        if (tid * 4 + k * 1024 < 3 * D) *reinterpret_cast<float4*>(v_b1 + tid * 4 + k * 1024) = bq[k];
+    }
+    __syncthreads();   // (the row sums go where the hidden chunk was)
+  }
+  // the new residual rows
+  if (kKind == kMid) {
+    uint32_t xs[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      xs[i] = ((uint32_t)(m0 + i * 32 + l32) * D + c0 + 4 * g) * 4u;
+      asm volatile("" : "+v"(xs[i]));   // worked out here, not kept from the top of the kernel
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      if (m0 + i * 32 + l32 < M)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<float4*>(reinterpret_cast<unsigned char*>(p.x) + (xs[i] + (uint32_t)(j * 128 + q * 32))) =
+                make_float4(acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]);
+  }
+  stats();
+  if (kKind == kLast) {
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int col = c0 + j * 32 + 8 * q + 4 * g;
+        const float4 ga = *reinterpret_cast<const float4*>(v_d + 3 * D + col);
+        const float4 of = *reinterpret_cast<const float4*>(v_d + 4 * D + col);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          const int m = m0 + i * 32 + l32;
+          if (m >= M) continue;
+          const float shift = -mean[i] * rstd[i];
+          const bool second = p.out2 != nullptr && m >= p.split_row;
+          float* o = (second ? p.out2 : p.out) + (size_t)(second ? m - p.split_row : m) * D + col;
+          *reinterpret_cast<float4*>(o) =
+              make_float4(fmaf(fmaf(acc[j][i][4 * q], rstd[i], shift), ga.x, of.x),
+                          fmaf(fmaf(acc[j][i][4 * q + 1], rstd[i], shift), ga.y, of.y),
+                          fmaf(fmaf(acc[j][i][4 * q + 2], rstd[i], shift), ga.z, of.z),
+                          fmaf(fmaf(acc[j][i][4 * q + 3], rstd[i], shift), ga.w, of.w));
+        }
+      }
+    return;
+  }
+  norm_to_lds(v_d + 3 * D, v_d + 4 * D);
+  // q, k, v of these rows
+#pragma nounroll
+  for (int part = 0; part < 3; ++part) {
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 b = *reinterpret_cast<const float4*>(v_b1 + part * D + c0 + j * 32 + 8 * q + 4 * g);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          acc[j][i][4 * q] = b.x;
+          acc[j][i][4 * q + 1] = b.y;
+          acc[j][i][4 * q + 2] = b.z;
+          acc[j][i][4 * q + 3] = b.w;
+        }
+      }
+    WIDE_PRODUCT(acc, NT, KS, sA, ROWB, ao);
+    if (part < 2) {
+      const float sc = part == 0 ? p.q_scale : 1.0f;
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          // 16 rows x 96 columns at a time through the wavefront's staging rows
+          if ((l32 >> 4) == half) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+              for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<uint2*>(stg + (l32 & 15) * 208 + j * 64 + q * 16 + g * 8) =
+                    make_uint2(pack_bf16x2(acc[j][i][4 * q] * sc, acc[j][i][4 * q + 1] * sc),
+                               pack_bf16x2(acc[j][i][4 * q + 2] * sc, acc[j][i][4 * q + 3] * sc));
+          }
+#pragma unroll
+          for (int t = 0; t < 3; ++t) {
+            const int u = t * 64 + lane, row = u / 12, c = u % 12;
+            const uint4 v = *reinterpret_cast<const uint4*>(stg + row * 208 + c * 16);
+            const int m = m0 + i * 32 + half * 16 + row;
+            if (m < M)
+              *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(p.qk + part * D + c0) +
+                                        ((uint32_t)m * (6u * D) + (uint32_t)c * 16u)) = v;
+          }
+        }
+    } else {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        // (in the global address space still after the pointer is made opaque: a flat store
+        // would make every later wait one for all that is in flight)
+        __attribute__((address_space(1))) bf16_t* vp =
+            (__attribute__((address_space(1))) bf16_t*)(p.vt + (size_t)(c0 + 4 * g) * p.vt_ld + vpos[i]);
+        asm volatile("" : "+v"(vp));
+        if (m0 + i * 32 + l32 < M) {
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              *vp = f32_to_bf16(acc[j][i][r]);
+              vp += (size_t)((r & 3) == 3 ? 5 : 1) * p.vt_ld;
+            }
+        }
+      }
+    }
+  }
+}
+
+// The weights of a layer in the order the wavefronts stream them (see wide_layer_kernel).
+// One thread per 16 bytes; with Wo null only the q/k/v part (the first layer's kernel).
+template <int D>
+__global__ __launch_bounds__(256) void wide_pack_kernel(const bf16_t* __restrict__ Wo, const bf16_t* __restrict__ W1,
+                                                        const bf16_t* __restrict__ W2, const bf16_t* __restrict__ Wqkv,
+                                                        int F, int blocks, bf16_t* __restrict__ out) {
+  constexpr int NT = D / 128, KS = D / 16;
+  const long u = (long)blockIdx.x * 256 + threadIdx.x;
+  if (u >= (long)blocks * 4 * 64) return;
+  const int lane = (int)(u & 63), l32 = lane & 31, g = lane >> 5;
+  const long blk = u >> 6;
+  const int w = (int)(blk / blocks);
+  int b = (int)(blk % blocks);
+  const int nc = F / kFC;
+  const bf16_t* src = nullptr;
+  const int c0 = w * (D / 4);
+  bool done = false;
+  if (Wo != nullptr) {
+    if (b < KS * NT) {
+      src = Wo + (size_t)(c0 + (b % NT) * 32 + l32) * D + (b / NT) * 16 + g * 8;
+      done = true;
+    }
+    b -= KS * NT;
+    // F1(0), then F1(c) F2(c - 1) ..., then F2(nc - 1)
+    const int f1 = KS, f2 = (kFC / 16) * NT;
+    if (!done && b < nc * (f1 + f2)) {
+      int c, r;
+      bool first;
+      if (b < f1) { c = 0; r = b; first = true; }
+      else if (b >= nc * (f1 + f2) - f2) { c = nc - 1; r = b - (nc * (f1 + f2) - f2); first = false; }
+      else {
+        const int t = b - f1, it = t / (f1 + f2), rr = t % (f1 + f2);
+        first = rr < f1;
+        c = first ? it + 1 : it;
+        r = first ? rr : rr - f1;
+      }
+      if (first) src = W1 + (size_t)(c * kFC + w * 32 + l32) * D + r * 16 + g * 8;
+      else src = W2 + (size_t)(c0 + (r % NT) * 32 + l32) * F + c * kFC + (r / NT) * 16 + g * 8;
+      done = true;
+    }
+    b -= nc * (f1 + f2);
+  }
+  if (!done && Wqkv != nullptr && b < 3 * KS * NT) {
+    const int part = b / (KS * NT), r = b % (KS * NT);
+    src = Wqkv + (size_t)(part * D + c0 + (r % NT) * 32 + l32) * D + (r / NT) * 16 + g * 8;
+  }
+  if (src) reinterpret_cast<uint4*>(out)[u] = *reinterpret_cast<const uint4*>(src);
+}
+
+template <int D, int MT, int kKind>
+hipError_t launch_wide(const WideArgs& p, int m_capacity, hipStream_t s) {
+  auto kern = wide_layer_kernel<D, MT, kKind>;
+  const size_t lds = WideLds<D, MT>::bytes(p.F);
+  static bool configured = false;
+  if (!configured) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       160 * 1024);
+    if (e != hipSuccess) return e;
+    configured = true;
+  }
+  hipLaunchKernelGGL(kern, dim3((m_capacity + 32 * MT - 1) / (32 * MT)), dim3(256), lds, s, p);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// F: the vectors of a layer have to fit beside the tiles of two workgroups per CU.  Rows: the
+// kernel addresses rows of x and of q/k/v with 32-bit byte offsets.
+bool wide_layer_supported(int d, int F, bool use_bf16, uint64_t rows) {
+  return use_bf16 && d == 384 && F % kFC == 0 && F <= 2048 && rows * 6 * d < (1ull << 32);
+}
+
+static int wide_blocks(int d, int F, bool head) {
+  const int nt = d / 128, ks = d / 16, nc = F / kFC;
+  return (head ? 0 : ks * nt + nc * (ks + (kFC / 16) * nt)) + 3 * ks * nt;
+}
+
+uint64_t wide_layer_packed_bytes(int d, int F, bool head) {
+  return ((uint64_t)wide_blocks(d, F, head) * 4 + kRingMax) * 1024;   // (the ring reads ahead of the end)
+}
+
+hipError_t launch_wide_pack(const void* Wo, const void* W1, const void* W2, const void* Wqkv, int d, int F,
+                            void* packed, hipStream_t s) {
+  if (d != 384) return hipErrorInvalidValue;
+  const int blocks = wide_blocks(d, F, Wo == nullptr);
+  const long units = (long)blocks * 4 * 64;
+  auto a = [](const void* q) { return static_cast<const bf16_t*>(q); };
+  hipLaunchKernelGGL(wide_pack_kernel<384>, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s, a(Wo), a(W1), a(W2),
+                     a(Wqkv), F, blocks, static_cast<bf16_t*>(packed));
+  return hipGetLastError();
+}
+
+// Rows per workgroup, by the rows expected (a guess is enough: every height gives the same
+// bits).  One workgroup per CU is the fastest there is, so the lowest tile that gets by with
+// that; a workgroup of 96 rows has a CU to itself, one of 64 shares it with a second one,
+// whose vector work then runs under its MFMAs, and is the best where CUs get several.
+// Encoder passes of 12 layers in us, at 32 / 64 / 96 rows: 5,669 rows 1131 / 1314 / 1616;
+// 11,248 rows 1776 / 1689 / 1985; 22,421 rows 2809 / 2673 / 2566; 33,729 rows 4491 / 4115 / 4299.
+int wide_layer_tiles(int rows, int cus) {
+  for (int mt = 1; mt <= 3; ++mt)
+    if (rows <= 32 * mt * cus) return mt;
+  return 2;
+}
+
+hipError_t launch_wide_layer(const WideLayerArgs& a, int d, int F, int mt, const int32_t* m_ptr, int m_host,
+                             int m_capacity, hipStream_t s) {
+  if (!wide_layer_supported(d, F, true, m_capacity)) return hipErrorInvalidValue;
+  WideArgs p{};
+  const bool head = a.O == nullptr;
+  p.O = static_cast<const bf16_t*>(a.O);
+  p.packed = static_cast<const unsigned char*>(a.packed);
+  p.stream = (uint32_t)wide_blocks(d, F, head) * 1024;
+  p.b_o = a.b_o;
+  p.ln2_g = a.ln2_g;
+  p.ln2_b = a.ln2_b;
+  p.b1 = a.b_ff1;
+  p.b2 = a.b_ff2;
+  p.F = F;
+  p.x = a.resid;
+  p.ln_g = a.ln_g;
+  p.ln_b = a.ln_b;
+  p.eps = a.eps;
+  p.out = a.out;
+  p.split_row = a.split_row;
+  p.out2 = a.out2;
+  p.b_qkv = a.b_qkv;
+  p.q_scale = a.q_scale;
+  p.qk = static_cast<bf16_t*>(a.qk);
+  p.vt = static_cast<bf16_t*>(a.vt);
+  p.vt_ld = a.vt_ld;
+  p.vt_pos = a.vt_pos;
+  p.cu = a.cu;
+  p.pcu = a.pcu;
+  p.nseq = a.B;
+  p.m_ptr = m_ptr;
+  p.m_host = m_host;
+  auto kind = [&](auto tiles) {
+    constexpr int MT = decltype(tiles)::value;
+    return head ? launch_wide<384, MT, kHead>(p, m_capacity, s)
+                : a.last ? launch_wide<384, MT, kLast>(p, m_capacity, s) : launch_wide<384, MT, kMid>(p, m_capacity, s);
+  };
+  return mt >= 3 ? kind(std::integral_constant<int, 3>{})
+                 : mt == 2 ? kind(std::integral_constant<int, 2>{}) : kind(std::integral_constant<int, 1>{});
+}
+
+}  // namespace cfdetr

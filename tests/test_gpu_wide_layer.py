@@ -1,0 +1,54 @@
+"""The fused layer kernel of width 384: workgroups of 32, 64 and 96 rows (chosen by the number of
+rows) give every row the same bits, down to a single row, for feed-forward blocks of one hidden
+chunk, several, and as many as it takes; and they give what the oracle gives.  899 tokens a frame
+(rows no tile height divides): one frame is in the first range of the rule, 10, 19 and 28 frames
+are just inside the others."""
+import numpy as np
+import pytest
+
+from oracle import cfdetr_oracle as O
+from paper_2505_23317_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+BAR = 2e-2
+
+
+def _coarse(cfg, w, images):
+    from paper_2505_23317_amd import cfdetr as K
+    enc = K.Encoder(cfg, w)
+    n = images.shape[0]
+    out = enc.alloc_outputs(n)
+    enc.coarse_encode(enc.upload_images(images), n, out["x0_cache"], out["y_coarse"])
+    enc.sync_status()
+    y = out["y_coarse"].reshape(n, -1, cfg.d).clone()
+    enc.close()
+    return y
+
+
+@pytest.mark.parametrize("ffn, frames", [(128, 10), (640, 19), (2048, 28)])
+def test_rows_per_workgroup_do_not_change_a_result(ffn, frames):
+    import torch
+
+    cfg = synth.Config("wide", frames, 232, 248, (8,), 384, 6, 2, ffn, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 7)
+    rng = np.random.default_rng(3)
+    images = synth.bf16_round(rng.normal(0.5, 0.25, (frames, 3, cfg.H, cfg.W)).astype(np.float32))
+    many = _coarse(cfg, w, images)
+    assert torch.isfinite(many).all()
+    for f in (0, frames - 1):
+        assert torch.equal(_coarse(synth.replace(cfg, B=1), w, images[f:f + 1])[0], many[f]), f
+    ref = np.asarray(O.coarse_encode(images[:1], cfg.patch, w, cfg.heads)[-1]).reshape(-1, cfg.d)
+    err = float(np.abs(many[0].cpu().numpy() - ref).max() / np.abs(ref).max())
+    print("fused layer against the oracle:", err, flush=True)
+    assert err <= BAR
+
+
+@pytest.mark.parametrize("rows", [(1, 1), (1, 31), (3, 11), (5, 13)])
+def test_few_rows(rows):
+    cfg = synth.Config("narrow", 1, 8 * rows[0], 8 * rows[1], (8,), 384, 6, 1, 256, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 9)
+    images = synth.bf16_round(np.random.default_rng(5).normal(0.5, 0.25, (1, 3, cfg.H, cfg.W)).astype(np.float32))
+    y = _coarse(cfg, w, images)[0].cpu().numpy()
+    ref = np.asarray(O.coarse_encode(images, cfg.patch, w, cfg.heads)[-1]).reshape(-1, cfg.d)
+    assert float(np.abs(y - ref).max() / np.abs(ref).max()) <= BAR
