@@ -63,7 +63,11 @@ struct cfdetr_ctx {
   void* wide_packed = nullptr;      // the same for width 384 (layer.hip)
   uint64_t wide_layer = 0;
   void* wide_head = nullptr;
+  float* x_blocks = nullptr;        // and its residual rows
   int cus = 256;                    // compute units of the device
+  // w_qkv, w_o, w_ff1, w_ff2 of all layers as the kernels for few rows read them (slim.hip);
+  // null where the shape has none
+  char *slim_qkv = nullptr, *slim_o = nullptr, *slim_ff1 = nullptr, *slim_ff2 = nullptr;
 
   // decoder (cfdetr_decoder_attach): its own allocation
   bool has_dec = false;
@@ -91,6 +95,9 @@ struct cfdetr_ctx {
   void* dtail_packed = nullptr;   // per layer: w_o2, w_ff1, w_ff2, next w_qkv in the fused
   uint64_t dtail_packed_layer = 0;   // kernel's order (0: no fused kernel for this shape)
   void* dhead_packed = nullptr;   // w_qkv of the first layer
+  // the matrices as the kernels for few rows read them (few_rows.h), null where there are none
+  char *dslim_qkv = nullptr, *dslim_o = nullptr, *dslim_q = nullptr, *dslim_o2 = nullptr, *dslim_ff1 = nullptr,
+       *dslim_ff2 = nullptr, *dslim_box1 = nullptr, *dslim_box2 = nullptr;
   float* dz = nullptr;            // final LayerNorm of the queries in fp32 (fused path)
 
   std::string err;
@@ -303,6 +310,8 @@ PlanArgs encoder_plan(const cfdetr_ctx* ctx, int n_prefix, const RunShape& shape
   return p;
 }
 
+const void* packed(const char* base, size_t elements) { return base ? base + elements * 2 : nullptr; }
+
 // All layers + final LayerNorm over the tokens in ctx->x.  The sequences are
 // n_prefix coarse grids (n0 tokens each) followed by B sequences of the caller's; the
 // plan kernel, launched before, has turned that into ctx->cu_all / ctx->m_all, which every
@@ -322,12 +331,54 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
   // LayerNorm that follows them, and only the very first one is a launch of its own.
   const bool fused_ln = gemm_residual_ln_supported(d, bf);
   const bool fused_tail = fused_ln && ctx->tail_packed_layer != 0;
+  // width 384, few rows: four launches a layer over all CUs instead of one over the CUs that the
+  // rows fill.  Passes of 12 layers in us, spread / fused: 64 rows 375 / 575, 920 rows 552 / 667,
+  // 1,840 rows 655 / 671, 2,760 rows 835 / 690.
+  if (ctx->wide_layer && ctx->slim_qkv && shape.rows > 0 && shape.rows <= 7 * ctx->cus) {
+    SlimLayerArgs a{};
+    a.x0 = ctx->x;
+    a.x = ctx->x_blocks;
+    a.eps = eps;
+    a.q_scale = attention_q_scale(d / c.n_heads);
+    a.vt = ctx->vt;
+    a.vt_ld = ctx->vt_ld;
+    a.vt_pos = ctx->vt_pos;
+    a.cu = cu_all;
+    a.pcu = ctx->pcu;
+    a.nseq = nseq;
+    auto step = [&](SlimStep what, const void* wt, const float* bias, const float* g, const float* b, const void* rows,
+                    void* out) {
+      a.w = wt;
+      a.bias = bias;
+      a.ln_g = g;
+      a.ln_b = b;
+      a.rows = rows;
+      a.out = out;
+      return launch_slim(a, what, d, F, shape.rows, m_ptr, 0, m_cap, s);
+    };
+    for (size_t l = 0; l < (size_t)c.n_layers; ++l) {
+      CF_LAUNCH(CFDETR_K_QKV, step(l == 0 ? SlimStep::kFirstQkv : SlimStep::kQkv, ctx->slim_qkv + l * 3 * d * d * 2,
+                                   w.b_qkv + l * 3 * d, w.ln1_g + l * d, w.ln1_b + l * d, nullptr, ctx->qkv));
+      CF_LAUNCH(CFDETR_K_ATTN,
+                launch_attention(ctx->qkv, ctx->vt, ctx->vt_ld, ctx->o, d, c.n_heads, ctx->items, ctx->cap8, ctx->queue_heads + 8 * l,
+                                 shape.attn_grid, shape.block_q, bf, kv_len, s));
+      CF_LAUNCH(CFDETR_K_OUT, step(SlimStep::kOut, ctx->slim_o + l * d * d * 2, w.b_o + l * d, nullptr, nullptr, ctx->o,
+                                   nullptr));
+      CF_LAUNCH(CFDETR_K_FF1, step(SlimStep::kHidden, ctx->slim_ff1 + l * F * d * 2, w.b_ff1 + l * F, w.ln2_g + l * d,
+                                   w.ln2_b + l * d, nullptr, ctx->h));
+      CF_LAUNCH(CFDETR_K_FF2, step(SlimStep::kDown, ctx->slim_ff2 + l * F * d * 2, w.b_ff2 + l * d, nullptr, nullptr, ctx->h,
+                                   nullptr));
+    }
+    CF_LAUNCH(CFDETR_K_LN, launch_wide_norm(ctx->x_blocks, w.lnf_g, w.lnf_b, d, eps, y0, split_row, y1, m_ptr, 0, m_cap, s));
+    return CFDETR_OK;
+  }
   if (ctx->wide_layer) {
     // width 384: one kernel ahead of the loop and one behind each attention
     const int mt = wide_layer_tiles(shape.rows ? shape.rows : m_cap, ctx->cus);
     WideLayerArgs wa{};
     wa.packed = ctx->wide_head;
-    wa.resid = ctx->x;
+    wa.x0 = ctx->x;
+    wa.resid = ctx->x_blocks;
     wa.ln_g = w.ln1_g;
     wa.ln_b = w.ln1_b;
     wa.eps = eps;
@@ -390,7 +441,7 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
                 launch_gemm_qkv(ctx->a, wqkv, w.b_qkv + (size_t)l * 3 * d, d,
                                 attention_q_scale(d / c.n_heads), ctx->qkv, ctx->vt,
                                 ctx->vt_ld, cu_all, ctx->pcu, nseq, m_ptr, m_hint, m_cap, s,
-                                d % 4 == 0 ? ctx->vt_pos : nullptr));
+                                d % 4 == 0 ? ctx->vt_pos : nullptr, packed(ctx->slim_qkv, (size_t)l * 3 * d * d)));
     else
       CF_LAUNCH(CFDETR_K_QKV, launch_gemm(ctx->a, wqkv, w.b_qkv + (size_t)l * 3 * d, 3 * d, d,
                                           Epilogue::kBias, ctx->qkv, nullptr, bf, m_ptr, m_hint, m_cap,
@@ -436,14 +487,14 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
     } else {
       CF_LAUNCH(CFDETR_K_OUT, launch_gemm(ctx->o, wo, w.b_o + (size_t)l * d, d, d,
                                           Epilogue::kBiasResidual, nullptr, ctx->x, bf, m_ptr, m_hint,
-                                          m_cap, s));
+                                          m_cap, s, 1.0f, packed(ctx->slim_o, (size_t)l * d * d)));
       CF_LAUNCH(CFDETR_K_LN,
                 launch_layernorm(ctx->x, w.ln2_g + (size_t)l * d, w.ln2_b + (size_t)l * d, ctx->a,
                                  bf, d, eps, m_ptr, 0, m_cap, 0, nullptr, s));
     }
     CF_LAUNCH(CFDETR_K_FF1, launch_gemm(ctx->a, w1, w.b_ff1 + (size_t)l * F, F, d,
                                         Epilogue::kBiasGelu, ctx->h, nullptr, bf, m_ptr, m_hint, m_cap,
-                                        s));
+                                        s, 1.0f, packed(ctx->slim_ff1, (size_t)l * F * d)));
     if (fused_ln && !last)
       CF_LAUNCH(CFDETR_K_FF2,
                 launch_gemm_residual_ln(ctx->h, w2, w.b_ff2 + (size_t)l * d, d, F, ctx->x,
@@ -458,7 +509,7 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
     else
       CF_LAUNCH(CFDETR_K_FF2, launch_gemm(ctx->h, w2, w.b_ff2 + (size_t)l * d, d, F,
                                           Epilogue::kBiasResidual, nullptr, ctx->x, bf, m_ptr, m_hint,
-                                          m_cap, s));
+                                          m_cap, s, 1.0f, packed(ctx->slim_ff2, (size_t)l * F * d)));
   }
   if (!fused_ln)
     CF_LAUNCH(CFDETR_K_LN, launch_layernorm(ctx->x, w.lnf_g, w.lnf_b, y0, false, d, eps, m_ptr, 0,
@@ -614,7 +665,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
       CF_LAUNCH(CFDETR_K_QKV,
                 launch_gemm_qkv(ctx->da, wqkv + (size_t)l * 3 * d * d * 2, w.b_qkv + (size_t)l * 3 * d,
                                 d, qs, ctx->dqkv, ctx->dvt, ctx->dvt_ld, ctx->dcu_all, ctx->dpcu, B,
-                                nullptr, Mq, Mq, s));
+                                nullptr, Mq, Mq, s, nullptr, packed(ctx->dslim_qkv, (size_t)l * 3 * d * d)));
     }
     CF_LAUNCH(CFDETR_K_ATTN,
               launch_attention(ctx->dqkv, ctx->dvt, ctx->dvt_ld, ctx->d_o, d, c.n_heads, ctx->ditems, ctx->dcap8, ctx->dqueue + 16 * l,
@@ -629,14 +680,14 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
     } else {
       CF_LAUNCH(CFDETR_K_OUT, launch_gemm(ctx->d_o, wo + (size_t)l * d * d * 2, w.b_o + (size_t)l * d,
                                           d, d, Epilogue::kBiasResidual, nullptr, ctx->dx, true,
-                                          nullptr, Mq, Mq, s));
+                                          nullptr, Mq, Mq, s, 1.0f, packed(ctx->dslim_o, (size_t)l * d * d)));
       CF_LAUNCH(CFDETR_K_LN, launch_layernorm(ctx->dx, w.ln2_g + (size_t)l * d, w.ln2_b + (size_t)l * d,
                                               ctx->da, true, d, eps, nullptr, Mq, Mq, 0, nullptr, s));
     }
     if (!fused)
       CF_LAUNCH(CFDETR_K_QKV, launch_gemm(ctx->da, wq + (size_t)l * d * d * 2, w.b_q + (size_t)l * d, d,
                                           d, Epilogue::kBias, ctx->dh, nullptr, true, nullptr, Mq,
-                                          Mq, s, qs));
+                                          Mq, s, qs, packed(ctx->dslim_q, (size_t)l * d * d)));
     CF_LAUNCH(CFDETR_K_ATTN,
               launch_cross_attention(ctx->dh, static_cast<const bf16_t*>(ctx->dk_all) + l * k_stride,
                                      static_cast<const bf16_t*>(ctx->dvt_all) + l * v_stride,
@@ -673,16 +724,16 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
     }
     CF_LAUNCH(CFDETR_K_OUT, launch_gemm(ctx->d_o, wo2 + (size_t)l * d * d * 2, w.b_o2 + (size_t)l * d,
                                         d, d, Epilogue::kBiasResidual, nullptr, ctx->dx, true,
-                                        nullptr, Mq, Mq, s));
+                                        nullptr, Mq, Mq, s, 1.0f, packed(ctx->dslim_o2, (size_t)l * d * d)));
     // feed-forward
     CF_LAUNCH(CFDETR_K_LN, launch_layernorm(ctx->dx, w.ln3_g + (size_t)l * d, w.ln3_b + (size_t)l * d,
                                             ctx->da, true, d, eps, nullptr, Mq, Mq, 0, nullptr, s));
     CF_LAUNCH(CFDETR_K_FF1, launch_gemm(ctx->da, w1 + (size_t)l * F * d * 2, w.b_ff1 + (size_t)l * F,
                                         F, d, Epilogue::kBiasGelu, ctx->dh, nullptr, true, nullptr,
-                                        Mq, Mq, s));
+                                        Mq, Mq, s, 1.0f, packed(ctx->dslim_ff1, (size_t)l * F * d)));
     CF_LAUNCH(CFDETR_K_FF2, launch_gemm(ctx->dh, w2 + (size_t)l * d * F * 2, w.b_ff2 + (size_t)l * d,
                                         d, F, Epilogue::kBiasResidual, nullptr, ctx->dx, true,
-                                        nullptr, Mq, Mq, s));
+                                        nullptr, Mq, Mq, s, 1.0f, packed(ctx->dslim_ff2, (size_t)l * F * d)));
   }
   // heads: z = final LayerNorm (bf16); box perceptron hidden rows in dqkv / d_o
   if (fused)
@@ -691,9 +742,9 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
     CF_LAUNCH(CFDETR_K_LN, launch_layernorm(ctx->dx, w.lnf_g, w.lnf_b, ctx->da, true, d, eps, nullptr,
                                             Mq, Mq, 0, nullptr, s));
   CF_LAUNCH(CFDETR_K_DEC, launch_gemm(ctx->da, w.w_box1, w.b_box1, d, d, Epilogue::kBiasRelu,
-                                      ctx->dqkv, nullptr, true, nullptr, Mq, Mq, s));
+                                      ctx->dqkv, nullptr, true, nullptr, Mq, Mq, s, 1.0f, ctx->dslim_box1));
   CF_LAUNCH(CFDETR_K_DEC, launch_gemm(ctx->dqkv, w.w_box2, w.b_box2, d, d, Epilogue::kBiasRelu,
-                                      ctx->d_o, nullptr, true, nullptr, Mq, Mq, s));
+                                      ctx->d_o, nullptr, true, nullptr, Mq, Mq, s, 1.0f, ctx->dslim_box2));
   CF_LAUNCH(CFDETR_K_DEC, launch_decoder_heads(ctx->da, ctx->d_o, w.w_cls, w.b_cls, w.w_box3,
                                                w.b_box3, d, Mq, queries, s));
   return CFDETR_OK;
@@ -790,7 +841,7 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   Carver cv;
   const uint64_t o_x = cv.take(Tm * d * 4), o_a = cv.take(Tm * d * c->esz);
   const uint64_t o_qkv = cv.take(Tm * 3 * d * c->esz), o_o = cv.take(Tm * d * c->esz);
-  const uint64_t o_h = cv.take(Tm * F * c->esz), o_x0 = cv.take(Bm * c->n0 * d * 4);
+  const uint64_t o_h = cv.take((Tm + 31) * F * c->esz), o_x0 = cv.take(Bm * c->n0 * d * 4);
   c->vt_ld = (int)((Tm + 64 * 2 * Bm + 63) & ~uint64_t(63));
   const uint64_t vt_bytes = c->bf16 ? d * (uint64_t)c->vt_ld * 2 : 256;
   const uint64_t o_vt = cv.take(vt_bytes), o_pcu = cv.take((2 * Bm + 1) * 4);
@@ -818,6 +869,11 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
     c->wide_layer = wide_layer_packed_bytes((int)d, (int)F, false);
   const uint64_t o_wide = cv.take(c->wide_layer * cfg->n_layers);
   const uint64_t o_whead = cv.take(c->wide_layer ? wide_layer_packed_bytes((int)d, (int)F, true) : 0);
+  const uint64_t o_xb = cv.take(c->wide_layer ? (Tm + 95) / 96 * 96 * d * 4 : 0);
+  const bool slim = c->bf16 && !c->tail_packed_layer && few_rows_supported((int)d, (int)d) && few_rows_supported((int)F, (int)F);
+  const uint64_t Lw = cfg->n_layers;
+  const uint64_t o_sq = cv.take(slim ? slim_packed_bytes(Lw * 3 * d, d) : 0), o_so = cv.take(slim ? slim_packed_bytes(Lw * d, d) : 0);
+  const uint64_t o_s1 = cv.take(slim ? slim_packed_bytes(Lw * F, d) : 0), o_s2 = cv.take(slim ? slim_packed_bytes(Lw * d, F) : 0);
   c->arena_bytes = cv.off;
   e = hipMalloc(&c->arena, c->arena_bytes);
   if (e != hipSuccess) {
@@ -862,6 +918,13 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   c->head_packed = base + o_hpack;
   c->wide_packed = base + o_wide;
   c->wide_head = base + o_whead;
+  c->x_blocks = reinterpret_cast<float*>(base + o_xb);
+  if (slim) {
+    c->slim_qkv = base + o_sq;
+    c->slim_o = base + o_so;
+    c->slim_ff1 = base + o_s1;
+    c->slim_ff2 = base + o_s2;
+  }
 
   // static tables: coarse grid descriptors, zeroed counters, position tables
   std::vector<int32_t> desc(Bm * c->n0), cu(Bm + 1);
@@ -903,6 +966,10 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
         (int)d, (int)F, static_cast<char*>(c->wide_packed) + (size_t)l * c->wide_layer, nullptr);
   if (e == hipSuccess && c->wide_layer)
     e = launch_wide_pack(nullptr, nullptr, nullptr, w->w_qkv, (int)d, (int)F, c->wide_head, nullptr);
+  if (e == hipSuccess && slim) e = launch_slim_pack(w->w_qkv, Lw * 3 * d, (int)d, c->slim_qkv, nullptr);
+  if (e == hipSuccess && slim) e = launch_slim_pack(w->w_o, Lw * d, (int)d, c->slim_o, nullptr);
+  if (e == hipSuccess && slim) e = launch_slim_pack(w->w_ff1, Lw * F, (int)d, c->slim_ff1, nullptr);
+  if (e == hipSuccess && slim) e = launch_slim_pack(w->w_ff2, Lw * d, (int)F, c->slim_ff2, nullptr);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     if (c->m_seen) hipHostFree(c->m_seen);
@@ -1150,6 +1217,21 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
   const uint64_t o_tail = cv.take(tail_bytes * w->n_layers);
   const uint64_t o_head = cv.take(fused ? 3 * d * d * 2 : 0), o_z = cv.take(fused ? Mq * d * 4 : 0);
   const uint64_t o_mid = cv.take(fused ? 2 * d * d * 2 * w->n_layers : 0);
+  const bool slim = !fused && few_rows_supported((int)d, (int)d) && few_rows_supported((int)F, (int)F);
+  struct Slim {
+    char** where;
+    const void* w;
+    uint64_t N, K, at;
+  };
+  std::vector<Slim> slims;
+  if (slim) {
+    const uint64_t L = w->n_layers;
+    slims = {{&ctx->dslim_qkv, w->w_qkv, L * 3 * d, d, 0}, {&ctx->dslim_o, w->w_o, L * d, d, 0},
+             {&ctx->dslim_q, w->w_q, L * d, d, 0},         {&ctx->dslim_o2, w->w_o2, L * d, d, 0},
+             {&ctx->dslim_ff1, w->w_ff1, L * F, d, 0},     {&ctx->dslim_ff2, w->w_ff2, L * d, F, 0},
+             {&ctx->dslim_box1, w->w_box1, d, d, 0},       {&ctx->dslim_box2, w->w_box2, d, d, 0}};
+    for (Slim& m : slims) m.at = cv.take(slim_packed_bytes(m.N, m.K));
+  }
   const uint64_t k_bytes = (uint64_t)c.max_tokens_total * d * 2, v_bytes = d * (uint64_t)ctx->vt_ld * 2;
   const uint64_t o_kall = cv.take(k_bytes * w->n_layers), o_vall = cv.take(v_bytes * w->n_layers);
   hipError_t e = hipMalloc(&ctx->dec_arena, cv.off);
@@ -1188,6 +1270,10 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
         l + 1 < w->n_layers ? static_cast<const char*>(w->w_qkv) + (size_t)(l + 1) * 3 * d * d * 2
                             : nullptr,
         (int)d, (int)F, static_cast<char*>(ctx->dtail_packed) + (size_t)l * tail_bytes, nullptr);
+  for (const Slim& m : slims) {
+    *m.where = base + m.at;
+    if (e == hipSuccess) e = launch_slim_pack(m.w, m.N, (int)m.K, *m.where, nullptr);
+  }
   if (e == hipSuccess && fused) e = launch_layer_head_pack(w->w_qkv, (int)d, ctx->dhead_packed, nullptr);
   for (int l = 0; l < w->n_layers && e == hipSuccess && fused; ++l)
     e = launch_layer_mid_pack(static_cast<const char*>(w->w_o) + (size_t)l * d * d * 2,
@@ -1197,6 +1283,7 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
   if (e != hipSuccess) {
     hipFree(ctx->dec_arena);
     ctx->dec_arena = nullptr;
+    for (const Slim& m : slims) *m.where = nullptr;
     return fail_hip(ctx, "decoder work space set-up", e);
   }
   ctx->dw = *w;

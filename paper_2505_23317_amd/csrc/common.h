@@ -66,4 +66,29 @@ __device__ __forceinline__ T wave_sum(T v) {
   return v;
 }
 
+// LayerNorm of a row that a wavefront holds in quads of columns (quad lane + 64 j in v[j],
+// zeros beyond `quads`): mean first, then the variance of the centred values.  Fused
+// multiply-adds are written out, so that every kernel that does this gets the same bits.
+template <int NQ>
+__device__ __forceinline__ void ln_quad_stats(const float4 (&v)[NQ], int quads, int lane, int d, float eps, float& mean,
+                                              float& rstd) {
+  float sum = 0.f;
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) sum += (v[j].x + v[j].y) + (v[j].z + v[j].w);
+  mean = wave_sum(sum) / (float)d;
+  float sq = 0.f;
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+    if (lane + 64 * j < quads) {
+      const float cx = v[j].x - mean, cy = v[j].y - mean, cz = v[j].z - mean, cw = v[j].w - mean;
+      sq += fmaf(cx, cx, cy * cy) + fmaf(cz, cz, cw * cw);
+    }
+  }
+  rstd = rsqrtf(wave_sum(sq) / (float)d + eps);
+}
+__device__ __forceinline__ float4 ln_quad(const float4& v, float mean, float rstd, const float4& g, const float4& b) {
+  return make_float4(fmaf((v.x - mean) * rstd, g.x, b.x), fmaf((v.y - mean) * rstd, g.y, b.y),
+                     fmaf((v.z - mean) * rstd, g.z, b.z), fmaf((v.w - mean) * rstd, g.w, b.w));
+}
+
 }  // namespace cfdetr

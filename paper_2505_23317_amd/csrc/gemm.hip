@@ -24,6 +24,7 @@
 // A workgroup -> tile mapping that gives each XCD (own L2) a contiguous run of tiles,
 // M read from device memory (grids are sized for the capacity; surplus workgroups
 // leave at once), and an all-fp32 kernel for the check mode complete the file.
+#include "few_rows.h"
 #include "kernels.h"
 
 namespace cfdetr {
@@ -1043,6 +1044,52 @@ __device__ __forceinline__ float row16_sum(float v) {
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true));
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, true));
   return v;
+}
+
+// Few rows (few_rows.h): 32 MT rows x 128 columns a workgroup, weights packed.  The sums and
+// the epilogue are those of the other forms, so the results are the same bits.
+template <int MT, typename EP>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_few_kernel(const bf16_t* __restrict__ A, const unsigned char* W, int N, int K,
+                                                               EP ep, const int32_t* __restrict__ m_ptr, int m_host,
+                                                               int row_groups) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int M = m_ptr ? *m_ptr : m_host;
+  const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), N / 128, row_groups);
+  const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int t = blockIdx.x >> 3; t < tiles.count; t += gridDim.x >> 3) {
+    const int part = tiles.p0 + t / tiles.rows, m0 = (tiles.r0 + t % tiles.rows) * (32 * MT), n0 = part * 128 + wave * 32;
+    int32_t info[MT];
+    float4 b[4], x[MT][4];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int m = min(m0 + i * 32 + l32, M - 1);
+      info[i] = ep.row_info(m);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[i][q] = ep.extra4(m, n0 + 8 * q + 4 * g, info[i]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) b[q] = ep.bias4(n0 + 8 * q + 4 * g);
+    f32x16 acc[MT];
+    few_rows_product<MT, false>(A, K, M, m0, W + (size_t)(part * 4 + wave) * (K >> 4) * 1024, smem, acc, [&]() {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    });
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int m = m0 + i * 32 + l32;
+      if (m < M && ep.row_ok(info[i])) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float v[4] = {acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+          ep.store4(m, n0 + 8 * q + 4 * g, v, b[q], x[i][q], info[i]);
+        }
+      }
+    }
+    __syncthreads();   // the stages' places are free
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2277,9 +2324,22 @@ hipError_t launch_persist_tile(const DenseRows& a, const bf16_t* w, int N, int K
 // decides at a few rounds is how full the last round is: the estimate is rounds x time per
 // round.  (24 470 rows x 384 columns are 576 tiles of 128x128 for 512 places, two rounds
 // of which the second is an eighth full, and 384 tiles of 192x128, one round.)
+template <int MT, typename EP>
+hipError_t launch_few(const bf16_t* a, const void* packed, int N, int K, const EP& ep, const int32_t* m_ptr, int m_host,
+                      int m_capacity, hipStream_t s) {
+  int row_groups = 1;
+  const dim3 grid = few_rows_grid(m_host, m_capacity, N / 128, K, MT, &row_groups);
+  constexpr auto kern = gemm_bf16_few_kernel<MT, EP>;
+  hipLaunchKernelGGL(kern, grid, dim3(256), few_rows_lds(MT), s, a, static_cast<const unsigned char*>(packed), N, K, ep, m_ptr,
+                     m_host, row_groups);
+  return hipSuccess;
+}
+
+// `packed`: the weights once more as launch_slim_pack lays them out, or null.
 template <typename EP>
 hipError_t launch_direct(const void* A, const void* W, int N, int K, const EP& ep,
-                         const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s) {
+                         const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s,
+                         const void* packed = nullptr) {
   const DenseRows a{static_cast<const bf16_t*>(A), K};
   const bf16_t* w = static_cast<const bf16_t*>(W);
   if ((size_t)m_capacity * K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
@@ -2293,6 +2353,19 @@ hipError_t launch_direct(const void* A, const void* W, int N, int K, const EP& e
   const long rounds192 = (tiles192 + cus - 1) / cus, rounds192n = (tiles192n + 2 * cus - 1) / (2 * cus);
   const long t128 = 100 * rounds128, t192n = 150 * rounds192n;
   const bool narrow_ok = N % 128 == 0 && tiles128 >= cus;
+  // Few rows: 32 or 64 rows a workgroup as long as no CU gets two, and twice as many where K is
+  // so long that a tile's chain of slabs counts and not the number of tiles.  In us, 64 x 64 or
+  // 128 x 128 tiles / 32 rows / 64 rows, N x K = 768 x 3072: 1024 rows 26.7 / 14.3 / 18.8, 2048
+  // rows 36.3 / 28.9 / 21.9, 4800 rows 43.7 / 53.9 / 39.1; 768 x 768: 1024 rows 10.6 / 7.1 / 9.5,
+  // 2048 rows 12.5 / 11.7 / 9.8, 3072 rows 14.1 / 16.4 / 15.2; 2304 x 768: 256 rows 8.6 / 6.5 /
+  // 8.1, 512 rows 10.1 / 10.8 / 8.6, 1024 rows 11.8 / 14.1 / 12.8; 384 x 384: 256 rows 6.0 / 4.4
+  // / 5.8, 2400 rows 6.1 / 5.1 / 6.1.
+  if (packed && few_rows_supported(N, K)) {
+    const long few32 = (long)((m + 31) / 32) * (N / 128), few64 = (long)((m + 63) / 64) * (N / 128);
+    if (few32 <= cus) return launch_few<1>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+    if (few64 <= cus || (K >= 2048 && few64 <= 2 * cus))
+      return launch_few<2>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+  }
   // A deeper ring (3 or 4 buffers, also with slabs of 32) measured no faster for these
   // tiles: their main loops are bound by LDS traffic, not by the latency of the loads.
   if (N % 256 == 0 && m >= 8192) {
@@ -2511,10 +2584,10 @@ hipError_t launch_embed(const EmbedArgs& a, const void* w, const float* bias, in
 hipError_t launch_gemm_qkv(const void* A, const void* W, const float* bias, int d,
                            float q_scale, void* qk, void* vt, int vt_ld, const int32_t* cu_seqlens, const int32_t* pcu,
                            int B, const int32_t* m_ptr, int m_host, int m_capacity,
-                           hipStream_t s, const int32_t* vt_pos) {
+                           hipStream_t s, const int32_t* vt_pos, const void* packed) {
   EpiQkv ep{bias, static_cast<bf16_t*>(qk), 3 * d, 2 * d, d, q_scale, static_cast<bf16_t*>(vt),
             vt_ld, cu_seqlens, pcu, B, vt_pos};
-  hipError_t e = launch_direct(A, W, 3 * d, d, ep, m_ptr, m_host, m_capacity, s);
+  hipError_t e = launch_direct(A, W, 3 * d, d, ep, m_ptr, m_host, m_capacity, s, packed);
   if (e != hipSuccess) return e;
   return hipGetLastError();
 }
@@ -2534,25 +2607,25 @@ hipError_t launch_gemm_kv_layers(const void* A, const void* W, const float* bias
 hipError_t launch_gemm(const void* A, const void* W, const float* bias, int N, int K,
                        Epilogue epi, void* out_act, float* resid, bool use_bf16,
                        const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s,
-                       float scale) {
+                       float scale, const void* packed) {
   hipError_t e = hipSuccess;
   if (use_bf16) {
     bf16_t* o = static_cast<bf16_t*>(out_act);
     switch (epi) {
       case Epilogue::kBias:
         e = launch_direct(A, W, N, K, EpiAct<bf16_t, kActNone>{bias, o, N, scale}, m_ptr, m_host,
-                          m_capacity, s);
+                          m_capacity, s, packed);
         break;
       case Epilogue::kBiasGelu:
         e = launch_direct(A, W, N, K, EpiAct<bf16_t, kActGelu>{bias, o, N, scale}, m_ptr, m_host,
-                          m_capacity, s);
+                          m_capacity, s, packed);
         break;
       case Epilogue::kBiasRelu:
         e = launch_direct(A, W, N, K, EpiAct<bf16_t, kActRelu>{bias, o, N, scale}, m_ptr, m_host,
-                          m_capacity, s);
+                          m_capacity, s, packed);
         break;
       case Epilogue::kBiasResidual:
-        e = launch_direct(A, W, N, K, EpiResidual{bias, resid, N}, m_ptr, m_host, m_capacity, s);
+        e = launch_direct(A, W, N, K, EpiResidual{bias, resid, N}, m_ptr, m_host, m_capacity, s, packed);
         break;
     }
   } else {

@@ -153,7 +153,7 @@ enum class Epilogue { kBias, kBiasGelu, kBiasRelu, kBiasResidual };
 hipError_t launch_gemm(const void* A, const void* W, const float* bias, int N, int K,
                        Epilogue epi, void* out_act, float* resid, bool use_bf16,
                        const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s,
-                       float scale = 1.0f);
+                       float scale = 1.0f, const void* packed = nullptr);
 
 // bf16 key/value projections of the decoder's cross-attention for `layers` layers at once
 // (the tokens are the same for all of them): W [layers * 2d, d] and bias [layers * 2d] stack
@@ -233,7 +233,8 @@ struct WideLayerArgs {
   const void* O;
   const void* packed;   // launch_wide_pack's
   const float *b_o, *ln2_g, *ln2_b, *b_ff1, *b_ff2;
-  float* resid;
+  const float* x0;      // the embedded rows, which that first launch reads
+  float* resid;         // residual blocks (wide_row.h) that it writes, whole tiles of 96 rows
   const float *ln_g, *ln_b;
   float eps;
   bool last;
@@ -259,6 +260,45 @@ hipError_t launch_wide_pack(const void* Wo, const void* W1, const void* W2, cons
 hipError_t launch_wide_layer(const WideLayerArgs& a, int d, int F, int mt, const int32_t* m_ptr,
                              int m_host, int m_capacity, hipStream_t s);
 
+// Weights for the kernels that take few rows (few_rows.h): [N, K] in MFMA operand order.  N and
+// K that few_rows_supported names.
+bool few_rows_supported(int N, int K);
+uint64_t slim_packed_bytes(uint64_t N, uint64_t K);
+hipError_t launch_slim_pack(const void* W, uint64_t N, int K, void* packed, hipStream_t s);
+
+// A step of a layer of width 384 where there are few rows, with the results of
+// wide_layer_kernel and on the same residual blocks (few_rows.hip):
+//   kFirstQkv  LayerNorm of x0 and q/k/v; writes x and vt_pos, which the others read
+//   kQkv       the same of x
+//   kOut       x += rows . W^T + bias (rows: the attention's)
+//   kHidden    LayerNorm of x, first feed-forward matrix and activation, to `out` as operand
+//              blocks: tiles of 32 rows, F x 64 bytes each
+//   kDown      x += blocks (rows) . W^T + bias
+// `rows`: those expected (0: unknown).
+enum class SlimStep { kFirstQkv, kQkv, kOut, kHidden, kDown };
+struct SlimLayerArgs {
+  const void* rows;
+  const float* x0;
+  float* x;
+  const float *ln_g, *ln_b;
+  float eps;
+  const void* w;        // launch_slim_pack's
+  const float* bias;
+  float q_scale;
+  void* out;
+  void* vt;
+  int vt_ld;
+  int32_t* vt_pos;
+  const int32_t* cu;
+  const int32_t* pcu;
+  int nseq;
+};
+hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int rows, const int32_t* m_ptr, int m_host,
+                       int m_capacity, hipStream_t s);
+// wide_layer_kernel's final LayerNorm as a kernel of its own
+hipError_t launch_wide_norm(float* x, const float* ln_g, const float* ln_b, int d, float eps, float* out, int split_row,
+                            float* out2, const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s);
+
 // Between the decoder's two attentions, in the same style (width 256, bf16): the output
 // projection of the first with its residual, the LayerNorm behind it and the query
 // projection of the second:  resid[M,d] += O . Wo^T + b_o;  q_out[M,d] (bf16) =
@@ -279,7 +319,7 @@ hipError_t launch_gemm_qkv(const void* A, const void* W, const float* bias, int 
                            float q_scale, void* qk, void* vt, int vt_ld,
                            const int32_t* cu_seqlens, const int32_t* pcu, int B,
                            const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s,
-                           const int32_t* vt_pos = nullptr);
+                           const int32_t* vt_pos = nullptr, const void* packed = nullptr);
 // log2(e) / sqrt(d_head): the factor the bf16 attention kernel expects folded into q.
 float attention_q_scale(int d_head);
 

@@ -2,6 +2,7 @@
 // LayerNorm, feed-forward block, residual, the next LayerNorm and the next layer's q/k/v
 // projection), as layer_tail_kernel (gemm.hip) is for width 256.
 #include "kernels.h"
+#include "wide_row.h"
 
 #include <type_traits>
 
@@ -12,25 +13,14 @@ namespace {
 constexpr int kRingMax = 24;    // most weight blocks of 1 KB a wavefront holds in registers
 constexpr int kFC = 128;        // hidden units of a chunk: one 32-wide tile per wavefront
 
-__device__ __forceinline__ int tile_order(int pid, int total) {
-  const int per = total >> 3;
-  return (pid < (per << 3)) ? (pid & 7) * per + (pid >> 3) : pid;
-}
-
-__device__ __forceinline__ float gelu_sig(float x) {
-  const float xc = __builtin_amdgcn_fmed3f(x, -8.0f, 8.0f);
-  const float x2 = xc * xc;
-  const float t = fmaf(fmaf(1.0142780e-03f, x2, -1.0677580e-01f), x2, -2.3011212e+00f) * xc;
-  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
-}
-
 struct WideArgs {
   const bf16_t* O;
   const unsigned char* packed;   // four weight streams, one per wavefront
   uint32_t stream;               // bytes of one of them
   const float *b_o, *ln2_g, *ln2_b, *b1, *b2;
   int F;
-  float* x;
+  const float* x0;           // kHead: the rows as the embedding left them
+  float* x;                  // residual blocks (wide_row.h)
   const float *ln_g, *ln_b;
   float eps;
   float* out;
@@ -83,8 +73,8 @@ constexpr int kHead = 0, kMid = 1, kLast = 2;
 // pair against 32), and the CU's vector-memory path: 64 B/clk for 3.5 MB of weights per
 // workgroup, which is what taller tiles save.  Measured per layer at D = 384, F = 1536
 // against q/k/v, out-projection, two LayerNorms and the two feed-forward matrices as kernels
-// of their own: 22,400 rows 168 -> 111 us, 64,000 rows 430 -> 261 us, 3,520 rows 54 -> 45 us,
-// 920 rows 45 -> 43 us.
+// of their own: 22,400 rows 168 -> 109 us, 64,000 rows 430 -> 247 us, 3,520 rows 54 -> 43 us,
+// 920 rows 45 -> 42 us (few_rows.hip takes those).
 template <int D, int MT, int kKind>
 __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArgs p) {
   constexpr int kRing = MT > 2 ? 24 : 12;   // what the registers of one or two workgroups per CU hold
@@ -168,9 +158,7 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
     }
   }
   // residual rows (plus the bias of what is added to them) as start values
-  uint32_t xo[MT];   // byte offset of the lane's first column of its rows in x
-#pragma unroll
-  for (int i = 0; i < MT; ++i) xo[i] = ((uint32_t)min(m0 + i * 32 + l32, M - 1) * D + c0 + 4 * g) * 4u;
+  unsigned char* const xw = reinterpret_cast<unsigned char*>(p.x) + (size_t)(m0 >> 5) * (D * 128) + wave * (NT * 4096);
   f32x16 acc[NT][MT];
 #pragma unroll
   for (int j = 0; j < NT; ++j)
@@ -181,8 +169,10 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
       if (kKind != kHead) b = *reinterpret_cast<const float4*>(p.b_o + col);
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
-        const float4 v = *reinterpret_cast<const float4*>(
-            reinterpret_cast<const unsigned char*>(p.x) + (xo[i] + (uint32_t)(j * 128 + q * 32)));
+        const float4 v =
+            kKind == kHead
+                ? *reinterpret_cast<const float4*>(p.x0 + (size_t)min(m0 + i * 32 + l32, M - 1) * D + col)
+                : *reinterpret_cast<const float4*>(xw + i * (D * 128) + j * 4096 + q * 1024 + voff);
         acc[j][i][4 * q] = v.x + b.x;
         acc[j][i][4 * q + 1] = v.y + b.y;
         acc[j][i][4 * q + 2] = v.z + b.z;
@@ -235,77 +225,13 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
     }                                                                                            \
   } while (0)
 
-  // mean and 1/sigma of the complete rows in acc (fused multiply-adds written out here and
-  // below: left to the compiler they would differ between instances, and so would the bits)
   float mean[MT], rstd[MT];
-  auto stats = [&]() {
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      float s = 0.f;
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          s += (acc[j][i][4 * q] + acc[j][i][4 * q + 1]) + (acc[j][i][4 * q + 2] + acc[j][i][4 * q + 3]);
-      s += __shfl_xor(s, 32, kWave);
-      float v = 0.f;
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float e = fmaf(s, -4.0f / D, acc[j][i][r]);
-          v = fmaf(e, e, v);
-        }
-      v += __shfl_xor(v, 32, kWave);
-      if (g == 0) {
-        s_red[(i * 32 + l32) * 8 + wave] = s;
-        s_red[(i * 32 + l32) * 8 + 4 + wave] = v;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      const float4 s = *reinterpret_cast<const float4*>(s_red + (i * 32 + l32) * 8);
-      const float4 v = *reinterpret_cast<const float4*>(s_red + (i * 32 + l32) * 8 + 4);
-      mean[i] = ((s.x + s.y) + (s.z + s.w)) * (1.0f / D);
-      const float d0 = fmaf(mean[i], -(D / 4), s.x), d1 = fmaf(mean[i], -(D / 4), s.y);
-      const float d2 = fmaf(mean[i], -(D / 4), s.z), d3 = fmaf(mean[i], -(D / 4), s.w);
-      const float between = fmaf(d0, d0, d1 * d1) + fmaf(d2, d2, d3 * d3);
-      const float within = (v.x + v.y) + (v.z + v.w);
-      rstd[i] = rsqrtf(fmaf(fmaf(between, 4.0f / D, within), 1.0f / D, p.eps));
-    }
-  };
-  auto norm_to_lds = [&](const float* gain, const float* offs) {
-    float shift[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) shift[i] = -mean[i] * rstd[i];
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int col = c0 + j * 32 + 8 * q + 4 * g;
-        const float4 ga = *reinterpret_cast<const float4*>(gain + col);
-        const float4 of = *reinterpret_cast<const float4*>(offs + col);
-        const int chunk = (c0 >> 3) + j * 4 + q;
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          const float r0 = fmaf(fmaf(acc[j][i][4 * q], rstd[i], shift[i]), ga.x, of.x);
-          const float r1 = fmaf(fmaf(acc[j][i][4 * q + 1], rstd[i], shift[i]), ga.y, of.y);
-          const float r2 = fmaf(fmaf(acc[j][i][4 * q + 2], rstd[i], shift[i]), ga.z, of.z);
-          const float r3 = fmaf(fmaf(acc[j][i][4 * q + 3], rstd[i], shift[i]), ga.w, of.w);
-          *reinterpret_cast<uint2*>(sA + (i * 32 + l32) * ROWB + ((chunk ^ (l32 & 15)) << 4) + g * 8) =
-              make_uint2(pack_bf16x2(r0, r1), pack_bf16x2(r2, r3));
-        }
-      }
-    __syncthreads();
-  };
-
   if (kKind != kHead) {
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
     WIDE_PRODUCT(acc, NT, KS, sA, ROWB, ao);   // attention output times Wo
-    stats();
-    norm_to_lds(v_d, v_d + D);
+    wide_stats(acc, s_red, l32, g, wave, p.eps, mean, rstd);
+    wide_norm_to_lds(acc, mean, rstd, v_d, v_d + D, sA, l32, g, wave);
     // bias of the second FFN matrix
 #pragma unroll
     for (int j = 0; j < NT; ++j)
@@ -444,24 +370,22 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
     __syncthreads();   // (the row sums go where the hidden chunk was)
   }
   // the new residual rows
-  if (kKind == kMid) {
-    uint32_t xs[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      xs[i] = ((uint32_t)(m0 + i * 32 + l32) * D + c0 + 4 * g) * 4u;
-      asm volatile("" : "+v"(xs[i]));   // worked out here, not kept from the top of the kernel
-    }
+  if (kKind != kLast) {
+    typedef __attribute__((address_space(1))) unsigned char* gwptr;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    gwptr xo = (gwptr)xw;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
-      if (m0 + i * 32 + l32 < M)
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+      for (int j = 0; j < NT; ++j) {
+        asm volatile("" : "+s"(xo));   // addresses worked out here, not kept from the top of the kernel
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<float4*>(reinterpret_cast<unsigned char*>(p.x) + (xs[i] + (uint32_t)(j * 128 + q * 32))) =
-                make_float4(acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]);
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<__attribute__((address_space(1))) f32x4*>(xo + (i * (D * 128) + j * 4096 + q * 1024) + voff) =
+              f32x4{acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
+      }
   }
-  stats();
+  wide_stats(acc, s_red, l32, g, wave, p.eps, mean, rstd);
   if (kKind == kLast) {
 #pragma unroll
     for (int j = 0; j < NT; ++j)
@@ -486,7 +410,7 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
       }
     return;
   }
-  norm_to_lds(v_d + 3 * D, v_d + 4 * D);
+  wide_norm_to_lds(acc, mean, rstd, v_d + 3 * D, v_d + 4 * D, sA, l32, g, wave);
   // q, k, v of these rows
 #pragma nounroll
   for (int part = 0; part < 3; ++part) {
@@ -670,6 +594,7 @@ hipError_t launch_wide_layer(const WideLayerArgs& a, int d, int F, int mt, const
   p.b1 = a.b_ff1;
   p.b2 = a.b_ff2;
   p.F = F;
+  p.x0 = a.x0;
   p.x = a.resid;
   p.ln_g = a.ln_g;
   p.ln_b = a.ln_b;

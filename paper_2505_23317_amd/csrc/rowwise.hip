@@ -105,23 +105,13 @@ __global__ __launch_bounds__(256) void layernorm4_kernel(
   const int quads = d >> 2;
   const float4* xr = reinterpret_cast<const float4*>(x + (size_t)row * d);
   float4 v[kLnMaxQuads];
-  float sum = 0.f;
 #pragma unroll
   for (int j = 0; j < kLnMaxQuads; ++j) {
     const int i = lane + 64 * j;
     v[j] = (i < quads) ? xr[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-    sum += (v[j].x + v[j].y) + (v[j].z + v[j].w);
   }
-  const float mean = wave_sum(sum) / (float)d;
-  float sq = 0.f;
-#pragma unroll
-  for (int j = 0; j < kLnMaxQuads; ++j) {
-    if (lane + 64 * j < quads) {
-      const float cx = v[j].x - mean, cy = v[j].y - mean, cz = v[j].z - mean, cw = v[j].w - mean;
-      sq += (cx * cx + cy * cy) + (cz * cz + cw * cw);
-    }
-  }
-  const float rstd = rsqrtf(wave_sum(sq) / (float)d + eps);
+  float mean, rstd;
+  ln_quad_stats(v, quads, lane, d, eps, mean, rstd);
   TOut* orow = (out2 != nullptr && row >= split_row) ? out2 + (size_t)(row - split_row) * d
                                                      : out + (size_t)row * d;
   const float4* g4 = reinterpret_cast<const float4*>(g);
@@ -131,9 +121,8 @@ __global__ __launch_bounds__(256) void layernorm4_kernel(
     const int i = lane + 64 * j;
     if (i < quads) {
       const float4 gg = g4[i], bb = b4[i];
-      store_quad(orow + 4 * i, (v[j].x - mean) * rstd * gg.x + bb.x,
-                 (v[j].y - mean) * rstd * gg.y + bb.y, (v[j].z - mean) * rstd * gg.z + bb.z,
-                 (v[j].w - mean) * rstd * gg.w + bb.w);
+      const float4 y = ln_quad(v[j], mean, rstd, gg, bb);
+      store_quad(orow + 4 * i, y.x, y.y, y.z, y.w);
     }
   }
 }
