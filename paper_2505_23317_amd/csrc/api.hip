@@ -60,7 +60,7 @@ struct cfdetr_ctx {
   void* tail_packed = nullptr;   // w_o, w_ff1, w_ff2 of every layer in the fused kernel's order
   uint64_t tail_packed_layer = 0;   // bytes per layer; 0: the shape has no fused kernel
   void* head_packed = nullptr;      // w_qkv of the first layer in the same layout
-  void* wide_packed = nullptr;      // the same for width 384 (layer.hip)
+  void* wide_packed = nullptr;      // the same in layer.hip's order
   uint64_t wide_layer = 0;
   void* wide_head = nullptr;
   float* x_blocks = nullptr;        // and its residual rows
@@ -373,8 +373,8 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
     return CFDETR_OK;
   }
   if (ctx->wide_layer) {
-    // width 384: one kernel ahead of the loop and one behind each attention
-    const int mt = wide_layer_tiles(shape.rows ? shape.rows : m_cap, ctx->cus);
+    // widths 256 and 384: one kernel ahead of the loop and one behind each attention
+    const int mt = wide_layer_tiles(d, shape.rows ? shape.rows : m_cap, ctx->cus);
     WideLayerArgs wa{};
     wa.packed = ctx->wide_head;
     wa.x0 = ctx->x;
@@ -861,16 +861,17 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   const uint64_t o_nroi = cv.take((uint64_t)kMaxBatch * 4);
   const uint64_t o_tpad = cv.take((uint64_t)cfg->max_tokens_total * 4);
   const uint64_t o_cupad = cv.take((uint64_t)(kMaxBatch + 1) * 4), o_kvlen = cv.take((uint64_t)kMaxBatch * 4);
-  if (layer_tail_supported((int)d, (int)F, c->bf16))
-    c->tail_packed_layer = layer_tail_packed_bytes((int)d, (int)F);
-  const uint64_t o_pack = cv.take(c->tail_packed_layer * cfg->n_layers);
-  const uint64_t o_hpack = cv.take(c->tail_packed_layer ? 3 * d * d * 2 : 0);
   if (wide_layer_supported((int)d, (int)F, c->bf16, Tm))
     c->wide_layer = wide_layer_packed_bytes((int)d, (int)F, false);
+  else if (layer_tail_supported((int)d, (int)F, c->bf16))
+    c->tail_packed_layer = layer_tail_packed_bytes((int)d, (int)F);
+  // (layer_tail_kernel: feed-forward widths that are no multiple of 256, and past the row limit)
+  const uint64_t o_pack = cv.take(c->tail_packed_layer * cfg->n_layers);
+  const uint64_t o_hpack = cv.take(c->tail_packed_layer ? 3 * d * d * 2 : 0);
   const uint64_t o_wide = cv.take(c->wide_layer * cfg->n_layers);
   const uint64_t o_whead = cv.take(c->wide_layer ? wide_layer_packed_bytes((int)d, (int)F, true) : 0);
   const uint64_t o_xb = cv.take(c->wide_layer ? (Tm + 95) / 96 * 96 * d * 4 : 0);
-  const bool slim = c->bf16 && !c->tail_packed_layer && few_rows_supported((int)d, (int)d) && few_rows_supported((int)F, (int)F);
+  const bool slim = c->bf16 && !c->tail_packed_layer && !(d == 256 && c->wide_layer) && few_rows_supported((int)d, (int)d) && few_rows_supported((int)F, (int)F);
   const uint64_t Lw = cfg->n_layers;
   const uint64_t o_sq = cv.take(slim ? slim_packed_bytes(Lw * 3 * d, d) : 0), o_so = cv.take(slim ? slim_packed_bytes(Lw * d, d) : 0);
   const uint64_t o_s1 = cv.take(slim ? slim_packed_bytes(Lw * F, d) : 0), o_s2 = cv.take(slim ? slim_packed_bytes(Lw * d, F) : 0);

@@ -113,8 +113,8 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
               make_float4(xa[j][0][4 * q], xa[j][0][4 * q + 1], xa[j][0][4 * q + 2], xa[j][0][4 * q + 3]);
     }
     float mean[1], rstd[1];
-    wide_stats(xa, s_red, l32, g, wave, p.eps, mean, rstd);
-    wide_norm_to_lds(xa, mean, rstd, s_vec, s_vec + D, sA, l32, g, wave);
+    wide_stats<4>(xa, s_red, l32, g, wave, p.eps, mean, rstd);
+    wide_norm_to_lds<4>(xa, mean, rstd, s_vec, s_vec + D, sA, l32, g, wave);
 
     f32x16 acc;
 #pragma unroll
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256) void wide_norm_kernel(float* x, const float* l
       xa[j][0][4 * q + 3] = v.w;
     }
   float mean[1], rstd[1];
-  wide_stats(xa, s_red, l32, g, wave, eps, mean, rstd);
+  wide_stats<4>(xa, s_red, l32, g, wave, eps, mean, rstd);
   if (m >= M) return;
   const float shift = -mean[0] * rstd[0];
   const bool second = out2 != nullptr && m >= split_row;

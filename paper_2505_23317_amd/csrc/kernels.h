@@ -225,7 +225,7 @@ hipError_t launch_layer_head(const float* x, const void* packed, const float* ln
                              int B, int d, const int32_t* m_ptr, int m_host, int m_capacity,
                              hipStream_t s);
 
-// The same for width 384 (layer.hip), the first layer's LayerNorm and projection included:
+// The same for widths 256 and 384 (layer.hip), the first layer's LayerNorm and projection included:
 // LayerTailArgs' fields, with O null for that first launch.  It lists the rows' places in vt
 // (vt_pos), which the layers' launches read.  `mt`: 32-row tiles per workgroup (1 to 3, all
 // with the same results); wide_layer_tiles chooses it for the rows expected.
@@ -252,7 +252,7 @@ struct WideLayerArgs {
   int B;
 };
 bool wide_layer_supported(int d, int F, bool use_bf16, uint64_t rows);
-int wide_layer_tiles(int rows, int cus);
+int wide_layer_tiles(int d, int rows, int cus);
 uint64_t wide_layer_packed_bytes(int d, int F, bool head);
 // Wo, W1 and W2 null: the first launch's; Wqkv (the next layer's) null: the last layer's.
 hipError_t launch_wide_pack(const void* Wo, const void* W1, const void* W2, const void* Wqkv, int d,

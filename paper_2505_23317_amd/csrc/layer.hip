@@ -1,21 +1,21 @@
-// Width 384: everything of a layer after attention in one kernel (out-projection, residual,
-// LayerNorm, feed-forward block, residual, the next LayerNorm and the next layer's q/k/v
-// projection), as layer_tail_kernel (gemm.hip) is for width 256.
+// Widths 256 and 384: everything of a layer after attention in one kernel (out-projection,
+// residual, LayerNorm, feed-forward block, residual, the next LayerNorm and the next layer's
+// q/k/v projection).
 #include "kernels.h"
 #include "wide_row.h"
 
 #include <type_traits>
+#include <utility>
 
 namespace cfdetr {
 
 namespace {
 
 constexpr int kRingMax = 24;    // most weight blocks of 1 KB a wavefront holds in registers
-constexpr int kFC = 128;        // hidden units of a chunk: one 32-wide tile per wavefront
 
 struct WideArgs {
   const bf16_t* O;
-  const unsigned char* packed;   // four weight streams, one per wavefront
+  const unsigned char* packed;   // weight streams, one per wavefront
   uint32_t stream;               // bytes of one of them
   const float *b_o, *ln2_g, *ln2_b, *b1, *b2;
   int F;
@@ -41,20 +41,22 @@ struct WideArgs {
 
 // LDS of a workgroup: operand rows, a hidden chunk (its place also serves the row sums and the
 // staging of outputs), and the vectors of the layer.
-template <int D, int MT>
+template <int D, int NW, int MT>
 struct WideLds {
-  static constexpr int kA = MT * 32 * D * 2, kH = MT * 32 * kFC * 2, kStg = 4 * 16 * 208;
+  static constexpr int kFC = 32 * NW;                    // hidden units of a chunk: one 32-wide tile per wavefront
+  static constexpr int kRow = D / NW * 2 + 16;           // staging row: the columns of a wavefront
+  static constexpr int kA = MT * 32 * D * 2, kH = MT * 32 * kFC * 2, kStg = NW * 16 * kRow;
   static constexpr int kHS = kH > kStg ? kH : kStg;
-  static constexpr int kVec = kA + kHS;                  // [b1 or b_qkv][ln2_g][ln2_b][b2][ln_g][ln_b]
-  static int bytes(int F) { return kVec + ((F > 3 * D ? F : 3 * D) + 5 * D) * 4; }
+  static constexpr int kVec = kA + kHS;                  // [b1 or b_qkv][ln2_g][ln2_b][b2][ln_g][ln_b][NW = 8: b_qkv]
+  static int bytes(int F) { return kVec + ((F > 3 * D ? F : 3 * D) + 5 * D + (NW == 8 ? 3 * D : 0)) * 4; }
 };
 
 // What a launch does: the first layer's LayerNorm and projection only, a whole layer, or the
 // last layer (which ends in the final LayerNorm).
 constexpr int kHead = 0, kMid = 1, kLast = 2;
 
-// A workgroup of four wavefronts owns 32 MT complete rows; wavefront w owns columns
-// [w D/4, (w + 1) D/4) of them.  The rows' residuals stay in the accumulators from the first
+// A workgroup of NW wavefronts owns 32 MT complete rows; wavefront w owns columns
+// [w D/NW, (w + 1) D/NW) of them.  The rows' residuals stay in the accumulators from the first
 // product to the last: they start as x + b_o, the out-projection is added on top by its MFMAs,
 // LayerNorm reads them there, b2 and the second feed-forward matrix come on top again.  Per
 // row only O and x are read and x, q, k, v written; as separate kernels the same rows made
@@ -63,7 +65,7 @@ constexpr int kHead = 0, kMid = 1, kLast = 2;
 // order of use, 1 KB per MFMA operand, and stream through a ring of registers that is refilled
 // right behind the MFMA that used a block.  Operand rows and hidden chunk lie in LDS with
 // 16-byte chunks XORed by the row (row lengths are multiples of 256 bytes, all 64 banks).
-// The feed-forward block goes in chunks of 128 hidden units; the activation of chunk c runs
+// The feed-forward block goes in chunks of 32 NW hidden units; the activation of chunk c runs
 // between the MFMAs of the second matrix on chunk c - 1, laid out instruction by instruction
 // (the compiler puts it in front of them otherwise).  Vectors are in LDS because a global load
 // that is waited for waits for the whole ring behind which it was issued.
@@ -75,11 +77,21 @@ constexpr int kHead = 0, kMid = 1, kLast = 2;
 // against q/k/v, out-projection, two LayerNorms and the two feed-forward matrices as kernels
 // of their own: 22,400 rows 168 -> 109 us, 64,000 rows 430 -> 247 us, 3,520 rows 54 -> 43 us,
 // 920 rows 45 -> 42 us (few_rows.hip takes those).
-template <int D, int MT, int kKind>
-__global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArgs p) {
-  constexpr int kRing = MT > 2 ? 24 : 12;   // what the registers of one or two workgroups per CU hold
-  constexpr int NT = D / 128, KS = D / 16, BM = 32 * MT, ROWB = D * 2, HROWB = kFC * 2;
-  using L = WideLds<D, MT>;
+//
+// Width 384 has four wavefronts of 96 columns, width 256 eight of 32: two on each SIMD, so that
+// one's waits (barriers, row sums, the activation's chain of dependent operations) are the
+// other's work.  With four of 64 columns a layer of 1,200 rows took 24 us, with eight 18 us:
+// 1.5 MB of weights per workgroup then come at two thirds of the CU's 64 B/clk.  Encoder passes
+// of 6 layers against layer_tail_kernel (gemm.hip: 32 rows, a split of roles in the feed-forward
+// block): 1,200 rows 224 -> 191 us, 6,400 rows 283 -> 260 us, 11,200 rows 470 -> 344 us,
+// 24,000 rows 857 -> 676 us.
+template <int D, int NW, int MT, int kKind>
+__global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer_kernel(WideArgs p) {
+  using L = WideLds<D, NW, MT>;
+  // what the registers of one or two workgroups per CU hold
+  constexpr int kRing = NW == 8 ? 16 : MT > 2 ? 24 : 12;
+  constexpr int kFC = L::kFC, kThreads = 64 * NW;
+  constexpr int NT = D / (32 * NW), KS = D / 16, BM = 32 * MT, ROWB = D * 2, HROWB = kFC * 2;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* const sA = smem;
   unsigned char* const sH = smem + L::kA;
@@ -92,10 +104,11 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  unsigned char* const stg = smem + L::kA + wave * (16 * 208);
+  unsigned char* const stg = smem + L::kA + wave * (16 * L::kRow);
   float* const v_b1 = reinterpret_cast<float*>(smem + L::kVec);
   float* const v_d = v_b1 + max(p.F, 3 * D);   // five vectors of D
-  const int c0 = wave * (D / 4);
+  float* const v_qkv = NW == 8 ? v_d + 5 * D : v_b1;
+  const int c0 = wave * (D / NW);
 
   int vpos[MT];
 #pragma unroll
@@ -112,9 +125,10 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
 
   // the vectors of the layer
   if (kKind != kHead) {
-    for (int i = tid * 4; i < p.F; i += 1024) *reinterpret_cast<float4*>(v_b1 + i) = *reinterpret_cast<const float4*>(p.b1 + i);
-  } else {
-    for (int i = tid * 4; i < 3 * D; i += 1024) *reinterpret_cast<float4*>(v_b1 + i) = *reinterpret_cast<const float4*>(p.b_qkv + i);
+    for (int i = tid * 4; i < p.F; i += 4 * kThreads) *reinterpret_cast<float4*>(v_b1 + i) = *reinterpret_cast<const float4*>(p.b1 + i);
+  }
+  if (kKind == kHead || (NW == 8 && kKind == kMid)) {
+    for (int i = tid * 4; i < 3 * D; i += 4 * kThreads) *reinterpret_cast<float4*>(v_qkv + i) = *reinterpret_cast<const float4*>(p.b_qkv + i);
   }
   if (tid < D / 4) {
     if (kKind != kHead) {
@@ -147,7 +161,7 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
     // rows of O into sA
     constexpr int UNITS = BM * (ROWB / 16);
 #pragma unroll
-    for (int u0 = 0; u0 < UNITS; u0 += 256) {
+    for (int u0 = 0; u0 < UNITS; u0 += kThreads) {
       const int u = u0 + tid;
       const int row = u / (ROWB / 16), pos = u % (ROWB / 16);
       const int c = (pos & ~15) | ((pos ^ row) & 15);
@@ -230,8 +244,8 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
     WIDE_PRODUCT(acc, NT, KS, sA, ROWB, ao);   // attention output times Wo
-    wide_stats(acc, s_red, l32, g, wave, p.eps, mean, rstd);
-    wide_norm_to_lds(acc, mean, rstd, v_d, v_d + D, sA, l32, g, wave);
+    wide_stats<NW>(acc, s_red, l32, g, wave, p.eps, mean, rstd);
+    wide_norm_to_lds<NW>(acc, mean, rstd, v_d, v_d + D, sA, l32, g, wave);
     // bias of the second FFN matrix
 #pragma unroll
     for (int j = 0; j < NT; ++j)
@@ -288,17 +302,18 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
       {
         constexpr int NM = NT * MT;
         bf16x8 a_[2][MT];
-        float ge[MT][4];
+        // two registers of every hidden tile at a time: V values, nine steps each, step by step,
+        // over TS k-steps
+        constexpr int TS = kFC / 128, V = 2 * MT, OPS = 9 * V, PER = (OPS + NM * TS - 1) / (NM * TS);
+        float ge[MT][4], gx[V], gc[V], gt[V], g2[V];
 #pragma unroll
         for (int i = 0; i < MT; ++i)
           a_[0][i] = *reinterpret_cast<const bf16x8*>(sH + ho[0] + i * (32 * HROWB));
-#pragma unroll
-        for (int t = 0; t < kFC / 16; ++t) {
+        // (t a constant of its own type: the registers below are indexed by it)
+        auto step = [&](auto t_) {
+          constexpr int t = decltype(t_)::value;
           constexpr int UN = kRing / NT;
           if (t % UN == 0) wp += kRing * 1024;
-          // registers 2 t and 2 t + 1 of every hidden tile: V values, nine steps each, step by step
-          constexpr int V = 2 * MT, OPS = 9 * V, PER = (OPS + NM - 1) / NM;
-          float gx[V], gc[V], gt[V], g2[V];
 #pragma unroll
           for (int m = 0; m < NM; ++m) {
             const int j = m / MT, i = m % MT;
@@ -307,9 +322,9 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
               a_[(t + 1) & 1][m] = *reinterpret_cast<const bf16x8*>(sH + ho[(t + 1) & 7] + ((t + 1) / 8) * 256 + m * (32 * HROWB));
             if (i == MT - 1) wr[(t % UN) * NT + j] = next_block((t % UN) * NT + j);
 #pragma unroll
-            for (int o = m * PER; o < (m + 1) * PER && o < OPS; ++o) {
+            for (int o = (t % TS * NM + m) * PER; o < (t % TS * NM + m + 1) * PER && o < OPS; ++o) {
               const int s = o / V, v = o % V;
-              const int vi = v / 2, r = 2 * t + v % 2;
+              const int vi = v / 2, r = 2 * (t / TS) + v % 2;
               if (s == 0) {
                 gx[v] = hid[0][vi][r];
                 asm volatile("" : "+v"(gx[v]));
@@ -349,20 +364,22 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
             }
             __builtin_amdgcn_sched_barrier(0);
           }
-        }
+        };
+        [&]<int... kT>(std::integer_sequence<int, kT...>) { (step(std::integral_constant<int, kT>{}), ...); }
+        (std::make_integer_sequence<int, kFC / 16>{});
       }
       __syncthreads();
     }
     put_hidden();
     __syncthreads();
     float4 bq[2];
-    if (kKind == kMid) {
+    if (NW == 4 && kKind == kMid) {
       // the next projection's bias takes the place of b1 (everybody is done with that)
 #pragma unroll
       for (int k = 0; k < 2; ++k) bq[k] = *reinterpret_cast<const float4*>(p.b_qkv + min(tid * 4 + k * 1024, 3 * D - 4));
     }
     WIDE_PRODUCT(acc, NT, kFC / 16, sH, HROWB, ho);
-    if (kKind == kMid) {
+    if (NW == 4 && kKind == kMid) {
 #pragma unroll
       for (int k = 0; k < 2; ++k)
         if (tid * 4 + k * 1024 < 3 * D) *reinterpret_cast<float4*>(v_b1 + tid * 4 + k * 1024) = bq[k];
@@ -385,7 +402,7 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
               f32x4{acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
       }
   }
-  wide_stats(acc, s_red, l32, g, wave, p.eps, mean, rstd);
+  wide_stats<NW>(acc, s_red, l32, g, wave, p.eps, mean, rstd);
   if (kKind == kLast) {
 #pragma unroll
     for (int j = 0; j < NT; ++j)
@@ -410,7 +427,7 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
       }
     return;
   }
-  wide_norm_to_lds(acc, mean, rstd, v_d + 3 * D, v_d + 4 * D, sA, l32, g, wave);
+  wide_norm_to_lds<NW>(acc, mean, rstd, v_d + 3 * D, v_d + 4 * D, sA, l32, g, wave);
   // q, k, v of these rows
 #pragma nounroll
   for (int part = 0; part < 3; ++part) {
@@ -418,7 +435,7 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
     for (int j = 0; j < NT; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const float4 b = *reinterpret_cast<const float4*>(v_b1 + part * D + c0 + j * 32 + 8 * q + 4 * g);
+        const float4 b = *reinterpret_cast<const float4*>(v_qkv + part * D + c0 + j * 32 + 8 * q + 4 * g);
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
           acc[j][i][4 * q] = b.x;
@@ -434,20 +451,20 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
       for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
-          // 16 rows x 96 columns at a time through the wavefront's staging rows
+          // 16 rows x the columns of a wavefront at a time through the wavefront's staging rows
           if ((l32 >> 4) == half) {
 #pragma unroll
             for (int j = 0; j < NT; ++j)
 #pragma unroll
               for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<uint2*>(stg + (l32 & 15) * 208 + j * 64 + q * 16 + g * 8) =
+                *reinterpret_cast<uint2*>(stg + (l32 & 15) * L::kRow + j * 64 + q * 16 + g * 8) =
                     make_uint2(pack_bf16x2(acc[j][i][4 * q] * sc, acc[j][i][4 * q + 1] * sc),
                                pack_bf16x2(acc[j][i][4 * q + 2] * sc, acc[j][i][4 * q + 3] * sc));
           }
 #pragma unroll
-          for (int t = 0; t < 3; ++t) {
-            const int u = t * 64 + lane, row = u / 12, c = u % 12;
-            const uint4 v = *reinterpret_cast<const uint4*>(stg + row * 208 + c * 16);
+          for (int t = 0; t < NT; ++t) {
+            const int u = t * 64 + lane, row = u / (4 * NT), c = u % (4 * NT);
+            const uint4 v = *reinterpret_cast<const uint4*>(stg + row * L::kRow + c * 16);
             const int m = m0 + i * 32 + half * 16 + row;
             if (m < M)
               *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(p.qk + part * D + c0) +
@@ -478,20 +495,20 @@ __global__ __launch_bounds__(256, MT > 2 ? 1 : 2) void wide_layer_kernel(WideArg
 
 // The weights of a layer in the order the wavefronts stream them (see wide_layer_kernel).
 // One thread per 16 bytes; with Wo null only the q/k/v part (the first layer's kernel).
-template <int D>
+template <int D, int NW>
 __global__ __launch_bounds__(256) void wide_pack_kernel(const bf16_t* __restrict__ Wo, const bf16_t* __restrict__ W1,
                                                         const bf16_t* __restrict__ W2, const bf16_t* __restrict__ Wqkv,
                                                         int F, int blocks, bf16_t* __restrict__ out) {
-  constexpr int NT = D / 128, KS = D / 16;
+  constexpr int NT = D / (32 * NW), KS = D / 16, kFC = 32 * NW;
   const long u = (long)blockIdx.x * 256 + threadIdx.x;
-  if (u >= (long)blocks * 4 * 64) return;
+  if (u >= (long)blocks * NW * 64) return;
   const int lane = (int)(u & 63), l32 = lane & 31, g = lane >> 5;
   const long blk = u >> 6;
   const int w = (int)(blk / blocks);
   int b = (int)(blk % blocks);
   const int nc = F / kFC;
   const bf16_t* src = nullptr;
-  const int c0 = w * (D / 4);
+  const int c0 = w * (D / NW);
   bool done = false;
   if (Wo != nullptr) {
     if (b < KS * NT) {
@@ -525,10 +542,10 @@ __global__ __launch_bounds__(256) void wide_pack_kernel(const bf16_t* __restrict
   if (src) reinterpret_cast<uint4*>(out)[u] = *reinterpret_cast<const uint4*>(src);
 }
 
-template <int D, int MT, int kKind>
+template <int D, int NW, int MT, int kKind>
 hipError_t launch_wide(const WideArgs& p, int m_capacity, hipStream_t s) {
-  auto kern = wide_layer_kernel<D, MT, kKind>;
-  const size_t lds = WideLds<D, MT>::bytes(p.F);
+  auto kern = wide_layer_kernel<D, NW, MT, kKind>;
+  const size_t lds = WideLds<D, NW, MT>::bytes(p.F);
   static bool configured = false;
   if (!configured) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -536,45 +553,66 @@ hipError_t launch_wide(const WideArgs& p, int m_capacity, hipStream_t s) {
     if (e != hipSuccess) return e;
     configured = true;
   }
-  hipLaunchKernelGGL(kern, dim3((m_capacity + 32 * MT - 1) / (32 * MT)), dim3(256), lds, s, p);
+  hipLaunchKernelGGL(kern, dim3((m_capacity + 32 * MT - 1) / (32 * MT)), dim3(64 * NW), lds, s, p);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// F: the vectors of a layer have to fit beside the tiles of two workgroups per CU.  Rows: the
+// F: whole hidden chunks, and the vectors of a layer have to fit beside the tiles of the
+// workgroups of a CU.  Rows: the
 // kernel addresses rows of x and of q/k/v with 32-bit byte offsets.
 bool wide_layer_supported(int d, int F, bool use_bf16, uint64_t rows) {
-  return use_bf16 && d == 384 && F % kFC == 0 && F <= 2048 && rows * 6 * d < (1ull << 32);
+  return use_bf16 && ((d == 256 && F % 256 == 0) || (d == 384 && F % 128 == 0)) && F <= 2048 && rows * 6 * d < (1ull << 32);
 }
 
+static int wide_waves(int d) { return d == 256 ? 8 : 4; }
+
 static int wide_blocks(int d, int F, bool head) {
-  const int nt = d / 128, ks = d / 16, nc = F / kFC;
-  return (head ? 0 : ks * nt + nc * (ks + (kFC / 16) * nt)) + 3 * ks * nt;
+  const int nw = wide_waves(d), nt = d / (32 * nw), ks = d / 16, nc = F / (32 * nw);
+  return (head ? 0 : ks * nt + nc * (ks + 2 * nw * nt)) + 3 * ks * nt;
 }
 
 uint64_t wide_layer_packed_bytes(int d, int F, bool head) {
-  return ((uint64_t)wide_blocks(d, F, head) * 4 + kRingMax) * 1024;   // (the ring reads ahead of the end)
+  return ((uint64_t)wide_blocks(d, F, head) * wide_waves(d) + kRingMax) * 1024;   // (the ring reads ahead of the end)
 }
 
 hipError_t launch_wide_pack(const void* Wo, const void* W1, const void* W2, const void* Wqkv, int d, int F,
                             void* packed, hipStream_t s) {
-  if (d != 384) return hipErrorInvalidValue;
+  if (d != 256 && d != 384) return hipErrorInvalidValue;
   const int blocks = wide_blocks(d, F, Wo == nullptr);
-  const long units = (long)blocks * 4 * 64;
+  const long units = (long)blocks * wide_waves(d) * 64;
   auto a = [](const void* q) { return static_cast<const bf16_t*>(q); };
-  hipLaunchKernelGGL(wide_pack_kernel<384>, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s, a(Wo), a(W1), a(W2),
+  hipLaunchKernelGGL((d == 256 ? wide_pack_kernel<256, 8> : wide_pack_kernel<384, 4>), dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s, a(Wo), a(W1), a(W2),
                      a(Wqkv), F, blocks, static_cast<bf16_t*>(packed));
   return hipGetLastError();
 }
 
 // Rows per workgroup, by the rows expected (a guess is enough: every height gives the same
-// bits).  One workgroup per CU is the fastest there is, so the lowest tile that gets by with
+// bits).  Width 384: one workgroup per CU is the fastest there is, so the lowest tile that gets by with
 // that; a workgroup of 96 rows has a CU to itself, one of 64 shares it with a second one,
 // whose vector work then runs under its MFMAs, and is the best where CUs get several.
 // Encoder passes of 12 layers in us, at 32 / 64 / 96 rows: 5,669 rows 1131 / 1314 / 1616;
 // 11,248 rows 1776 / 1689 / 1985; 22,421 rows 2809 / 2673 / 2566; 33,729 rows 4491 / 4115 / 4299.
-int wide_layer_tiles(int rows, int cus) {
+//
+// Width 256: a workgroup of eight wavefronts fills a CU at every height, so the rounds of the
+// busiest CU times what one costs (19, 26 and 36 us a layer) decide.  Encoder passes of 6 layers
+// in us, at 32 / 64 / 96 rows: 8,000 rows 279 / 302 / 365; 11,200 rows 413 / 344 / 408;
+// 16,000 rows 512 / 454 / 496; 24,000 rows 779 / 739 / 676.
+int wide_layer_tiles(int d, int rows, int cus) {
+  if (d == 256) {
+    const int cost[3] = {19, 26, 36};
+    int best = 1;
+    long least = 0;
+    for (int mt = 1; mt <= 3; ++mt) {
+      const long rounds = ((long)rows + 32L * mt * cus - 1) / (32L * mt * cus), t = rounds * cost[mt - 1];
+      if (mt == 1 || t < least) {
+        best = mt;
+        least = t;
+      }
+    }
+    return best;
+  }
   for (int mt = 1; mt <= 3; ++mt)
     if (rows <= 32 * mt * cus) return mt;
   return 2;
@@ -615,8 +653,11 @@ hipError_t launch_wide_layer(const WideLayerArgs& a, int d, int F, int mt, const
   p.m_host = m_host;
   auto kind = [&](auto tiles) {
     constexpr int MT = decltype(tiles)::value;
-    return head ? launch_wide<384, MT, kHead>(p, m_capacity, s)
-                : a.last ? launch_wide<384, MT, kLast>(p, m_capacity, s) : launch_wide<384, MT, kMid>(p, m_capacity, s);
+    if (d == 256)
+      return head ? launch_wide<256, 8, MT, kHead>(p, m_capacity, s)
+                  : a.last ? launch_wide<256, 8, MT, kLast>(p, m_capacity, s) : launch_wide<256, 8, MT, kMid>(p, m_capacity, s);
+    return head ? launch_wide<384, 4, MT, kHead>(p, m_capacity, s)
+                : a.last ? launch_wide<384, 4, MT, kLast>(p, m_capacity, s) : launch_wide<384, 4, MT, kMid>(p, m_capacity, s);
   };
   return mt >= 3 ? kind(std::integral_constant<int, 3>{})
                  : mt == 2 ? kind(std::integral_constant<int, 2>{}) : kind(std::integral_constant<int, 1>{});

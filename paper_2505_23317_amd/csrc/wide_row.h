@@ -24,14 +24,15 @@ __device__ __forceinline__ float gelu_sig(float x) {
 // instead would have every load touch 32 rows with 32 bytes each: 3 us for the rows of a
 // workgroup when it is alone, 10 us with all CUs at it.
 
-// Mean and 1/sigma of 32 MT rows that a workgroup of four wavefronts holds as MFMA results:
-// wavefront w has columns [w D/4, (w + 1) D/4), D = 128 NT.  Each quarter's squares are taken
-// about the quarter's own mean and put together exactly.  (Fused multiply-adds are written
+// Mean and 1/sigma of 32 MT rows that a workgroup of NW (four or eight) wavefronts holds as
+// MFMA results: wavefront w has columns [w D/NW, (w + 1) D/NW), D = 32 NT NW.  Each part's
+// squares are taken about the part's own mean and put together exactly.  (Fused multiply-adds are written
 // out: left to the compiler they would differ between kernels, and so would the bits.)
-template <int NT, int MT>
+template <int NW, int NT, int MT>
 __device__ __forceinline__ void wide_stats(const f32x16 (&acc)[NT][MT], float* s_red, int l32, int g, int wave, float eps,
                                            float (&mean)[MT], float (&rstd)[MT]) {
-  constexpr int D = 128 * NT;
+  constexpr int D = 32 * NT * NW;
+  constexpr float kInvN = (float)NW / D;   // of a part's columns
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     float s = 0.f;
@@ -46,36 +47,45 @@ __device__ __forceinline__ void wide_stats(const f32x16 (&acc)[NT][MT], float* s
     for (int j = 0; j < NT; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float e = fmaf(s, -4.0f / D, acc[j][i][r]);
+        const float e = fmaf(s, -kInvN, acc[j][i][r]);
         v = fmaf(e, e, v);
       }
     v += __shfl_xor(v, 32, kWave);
     if (g == 0) {
-      s_red[(i * 32 + l32) * 8 + wave] = s;
-      s_red[(i * 32 + l32) * 8 + 4 + wave] = v;
+      s_red[(i * 32 + l32) * (2 * NW) + wave] = s;
+      s_red[(i * 32 + l32) * (2 * NW) + NW + wave] = v;
     }
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
-    const float4 s = *reinterpret_cast<const float4*>(s_red + (i * 32 + l32) * 8);
-    const float4 v = *reinterpret_cast<const float4*>(s_red + (i * 32 + l32) * 8 + 4);
-    mean[i] = ((s.x + s.y) + (s.z + s.w)) * (1.0f / D);
-    const float d0 = fmaf(mean[i], -(D / 4), s.x), d1 = fmaf(mean[i], -(D / 4), s.y);
-    const float d2 = fmaf(mean[i], -(D / 4), s.z), d3 = fmaf(mean[i], -(D / 4), s.w);
-    const float between = fmaf(d0, d0, d1 * d1) + fmaf(d2, d2, d3 * d3);
-    const float within = (v.x + v.y) + (v.z + v.w);
-    rstd[i] = rsqrtf(fmaf(fmaf(between, 4.0f / D, within), 1.0f / D, eps));
+    const float4* const part = reinterpret_cast<const float4*>(s_red + (i * 32 + l32) * (2 * NW));
+    float sum = 0.f, within = 0.f, between = 0.f;
+#pragma unroll
+    for (int k = 0; k < NW / 4; ++k) {
+      const float4 s = part[k], v = part[NW / 4 + k];
+      sum += (s.x + s.y) + (s.z + s.w);
+      within += (v.x + v.y) + (v.z + v.w);
+    }
+    mean[i] = sum * (1.0f / D);
+#pragma unroll
+    for (int k = 0; k < NW / 4; ++k) {
+      const float4 s = part[k];
+      const float d0 = fmaf(mean[i], -(D / NW), s.x), d1 = fmaf(mean[i], -(D / NW), s.y);
+      const float d2 = fmaf(mean[i], -(D / NW), s.z), d3 = fmaf(mean[i], -(D / NW), s.w);
+      between += fmaf(d0, d0, d1 * d1) + fmaf(d2, d2, d3 * d3);
+    }
+    rstd[i] = rsqrtf(fmaf(fmaf(between, kInvN, within), 1.0f / D, eps));
   }
 }
 
 // The normalised rows in bf16 to LDS: rows of D, 16-byte chunks XORed by the row.  Ends with
 // a barrier.
-template <int NT, int MT>
+template <int NW, int NT, int MT>
 __device__ __forceinline__ void wide_norm_to_lds(const f32x16 (&acc)[NT][MT], const float (&mean)[MT], const float (&rstd)[MT],
                                                  const float* gain, const float* offs, unsigned char* sA, int l32, int g,
                                                  int wave) {
-  constexpr int D = 128 * NT;
+  constexpr int D = 32 * NT * NW;
   float shift[MT];
 #pragma unroll
   for (int i = 0; i < MT; ++i) shift[i] = -mean[i] * rstd[i];
@@ -83,10 +93,10 @@ __device__ __forceinline__ void wide_norm_to_lds(const f32x16 (&acc)[NT][MT], co
   for (int j = 0; j < NT; ++j)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int col = wave * (D / 4) + j * 32 + 8 * q + 4 * g;
+      const int col = wave * (D / NW) + j * 32 + 8 * q + 4 * g;
       const float4 ga = *reinterpret_cast<const float4*>(gain + col);
       const float4 of = *reinterpret_cast<const float4*>(offs + col);
-      const int chunk = (wave * (D / 4) >> 3) + j * 4 + q;
+      const int chunk = (wave * (D / NW) >> 3) + j * 4 + q;
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         const float r0 = fmaf(fmaf(acc[j][i][4 * q], rstd[i], shift[i]), ga.x, of.x);

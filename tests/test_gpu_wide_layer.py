@@ -1,4 +1,4 @@
-"""The fused layer kernel of width 384: workgroups of 32, 64 and 96 rows (chosen by the number of
+"""The fused layer kernel of widths 256 and 384: workgroups of 32, 64 and 96 rows (chosen by the number of
 rows) give every row the same bits, down to a single row, for feed-forward blocks of one hidden
 chunk, several, and as many as it takes; and they give what the oracle gives.  899 tokens a frame
 (rows no tile height divides): one frame is in the first range of the rule, 10, 19 and 28 frames
@@ -49,6 +49,33 @@ def test_few_rows(rows):
     cfg = synth.Config("narrow", 1, 8 * rows[0], 8 * rows[1], (8,), 384, 6, 1, 256, "bf16", box_rule="poisson")
     w = synth.make_weights(cfg, 9)
     images = synth.bf16_round(np.random.default_rng(5).normal(0.5, 0.25, (1, 3, cfg.H, cfg.W)).astype(np.float32))
+    y = _coarse(cfg, w, images)[0].cpu().numpy()
+    ref = np.asarray(O.coarse_encode(images, cfg.patch, w, cfg.heads)[-1]).reshape(-1, cfg.d)
+    assert float(np.abs(y - ref).max() / np.abs(ref).max()) <= BAR
+
+
+@pytest.mark.parametrize("ffn, frames", [(256, 10), (1024, 19), (2048, 28)])
+def test_rows_per_workgroup_at_width_256(ffn, frames):
+    """One frame has workgroups of 32 rows, 10 and 28 frames of 64, 19 frames of 96."""
+    import torch
+
+    cfg = synth.Config("wide256", frames, 232, 248, (8,), 256, 8, 2, ffn, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 11)
+    rng = np.random.default_rng(4)
+    images = synth.bf16_round(rng.normal(0.5, 0.25, (frames, 3, cfg.H, cfg.W)).astype(np.float32))
+    many = _coarse(cfg, w, images)
+    assert torch.isfinite(many).all()
+    for f in (0, frames - 1):
+        assert torch.equal(_coarse(synth.replace(cfg, B=1), w, images[f:f + 1])[0], many[f]), f
+    ref = np.asarray(O.coarse_encode(images[:1], cfg.patch, w, cfg.heads)[-1]).reshape(-1, cfg.d)
+    assert float(np.abs(many[0].cpu().numpy() - ref).max() / np.abs(ref).max()) <= BAR
+
+
+@pytest.mark.parametrize("rows", [(1, 1), (1, 31), (3, 11), (5, 13)])
+def test_few_rows_at_width_256(rows):
+    cfg = synth.Config("narrow256", 1, 8 * rows[0], 8 * rows[1], (8,), 256, 8, 1, 512, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 13)
+    images = synth.bf16_round(np.random.default_rng(6).normal(0.5, 0.25, (1, 3, cfg.H, cfg.W)).astype(np.float32))
     y = _coarse(cfg, w, images)[0].cpu().numpy()
     ref = np.asarray(O.coarse_encode(images, cfg.patch, w, cfg.heads)[-1]).reshape(-1, cfg.d)
     assert float(np.abs(y - ref).max() / np.abs(ref).max()) <= BAR
