@@ -9,9 +9,10 @@
 //     (l == finest or it is not hit itself): no recursion needed;
 //   * a frame has N0 + 3 * (number of hit cells) tokens, and 4*S(l-1) - S(l) of them
 //     at level l, with S(l) the hit cells of level l, S(finest) = 0, 4*S(-1) := N0.
-// Kernel 1 tests every non-finest cell against the boxes of its frame (kBoxLanes
-// threads share a cell, each taking every kBoxLanes-th box) and raises the cell's
-// flag; kernel 2 counts the flags of all frames (offsets), then compacts the tokens
+// One kernel (select_kernel) as long as a bit per non-finest cell of all frames fits the LDS.
+// Larger pyramids take two: kernel 1 tests every non-finest cell against the boxes of its
+// frame (kBoxLanes threads share a cell, each taking every kBoxLanes-th box) and raises the
+// cell's flag; kernel 2 counts the flags of all frames (offsets), then compacts the tokens
 // of its own frame with wavefront ballots and popcount prefix sums, and clears the
 // flag array that the NEXT call will use (two arrays alternate), so no memset is
 // ever needed.
@@ -71,15 +72,33 @@ __global__ __launch_bounds__(kHitThreads) void select_hit_kernel(
 // items, which is what cap8 provides.
 constexpr int kMaxHeads = 32;
 
+// Inclusive sum over the lanes of a wavefront: inside the rows of 16 lanes, then the last lane
+// of row 0 and 2 to the row behind, then that of row 1 to the upper half.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+  return v;
+}
+
+__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, kWave - 1); }
+
 // The plan proper: the lengths of the nseq sequences are in s_len (shared, published by a
 // barrier); all threads of a workgroup of at least 2 * kMaxBatch threads call it.
 __device__ __forceinline__ void plan_body(const PlanArgs& p, int nseq, const int* s_len, bool gated) {
   __shared__ int s_order[2 * kMaxBatch];
   __shared__ int s_gstart[2 * kMaxBatch * kMaxHeads];
   __shared__ int s_count[8];
-  __shared__ int s_cu[2 * kMaxBatch], s_pcu[2 * kMaxBatch];
+  __shared__ int s_cu[2 * kMaxBatch + 1], s_pcu[2 * kMaxBatch + 1];
   const int tid = threadIdx.x;
-  const int heads = p.heads, block_q = p.block_q, cap8 = p.cap8;
+  // (no integer divisions: the kernel's time is latency, the way of its code to the CU included)
+  const int heads = p.heads, cap8 = p.cap8, log_q = 31 - __clz(p.block_q);   // block_q: a power of two
+  const float per_head = 1.0f / heads;
+  auto sequence = [&](int G) { return s_order[(int)((G + 0.5f) * per_head)]; };   // (of at most 4096 groups)
+  auto tiles = [&](int f) { return (s_len[f] + p.block_q - 1) >> log_q; };
   int4* const items4 = reinterpret_cast<int4*>(p.items);
   if (tid < nseq) {
     const int len = s_len[tid];
@@ -92,33 +111,49 @@ __device__ __forceinline__ void plan_body(const PlanArgs& p, int nseq, const int
   }
   __syncthreads();
   const int ngroups = nseq * heads;
-  if (tid < 8) {   // XCD tid: slots of its groups
+  const int lane = tid & (kWave - 1), wave = tid / kWave, waves = blockDim.x / kWave;
+  for (int x = wave; x < 8; x += waves) {   // XCD x: slots of its groups, 64 at a time
     int pos = 0;
-    for (int G = tid; G < ngroups; G += 8) {
-      s_gstart[G] = pos;
-      pos += (s_len[s_order[G / heads]] + block_q - 1) / block_q;
+    for (int G0 = x; G0 < ngroups; G0 += 8 * kWave) {
+      const int G = G0 + 8 * lane;
+      const int nt = G < ngroups ? tiles(sequence(G)) : 0;
+      const int end = wave_scan(nt);
+      if (G < ngroups) s_gstart[G] = pos + end - nt;
+      pos += last_lane(end);
     }
-    s_count[tid] = gated ? 0 : min(pos, cap8);
+    if (lane == 0) s_count[x] = gated ? 0 : min(pos, cap8);
   }
-  if (tid == 8) {
+  if (wave == waves - 1) {
     int pos = 0, ppos = 0;
-    for (int i = 0; i < nseq; ++i) {
-      p.cu_all[i] = pos;
-      p.pcu[i] = ppos;
-      s_cu[i] = pos;
-      s_pcu[i] = ppos;
-      pos += s_len[i];
-      ppos += (s_len[i] + 63) & ~63;
+    for (int i0 = 0; i0 < nseq; i0 += kWave) {
+      const int i = i0 + lane;
+      const int len = i < nseq ? s_len[i] : 0, plen = (len + 63) & ~63;
+      const int end = wave_scan(len), pend = wave_scan(plen);
+      if (i < nseq) {
+        s_cu[i] = pos + end - len;
+        s_pcu[i] = ppos + pend - plen;
+      }
+      pos += last_lane(end);
+      ppos += last_lane(pend);
     }
-    p.cu_all[nseq] = pos;
-    p.pcu[nseq] = ppos;
-    *p.m_all = pos;
-    if (p.m_seen != nullptr) *p.m_seen = pos;
+    if (lane == 0) {
+      s_cu[nseq] = pos;
+      s_pcu[nseq] = ppos;
+    }
   }
   __syncthreads();
+  // (stores behind the barrier, which would wait for them; m_seen is in host memory)
+  for (int i = tid; i <= nseq; i += blockDim.x) {
+    p.cu_all[i] = s_cu[i];
+    p.pcu[i] = s_pcu[i];
+  }
+  if (tid == 0) {
+    *p.m_all = s_cu[nseq];
+    if (p.m_seen != nullptr) *p.m_seen = s_cu[nseq];
+  }
   for (int G = tid; G < ngroups; G += blockDim.x) {   // one thread per group
-    const int f = s_order[G / heads], h = G % heads, x = G & 7;
-    const int nt = (s_len[f] + block_q - 1) / block_q;
+    const int at = (int)((G + 0.5f) * per_head), f = s_order[at], h = G - at * heads, x = G & 7;
+    const int nt = tiles(f);
     const int j0 = s_gstart[G];
     for (int q = 0; q < nt && j0 + q < cap8; ++q)
       items4[8 * (j0 + q) + x] = make_int4((f << 24) | (h << 19) | q, s_cu[f], s_len[f], s_pcu[f]);
@@ -295,6 +330,162 @@ __global__ __launch_bounds__(kCompactThreads) void select_compact_kernel(
   }
 }
 
+// The bit maps of one frame: 32 columns a word, rows of whole words, level after level.
+__host__ __device__ inline int row_words(const Pyramid& pyr, int level) { return (pyr.cols[level] + 31) >> 5; }
+
+// 16 bits to 32, every bit twice (a parent's columns to its children's).
+__device__ __forceinline__ uint32_t twice(uint32_t x) {
+  x = (x | (x << 8)) & 0x00ff00ffu;
+  x = (x | (x << 4)) & 0x0f0f0f0fu;
+  x = (x | (x << 2)) & 0x33333333u;
+  x = (x | (x << 1)) & 0x55555555u;
+  return x | (x << 1);
+}
+
+// The whole selection: workgroup f does frame f, workgroup B (if there) makes the plan.
+// A token's place depends on all frames, so every workgroup needs the hit cells of all of
+// them, and two kernels with the flags in memory between them spent their time on launches
+// and on memory's latency (a trip per 1024 cells).  Painting the boxes is cheap enough to do
+// in every workgroup instead: eight lanes a box, one row each, an OR per 32 cells into a bit
+// map in LDS.  Counts are popcounts of words; the tokens of a level's word are the children of
+// the parents' bits without the word's own, so one scan over the words of the frame gives
+// every token its place.
+// Measured, two kernels / this one: six frames of 640 x 640 10.4 / 7.8 us, twelve of three
+// levels at 1024 x 1024 with the plan 28 / 9 us.
+constexpr int kPaintLanes = 8;
+constexpr int kSelectLds = 96 * 1024;   // most of its dynamic LDS (the plan's tables take 20 KB)
+
+__global__ __launch_bounds__(kCompactThreads) void select_kernel(
+    Pyramid pyr, const int32_t* __restrict__ boxes, const uint8_t* __restrict__ tier,
+    const int32_t* __restrict__ box_offsets, int B, int frame_words, int leaf_words, int max_tokens,
+    int32_t* __restrict__ tok_desc, int32_t* __restrict__ cu_seqlens, int32_t* __restrict__ level_counts,
+    int32_t* __restrict__ err_flag, const int32_t* __restrict__ hard, PlanArgs plan) {
+  extern __shared__ uint32_t s_select[];
+  uint32_t* const s_bits = s_select;                        // [B][frame_words] hit cells
+  uint32_t* const s_leaf = s_bits + B * frame_words;        // [leaf_words] tokens of this frame,
+  int* const s_before = reinterpret_cast<int*>(s_leaf + leaf_words);   // those in front of the word,
+  int* const s_desc = s_before + leaf_words;                // descriptor of its first column
+  __shared__ int s_split[kMaxBatch][kMaxLevels];            // hit cells per (frame, level)
+  __shared__ int s_wave[kCompactThreads / kWave];
+  const int frame = blockIdx.x, tid = threadIdx.x, n = pyr.n_levels;
+  const int lane = tid & (kWave - 1), wave = tid / kWave;
+
+  // threads of a frame: 1024 over the next power of two of B
+  const int per_frame = kCompactThreads >> (B > 1 ? 32 - __clz(B - 1) : 0);
+  const int pf = tid / per_frame;
+  int lo = 0, hi = 0;
+  if (pf < B) {
+    lo = box_offsets[pf];
+    hi = box_offsets[pf + 1];
+  }
+  const bool easy = hard != nullptr && lane < B && hard[lane] == 0;
+  for (int i = tid; i < B * frame_words; i += kCompactThreads) s_bits[i] = 0;
+  for (int i = tid; i < kMaxBatch * kMaxLevels; i += kCompactThreads) (&s_split[0][0])[i] = 0;
+  __syncthreads();
+  for (int b = lo + (tid % per_frame) / kPaintLanes; b < hi; b += per_frame / kPaintLanes) {
+    const int4 raw = *reinterpret_cast<const int4*>(boxes + 4 * (size_t)b);
+    const int levels = min((int)tier[b], n - 1);   // those that the box splits
+    const int x0 = max(raw.x, 0), y0 = max(raw.y, 0);
+    const int x1 = min(raw.z, pyr.img_w), y1 = min(raw.w, pyr.img_h);
+    if (x1 <= x0 || y1 <= y0) continue;
+    uint32_t* map = s_bits + pf * frame_words;
+    for (int l = 0; l < levels; ++l) {
+      const int shift = __ffs(pyr.patch[l]) - 1, words = row_words(pyr, l);
+      const int c0 = x0 >> shift, c1 = (x1 - 1) >> shift, r1 = (y1 - 1) >> shift;
+      for (int r = (y0 >> shift) + (tid & (kPaintLanes - 1)); r <= r1; r += kPaintLanes)
+        for (int w = c0 >> 5; w <= c1 >> 5; ++w) {
+          const uint32_t from = w == c0 >> 5 ? ~0u << (c0 & 31) : ~0u;
+          const uint32_t to = w == c1 >> 5 ? ~0u >> (31 - (c1 & 31)) : ~0u;
+          atomicOr(&map[r * words + w], from & to);
+        }
+      map += pyr.rows[l] * words;
+    }
+  }
+  __syncthreads();
+  const int words0 = pyr.rows[0] * row_words(pyr, 0);   // of the coarsest level
+  for (int i = tid; i < B * frame_words; i += kCompactThreads) {
+    const int hits = __popc(s_bits[i]);
+    if (hits) {
+      const int f = i / frame_words;
+      atomicAdd(&s_split[f][i - f * frame_words >= words0 ? 1 : 0], hits);
+    }
+  }
+  if (frame < B) {
+    const uint32_t* const map = s_bits + frame * frame_words;
+    int running = 0;
+    for (int start = 0; start < leaf_words; start += kCompactThreads) {
+      const int i = start + tid;
+      uint32_t leaf = 0;
+      if (i < leaf_words) {
+        int l = 0, first = 0, before = 0;   // level, its first word, the first of the level before
+        while (i >= first + pyr.rows[l] * row_words(pyr, l)) {
+          before = first;
+          first += pyr.rows[l] * row_words(pyr, l);
+          ++l;
+        }
+        const int words = row_words(pyr, l), row = (i - first) / words, w = (i - first) - row * words;
+        const int rest = pyr.cols[l] - w * 32;
+        leaf = rest < 32 ? (1u << rest) - 1 : ~0u;
+        if (l > 0) leaf &= twice((map[before + (row >> 1) * row_words(pyr, l - 1) + (w >> 1)] >> (16 * (w & 1))) & 0xffffu);
+        if (l + 1 < n) leaf &= ~map[i];
+        s_leaf[i] = leaf;
+        s_desc[i] = (l << 28) | (row << 14) | (w * 32);
+      }
+      const int mine = __popc(leaf), end = wave_scan(mine);
+      if (lane == kWave - 1) s_wave[wave] = end;
+      __syncthreads();
+      int wave_off = 0, chunk = 0;
+      for (int w = 0; w < kCompactThreads / kWave; ++w) {
+        const int c = s_wave[w];
+        if (w < wave) wave_off += c;
+        chunk += c;
+      }
+      if (i < leaf_words) s_before[i] = running + wave_off + end - mine;
+      running += chunk;
+      __syncthreads();
+    }
+  } else {
+    __syncthreads();
+  }
+  // tokens of frame `lane` (kMaxBatch is a wavefront), and those in front of it.  A frame
+  // marked easy (hard given and 0 for it) has no fine stage: no token at all.
+  int tokens = 0;
+  if (lane < B && !easy) {
+    tokens = pyr.rows[0] * pyr.cols[0];
+    for (int l = 0; l + 1 < n; ++l) tokens += 3 * s_split[lane][l];
+  }
+  const int lower = wave_scan(tokens & 0xffff), upper = wave_scan(tokens >> 16);   // (the sum may pass 32 bits)
+  const long long total = ((long long)last_lane(upper) << 16) + last_lane(lower);
+  const bool overflow = total > (long long)max_tokens;   // then every length is 0
+  if (frame >= B) {
+    __shared__ int s_len[2 * kMaxBatch];
+    if (wave == 0) {
+      for (int i = lane; i < plan.n_prefix; i += kWave) s_len[i] = plan.prefix_len;
+      if (lane < B) s_len[plan.n_prefix + lane] = overflow ? 0 : tokens;
+    }
+    __syncthreads();
+    plan_body(plan, plan.n_prefix + B, s_len, false);
+    return;
+  }
+  const int base = __builtin_amdgcn_readlane((upper << 16) + lower - tokens, frame);   // (right where nothing overflows)
+  const bool skipped = __builtin_amdgcn_readlane((int)easy, frame) != 0;
+  if (tid == 0) {
+    cu_seqlens[frame] = overflow ? 0 : base;
+    if (frame == B - 1) cu_seqlens[B] = overflow ? 0 : (int)total;
+    if (overflow && frame == 0) *err_flag = 1;
+  }
+  if (level_counts != nullptr && tid < n) {
+    const int prev4 = tid == 0 ? pyr.rows[0] * pyr.cols[0] : 4 * s_split[frame][tid - 1];
+    const int cur = (tid + 1 < n) ? s_split[frame][tid] : 0;
+    level_counts[frame * n + tid] = (overflow || skipped) ? 0 : prev4 - cur;
+  }
+  if (overflow || skipped) return;
+  for (int i = tid; i < leaf_words * 32; i += kCompactThreads) {   // a half wavefront per word
+    const uint32_t leaf = s_leaf[i >> 5], bit = 1u << (i & 31);
+    if (leaf & bit) tok_desc[base + s_before[i >> 5] + __popc(leaf & (bit - 1))] = s_desc[i >> 5] + (i & 31);
+  }
+}
+
 __global__ __launch_bounds__(256) void pad_tokens_kernel(const int32_t* __restrict__ tok_desc,
                                                          const int32_t* __restrict__ cu, int B,
                                                          int t_pad, int32_t* __restrict__ tok_pad,
@@ -330,13 +521,37 @@ hipError_t launch_select(const Pyramid& pyr, const int32_t* boxes, const uint8_t
                          uint8_t* hit_next, int hit_bytes, int max_tokens, int32_t* tok_desc,
                          int32_t* cu_seqlens, int32_t* level_counts, int32_t* err_flag,
                          hipStream_t s, const PlanArgs* plan, const int32_t* hard) {
+  const PlanArgs none{};
+  // One kernel where its bit maps and word lists fit beside the plan's tables; frames are
+  // counted at the capacity of the flag arrays, so that a context keeps to one of the two forms
+  // (the two-kernel form relies on what its last call left in them).
+  size_t frame_words = 0, leaf_words = 0;
+  for (int l = 0; l < pyr.n_levels; ++l) {
+    const size_t words = (size_t)pyr.rows[l] * row_words(pyr, l);
+    leaf_words += words;
+    if (l + 1 < pyr.n_levels) frame_words += words;
+  }
+  const size_t frames = hit_bytes > 0 && nonfinest > 0 ? (size_t)(hit_bytes / nonfinest) : (size_t)B;
+  if ((frames * frame_words + 3 * leaf_words) * 4 <= (size_t)kSelectLds) {
+    static bool configured = false;
+    if (!configured) {
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_kernel),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, kSelectLds);
+      if (e != hipSuccess) return e;
+      configured = true;
+    }
+    hipLaunchKernelGGL(select_kernel, dim3(B + (plan ? 1 : 0)), dim3(kCompactThreads),
+                       (B * frame_words + 3 * leaf_words) * 4, s, pyr, boxes, tier, box_offsets, B, (int)frame_words,
+                       (int)leaf_words, max_tokens, tok_desc, cu_seqlens, level_counts, err_flag, hard,
+                       plan ? *plan : none);
+    return hipGetLastError();
+  }
   if (nonfinest > 0) {
     const int cells_per_block = kHitThreads / kBoxLanes;
     dim3 grid((nonfinest + cells_per_block - 1) / cells_per_block, B);
     hipLaunchKernelGGL(select_hit_kernel, grid, dim3(kHitThreads), 0, s, pyr, boxes, tier,
                        box_offsets, nonfinest, hit);
   }
-  PlanArgs none{};
   hipLaunchKernelGGL(select_compact_kernel, dim3(B + (plan ? 1 : 0)), dim3(kCompactThreads), 0, s,
                      pyr, B, nonfinest, hit, hit_next, hit_bytes, max_tokens, tok_desc, cu_seqlens,
                      level_counts, err_flag, hard, plan ? *plan : none);

@@ -103,3 +103,53 @@ def test_static_selection_reports_overflow_and_rejects_sizes_beyond_its_array(K)
                                     ovf.data_ptr(), 0)
     assert ei.value.status == K.CFDETR_ECAPACITY
     assert "static scratch" in str(ei.value)
+
+
+@pytest.mark.parametrize("frames, height, width, patch", [
+    (48, 2048, 2048, (32, 16, 8)),      # more cells than the one-kernel form holds
+    (25, 2048, 2048, (32, 16, 8)),      # as many as it holds
+    (7, 256, 4128, (32, 16, 8)), (64, 96, 64, (32, 16)), (3, 64, 992, (32, 16)),
+    (1, 64, 64, (64,)), (33, 320, 1056, (32, 16, 8))])
+def test_static_selection_over_words_and_frames(K, frames, height, width, patch):
+    """Rows of one, of whole and of partly used 32-cell words, frames that share the threads evenly
+    or not, boxes outside, clipped, empty, of one pixel and of the whole frame."""
+    import torch
+    from oracle import cfdetr_oracle as O
+    cfg = synth.Config("static", frames, height, width, patch, 64, 2, 1, 128, "f32")
+    rng = np.random.default_rng(frames + width)
+    boxes, tier, offs = [], [], [0]
+    for f in range(frames):
+        for _ in range(0 if f % 5 == 3 else int(rng.integers(1, 40))):
+            x0, y0 = int(rng.integers(-60, width + 40)), int(rng.integers(-60, height + 40))
+            w, h = (int(rng.choice([0, 1, 7, 60, 300])) for _ in range(2))
+            boxes.append((x0, y0, x0 + w, y0 + h))
+            tier.append(int(rng.integers(0, 4)))
+        if f == frames - 1 and frames > 1:
+            boxes.append((0, 0, width, height))
+            tier.append(1)
+        offs.append(len(boxes))
+    boxes = np.asarray(boxes, np.int32).reshape(-1, 4)
+    tier, offs = np.asarray(tier, np.uint8), np.asarray(offs, np.int32)
+    top = len(patch) - 1
+    tok, cu, counts = O.select_fine(boxes, np.minimum(tier, top), offs, frames, height, width, patch)
+    c = K.CfdetrConfig()
+    c.n_levels = len(patch)
+    for level, p in enumerate(patch):
+        c.patch[level] = p
+    c.img_h, c.img_w, c.d_model, c.n_heads, c.n_layers, c.d_ffn = height, width, 64, 2, 1, 128
+    c.max_batch, c.max_tokens_total = frames, int(cu[-1])
+    c.image_dtype, c.act_dtype, c.ln_eps = K.CFDETR_FP32, K.CFDETR_FP32, 1e-5
+
+    def dev(a):
+        return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    b, t, o = dev(boxes if len(boxes) else np.zeros((1, 4), np.int32)), dev(tier if len(tier) else np.zeros(1, np.uint8)), dev(offs)
+    got = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (int(cu[-1]) + 8, frames + 1, frames * len(patch), 1)]
+    _say(f"[case] static selection, {frames} frames of {height} x {width}")
+    K.cfdetr_select_fine_static(c, *(x.data_ptr() for x in (b, t, o)), frames, *(g.data_ptr() for g in got))
+    torch.cuda.synchronize()
+    got = [g.cpu().numpy() for g in got]
+    assert got[3][0] == 0
+    np.testing.assert_array_equal(got[1], cu)
+    np.testing.assert_array_equal(got[2].reshape(frames, -1), counts)
+    np.testing.assert_array_equal(got[0][:cu[-1]], O.pack_tok_desc(tok))
+    assert (got[0][cu[-1]:] == -7).all()
