@@ -1995,19 +1995,22 @@ struct PatchRows {
     const int x = k & ((1 << log2p) - 1);
     return ((size_t)c * img_h + r) * img_w + x;
   }
-  __device__ uint4 load8(size_t row_off, int k) const;
+  // eight pixels as they lie in memory, and as bf16
+  typedef uint32_t Raw __attribute__((ext_vector_type(2 * sizeof(TPix)), aligned(16)));
+  __device__ __forceinline__ Raw load8(size_t row_off, int k) const {
+    return *reinterpret_cast<const Raw*>(images + row_off + pix_off(k));
+  }
+  static __device__ __forceinline__ uint4 as_bf16(Raw r);
   __device__ float load1(size_t row_off, int k) const;
 };
 template <>
-__device__ uint4 PatchRows<bf16_t>::load8(size_t row_off, int k) const {
-  return *reinterpret_cast<const uint4*>(images + row_off + pix_off(k));
-}
+__device__ __forceinline__ uint4 PatchRows<bf16_t>::as_bf16(Raw r) { return make_uint4(r[0], r[1], r[2], r[3]); }
 template <>
-__device__ uint4 PatchRows<float>::load8(size_t row_off, int k) const {
-  const float4* p = reinterpret_cast<const float4*>(images + row_off + pix_off(k));
-  const float4 a = p[0], b = p[1];
-  return make_uint4(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w), pack_bf16x2(b.x, b.y),
-                    pack_bf16x2(b.z, b.w));
+__device__ __forceinline__ uint4 PatchRows<float>::as_bf16(Raw r) {
+  return make_uint4(pack_bf16x2(__uint_as_float(r[0]), __uint_as_float(r[1])),
+                    pack_bf16x2(__uint_as_float(r[2]), __uint_as_float(r[3])),
+                    pack_bf16x2(__uint_as_float(r[4]), __uint_as_float(r[5])),
+                    pack_bf16x2(__uint_as_float(r[6]), __uint_as_float(r[7])));
 }
 template <>
 __device__ float PatchRows<bf16_t>::load1(size_t row_off, int k) const {
@@ -2018,28 +2021,38 @@ __device__ float PatchRows<float>::load1(size_t row_off, int k) const {
   return images[row_off + pix_off(k)];
 }
 
-template <int BM, int BN>
+template <int BM, int BN, int KS>
 constexpr size_t gather_lds_bytes() {
-  return (size_t)2 * (BM + BN) * LDS_LD * sizeof(bf16_t) + BM * sizeof(int32_t) + 16;
+  return (size_t)KS * 2 * (BM + BN) * LDS_LD * sizeof(bf16_t) + BM * sizeof(int32_t) + 16;
 }
 
 // Register-staged, double-buffered (global -> registers -> padded LDS rows, one
-// barrier per slab).  The staging registers are plain unrolled arrays; closures over
-// them would push them into scratch memory.
-template <int BM, int BN, int NWM, int NWN, typename TPix>
-__global__ __launch_bounds__(64 * NWM * NWN) void gemm_bf16_gather_kernel(
+// barrier per slab, the loads one or two slabs ahead).  The staging registers are plain unrolled
+// arrays; closures over them would push them into scratch memory.
+// Frames in fp32 come this way (the conversion needs the registers).  What takes the time is
+// the chain of slabs, 0.45 us each with the loads one slab ahead: 48 of them for patches of 32 x
+// 32, whatever the number of tiles.  With KS = 4 four groups of wavefronts, each with its own
+// LDS rows, contract a quarter of K each for the same tile; the quarters are added in their
+// order by all forms, so that a token has the same bits in each.  Launches before / after:
+// 16 tokens of width 64 23.4 / 14.4 us, up to 80 of 16 x 16 pixels 9.8 / 8.0 us, 920 tokens of width
+// 384 37.1 / 20.8 us.
+template <int BM, int BN, int NWM, int NWN, int KS, typename TPix>
+__global__ __launch_bounds__(64 * NWM * NWN * KS, KS == 4 ? 4 : BM == 128 ? 2 : 1) void gemm_bf16_gather_kernel(
     PatchRows<TPix> al, const bf16_t* __restrict__ W, int N, int K, EpiEmbed ep,
     const int32_t* __restrict__ m_ptr, int m_host) {
-  constexpr int THREADS = 64 * NWM * NWN;
+  constexpr int THREADS = 64 * NWM * NWN;   // of a group
   constexpr int WTM = BM / NWM, WTN = BN / NWN;
   constexpr int MT = WTM / 32, NT = WTN / 32;
   constexpr int PASS_ROWS = THREADS / 8;  // rows staged per pass (8 x 16 B per row)
   constexpr int A_LOADS = BM / PASS_ROWS, B_LOADS = BN / PASS_ROWS;
   static_assert(BM % PASS_ROWS == 0 && BN % PASS_ROWS == 0, "tile / thread mismatch");
+  static_assert(KS == 1 || (KS == 4 && MT * NT == 1), "K split: single-tile wavefronts");
+  constexpr int SETS = KS == 4 ? 2 : 1;   // slabs on the way
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_gather[];
-  bf16_t* sA = reinterpret_cast<bf16_t*>(smem_gather);                 // [2][BM * LDS_LD]
-  bf16_t* sB = sA + 2 * BM * LDS_LD;                                   // [2][BN * LDS_LD]
-  int32_t* s_desc = reinterpret_cast<int32_t*>(sB + 2 * BN * LDS_LD);  // [BM], -1 = not ours
+  const int grp = KS == 1 ? 0 : threadIdx.x / THREADS;
+  bf16_t* sA = reinterpret_cast<bf16_t*>(smem_gather) + grp * (2 * (BM + BN) * LDS_LD);   // [2][BM * LDS_LD]
+  bf16_t* sB = sA + 2 * BM * LDS_LD;                                                      // [2][BN * LDS_LD]
+  int32_t* s_desc = reinterpret_cast<int32_t*>(smem_gather) + KS * (BM + BN) * LDS_LD;    // [BM], -1 = not ours
   int32_t* s_any = s_desc + BM;
 
   const int M = m_ptr ? *m_ptr : m_host;
@@ -2050,11 +2063,21 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bf16_gather_kernel(
   const int m0 = (pid / n_blocks) * BM;
   const int n0 = (pid % n_blocks) * BN;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x % THREADS, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / NWN, wn = wave % NWN;
   const int chunk = tid & 7, srow = tid >> 3;
+  const int nk = K / (BK * KS);       // slabs of a group
+  const int kbase = grp * nk * BK;
 
-  if (tid == 0) *s_any = 0;
+  const bf16_t* wrow[B_LOADS];
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 rb[SETS][B_LOADS];
+#pragma unroll
+  for (int j = 0; j < B_LOADS; ++j) {
+    wrow[j] = W + (size_t)(n0 + srow + PASS_ROWS * j) * K + kbase + chunk * 8;
+    rb[0][j] = *reinterpret_cast<const u32x4*>(wrow[j]);
+  }
+  if (threadIdx.x == 0) *s_any = 0;
   __syncthreads();
   size_t arow[A_LOADS];
   bool any_valid = false;
@@ -2063,18 +2086,14 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bf16_gather_kernel(
     const int r = srow + PASS_ROWS * j;
     bool valid = (m0 + r) < M;
     arow[j] = al.prepare(m0 + r, valid);
-    if (chunk == 0) s_desc[r] = valid ? al.tok_desc[m0 + r] : -1;
+    if (chunk == 0 && grp == 0) s_desc[r] = valid ? al.tok_desc[m0 + r] : -1;
     any_valid |= valid;
   }
   if (any_valid) *s_any = 1;
   __syncthreads();
   if (!*s_any) return;  // no token of this level in the tile
-  const bf16_t* wrow[B_LOADS];
-#pragma unroll
-  for (int j = 0; j < B_LOADS; ++j)
-    wrow[j] = W + (size_t)(n0 + srow + PASS_ROWS * j) * K + chunk * 8;
 
-  f32x16 acc[MT][NT];
+  f32x16 acc[MT][NT], lo[MT][NT];   // lo: the sum of the finished quarters
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -2087,55 +2106,91 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bf16_gather_kernel(
   const int b_off = (wn * WTN + l32) * LDS_LD + g * 8;
   const int st_off = srow * LDS_LD + chunk * 8;
 
-  uint4 ra[A_LOADS], rb[B_LOADS];
+  // slab 0 into LDS, slab 1 on its way into the registers
+  typename PatchRows<TPix>::Raw ra[SETS][A_LOADS];
 #pragma unroll
-  for (int j = 0; j < A_LOADS; ++j) ra[j] = al.load8(arow[j], chunk * 8);
+  for (int j = 0; j < A_LOADS; ++j) ra[0][j] = al.load8(arow[j], kbase + chunk * 8);
+  if constexpr (SETS == 2) {
+    const int k1 = min(1, nk - 1) * BK;
 #pragma unroll
-  for (int j = 0; j < B_LOADS; ++j) rb[j] = *reinterpret_cast<const uint4*>(wrow[j]);
+    for (int j = 0; j < A_LOADS; ++j) ra[1][j] = al.load8(arow[j], kbase + k1 + chunk * 8);
+#pragma unroll
+    for (int j = 0; j < B_LOADS; ++j) rb[1][j] = *reinterpret_cast<const u32x4*>(wrow[j] + k1);
+  }
 #pragma unroll
   for (int j = 0; j < A_LOADS; ++j)
-    *reinterpret_cast<uint4*>(sA + st_off + PASS_ROWS * j * LDS_LD) = ra[j];
+    *reinterpret_cast<uint4*>(sA + st_off + PASS_ROWS * j * LDS_LD) = PatchRows<TPix>::as_bf16(ra[0][j]);
 #pragma unroll
   for (int j = 0; j < B_LOADS; ++j)
-    *reinterpret_cast<uint4*>(sB + st_off + PASS_ROWS * j * LDS_LD) = rb[j];
+    *reinterpret_cast<u32x4*>(sB + st_off + PASS_ROWS * j * LDS_LD) = rb[0][j];
   __syncthreads();
 
-  const int nk = K / BK;
-  for (int it = 0; it < nk; ++it) {
-    // The last pass fetches its own slab again (unused) so that the loop body is
-    // free of conditionals around the register arrays.
-    const int kn = min(it + 1, nk - 1) * BK;
-#pragma unroll
-    for (int j = 0; j < A_LOADS; ++j) ra[j] = al.load8(arow[j], kn + chunk * 8);
-#pragma unroll
-    for (int j = 0; j < B_LOADS; ++j) rb[j] = *reinterpret_cast<const uint4*>(wrow[j] + kn);
-    const bf16_t* pa = sA + (it & 1) * BM * LDS_LD + a_off;
-    const bf16_t* pb = sB + (it & 1) * BN * LDS_LD + b_off;
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      bf16x8 fa[MT], fb[NT];
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-        fa[i] = *reinterpret_cast<const bf16x8*>(pa + i * 32 * LDS_LD + ks * 16);
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-        fb[j] = *reinterpret_cast<const bf16x8*>(pb + j * 32 * LDS_LD + ks * 16);
+  // One slab: the loads of slab it + SETS into register set IN_, the products of slab it from LDS
+  // place CUR_, slab it + 1 from set OUT_ into the other place.  (The last passes fetch the
+  // last slab again, unused, so that there are no conditionals around the register arrays.)
+#define CFDETR_GATHER_SLAB(IN_, OUT_, CUR_)                                                                       \
+  do {                                                                                                            \
+    const int kn = min(it + SETS, nk - 1) * BK;                                                                   \
+    _Pragma("unroll") for (int j = 0; j < A_LOADS; ++j) ra[IN_][j] = al.load8(arow[j], kbase + kn + chunk * 8);   \
+    _Pragma("unroll") for (int j = 0; j < B_LOADS; ++j) rb[IN_][j] = *reinterpret_cast<const u32x4*>(wrow[j] + kn); \
+    const bf16_t* pa = sA + (CUR_) * BM * LDS_LD + a_off;                                                         \
+    const bf16_t* pb = sB + (CUR_) * BN * LDS_LD + b_off;                                                         \
+    _Pragma("unroll") for (int ks = 0; ks < BK / 16; ++ks) {                                                      \
+      bf16x8 fa[MT], fb[NT];                                                                                      \
+      _Pragma("unroll") for (int i = 0; i < MT; ++i)                                                              \
+          fa[i] = *reinterpret_cast<const bf16x8*>(pa + i * 32 * LDS_LD + ks * 16);                               \
+      _Pragma("unroll") for (int j = 0; j < NT; ++j)                                                              \
+          fb[j] = *reinterpret_cast<const bf16x8*>(pb + j * 32 * LDS_LD + ks * 16);                               \
+      _Pragma("unroll") for (int i = 0; i < MT; ++i)                                                              \
+          _Pragma("unroll") for (int j = 0; j < NT; ++j) acc[i][j] =                                              \
+              __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);                          \
+    }                                                                                                             \
+    bf16_t* qa = sA + ((CUR_) ^ 1) * BM * LDS_LD + st_off;                                                        \
+    bf16_t* qb = sB + ((CUR_) ^ 1) * BN * LDS_LD + st_off;                                                        \
+    _Pragma("unroll") for (int j = 0; j < A_LOADS; ++j)                                                           \
+        *reinterpret_cast<uint4*>(qa + PASS_ROWS * j * LDS_LD) = PatchRows<TPix>::as_bf16(ra[OUT_][j]);           \
+    _Pragma("unroll") for (int j = 0; j < B_LOADS; ++j)                                                           \
+        *reinterpret_cast<u32x4*>(qb + PASS_ROWS * j * LDS_LD) = rb[OUT_][j];                                     \
+    __syncthreads();                                                                                              \
+  } while (0)
+
+  if constexpr (KS == 1) {
+    // (a loop per quarter: sums set aside inside the loop would move with every slab)
+    const int parts = K % (4 * BK) == 0 ? 4 : 1;
+    int it = 0;
+    for (int part = 1; part <= parts; ++part) {
+      for (const int end = nk / parts * part; it < end; ++it) CFDETR_GATHER_SLAB(0, 0, it & 1);
+      if (parts == 1) break;
 #pragma unroll
       for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            lo[i][j][r] = part == 1 ? acc[i][j][r] : lo[i][j][r] + acc[i][j][r];
+            acc[i][j][r] = part == 4 ? lo[i][j][r] : 0.f;
+          }
     }
-    bf16_t* qa = sA + ((it + 1) & 1) * BM * LDS_LD + st_off;
-    bf16_t* qb = sB + ((it + 1) & 1) * BN * LDS_LD + st_off;
+  } else {
+    for (int it = 0; it < nk; ++it) {
+      CFDETR_GATHER_SLAB(0, 1, 0);
+      if (++it >= nk) break;
+      CFDETR_GATHER_SLAB(1, 0, 1);
+    }
+    // the other groups' sums cross through their LDS rows, register by register
+    float* const own = reinterpret_cast<float*>(sA) + tid;
+    if (grp != 0) {
 #pragma unroll
-    for (int j = 0; j < A_LOADS; ++j)
-      *reinterpret_cast<uint4*>(qa + PASS_ROWS * j * LDS_LD) = ra[j];
-#pragma unroll
-    for (int j = 0; j < B_LOADS; ++j)
-      *reinterpret_cast<uint4*>(qb + PASS_ROWS * j * LDS_LD) = rb[j];
+      for (int r = 0; r < 16; ++r) own[r * THREADS] = acc[0][0][r];
+    }
     __syncthreads();
+    if (grp != 0) return;
+#pragma unroll
+    for (int o = 1; o < KS; ++o)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[0][0][r] += own[o * ((BM + BN) * LDS_LD) + r * THREADS];
   }
+#undef CFDETR_GATHER_SLAB
 
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
@@ -2384,20 +2439,23 @@ hipError_t launch_direct(const void* A, const void* W, int N, int K, const EP& e
   return launch_persist_tile<64, 64, 2, 1>(a, w, N, K, ep, m_ptr, m_host, m_capacity, 4, s);
 }
 
-template <int BM, int BN, typename TPix>
+template <int BM, int BN, int KS, typename TPix>
 hipError_t launch_gather_tile(const PatchRows<TPix>& al, const bf16_t* w, int N, int K,
                               const EpiEmbed& ep, const int32_t* m_ptr, int m_host,
                               int m_capacity, hipStream_t s) {
-  auto kern = gemm_bf16_gather_kernel<BM, BN, 2, 2, TPix>;
-  constexpr size_t lds = gather_lds_bytes<BM, BN>();
+  auto kern = gemm_bf16_gather_kernel<BM, BN, 2, 2, KS, TPix>;
+  constexpr size_t lds = gather_lds_bytes<BM, BN, KS>();
   static bool configured = false;
   hipError_t e = allow_lds(kern, lds, &configured);
   if (e != hipSuccess) return e;
   dim3 grid(((m_capacity + BM - 1) / BM) * (N / BN));
-  hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, al, w, N, K, ep, m_ptr, m_host);
+  hipLaunchKernelGGL(kern, grid, dim3(256 * KS), lds, s, al, w, N, K, ep, m_ptr, m_host);
   return hipSuccess;
 }
 
+// 128 x 128 tiles as long as they fill the chip, else 64 x 64.  Four groups of wavefronts share
+// a tile where no CU gets two (a workgroup of 16 wavefronts is slower than four of four: 338 tiles
+// 83 against 64 us) and K has quarters of whole slabs (patches from 16 x 16 on).
 template <typename TPix>
 hipError_t launch_gather(const PatchRows<TPix>& al, const void* W, int N, int K,
                          const EpiEmbed& ep, const int32_t* m_ptr, int m_host, int m_capacity,
@@ -2405,8 +2463,11 @@ hipError_t launch_gather(const PatchRows<TPix>& al, const void* W, int N, int K,
   const bf16_t* w = static_cast<const bf16_t*>(W);
   const long tiles128 = (long)((m_capacity + 127) / 128) * (N / 128);
   if (N % 128 == 0 && tiles128 >= 256)
-    return launch_gather_tile<128, 128>(al, w, N, K, ep, m_ptr, m_host, m_capacity, s);
-  return launch_gather_tile<64, 64>(al, w, N, K, ep, m_ptr, m_host, m_capacity, s);
+    return launch_gather_tile<128, 128, 1>(al, w, N, K, ep, m_ptr, m_host, m_capacity, s);
+  const long tiles64 = (long)((m_capacity + 63) / 64) * (N / 64);
+  if (K % (4 * BK) == 0 && tiles64 <= cu_count())
+    return launch_gather_tile<64, 64, 4>(al, w, N, K, ep, m_ptr, m_host, m_capacity, s);
+  return launch_gather_tile<64, 64, 1>(al, w, N, K, ep, m_ptr, m_host, m_capacity, s);
 }
 
 template <typename AL, typename EP>

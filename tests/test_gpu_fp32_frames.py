@@ -1,0 +1,41 @@
+"""Patch embedding of fp32 frames: a tile by four groups of wavefronts (few tiles), by one group,
+and tiles of 128 x 128 give every token the same bits (K is summed in quarters by all), for
+patches of 8 (no quarters), 16, 32 and 64 pixels, and the oracle's values."""
+import numpy as np
+import pytest
+
+from oracle import cfdetr_oracle as O
+from paper_2505_23317_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _embed(cfg, w, images):
+    from paper_2505_23317_amd import cfdetr as K
+    enc = K.Encoder(cfg, w)
+    n = images.shape[0]
+    out = enc.alloc_outputs(n)
+    enc.coarse_encode(enc.upload_images(images), n, out["x0_cache"], out["y_coarse"])
+    enc.sync_status()
+    x = out["x0_cache"].reshape(n, -1, cfg.d).clone()
+    enc.close()
+    return x
+
+
+# frames of the largest batch: 64 x 64 tiles beyond the CUs, 128 x 128 tiles from 256 on
+@pytest.mark.parametrize("patch, rows, cols, d, frames", [
+    (8, 37, 41, 128, (1, 6, 24)), (16, 37, 41, 128, (1, 6, 24)), (32, 13, 17, 256, (1, 32, 64)),
+    (64, 5, 3, 768, (1, 40)), (16, 1, 1, 64, (1, 2))])
+def test_every_form_gives_the_same_bits(patch, rows, cols, d, frames):
+    import torch
+
+    cfg = synth.Config("fp32", max(frames), rows * patch, cols * patch, (patch,), d, d // 32 if d < 768 else 12, 1, 128, "f32",
+                       box_rule="poisson")
+    w = synth.make_weights(cfg, 17)
+    images = np.random.default_rng(8).random((max(frames), 3, cfg.H, cfg.W), dtype=np.float32)
+    few = _embed(synth.replace(cfg, B=1), w, images[:1])
+    ref = np.asarray(O.coarse_encode(images[:1], cfg.patch, w, cfg.heads)[0]).reshape(-1, d)
+    # pixels round to bf16 (2^-9), K products of them add up in fp32: relative to the largest value
+    assert float(np.abs(few[0].cpu().numpy() - ref).max() / np.abs(ref).max()) <= 2.0 ** -8
+    for n in frames[1:]:
+        assert torch.equal(_embed(synth.replace(cfg, B=n), w, images[:n])[0], few[0]), n
