@@ -1,6 +1,6 @@
-"""Patch embedding of fp32 frames: a tile by four groups of wavefronts (few tiles), by one group,
+"""Patch embedding.  Frames in fp32: a tile by four groups of wavefronts (few tiles), by one group,
 and tiles of 128 x 128 give every token the same bits (K is summed in quarters by all), for
-patches of 8 (no quarters), 16, 32 and 64 pixels, and the oracle's values."""
+patches of 8 (no quarters), 16, 32 and 64 pixels, and the oracle's values.  Frames in bf16: the same of the forms for patches of 64 pixels."""
 import numpy as np
 import pytest
 
@@ -39,3 +39,19 @@ def test_every_form_gives_the_same_bits(patch, rows, cols, d, frames):
     assert float(np.abs(few[0].cpu().numpy() - ref).max() / np.abs(ref).max()) <= 2.0 ** -8
     for n in frames[1:]:
         assert torch.equal(_embed(synth.replace(cfg, B=n), w, images[:n])[0], few[0]), n
+
+
+# 2 x 12 small tiles, two rounds and three of them on 256 CUs (there 128 x 128 tiles)
+@pytest.mark.parametrize("frames", [(1, 35, 40)])
+def test_bf16_frames_with_large_patches(frames):
+    import torch
+
+    cfg = synth.Config("bf16", max(frames), 8 * 64, 9 * 64, (64,), 768, 12, 1, 128, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 19)
+    images = synth.bf16_round(np.random.default_rng(9).random((max(frames), 3, cfg.H, cfg.W), dtype=np.float32))
+    few = _embed(synth.replace(cfg, B=1), w, images[:1])
+    ref = np.asarray(O.coarse_encode(images[:1], cfg.patch, w, cfg.heads)[0]).reshape(-1, cfg.d)
+    assert float(np.abs(few[0].cpu().numpy() - ref).max() / np.abs(ref).max()) <= 2.0 ** -8
+    for n in frames[1:]:
+        x = _embed(synth.replace(cfg, B=n), w, images[:n])
+        assert torch.equal(x[0], few[0]) and torch.isfinite(x).all(), n
