@@ -98,7 +98,7 @@ def cpu_baseline(cfg, wl, cfg_id, single_thread=False, budget_s=10.0):
 
 
 # kernel family of the profile interface -> names it may have in the counter summary (the
-# fused kernels of width 256 first: where they run, the separate ones do not)
+# fused kernels first: where they run, the separate ones do not)
 TRAFFIC_FAMILY = {"attention": ["attention"], "qkv": ["layer_head", "wide_head", "gemm_qkv"],
                   "ffn1": ["gemm_ffn1_gelu"], "out_proj": ["gemm_out_proj"],
                   "ffn2": ["layer_tail", "wide_layer", "gemm_ffn2"], "layernorm": ["layernorm"],

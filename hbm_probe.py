@@ -35,8 +35,11 @@ FAMILIES = [
     ("gemm_residual", r"gemm_bf16_(direct|persist)_kernel.*EpiResidual|gemm_bf16_rowln_kernel"),
     ("layer_tail", r"layer_tail_kernel"),
     ("layer_head", r"layer_head_kernel"),
+    ("wide_head", r"wide_layer_kernel<\d+, \d, ., 0>"),
+    ("wide_layer", r"wide_layer_kernel<\d+, \d, ., [12]>"),
     ("embed", r"gemm_bf16_gather_kernel|gemm_bf16_direct_kernel.*EpiEmbed"),
     ("layernorm", r"layernorm4?_kernel"),
+    ("select", r"select_kernel"),
     ("select_hit", r"select_hit_kernel"),
     ("select_compact", r"select_compact_kernel"),
     ("gather_coarse", r"gather_coarse_kernel"),

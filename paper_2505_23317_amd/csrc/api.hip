@@ -65,7 +65,7 @@ struct cfdetr_ctx {
   void* wide_head = nullptr;
   float* x_blocks = nullptr;        // and its residual rows
   int cus = 256;                    // compute units of the device
-  // w_qkv, w_o, w_ff1, w_ff2 of all layers as the kernels for few rows read them (slim.hip);
+  // w_qkv, w_o, w_ff1, w_ff2 of all layers as the kernels for few rows read them (few_rows.hip);
   // null where the shape has none
   char *slim_qkv = nullptr, *slim_o = nullptr, *slim_ff1 = nullptr, *slim_ff2 = nullptr;
 

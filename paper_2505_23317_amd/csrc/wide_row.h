@@ -1,4 +1,4 @@
-// What the kernels of the wider widths share (layer.hip, slim.hip).
+// What the kernels of the wider widths share (layer.hip, few_rows.hip).
 #pragma once
 #include "kernels.h"
 
@@ -18,7 +18,7 @@ __device__ __forceinline__ float gelu_sig(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
 }
 
-// Residual rows between the kernels of width 384 lie as these hold them, as MFMA results:
+// Residual rows between the kernels of these widths lie as these hold them, as MFMA results:
 // tiles of 32 rows; in a tile, 32 columns by 32, four blocks of 1 KB, lane l of a wavefront's
 // 64 with columns 8 q + 4 (l / 32) .. + 3 of row l % 32 at 16 l of block q.  Rows of floats
 // instead would have every load touch 32 rows with 32 bytes each: 3 us for the rows of a
