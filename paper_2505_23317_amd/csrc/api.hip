@@ -875,7 +875,8 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   const uint64_t o_hpack = cv.take(c->tail_packed_layer ? 3 * d * d * 2 : 0);
   const uint64_t o_wide = cv.take(c->wide_layer * cfg->n_layers);
   const uint64_t o_whead = cv.take(c->wide_layer ? wide_layer_packed_bytes((int)d, (int)F, true) : 0);
-  const uint64_t o_xb = cv.take(c->wide_layer ? (Tm + 95) / 96 * 96 * d * 4 : 0);
+  // (whole tiles of 32, 64 and 96 rows: a last tile of any height ends inside)
+  const uint64_t o_xb = cv.take(c->wide_layer ? (Tm + 191) / 192 * 192 * d * 4 : 0);
   const bool slim = c->bf16 && !c->tail_packed_layer && !(d == 256 && c->wide_layer) && few_rows_supported((int)d, (int)d) && few_rows_supported((int)F, (int)F);
   const uint64_t Lw = cfg->n_layers;
   const uint64_t o_sq = cv.take(slim ? slim_packed_bytes(Lw * 3 * d, d) : 0), o_so = cv.take(slim ? slim_packed_bytes(Lw * d, d) : 0);

@@ -79,3 +79,34 @@ def test_few_rows_at_width_256(rows):
     y = _coarse(cfg, w, images)[0].cpu().numpy()
     ref = np.asarray(O.coarse_encode(images, cfg.patch, w, cfg.heads)[-1]).reshape(-1, cfg.d)
     assert float(np.abs(y - ref).max() / np.abs(ref).max()) <= BAR
+
+
+@pytest.mark.parametrize("d", [256, 384])
+def test_last_tile_at_the_capacity_stays_inside_its_buffer(d):
+    """9,696 rows, all that the context has room for: the last workgroup's 64 rows end 32 rows past a
+    multiple of 96.  What lies behind (packed weights) is read by the passes of one frame."""
+    import torch
+    from paper_2505_23317_amd import cfdetr as K
+
+    cfg = synth.Config("full", 8, 48, 808, (8,), d, d // 64 if d == 384 else 8, 2, 256, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 21)
+    images = synth.bf16_round(np.random.default_rng(7).normal(0.5, 0.25, (cfg.B, 3, cfg.H, cfg.W)).astype(np.float32))
+    enc = K.Encoder(cfg, w)
+    out = enc.alloc_outputs(cfg.B)
+    img = enc.upload_images(images)
+    assert enc.max_tokens == cfg.B * 606
+
+    def one_frame():
+        enc.coarse_encode(img, 1, out["x0_cache"], out["y_coarse"])
+        enc.sync_status()
+        return out["y_coarse"].reshape(-1, d)[:606].clone()
+
+    before = one_frame()
+    b, t, o = enc.upload_boxes(np.zeros((0, 4), np.int32), np.zeros(0, np.uint8), np.zeros(cfg.B + 1, np.int32))
+    for _ in range(2):
+        enc.multilevel_batch(img, cfg.B, b, t, o, out)
+        enc.sync_status()
+        assert torch.equal(out["y_coarse"].reshape(-1, d)[:606], before)
+        assert torch.equal(out["y_mixed"].reshape(-1, d)[:4848], out["y_coarse"].reshape(-1, d)[:4848])
+    assert torch.equal(one_frame(), before)
+    enc.close()
