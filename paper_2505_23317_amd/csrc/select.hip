@@ -70,6 +70,9 @@ __global__ __launch_bounds__(kHitThreads) void select_hit_kernel(
 // 8*j + G%8 take its tiles in order.  Costs fall with G, so the XCD loads differ by at
 // most one group, and no XCD gets more than total/8 + (tiles of the longest sequence)
 // items, which is what cap8 provides.
+// gated: no item at all.  The items are then not written (and not only counted as none): there
+// is no barrier between the two loops over the entries, so where both wrote one, either could
+// be the last, and an item that is left sends a workgroup to a sequence without keys.
 constexpr int kMaxHeads = 32;
 
 // Inclusive sum over the lanes of a wavefront: inside the rows of 16 lanes, then the last lane
@@ -151,7 +154,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& p, int nseq, const int
     *p.m_all = s_cu[nseq];
     if (p.m_seen != nullptr) *p.m_seen = s_cu[nseq];
   }
-  for (int G = tid; G < ngroups; G += blockDim.x) {   // one thread per group
+  for (int G = tid; !gated && G < ngroups; G += blockDim.x) {   // one thread per group
     const int at = (int)((G + 0.5f) * per_head), f = s_order[at], h = G - at * heads, x = G & 7;
     const int nt = tiles(f);
     const int j0 = s_gstart[G];

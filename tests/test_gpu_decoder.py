@@ -295,3 +295,35 @@ def test_decoder_argument_and_sequence_errors(K):
         enc.attach_decoder(bad_w)
     assert e.value.status == K.CFDETR_ESHAPE
     enc.close()
+
+
+def test_refused_offsets_give_the_attention_no_work(K):
+    """Offsets that the device refuses leave both attentions without any item (768 and more would be
+    there: every entry of the list has a thread that fills it and one that empties it).  What a refused
+    call computes then rests on what the call before left behind, and on nothing else."""
+    import torch
+    d, heads, Q, frames, tokens = 768, 12, 97, 64, 37
+    cfg = model(d, heads, 768, frames)
+    enc = K.Encoder(cfg, synth.make_weights(cfg, 7))
+    enc.attach_decoder(synth.make_decoder_weights(cfg, 3, n_queries=Q, layers=2))
+    mem = torch.randn((frames * tokens, d), generator=torch.Generator().manual_seed(5)).cuda()
+    cu = torch.arange(frames + 1, dtype=torch.int32).cuda() * tokens
+    empty_frame, descending = cu.clone(), cu.clone()
+    empty_frame[5] = empty_frame[4]
+    descending[7] = descending[6] - 1
+    good, refused = [], []
+    for bad in (empty_frame, descending, empty_frame):
+        for offsets, results in ((cu, good), (bad, refused)):
+            out = torch.full((frames, Q, 5), -3.0, device="cuda")
+            enc.decode(mem, offsets, frames, out)
+            if results is good:
+                enc.sync_status()
+            else:
+                with pytest.raises(K.CfdetrError) as e:
+                    enc.sync_status()
+                assert e.value.status == K.CFDETR_ECAPACITY
+            results.append(out)
+    for results in (good, refused):
+        assert all(torch.equal(r, results[0]) for r in results[1:])
+    assert not torch.equal(good[0], refused[0])
+    enc.close()
