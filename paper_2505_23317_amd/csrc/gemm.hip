@@ -2305,15 +2305,6 @@ int ilog2(int v) {
   return l;
 }
 
-template <typename Kern>
-hipError_t allow_lds(Kern kern, size_t bytes, bool* configured) {
-  if (*configured) return hipSuccess;   // the attribute is sticky
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess) *configured = true;
-  return e;
-}
-
 template <int BM, int BN, int NWM, int NWN, int S, int BKT, int KS = 1, int WPE = 1, typename AROWS, typename EP>
 hipError_t launch_direct_tile(const AROWS& a, const bf16_t* w, int N, int K, const EP& ep,
                               const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s) {
@@ -2323,7 +2314,7 @@ hipError_t launch_direct_tile(const AROWS& a, const bf16_t* w, int N, int K, con
   if ((size_t)N * K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
   constexpr size_t lds = (size_t)KS * S * (BM + BN) * BKT * 2;
   static_assert(lds <= 160 * 1024, "ring exceeds the LDS");
-  static bool configured = false;
+  static DeviceOnce configured;
   hipError_t e = allow_lds(kern, lds, &configured);
   if (e != hipSuccess) return e;
   dim3 grid(((m_capacity + BM - 1) / BM) * (N / BN));
@@ -2355,7 +2346,7 @@ hipError_t launch_persist_tile(const DenseRows& a, const bf16_t* w, int N, int K
   if ((size_t)N * K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
   constexpr size_t lds = (size_t)2 * (BM + BN) * 64 * 2;
   static_assert(lds <= 160 * 1024, "ring exceeds the LDS");
-  static bool configured = false;
+  static DeviceOnce configured;
   hipError_t e = allow_lds(kern, lds, &configured);
   if (e != hipSuccess) return e;
   const long tiles = (long)((m_capacity + BM - 1) / BM) * (N / BN);
@@ -2445,7 +2436,7 @@ hipError_t launch_gather_tile(const PatchRows<TPix>& al, const bf16_t* w, int N,
                               int m_capacity, hipStream_t s) {
   auto kern = gemm_bf16_gather_kernel<BM, BN, 2, 2, KS, TPix>;
   constexpr size_t lds = gather_lds_bytes<BM, BN, KS>();
-  static bool configured = false;
+  static DeviceOnce configured;
   hipError_t e = allow_lds(kern, lds, &configured);
   if (e != hipSuccess) return e;
   dim3 grid(((m_capacity + BM - 1) / BM) * (N / BN));

@@ -3,8 +3,20 @@
 // synchronises or allocates.
 #pragma once
 #include "common.h"
+#include "device_once.h"
 
 namespace cfdetr {
+
+// Leave for `bytes` of dynamic LDS in a kernel's workgroups.  The attribute belongs to the
+// kernel as one device holds it, and stays.
+template <typename Kern>
+inline hipError_t allow_lds(Kern kern, size_t bytes, DeviceOnce* once) {
+  int dev = -1;
+  if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+  return once->run(dev, [&] {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  });
+}
 
 // What launch_plan writes and how (see there); also accepted by launch_select, whose last
 // workgroup then makes the plan for the run that follows (the n_prefix prefix sequences plus

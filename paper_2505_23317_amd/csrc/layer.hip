@@ -546,13 +546,9 @@ template <int D, int NW, int MT, int kKind>
 hipError_t launch_wide(const WideArgs& p, int m_capacity, hipStream_t s) {
   auto kern = wide_layer_kernel<D, NW, MT, kKind>;
   const size_t lds = WideLds<D, NW, MT>::bytes(p.F);
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       160 * 1024);
-    if (e != hipSuccess) return e;
-    configured = true;
-  }
+  static DeviceOnce configured;
+  hipError_t e = allow_lds(kern, 160 * 1024, &configured);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((m_capacity + 32 * MT - 1) / (32 * MT)), dim3(64 * NW), lds, s, p);
   return hipGetLastError();
 }

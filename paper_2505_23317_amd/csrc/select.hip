@@ -537,12 +537,10 @@ hipError_t launch_select(const Pyramid& pyr, const int32_t* boxes, const uint8_t
   const size_t frames = hit_bytes > 0 && nonfinest > 0 ? (size_t)(hit_bytes / nonfinest) : (size_t)B;
   if ((frames * frame_words + 3 * leaf_words) * 4 <= (size_t)kSelectLds) {
     const size_t lds = (B * frame_words + 3 * leaf_words) * 4;
-    static bool configured = false;
-    if (lds > 32 * 1024 && !configured) {   // (64 KB with the plan's tables need no leave)
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(select_kernel),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, kSelectLds);
+    static DeviceOnce configured;
+    if (lds > 32 * 1024) {   // (64 KB with the plan's tables need no leave)
+      hipError_t e = allow_lds(select_kernel, kSelectLds, &configured);
       if (e != hipSuccess) return e;
-      configured = true;
     }
     hipLaunchKernelGGL(select_kernel, dim3(B + (plan ? 1 : 0)), dim3(kCompactThreads),
                        lds, s, pyr, boxes, tier, box_offsets, B, (int)frame_words,

@@ -1,0 +1,46 @@
+"""What the launchers do once per device (leave for a kernel's dynamic LDS): a second device of the
+process has it done too, a failure is tried again, and no launcher keeps a once-per-process flag."""
+import glob
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_23317_amd", "csrc")
+
+DRIVER = """
+#include "device_once.h"
+#include <cstdio>
+#include <initializer_list>
+int main() {
+  static cfdetr::DeviceOnce once, other;
+  int calls = 0, answer = 0;
+  auto f = [&] { ++calls; return answer; };
+  for (int device : {0, 0, 3, 0, 3, 63, 63}) std::printf("%d ", (once.run(device, f), calls));
+  answer = 7;
+  for (int i = 0; i < 2; ++i) std::printf("%d:%d ", once.run(5, f), calls);
+  answer = 0;
+  for (int i = 0; i < 2; ++i) std::printf("%d:%d ", once.run(5, f), calls);
+  for (int i = 0; i < 2; ++i) std::printf("%d:%d ", once.run(64, f), calls);
+  std::printf("%d:%d", other.run(0, f), calls);
+}
+"""
+
+
+def test_every_device_of_the_process(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host compiler")
+    (tmp_path / "driver.cc").write_text(DRIVER)
+    exe = str(tmp_path / "driver")
+    subprocess.run([gxx, "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(tmp_path / "driver.cc"), "-o", exe], check=True)
+    got = subprocess.run([exe], capture_output=True, text=True, check=True).stdout.split()
+    assert got == ["1", "1", "2", "2", "2", "3", "3", "7:4", "7:5", "0:6", "0:6", "0:7", "0:8", "0:9"]
+
+
+def test_no_launcher_goes_by_a_flag_of_the_process():
+    for path in glob.glob(os.path.join(CSRC, "*.hip")):
+        with open(path) as f:
+            assert not re.search(r"\bstatic bool\s+\w+\s*=", f.read()), path
