@@ -18,13 +18,17 @@ int main() {
   static cfdetr::DeviceOnce once, other;
   int calls = 0, answer = 0;
   auto f = [&] { ++calls; return answer; };
-  for (int device : {0, 0, 3, 0, 3, 63, 63}) std::printf("%d ", (once.run(device, f), calls));
+  auto tell = [&](cfdetr::DeviceOnce& which, int device) {
+    const int got = which.run(device, f);
+    std::printf("%d:%d ", got, calls);
+  };
+  for (int device : {0, 0, 3, 0, 3, 63, 63}) tell(once, device);
   answer = 7;
-  for (int i = 0; i < 2; ++i) std::printf("%d:%d ", once.run(5, f), calls);
+  for (int i = 0; i < 2; ++i) tell(once, 5);
   answer = 0;
-  for (int i = 0; i < 2; ++i) std::printf("%d:%d ", once.run(5, f), calls);
-  for (int i = 0; i < 2; ++i) std::printf("%d:%d ", once.run(64, f), calls);
-  std::printf("%d:%d", other.run(0, f), calls);
+  for (int i = 0; i < 2; ++i) tell(once, 5);
+  for (int i = 0; i < 2; ++i) tell(once, 64);
+  tell(other, 0);
 }
 """
 
@@ -37,7 +41,7 @@ def test_every_device_of_the_process(tmp_path):
     exe = str(tmp_path / "driver")
     subprocess.run([gxx, "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(tmp_path / "driver.cc"), "-o", exe], check=True)
     got = subprocess.run([exe], capture_output=True, text=True, check=True).stdout.split()
-    assert got == ["1", "1", "2", "2", "2", "3", "3", "7:4", "7:5", "0:6", "0:6", "0:7", "0:8", "0:9"]
+    assert got == ["0:1", "0:1", "0:2", "0:2", "0:2", "0:3", "0:3", "7:4", "7:5", "0:6", "0:6", "0:7", "0:8", "0:9"]
 
 
 def test_no_launcher_goes_by_a_flag_of_the_process():
