@@ -1,7 +1,7 @@
 // Layers of width 384 when there are few rows: wide_layer_kernel (layer.hip) gives every row to
 // one CU, which streams all the weights of the layer past it; below some two thousand rows most
 // CUs would have none.  Here a layer is four launches, each spread over the chip, with the same
-// arithmetic in the same order (sums that start at the bias or at residual + bias, its
+// arithmetic in the same order (sums that start at the bias or at the residual's low part, its
 // LayerNorm), so that a row's result does not depend on how many others there are.
 #include "few_rows.h"
 #include "wide_row.h"
@@ -170,26 +170,28 @@ __global__ __launch_bounds__(256, 2) void slim_residual_kernel(SlimArgs p) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int t = blockIdx.x >> 3; t < tiles.count; t += gridDim.x >> 3) {
     const int part = tiles.p0 + t / tiles.rows, m0 = (tiles.r0 + t % tiles.rows) * 32, n0 = part * 128 + wave * 32;
-    float4 b[4], xr[4];
+    float4 b[4];
+    f32x16 x, acc[1];
+    u32x8 hi;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       b[q] = *reinterpret_cast<const float4*>(p.bias + n0 + 8 * q + 4 * g);
-      xr[q] = *reinterpret_cast<const float4*>(x_block<D>(p.x, m0, n0, q, lane));
+      const float4 v = *reinterpret_cast<const float4*>(x_block<D>(p.x, m0, n0, q, lane));
+      x[4 * q] = v.x;
+      x[4 * q + 1] = v.y;
+      x[4 * q + 2] = v.z;
+      x[4 * q + 3] = v.w;
     }
-    f32x16 acc[1];
     few_rows_product<1, kBlocks>(p.rows, p.K, M, m0, p.w + (size_t)(part * 4 + wave) * (p.K >> 4) * 1024, smem, acc, [&]() {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        acc[0][4 * q] = xr[q].x + b[q].x;
-        acc[0][4 * q + 1] = xr[q].y + b[q].y;
-        acc[0][4 * q + 2] = xr[q].z + b[q].z;
-        acc[0][4 * q + 3] = xr[q].w + b[q].w;
-      }
+      acc[0] = x;
+      residual_split(acc[0], hi);
     });
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < 4; ++q) {
+      residual_join(acc[0], hi, q, b[q]);
       *reinterpret_cast<float4*>(x_block<D>(p.x, m0, n0, q, lane)) =
           make_float4(acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]);
+    }
     __syncthreads();
   }
 }

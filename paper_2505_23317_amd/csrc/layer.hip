@@ -56,11 +56,14 @@ struct WideLds {
 constexpr int kHead = 0, kMid = 1, kLast = 2;
 
 // A workgroup of NW wavefronts owns 32 MT complete rows; wavefront w owns columns
-// [w D/NW, (w + 1) D/NW) of them.  The rows' residuals stay in the accumulators from the first
-// product to the last: they start as x + b_o, the out-projection is added on top by its MFMAs,
-// LayerNorm reads them there, b2 and the second feed-forward matrix come on top again.  Per
-// row only O and x are read and x, q, k, v written; as separate kernels the same rows made
-// 30 KB of traffic more per layer (bf16 rows of both LayerNorms, hidden activations, x twice).
+// [w D/NW, (w + 1) D/NW) of them.  The two products that end in the residual are not summed on
+// top of it, where every MFMA would round at its magnitude (ten times the error where it is 30
+// times what is added): the accumulators start at the residual's low part and its high part, a
+// bf16, is added once (wide_row.h).  Through the feed-forward block the high parts wait in
+// registers, where there is room for them (kKeep), or in memory in the rows' own place.  Per row
+// only O and x are read and x, q, k, v written (half of x once more where it waits in memory); as
+// separate kernels the same rows made 30 KB of traffic more per layer (bf16 rows of both
+// LayerNorms, hidden activations, x twice).
 // Weights: no wavefront shares one with another, so they skip the LDS.  They are packed in the
 // order of use, 1 KB per MFMA operand, and stream through a ring of registers that is refilled
 // right behind the MFMA that used a block.  Operand rows and hidden chunk lie in LDS with
@@ -91,6 +94,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
   // what the registers of one or two workgroups per CU hold
   constexpr int kRing = NW == 8 ? 16 : MT > 2 ? 24 : 12;
   constexpr int kFC = L::kFC, kThreads = 64 * NW;
+  constexpr bool kKeep = NW == 8 || MT == 1;
   constexpr int NT = D / (32 * NW), KS = D / 16, BM = 32 * MT, ROWB = D * 2, HROWB = kFC * 2;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* const sA = smem;
@@ -108,18 +112,19 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
   float* const v_b1 = reinterpret_cast<float*>(smem + L::kVec);
   float* const v_d = v_b1 + max(p.F, 3 * D);   // five vectors of D
   float* const v_qkv = NW == 8 ? v_d + 5 * D : v_b1;
+  // (behind the row sums' place; the hidden chunk comes there later)
+  float* const v_bo = reinterpret_cast<float*>(smem + L::kVec) - D;
+  static_assert(L::kHS >= MT * 32 * 2 * NW * 4 + D * 4, "bias behind the row sums");
   const int c0 = wave * (D / NW);
 
   int vpos[MT];
+  if (kKind == kHead) {
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int m = min(m0 + i * 32 + l32, M - 1);
-    if (kKind == kHead) {
+    for (int i = 0; i < MT; ++i) {
+      const int m = min(m0 + i * 32 + l32, M - 1);
       const int f = frame_of_token(p.cu, p.nseq, m);
       vpos[i] = p.pcu[f] + (m - p.cu[f]);
       if (wave == 0 && g == 0 && m0 + i * 32 + l32 < M) p.vt_pos[m] = vpos[i];
-    } else if (kKind == kMid) {
-      vpos[i] = p.vt_pos[m];
     }
   }
 
@@ -132,6 +137,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
   }
   if (tid < D / 4) {
     if (kKind != kHead) {
+      *reinterpret_cast<float4*>(v_bo + tid * 4) = *reinterpret_cast<const float4*>(p.b_o + tid * 4);
       *reinterpret_cast<float4*>(v_d + tid * 4) = *reinterpret_cast<const float4*>(p.ln2_g + tid * 4);
       *reinterpret_cast<float4*>(v_d + D + tid * 4) = *reinterpret_cast<const float4*>(p.ln2_b + tid * 4);
       *reinterpret_cast<float4*>(v_d + 2 * D + tid * 4) = *reinterpret_cast<const float4*>(p.b2 + tid * 4);
@@ -171,28 +177,45 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
                    : : "s"(dst), "v"(src) : "memory");
     }
   }
-  // residual rows (plus the bias of what is added to them) as start values
+  // residual rows: into the accumulators, in two parts where something is added to them
   unsigned char* const xw = reinterpret_cast<unsigned char*>(p.x) + (size_t)(m0 >> 5) * (D * 128) + wave * (NT * 4096);
   f32x16 acc[NT][MT];
+  u32x8 hi[NT][MT];
 #pragma unroll
   for (int j = 0; j < NT; ++j)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int col = c0 + j * 32 + 8 * q + 4 * g;
-      float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (kKind != kHead) b = *reinterpret_cast<const float4*>(p.b_o + col);
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
         const float4 v =
             kKind == kHead
-                ? *reinterpret_cast<const float4*>(p.x0 + (size_t)min(m0 + i * 32 + l32, M - 1) * D + col)
+                ? *reinterpret_cast<const float4*>(p.x0 + (size_t)min(m0 + i * 32 + l32, M - 1) * D + c0 + j * 32 + 8 * q + 4 * g)
                 : *reinterpret_cast<const float4*>(xw + i * (D * 128) + j * 4096 + q * 1024 + voff);
-        acc[j][i][4 * q] = v.x + b.x;
-        acc[j][i][4 * q + 1] = v.y + b.y;
-        acc[j][i][4 * q + 2] = v.z + b.z;
-        acc[j][i][4 * q + 3] = v.w + b.w;
+        acc[j][i][4 * q] = v.x;
+        acc[j][i][4 * q + 1] = v.y;
+        acc[j][i][4 * q + 2] = v.z;
+        acc[j][i][4 * q + 3] = v.w;
       }
-    }
+  auto split = [&]() {
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) residual_split(acc[j][i], hi[j][i]);
+  };
+  auto join = [&](const float* b) {   // `b` in LDS, the columns of D
+    int g4 = 4 * g;
+    work_out_here(g4);
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 bq = *reinterpret_cast<const float4*>(b + c0 + j * 32 + 8 * q + g4);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) residual_join(acc[j][i], hi[j][i], q, bq);
+      }
+  };
+  typedef __attribute__((address_space(1))) unsigned char* gwptr;
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
   // LDS operand addresses (chunk swizzled with the row), k-step modulo 4
   uint32_t ao[8], ho[8];
@@ -241,25 +264,30 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
 
   float mean[MT], rstd[MT];
   if (kKind != kHead) {
+    split();
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
     WIDE_PRODUCT(acc, NT, KS, sA, ROWB, ao);   // attention output times Wo
+    join(v_bo);
     wide_stats<NW>(acc, s_red, l32, g, wave, p.eps, mean, rstd);
     wide_norm_to_lds<NW>(acc, mean, rstd, v_d, v_d + D, sA, l32, g, wave);
-    // bias of the second FFN matrix
+    if (kKeep) {
+      split();
+    } else {
+      gwptr xo = (gwptr)xw;
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
+      for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 b = *reinterpret_cast<const float4*>(v_d + 2 * D + c0 + j * 32 + 8 * q + 4 * g);
+        for (int j = 0; j < NT; ++j) {
+          asm volatile("" : "+s"(xo));   // addresses worked out here, not kept from the top of the kernel
+          residual_split(acc[j][i], hi[j][i]);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          acc[j][i][4 * q] += b.x;
-          acc[j][i][4 * q + 1] += b.y;
-          acc[j][i][4 * q + 2] += b.z;
-          acc[j][i][4 * q + 3] += b.w;
+          for (int h = 0; h < 2; ++h)
+            *reinterpret_cast<__attribute__((address_space(1))) u32x4*>(xo + (i * (D * 128) + j * 4096 + h * 1024) + voff) =
+                u32x4{hi[j][i][4 * h], hi[j][i][4 * h + 1], hi[j][i][4 * h + 2], hi[j][i][4 * h + 3]};
+          __builtin_amdgcn_sched_barrier(0);
         }
-      }
+    }
     f32x16 hid[1][MT];
     uint2 pk[MT][4];
     auto hid_bias = [&](int c) {
@@ -372,30 +400,49 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
     }
     put_hidden();
     __syncthreads();
-    float4 bq[2];
+    float4 bq0, bq1;
+    if (kKind == kMid) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) vpos[i] = p.vt_pos[min(m0 + i * 32 + l32, M - 1)];
+    }
     if (NW == 4 && kKind == kMid) {
       // the next projection's bias takes the place of b1 (everybody is done with that)
-#pragma unroll
-      for (int k = 0; k < 2; ++k) bq[k] = *reinterpret_cast<const float4*>(p.b_qkv + min(tid * 4 + k * 1024, 3 * D - 4));
+      static_assert(NW == 8 || (3 * D > 1024 && 3 * D <= 2048), "two pieces");
+      bq0 = *reinterpret_cast<const float4*>(p.b_qkv + tid * 4);
+      bq1 = *reinterpret_cast<const float4*>(p.b_qkv + min(tid * 4 + 1024, 3 * D - 4));
     }
     WIDE_PRODUCT(acc, NT, kFC / 16, sH, HROWB, ho);
     if (NW == 4 && kKind == kMid) {
-#pragma unroll
-      for (int k = 0; k < 2; ++k)
-        if (tid * 4 + k * 1024 < 3 * D) *reinterpret_cast<float4*>(v_b1 + tid * 4 + k * 1024) = bq[k];
+      *reinterpret_cast<float4*>(v_b1 + tid * 4) = bq0;
+      if (tid * 4 + 1024 < 3 * D) *reinterpret_cast<float4*>(v_b1 + tid * 4 + 1024) = bq1;
     }
+    if (!kKeep) {
+      gwptr xi = (gwptr)xw;
+      asm volatile("" : "+s"(xi) : : "memory");   // (not what was stored there, still in registers)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const u32x4 v =
+                *reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(xi + (i * (D * 128) + j * 4096 + h * 1024) + voff);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) hi[j][i][4 * h + e] = v[e];
+          }
+    }
+    join(v_d + 2 * D);
     __syncthreads();   // (the row sums go where the hidden chunk was)
   }
   // the new residual rows
   if (kKind != kLast) {
-    typedef __attribute__((address_space(1))) unsigned char* gwptr;
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     gwptr xo = (gwptr)xw;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
-        asm volatile("" : "+s"(xo));   // addresses worked out here, not kept from the top of the kernel
+        asm volatile("" : "+s"(xo));
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           *reinterpret_cast<__attribute__((address_space(1))) f32x4*>(xo + (i * (D * 128) + j * 4096 + q * 1024) + voff) =

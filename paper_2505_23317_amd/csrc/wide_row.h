@@ -10,6 +10,11 @@ __device__ __forceinline__ int tile_order(int pid, int total) {
   return (pid < (per << 3)) ? (pid & 7) * per + (pid >> 3) : pid;
 }
 
+// Addresses that follow from a lane's numbers are the same at every use, and the compiler keeps
+// them from the first to the last, in scratch memory where registers run out.  Behind this call it
+// does not know that they are.
+__device__ __forceinline__ void work_out_here(int& v) { asm volatile("" : "+v"(v)); }
+
 // gemm.hip's gelu_fast
 __device__ __forceinline__ float gelu_sig(float x) {
   const float xc = __builtin_amdgcn_fmed3f(x, -8.0f, 8.0f);
@@ -24,6 +29,30 @@ __device__ __forceinline__ float gelu_sig(float x) {
 // instead would have every load touch 32 rows with 32 bytes each: 3 us for the rows of a
 // workgroup when it is alone, 10 us with all CUs at it.
 
+// A residual and what is added to it.  An MFMA rounds its sum, so a product that is accumulated
+// on top of the residual rounds at the residual's magnitude in every step.  Here it starts at the
+// low part: residual_split leaves x - hi in acc, hi the bf16 next to x (the difference is exact),
+// and residual_join gives hi + (acc + b), one rounding at x's magnitude.  The low part, 2^-9 of x
+// at most, is what a sum from 0 would start at as far as rounding goes, and hi is half the bytes
+// that x would be.
+typedef __attribute__((ext_vector_type(8))) uint32_t u32x8;
+__device__ __forceinline__ void residual_split(f32x16& acc, u32x8& hi) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    uint32_t h = pack_bf16x2(acc[2 * e], acc[2 * e + 1]);
+    acc[2 * e] -= __uint_as_float(h << 16);
+    acc[2 * e + 1] -= __uint_as_float(h & 0xffff0000u);
+    asm volatile("" : "+v"(h));   // (or the compiler keeps both halves as floats)
+    hi[e] = h;
+  }
+}
+__device__ __forceinline__ void residual_join(f32x16& acc, const u32x8& hi, int q, const float4& b) {
+  acc[4 * q] = __uint_as_float(hi[2 * q] << 16) + (acc[4 * q] + b.x);
+  acc[4 * q + 1] = __uint_as_float(hi[2 * q] & 0xffff0000u) + (acc[4 * q + 1] + b.y);
+  acc[4 * q + 2] = __uint_as_float(hi[2 * q + 1] << 16) + (acc[4 * q + 2] + b.z);
+  acc[4 * q + 3] = __uint_as_float(hi[2 * q + 1] & 0xffff0000u) + (acc[4 * q + 3] + b.w);
+}
+
 // Mean and 1/sigma of 32 MT rows that a workgroup of NW (four or eight) wavefronts holds as
 // MFMA results: wavefront w has columns [w D/NW, (w + 1) D/NW), D = 32 NT NW.  Each part's
 // squares are taken about the part's own mean and put together exactly.  (Fused multiply-adds are written
@@ -33,6 +62,7 @@ __device__ __forceinline__ void wide_stats(const f32x16 (&acc)[NT][MT], float* s
                                            float (&mean)[MT], float (&rstd)[MT]) {
   constexpr int D = 32 * NT * NW;
   constexpr float kInvN = (float)NW / D;   // of a part's columns
+  work_out_here(l32);
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     float s = 0.f;
@@ -86,6 +116,8 @@ __device__ __forceinline__ void wide_norm_to_lds(const f32x16 (&acc)[NT][MT], co
                                                  const float* gain, const float* offs, unsigned char* sA, int l32, int g,
                                                  int wave) {
   constexpr int D = 32 * NT * NW;
+  work_out_here(l32);
+  work_out_here(g);
   float shift[MT];
 #pragma unroll
   for (int i = 0; i < MT; ++i) shift[i] = -mean[i] * rstd[i];

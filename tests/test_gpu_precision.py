@@ -1,0 +1,66 @@
+"""What the kernels hold in fp32 between their bf16 operands.  The weights are chosen so that no
+operand is rounded (attention that averages equal values, hidden units that the activation passes
+through), which leaves the rounding of the fp32 sums alone; the reference is float64."""
+import numpy as np
+import pytest
+
+from paper_2505_23317_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# 899 tokens a frame: one frame goes where few rows go (width 384: the spread kernels), the others
+# to workgroups of 32, 64 and 96 rows
+FORMS = [(256, 1), (256, 10), (256, 19), (384, 1), (384, 4), (384, 10), (384, 19)]
+
+
+def _weights(cfg, seed):
+    """Every matrix and bias zero but what follows: values v for all tokens (queries and keys are zero,
+    so attention returns v), hidden units h between 8 and 16 (the activation returns them)."""
+    rng = np.random.default_rng(seed)
+    w = {k: np.zeros_like(a) for k, a in synth.make_weights(cfg, seed).items()}
+    for k in ("ln1_g", "ln2_g", "lnf_g"):
+        w[k] += 1.0
+    w["b_qkv"][0, 2 * cfg.d:] = v = synth.bf16_round(rng.uniform(-2.0, 2.0, cfg.d).astype(np.float32))
+    w["b_ff1"][0] = h = synth.bf16_round(rng.uniform(8.0, 15.9, cfg.ffn).astype(np.float32))
+    return w, v.astype(np.float64), h.astype(np.float64), rng
+
+
+def _coarse(cfg, w):
+    """(embedded tokens, result) of black frames"""
+    import torch
+    from paper_2505_23317_amd import cfdetr as K
+    enc = K.Encoder(cfg, w)
+    out = enc.alloc_outputs(cfg.B)
+    img = enc.upload_images(np.zeros((cfg.B, 3, cfg.H, cfg.W), np.float32))
+    enc.coarse_encode(img, cfg.B, out["x0_cache"], out["y_coarse"])
+    enc.sync_status()
+    torch.cuda.synchronize()
+    x0, y = (out[k].cpu().numpy().astype(np.float64) for k in ("x0_cache", "y_coarse"))
+    enc.close()
+    return x0, y
+
+
+@pytest.mark.parametrize("ratio", [1.0, 30.0, 1000.0])
+@pytest.mark.parametrize("d, frames", FORMS)
+def test_products_are_not_rounded_at_the_residuals_magnitude(d, frames, ratio):
+    """Residual rows of the size of what the two products of a layer add to them, and of 30 and 1000
+    times that.  A product that is summed by itself and added once leaves half a unit at the residual's
+    magnitude at most (3e-8 root mean square of it for both), its own sum's rounding, which is as much
+    where the two are of a size, and that of LayerNorm's few operations: 1.3e-7 is above their sum.
+    Summed on top of the residual a product leaves a rounding for each of its 16 to 96 steps."""
+    cfg = synth.Config("sums", frames, 232, 248, (8,), d, 8 if d == 256 else 6, 1, 4 * d, "bf16", box_rule="poisson")
+    w, v, h, rng = _weights(cfg, 3)
+    w["b_embed0"] += rng.normal(0.0, ratio, d).astype(np.float32)
+    w["w_o"][0] = synth.bf16_round(rng.normal(0.0, 0.9 / np.sqrt(d), (d, d)).astype(np.float32))
+    w["w_ff2"][0] = synth.bf16_round(rng.normal(0.0, 0.08 / np.sqrt(cfg.ffn), (d, cfg.ffn)).astype(np.float32))
+    w["b_o"][0] = rng.normal(0.0, 0.1, d)
+    w["b_ff2"][0] = rng.normal(0.0, 0.1, d)
+    x0, y = _coarse(cfg, w)
+    x1 = x0 + (w["w_o"][0].astype(np.float64) @ v + w["b_o"][0].astype(np.float64))
+    x2 = x1 + (w["w_ff2"][0].astype(np.float64) @ h + w["b_ff2"][0].astype(np.float64))
+    assert 0.5 < np.std(x1 - x0) < 2.0 and 0.5 < np.std(x2 - x1) < 2.0 and 0.7 * ratio < np.std(x0) < 2.0 * ratio
+    c = x2 - x2.mean(axis=1, keepdims=True)
+    ref = c / np.sqrt((c * c).mean(axis=1, keepdims=True) + 1e-5)
+    rms = float(np.sqrt(((y - ref) ** 2).mean()))
+    print(f"residual {ratio} times the products, width {d}, {frames} frames: {rms:.2e}", flush=True)
+    assert rms <= 1.3e-7
