@@ -220,7 +220,6 @@ __global__ __launch_bounds__(256) void wide_norm_kernel(float* x, const float* l
   float mean[1], rstd[1];
   wide_stats<4>(xa, s_red, l32, g, wave, eps, mean, rstd);
   if (m >= M) return;
-  const float shift = -mean[0] * rstd[0];
   const bool second = out2 != nullptr && m >= split_row;
   float* const o = (second ? out2 : out) + (size_t)(second ? m - split_row : m) * D;
 #pragma unroll
@@ -229,10 +228,10 @@ __global__ __launch_bounds__(256) void wide_norm_kernel(float* x, const float* l
     for (int q = 0; q < 4; ++q) {
       const int col = wave * (D / 4) + j * 32 + 8 * q + 4 * g;
       const float4 ga = *reinterpret_cast<const float4*>(ln_g + col), of = *reinterpret_cast<const float4*>(ln_b + col);
-      *reinterpret_cast<float4*>(o + col) = make_float4(fmaf(fmaf(xa[j][0][4 * q], rstd[0], shift), ga.x, of.x),
-                                                        fmaf(fmaf(xa[j][0][4 * q + 1], rstd[0], shift), ga.y, of.y),
-                                                        fmaf(fmaf(xa[j][0][4 * q + 2], rstd[0], shift), ga.z, of.z),
-                                                        fmaf(fmaf(xa[j][0][4 * q + 3], rstd[0], shift), ga.w, of.w));
+      *reinterpret_cast<float4*>(o + col) = make_float4(wide_normed(xa[j][0][4 * q], mean[0], rstd[0], ga.x, of.x),
+                                                        wide_normed(xa[j][0][4 * q + 1], mean[0], rstd[0], ga.y, of.y),
+                                                        wide_normed(xa[j][0][4 * q + 2], mean[0], rstd[0], ga.z, of.z),
+                                                        wide_normed(xa[j][0][4 * q + 3], mean[0], rstd[0], ga.w, of.w));
     }
 }
 

@@ -462,14 +462,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
         for (int i = 0; i < MT; ++i) {
           const int m = m0 + i * 32 + l32;
           if (m >= M) continue;
-          const float shift = -mean[i] * rstd[i];
           const bool second = p.out2 != nullptr && m >= p.split_row;
           float* o = (second ? p.out2 : p.out) + (size_t)(second ? m - p.split_row : m) * D + col;
           *reinterpret_cast<float4*>(o) =
-              make_float4(fmaf(fmaf(acc[j][i][4 * q], rstd[i], shift), ga.x, of.x),
-                          fmaf(fmaf(acc[j][i][4 * q + 1], rstd[i], shift), ga.y, of.y),
-                          fmaf(fmaf(acc[j][i][4 * q + 2], rstd[i], shift), ga.z, of.z),
-                          fmaf(fmaf(acc[j][i][4 * q + 3], rstd[i], shift), ga.w, of.w));
+              make_float4(wide_normed(acc[j][i][4 * q], mean[i], rstd[i], ga.x, of.x),
+                          wide_normed(acc[j][i][4 * q + 1], mean[i], rstd[i], ga.y, of.y),
+                          wide_normed(acc[j][i][4 * q + 2], mean[i], rstd[i], ga.z, of.z),
+                          wide_normed(acc[j][i][4 * q + 3], mean[i], rstd[i], ga.w, of.w));
         }
       }
     return;

@@ -97,7 +97,7 @@ __device__ __forceinline__ void wide_stats(const f32x16 (&acc)[NT][MT], float* s
       sum += (s.x + s.y) + (s.z + s.w);
       within += (v.x + v.y) + (v.z + v.w);
     }
-    mean[i] = sum * (1.0f / D);
+    mean[i] = sum / D;   // (1 / 384 is no float: times that, the mean of equal values would not be that value)
 #pragma unroll
     for (int k = 0; k < NW / 4; ++k) {
       const float4 s = part[k];
@@ -109,6 +109,12 @@ __device__ __forceinline__ void wide_stats(const f32x16 (&acc)[NT][MT], float* s
   }
 }
 
+// The mean is taken off first: next to it x - mean is exact, while x rstd and mean rstd would
+// each be rounded at the mean's magnitude.
+__device__ __forceinline__ float wide_normed(float x, float mean, float rstd, float gain, float offs) {
+  return fmaf((x - mean) * rstd, gain, offs);
+}
+
 // The normalised rows in bf16 to LDS: rows of D, 16-byte chunks XORed by the row.  Ends with
 // a barrier.
 template <int NW, int NT, int MT>
@@ -118,9 +124,6 @@ __device__ __forceinline__ void wide_norm_to_lds(const f32x16 (&acc)[NT][MT], co
   constexpr int D = 32 * NT * NW;
   work_out_here(l32);
   work_out_here(g);
-  float shift[MT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i) shift[i] = -mean[i] * rstd[i];
 #pragma unroll
   for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -131,10 +134,10 @@ __device__ __forceinline__ void wide_norm_to_lds(const f32x16 (&acc)[NT][MT], co
       const int chunk = (wave * (D / NW) >> 3) + j * 4 + q;
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
-        const float r0 = fmaf(fmaf(acc[j][i][4 * q], rstd[i], shift[i]), ga.x, of.x);
-        const float r1 = fmaf(fmaf(acc[j][i][4 * q + 1], rstd[i], shift[i]), ga.y, of.y);
-        const float r2 = fmaf(fmaf(acc[j][i][4 * q + 2], rstd[i], shift[i]), ga.z, of.z);
-        const float r3 = fmaf(fmaf(acc[j][i][4 * q + 3], rstd[i], shift[i]), ga.w, of.w);
+        const float r0 = wide_normed(acc[j][i][4 * q], mean[i], rstd[i], ga.x, of.x);
+        const float r1 = wide_normed(acc[j][i][4 * q + 1], mean[i], rstd[i], ga.y, of.y);
+        const float r2 = wide_normed(acc[j][i][4 * q + 2], mean[i], rstd[i], ga.z, of.z);
+        const float r3 = wide_normed(acc[j][i][4 * q + 3], mean[i], rstd[i], ga.w, of.w);
         *reinterpret_cast<uint2*>(sA + (i * 32 + l32) * (2 * D) + ((chunk ^ (l32 & 15)) << 4) + g * 8) =
             make_uint2(pack_bf16x2(r0, r1), pack_bf16x2(r2, r3));
       }

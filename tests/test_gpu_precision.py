@@ -64,3 +64,20 @@ def test_products_are_not_rounded_at_the_residuals_magnitude(d, frames, ratio):
     rms = float(np.sqrt(((y - ref) ** 2).mean()))
     print(f"residual {ratio} times the products, width {d}, {frames} frames: {rms:.2e}", flush=True)
     assert rms <= 1.3e-7
+
+
+@pytest.mark.parametrize("d, frames", FORMS + [(768, 1), (768, 10)])
+def test_rows_of_equal_values_normalise_to_the_offsets(d, frames):
+    """Every column 3 * 2^29 (the bias is added to tokens too small to change it; sums and mean of such
+    rows are exact): x - mean is 0, and the result is LayerNorm's offset to the bit.  With x / sigma and
+    mean / sigma rounded apart it is off by what a float leaves of 5e11, and so it is with a mean that
+    is rounded."""
+    cfg = synth.Config("equal", frames, 232, 248, (8,), d, 8 if d == 256 else d // 64, 1, 4 * d, "bf16", box_rule="poisson")
+    w, _, _, rng = _weights(cfg, 5)
+    w["b_qkv"][:] = 0.0
+    w["b_ff1"][:] = 0.0
+    w["b_o"][0] = 3.0 * 2.0 ** 29
+    w["lnf_b"][:] = rng.normal(0.0, 1.0, d)
+    x0, y = _coarse(cfg, w)
+    assert np.abs(x0).max() < 64.0
+    assert (y == w["lnf_b"].astype(np.float64)).all()
