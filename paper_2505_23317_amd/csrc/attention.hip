@@ -166,6 +166,7 @@ __device__ __attribute__((noinline)) void exact_queries(
         clear_v_padding<DH>(sV, TK - kv0, tid);
         __syncthreads();
       }
+      float l_tile = 0.f;
 #pragma unroll
       for (int sub = 0; sub < 2; ++sub) {
         f32x16 s;
@@ -192,7 +193,7 @@ __device__ __attribute__((noinline)) void exact_queries(
           for (int e = 0; e < 4; ++e) {
             const float p0 = __builtin_amdgcn_exp2f(s[8 * t + 2 * e] - m_ref);
             const float p1 = __builtin_amdgcn_exp2f(s[8 * t + 2 * e + 1] - m_ref);
-            l_run += p0 + p1;
+            l_tile += p0 + p1;
             w[e] = pack_bf16x2(p0, p1);
           }
           uint4 packed = make_uint4(w[0], w[1], w[2], w[3]);
@@ -206,6 +207,7 @@ __device__ __attribute__((noinline)) void exact_queries(
           }
         }
       }
+      l_run += l_tile;
     }
     if (pass == 0) m_ref = fmaxf(m_ref, __shfl_xor(m_ref, 32, kWave));
   }
@@ -336,7 +338,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4
         qf[qb][ks] = *reinterpret_cast<const bf16x8*>(qbase + (size_t)q_load * q_ld + ks * 16 + g * 8);
     }
     f32x16 acc_o[QB][MO];
-    float l_run[QB];
+    // sums of probabilities: over all tiles so far, and over the tile in hand, which is added when
+    // it is whole (thousands of keys added one pair at a time lose digits, equal ones 2e-5 at 6,400)
+    float l_run[QB], l_tile[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       l_run[qb] = 0.f;
@@ -394,9 +398,10 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4
     // unit u: behind every MFMA its share of that arithmetic and of the LDS reads, in an order
     // the compiler is not to change.  The values of unit u are read behind the first product.
     auto stage = [&](f32x16(&s)[QB], f32x16(&sn)[QB], bf16x8(&pc)[QB][2], bf16x8(&pp)[QB][2],
-                     const unsigned char* ktile, int ksub, const unsigned char* vtile, int vsub,
+                     const unsigned char* ktile, int ksub, const unsigned char* vtile, auto unit_tag,
                      auto more_tag) {
       constexpr bool kMore = decltype(more_tag)::value;   // there is a unit u + 1
+      constexpr int vsub = decltype(unit_tag)::value;     // which half of its tile unit u is
       constexpr int NQK = QB * KS, NPV = QB * 2 * MO, NM = NQK + NPV;
       constexpr int PAIRS = QB * 8, PPM = PAIRS / NM;
       static_assert(PAIRS % NM == 0, "exponentials per MFMA");
@@ -421,9 +426,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4
           // transcendental pipe by now
           if (x > 0) {
             const int qy = (x - 1) / 8;
-            l_run[qy] += e0 + e1;
+            l_tile[qy] = vsub == 0 && (x - 1) % 8 == 0 ? e0 + e1 : l_tile[qy] + (e0 + e1);
             w[qy][(x - 1) % 8] = pack_bf16x2(e0, e1);
-            asm volatile("" : "+v"(w[qy][(x - 1) % 8]), "+v"(l_run[qy]));
+            asm volatile("" : "+v"(w[qy][(x - 1) % 8]), "+v"(l_tile[qy]));
           }
           e0 = __builtin_amdgcn_exp2f(s[qb][2 * e]);
           e1 = __builtin_amdgcn_exp2f(s[qb][2 * e + 1]);
@@ -431,8 +436,12 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      l_run[QB - 1] += e0 + e1;
+      l_tile[QB - 1] += e0 + e1;
       w[QB - 1][7] = pack_bf16x2(e0, e1);
+      if (vsub == 1) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) l_run[qb] += l_tile[qb];
+      }
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
@@ -458,6 +467,8 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4
     read_v(smem, 0);   // (in front of the first unit: met with probabilities 0)
     const unsigned char* tcur = smem;
     int slot = 0;
+    const auto half0 = std::integral_constant<int, 0>{};
+    const auto half1 = std::integral_constant<int, 1>{};
     const auto yes = std::integral_constant<bool, true>{};
     const auto no = std::integral_constant<bool, false>{};
     // Three tiles at a time have constant slots, which makes every LDS address a lane constant
@@ -467,11 +478,11 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4
       constexpr int kSlot = decltype(slot_tag)::value, kNext = (kSlot + 1) % NB;
       const unsigned char* cur = smem + kSlot * TILE;
       const unsigned char* next = smem + kNext * TILE;
-      stage(sA, sB, pA, pB, cur, 1, cur, 0, yes);    // unit 2j
+      stage(sA, sB, pA, pB, cur, 1, cur, half0, yes);    // unit 2j
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
       issue(j + 2, (kSlot + 2) % NB);
-      stage(sB, sA, pB, pA, next, 0, cur, 1, yes);   // unit 2j + 1
+      stage(sB, sA, pB, pA, next, 0, cur, half1, yes);   // unit 2j + 1
     };
     int j = 0;
     for (; j + 5 <= n_kv; j += 3) {
@@ -480,7 +491,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4
       tile_step(j + 2, std::integral_constant<int, 2>{});
     }
     for (; j < n_kv - 1; ++j) {
-      stage(sA, sB, pA, pB, tcur, 1, tcur, 0, yes);    // unit 2j
+      stage(sA, sB, pA, pB, tcur, 1, tcur, half0, yes);    // unit 2j
       __builtin_amdgcn_s_waitcnt(0x0F70);
       __syncthreads();
       const int snext = slot == NB - 1 ? 0 : slot + 1;
@@ -491,7 +502,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4
         clear_v_padding<DH>(smem + snext * TILE + KBYTES, TK - (j + 1) * kBlockKV, tid);
         __syncthreads();
       }
-      stage(sB, sA, pB, pA, tnext, 0, tcur, 1, yes);   // unit 2j + 1
+      stage(sB, sA, pB, pA, tnext, 0, tcur, half1, yes);   // unit 2j + 1
       tcur = tnext;
       slot = snext;
     }
@@ -499,9 +510,9 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4
       // the last tile, ragged or not
       const int kv0 = (n_kv - 1) * kBlockKV;
       if (TK & (kBlockKV - 1)) mask(sA, kv0);
-      stage(sA, sB, pA, pB, tcur, 1, tcur, 0, yes);
+      stage(sA, sB, pA, pB, tcur, 1, tcur, half0, yes);
       if (TK & (kBlockKV - 1)) mask(sB, kv0 + 32);
-      stage(sB, sA, pB, pA, tcur, 0, tcur, 1, no);
+      stage(sB, sA, pB, pA, tcur, 0, tcur, half1, no);
 #pragma unroll
       for (int m = 0; m < QB * 2 * MO; ++m) pv1(pB, m);
     }

@@ -81,3 +81,61 @@ def test_rows_of_equal_values_normalise_to_the_offsets(d, frames):
     x0, y = _coarse(cfg, w)
     assert np.abs(x0).max() < 64.0
     assert (y == w["lnf_b"].astype(np.float64)).all()
+
+
+# Probabilities p, a head each, and its value v: attention over equal keys gives v bf16(p) / p, and p
+# is chosen so that this lies 1e-5 of itself below or above a boundary between two bf16 numbers.  Of
+# 6,400 equal probabilities a sum that runs over one pair after the other is off by 2.3e-5 (-2.3e-5 for
+# the first, 2.2e-5 for the second) and lands on the other side; tile by tile it is off by less than 1e-6.
+EDGES = [(1.203125, 1.5, 1.50390625, -1), (1.28125, 1.75, 1.75390625, 1)]   # bf16(p), v, boundary, side
+
+
+def _edge_probability(edge):
+    P, v, boundary, side = edge
+    return v * P / (boundary * (1.0 + side * 1e-5))
+
+
+def _summed(p, keys, pairs):
+    """Relative error of a lane's sum of half the keys in fp32, `pairs` pairs at a time."""
+    pair, total = np.float32(p) + np.float32(p), np.float32(0.0)
+    for _ in range(keys // (4 * pairs)):
+        part = np.float32(0.0)
+        for _ in range(pairs):
+            part = np.float32(part + pair)
+        total = np.float32(total + part)
+    return float(total) / (keys / 2 * float(np.float32(p))) - 1.0
+
+
+@pytest.mark.parametrize("heads, frames", [(2, 1), (2, 9), (4, 1)])
+def test_probabilities_are_summed_tile_by_tile(heads, frames):
+    """6,400 keys a frame; items of 128 queries, of 256 (nine frames) and heads of 32."""
+    d, keys = 128, 6400
+    for edge in EDGES:
+        p = _edge_probability(edge)
+        assert synth.bf16_round(np.array([p], np.float32))[0] == edge[0]
+        assert np.sign(_summed(p, keys, 1)) == edge[3] and abs(_summed(p, keys, 1)) > 1.8e-5
+        assert abs(_summed(p, keys, 16)) < 1e-6
+    cfg = synth.Config("tiles", frames, 640, 640, (8,), d, heads, 1, 64, "bf16", box_rule="poisson")
+    assert cfg.n_cells(0) == keys and (frames == 1 or frames * keys * heads > 3500 * 32)
+    w, _, _, _ = _weights(cfg, 9)
+    w["b_ff1"][:] = 0.0
+    dh = cfg.d_head
+    out = np.zeros(d)
+    for h in range(heads):
+        edge = EDGES[h % 2]
+        rest = np.float32(np.log2(_edge_probability(edge)))   # in three parts, so that no bf16 rounds it
+        for k in range(3):
+            part = synth.bf16_round(np.array([rest], np.float32))[0]
+            w["b_qkv"][0, h * dh + k] = part * np.sqrt(dh) / 1.4426950408889634
+            rest = np.float32(rest - part)
+        assert rest == 0.0
+        w["b_qkv"][0, d + h * dh:d + h * dh + 3] = 1.0
+        w["b_qkv"][0, 2 * d + h * dh:2 * d + (h + 1) * dh] = edge[1]
+        exact = edge[1] * edge[0] / _edge_probability(edge)
+        out[h * dh:(h + 1) * dh] = synth.bf16_round(np.array([exact], np.float32))[0]
+    w["w_o"][0] = np.eye(d)
+    x0, y = _coarse(cfg, w)
+    c = x0 + out - (x0 + out).mean(axis=1, keepdims=True)
+    ref = c / np.sqrt((c * c).mean(axis=1, keepdims=True) + 1e-5)
+    # a bf16 step of one head's output moves its columns by 4e-3 and more; fp32 leaves 1e-6
+    assert np.abs(y - ref).max() < 1e-4
