@@ -349,13 +349,15 @@ __device__ __forceinline__ uint32_t twice(uint32_t x) {
 // A token's place depends on all frames, so every workgroup needs the hit cells of all of
 // them, and two kernels with the flags in memory between them spent their time on launches
 // and on memory's latency (a trip per 1024 cells).  Painting the boxes is cheap enough to do
-// in every workgroup instead: eight lanes a box, one row each, an OR per 32 cells into a bit
-// map in LDS.  Counts are popcounts of words; the tokens of a level's word are the children of
+// in every workgroup instead: up to eight lanes a box, one row each, an OR per 32 cells into a bit
+// map in LDS.  Eight lanes halve the time of few boxes and do most of a box's work eight times, so
+// there are fewer the more boxes there are, and the next box is on its way while one is painted.  Counts are popcounts of words; the tokens of a level's word are the children of
 // the parents' bits without the word's own, so one scan over the words of the frame gives
 // every token its place.
 // Measured, two kernels / this one: six frames of 640 x 640 10.4 / 7.8 us, twelve of three
-// levels at 1024 x 1024 with the plan 28 / 9 us.
-constexpr int kPaintLanes = 8;
+// levels at 1024 x 1024 with the plan 28 / 9 us; with 300 boxes a frame 64 frames of 640 x 640
+// 43.0 / 21.6 us (eight lanes a box throughout 76.7), of 320 x 320 32.4 / 21.0 (76.1).
+constexpr int kPaintTrips = 4;          // boxes a lane paints before a box gets fewer lanes
 constexpr int kSelectLds = 96 * 1024;   // most of its dynamic LDS (the plan's tables take 20 KB)
 
 __global__ __launch_bounds__(kCompactThreads) void select_kernel(
@@ -381,13 +383,29 @@ __global__ __launch_bounds__(kCompactThreads) void select_kernel(
     lo = box_offsets[pf];
     hi = box_offsets[pf + 1];
   }
+  const int boxes_all = min(max(box_offsets[B] - box_offsets[0], 0), 1 << 24);
   const bool easy = hard != nullptr && lane < B && hard[lane] == 0;
   for (int i = tid; i < B * frame_words; i += kCompactThreads) s_bits[i] = 0;
   for (int i = tid; i < kMaxBatch * kMaxLevels; i += kCompactThreads) (&s_split[0][0])[i] = 0;
   __syncthreads();
-  for (int b = lo + (tid % per_frame) / kPaintLanes; b < hi; b += per_frame / kPaintLanes) {
-    const int4 raw = *reinterpret_cast<const int4*>(boxes + 4 * (size_t)b);
-    const int levels = min((int)tier[b], n - 1);   // those that the box splits
+  int log_lanes = 3;
+  while (log_lanes > 0 && (boxes_all << log_lanes) > kPaintTrips * kCompactThreads) --log_lanes;
+  const int lanes = 1 << log_lanes, stride = per_frame >> log_lanes;
+  int b = lo + ((tid & (per_frame - 1)) >> log_lanes);
+  int4 next = make_int4(0, 0, 0, 0);
+  int next_tier = 0;
+  auto fetch = [&]() {
+    if (b < hi) {
+      next = *reinterpret_cast<const int4*>(boxes + 4 * (size_t)b);
+      next_tier = tier[b];
+    }
+  };
+  fetch();
+  while (b < hi) {
+    const int4 raw = next;
+    const int levels = min(next_tier, n - 1);   // those that the box splits
+    b += stride;
+    fetch();
     const int x0 = max(raw.x, 0), y0 = max(raw.y, 0);
     const int x1 = min(raw.z, pyr.img_w), y1 = min(raw.w, pyr.img_h);
     if (x1 <= x0 || y1 <= y0) continue;
@@ -395,7 +413,7 @@ __global__ __launch_bounds__(kCompactThreads) void select_kernel(
     for (int l = 0; l < levels; ++l) {
       const int shift = __ffs(pyr.patch[l]) - 1, words = row_words(pyr, l);
       const int c0 = x0 >> shift, c1 = (x1 - 1) >> shift, r1 = (y1 - 1) >> shift;
-      for (int r = (y0 >> shift) + (tid & (kPaintLanes - 1)); r <= r1; r += kPaintLanes)
+      for (int r = (y0 >> shift) + (tid & (lanes - 1)); r <= r1; r += lanes)
         for (int w = c0 >> 5; w <= c1 >> 5; ++w) {
           const uint32_t from = w == c0 >> 5 ? ~0u << (c0 & 31) : ~0u;
           const uint32_t to = w == c1 >> 5 ? ~0u >> (31 - (c1 & 31)) : ~0u;

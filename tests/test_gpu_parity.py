@@ -134,6 +134,38 @@ def test_selection_edge_cases(K):
     enc.close()
 
 
+# frames, most boxes of a frame: the lanes that share a box go from eight to one with the number of
+# boxes to a thread's share (1024 threads over the frames), which these pass on both sides of
+@pytest.mark.parametrize("frames, most", [(1, 600), (5, 100), (12, 130), (33, 45), (64, 20), (64, 37), (64, 300)])
+def test_selection_of_many_boxes(K, frames, most):
+    cfg = synth.Config("many", frames, 256, 320, (32, 16, 8), 64, 2, 1, 128, "f32")
+    rng = np.random.default_rng(most)
+    boxes, tier, offs = [], [], [0]
+    for f in range(frames):
+        n = 0 if f == 3 else most if f == frames // 2 else int(rng.integers(0, most + 1))
+        # most boxes are a few pixels, so that cells stay whole; some are wide, outside, or empty
+        side = rng.choice([1, 6, 12, 200], n, p=[0.6, 0.3, 0.09, 0.01])
+        x0, y0 = rng.integers(-20, cfg.W + 20, n), rng.integers(-20, cfg.H + 20, n)
+        boxes.append(np.stack([x0, y0, x0 + rng.integers(0, side + 1), y0 + rng.integers(0, side + 1)], 1))
+        tier.append(rng.choice([0, 1, 2, 7], n, p=[0.3, 0.4, 0.2, 0.1]))
+        offs.append(offs[-1] + n)
+    boxes = np.concatenate(boxes).astype(np.int32).reshape(-1, 4)
+    tier, offs = np.concatenate(tier).astype(np.uint8), np.asarray(offs, np.int32)
+    _say(f"[case] selection of {offs[-1]} boxes in {frames} frames")
+    enc = K.Encoder(cfg, synth.make_weights(cfg, 4))
+    b, t, o = enc.upload_boxes(boxes, tier, offs)
+    out = enc.alloc_outputs(frames)
+    tok, cu, counts = O.select_fine(boxes, np.minimum(tier, 2), offs, frames, cfg.H, cfg.W, cfg.patch)
+    assert (counts.sum(axis=0) > 0).all()
+    for _ in range(2):
+        enc.select_fine(b, t, o, frames, out["tok_desc"], out["cu_seqlens"], out["level_counts"])
+        enc.sync_status()
+        np.testing.assert_array_equal(out["cu_seqlens"].cpu().numpy(), cu)
+        np.testing.assert_array_equal(out["level_counts"].cpu().numpy(), counts)
+        np.testing.assert_array_equal(out["tok_desc"].cpu().numpy()[:cu[-1]], O.pack_tok_desc(tok))
+    enc.close()
+
+
 def test_selection_with_changing_batch_size_on_one_context(K):
     # flags raised by a call with many frames must not leak into later, smaller or larger calls
     cfg = synth.Config("varb", 4, 128, 128, (64, 32, 16), 64, 2, 1, 128, "f32")
