@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
         // k-step n / 16 of the next contraction, the row's lane in it
         const size_t blk = (size_t)(m0 >> 5) * (p.parts * 8) + (n0 >> 4) + (q >> 1);
         *reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(p.out) + blk * 1024 + (l32 + 32 * (q & 1)) * 16 + g * 8) =
-            make_uint2(pack_bf16x2(gelu_sig(r0), gelu_sig(r1)), pack_bf16x2(gelu_sig(r2), gelu_sig(r3)));
+            make_uint2(pack_bf16x2(gelu_fast(r0), gelu_fast(r1)), pack_bf16x2(gelu_fast(r2), gelu_fast(r3)));
       } else if (v_cols) {
         if (in) {
           bf16_t* vp = p.vt + (size_t)(n - 2 * D) * p.vt_ld + vpos;

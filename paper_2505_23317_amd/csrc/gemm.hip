@@ -51,21 +51,6 @@ __device__ __forceinline__ float gelu_erf(float x) {
   return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f));
 }
 
-// x * Phi(x) for the bf16 path, with Phi(x) ~ 1 / (1 + exp(-x (a + b x^2 + c x^4))),
-// coefficients fitted to the erf form (maximum absolute error of the product 2.6e-5 over
-// all x, two orders below the bf16 resolution of the values that matter); x is clamped
-// to [-8, 8] inside the exponent, where the quartic is still positive.  The epilogue of
-// the first FFN contraction evaluates this once per output element, and with K = d the
-// main loop is short: seven plain operations and two transcendental ones per element
-// keep it well below the cost of the MFMA loop.
-__device__ __forceinline__ float gelu_fast(float x) {
-  const float xc = __builtin_amdgcn_fmed3f(x, -8.0f, 8.0f);
-  const float x2 = xc * xc;
-  // -log2(e) * (a, b, c)
-  const float t = fmaf(fmaf(1.0142780e-03f, x2, -1.0677580e-01f), x2, -2.3011212e+00f) * xc;
-  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
-}
-
 constexpr int kActNone = 0, kActGelu = 1, kActRelu = 2;
 
 template <typename TAct, int kAct>

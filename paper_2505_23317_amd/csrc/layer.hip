@@ -317,8 +317,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
     for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        pk[i][q] = make_uint2(pack_bf16x2(gelu_sig(hid[0][i][4 * q]), gelu_sig(hid[0][i][4 * q + 1])),
-                              pack_bf16x2(gelu_sig(hid[0][i][4 * q + 2]), gelu_sig(hid[0][i][4 * q + 3])));
+        pk[i][q] = make_uint2(pack_bf16x2(gelu_fast(hid[0][i][4 * q]), gelu_fast(hid[0][i][4 * q + 1])),
+                              pack_bf16x2(gelu_fast(hid[0][i][4 * q + 2]), gelu_fast(hid[0][i][4 * q + 3])));
 #pragma nounroll
     for (int c = 1; c < nc; ++c) {
       // chunk c - 1 is in pk (every wavefront has passed its reads of sH): into LDS
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
       {
         constexpr int NM = NT * MT;
         bf16x8 a_[2][MT];
-        // two registers of every hidden tile at a time: V values, nine steps each, step by step,
+        // two registers of every hidden tile at a time: V values, gelu_fast in nine steps, step by step,
         // over TS k-steps
         constexpr int TS = kFC / 128, V = 2 * MT, OPS = 9 * V, PER = (OPS + NM * TS - 1) / (NM * TS);
         float ge[MT][4], gx[V], gc[V], gt[V], g2[V];
@@ -362,10 +362,10 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
                 g2[v] = gc[v] * gc[v];
                 asm volatile("" : "+v"(g2[v]));
               } else if (s == 2) {
-                gt[v] = fmaf(1.0142780e-03f, g2[v], -1.0677580e-01f);
+                gt[v] = fmaf(kGelu5, g2[v], kGelu3);
                 asm volatile("" : "+v"(gt[v]));
               } else if (s == 3) {
-                gt[v] = fmaf(gt[v], g2[v], -2.3011212e+00f);
+                gt[v] = fmaf(gt[v], g2[v], kGelu1);
                 asm volatile("" : "+v"(gt[v]));
               } else if (s == 4) {
                 gt[v] = gt[v] * gc[v];

@@ -15,14 +15,6 @@ __device__ __forceinline__ int tile_order(int pid, int total) {
 // does not know that they are.
 __device__ __forceinline__ void work_out_here(int& v) { asm volatile("" : "+v"(v)); }
 
-// gemm.hip's gelu_fast
-__device__ __forceinline__ float gelu_sig(float x) {
-  const float xc = __builtin_amdgcn_fmed3f(x, -8.0f, 8.0f);
-  const float x2 = xc * xc;
-  const float t = fmaf(fmaf(1.0142780e-03f, x2, -1.0677580e-01f), x2, -2.3011212e+00f) * xc;
-  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t));
-}
-
 // Residual rows between the kernels of these widths lie as these hold them, as MFMA results:
 // tiles of 32 rows; in a tile, 32 columns by 32, four blocks of 1 KB, lane l of a wavefront's
 // 64 with columns 8 q + 4 (l / 32) .. + 3 of row l % 32 at 16 l of block q.  Rows of floats
