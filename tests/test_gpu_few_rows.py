@@ -47,7 +47,9 @@ def test_encoder_alone_and_in_a_batch(d, heads, ffn, cells, frames):
     assert err <= BAR
 
 
-@pytest.mark.parametrize("d, heads, ffn, queries", [(384, 6, 1536, 1), (384, 6, 384, 65), (768, 12, 1536, 97)])
+# (the last: 64 frames take the attention's items of 256 queries, one frame those of 128)
+@pytest.mark.parametrize("d, heads, ffn, queries",
+                         [(384, 6, 1536, 1), (384, 6, 384, 65), (768, 12, 1536, 97), (768, 12, 1536, 155)])
 def test_decoder_alone_and_in_a_batch(d, heads, ffn, queries):
     import torch
     from paper_2505_23317_amd import cfdetr as K
