@@ -145,9 +145,11 @@ typedef enum {
 
 /* Host-side.  Validates cfg, copies it, keeps the weight POINTERS, allocates
  * the work space on the current device and builds the position tables there.
- * For d_model 256 in bf16 with d_ffn a multiple of 128 up to 2048 it also
- * copies w_qkv, w_o, w_ff1, w_ff2 into the order its fused layer kernels read
- * (the weights are read once, here).
+ * In bf16 it also copies w_qkv, w_o, w_ff1, w_ff2 into the order in which its
+ * kernels read them (the weights are read once, here): d_model 256 with d_ffn a
+ * multiple of 128 up to 2048, one copy; d_model 384 or 768 with d_ffn a multiple
+ * of 384, one for passes of few rows; d_model 384 with d_ffn a multiple of 128 up
+ * to 2048, one (more) for the others.  cfdetr_workspace_bytes counts them.
  * On failure *out is NULL. */
 CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_weights* w,
                             cfdetr_ctx** out);

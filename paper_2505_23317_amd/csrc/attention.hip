@@ -634,6 +634,11 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(
 // 2800 of them 32 queries are 7 to 9 % faster (74 against 79 us, 32 against 35), at 4600 64
 // queries are 5 % and at 16000 8 % faster (141 -> 135, 454 -> 420).  At head width 32 the
 // exponentials bind whatever the LDS traffic is, and the small form is never slower.
+// How well the sequences fill their items does not move the line.  Passes with items of 128 / 256
+// in us: 300 decoder queries (384 / 512 places) of 64 frames x 6 heads 2546 / 2568, x 12 heads 3447 /
+// 3434; coarse grids of 1,600 tokens (1,664 / 1,792), 12 frames 1968 / 1910, 24 3562 / 3592, 32 4648 /
+// 4592; of 540 tokens (640 / 768) 1856 / 1804; of 121 tokens (128 / 256: two of an item's wavefronts
+// have nothing), 64 frames x 16 heads, 398 / 400.
 int attention_block_q(int d_head, bool use_bf16, int64_t rows, int heads) {
   return use_bf16 && d_head == 64 && rows * heads > (int64_t)3500 * 32 ? 256 : 128;
 }

@@ -2343,6 +2343,17 @@ hipError_t launch_persist_tile(const DenseRows& a, const bf16_t* w, int N, int K
   return hipSuccess;
 }
 
+template <int MT, typename EP>
+hipError_t launch_few(const bf16_t* a, const void* packed, int N, int K, const EP& ep, const int32_t* m_ptr, int m_host,
+                      int m_capacity, hipStream_t s) {
+  int row_groups = 1;
+  const dim3 grid = few_rows_grid(m_host, m_capacity, N / 128, K, MT, &row_groups);
+  constexpr auto kern = gemm_bf16_few_kernel<MT, EP>;
+  hipLaunchKernelGGL(kern, grid, dim3(256), few_rows_lds(MT), s, a, static_cast<const unsigned char*>(packed), N, K, ep, m_ptr,
+                     m_host, row_groups);
+  return hipSuccess;
+}
+
 // Tile choice by problem size: 256x256 (8 wavefronts, 128x64 each) or 192x256 (96x64
 // each) for wide outputs over many rows, 192x128 or 128x128 (4 wavefronts, 96x64 or 64x64
 // each, two workgroups per CU) while that still yields a workgroup per CU, else 64x64
@@ -2355,17 +2366,6 @@ hipError_t launch_persist_tile(const DenseRows& a, const bf16_t* w, int N, int K
 // decides at a few rounds is how full the last round is: the estimate is rounds x time per
 // round.  (24 470 rows x 384 columns are 576 tiles of 128x128 for 512 places, two rounds
 // of which the second is an eighth full, and 384 tiles of 192x128, one round.)
-template <int MT, typename EP>
-hipError_t launch_few(const bf16_t* a, const void* packed, int N, int K, const EP& ep, const int32_t* m_ptr, int m_host,
-                      int m_capacity, hipStream_t s) {
-  int row_groups = 1;
-  const dim3 grid = few_rows_grid(m_host, m_capacity, N / 128, K, MT, &row_groups);
-  constexpr auto kern = gemm_bf16_few_kernel<MT, EP>;
-  hipLaunchKernelGGL(kern, grid, dim3(256), few_rows_lds(MT), s, a, static_cast<const unsigned char*>(packed), N, K, ep, m_ptr,
-                     m_host, row_groups);
-  return hipSuccess;
-}
-
 // `packed`: the weights once more as launch_slim_pack lays them out, or null.
 template <typename EP>
 hipError_t launch_direct(const void* A, const void* W, int N, int K, const EP& ep,
@@ -2397,8 +2397,10 @@ hipError_t launch_direct(const void* A, const void* W, int N, int K, const EP& e
     if (few64 <= cus || (K >= 2048 && few64 <= 2 * cus))
       return launch_few<2>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
   }
-  // A deeper ring (3 or 4 buffers, also with slabs of 32) measured no faster for these
-  // tiles: their main loops are bound by LDS traffic, not by the latency of the loads.
+  // A deeper ring (3 or 4 buffers, also with slabs of 32) measured no faster for these tiles: the
+  // latency of the loads is not what bounds their main loops.  Nor is LDS traffic (weights straight
+  // from memory into registers: 106 -> 109 us at N = 3072, K = 768): matrix and vector phases of the
+  // wavefronts of a SIMD alternate, with both units busy 2.7 % of the time.
   if (N % 256 == 0 && m >= 8192) {
     const long t256 = 180 * rounds256, t192 = 145 * rounds192;
     const long tn = t192n < t128 ? t192n : t128;

@@ -78,8 +78,10 @@ constexpr int kHead = 0, kMid = 1, kLast = 2;
 // pair against 32), and the CU's vector-memory path: 64 B/clk for 3.5 MB of weights per
 // workgroup, which is what taller tiles save.  Measured per layer at D = 384, F = 1536
 // against q/k/v, out-projection, two LayerNorms and the two feed-forward matrices as kernels
-// of their own: 22,400 rows 168 -> 109 us, 64,000 rows 430 -> 247 us, 3,520 rows 54 -> 43 us,
-// 920 rows 45 -> 42 us (few_rows.hip takes those).
+// of their own: 22,400 rows 168 -> 109 us, 64,000 rows 430 -> 260 us, 3,520 rows 54 -> 43 us,
+// 920 rows 45 -> 42 us (few_rows.hip takes those).  Of that the residual's two parts are 1 % of a pass
+// (summed on top of it: eight frames of up to 8,000 tokens 8,262 us, so 8,349); the whole residual
+// in memory would be 4 %.
 //
 // Width 384 has four wavefronts of 96 columns, width 256 eight of 32: two on each SIMD, so that
 // one's waits (barriers, row sums, the activation's chain of dependent operations) are the
@@ -634,13 +636,16 @@ hipError_t launch_wide_pack(const void* Wo, const void* W1, const void* W2, cons
 // bits).  Width 384: one workgroup per CU is the fastest there is, so the lowest tile that gets by with
 // that; a workgroup of 96 rows has a CU to itself, one of 64 shares it with a second one,
 // whose vector work then runs under its MFMAs, and is the best where CUs get several.
-// Encoder passes of 12 layers in us, at 32 / 64 / 96 rows: 5,669 rows 1131 / 1314 / 1616;
-// 11,248 rows 1776 / 1689 / 1985; 22,421 rows 2809 / 2673 / 2566; 33,729 rows 4491 / 4115 / 4299.
+// Encoder passes of 4 layers over frames of 1,024 tokens in us, at 32 / 64 / 96 rows, F = 1536:
+// 8,192 rows 309 / 348 / 444; 16,384 rows 519 / 470 / 561; 24,576 rows 775 / 697 / 692; 32,768 rows
+// 1003 / 857 / 1077.  The same with F from 256 to 2048, but for 96 rows up to F = 512 (24,576 rows
+// 573 / 541 / 555).
 //
 // Width 256: a workgroup of eight wavefronts fills a CU at every height, so the rounds of the
-// busiest CU times what one costs (19, 26 and 36 us a layer) decide.  Encoder passes of 6 layers
-// in us, at 32 / 64 / 96 rows: 8,000 rows 279 / 302 / 365; 11,200 rows 413 / 344 / 408;
-// 16,000 rows 512 / 454 / 496; 24,000 rows 779 / 739 / 676.
+// busiest CU times what one costs decide.  A layer costs 19, 26 and 37 us at F = 1024, 12, 17 and 24
+// at 256, 29, 39 and 55 at 2048: 1 : 1.4 : 1.95 at all of them, and only the ratio counts.  Passes as
+// above, F = 1024: 8,192 rows 200 / 220 / 257; 16,384 rows 347 / 306 / 340; 24,576 rows 501 / 490 /
+// 438; 32,768 rows 660 / 592 / 657.  At F = 256, 512, 1536 and 2048 the same heights win.
 int wide_layer_tiles(int d, int rows, int cus) {
   if (d == 256) {
     const int cost[3] = {19, 26, 36};
