@@ -351,14 +351,18 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
     a.cu = cu_all;
     a.pcu = ctx->pcu;
     a.nseq = nseq;
+    // two places for the residual rows: the out-projection leaves the new ones in the other
+    a.x_new = ctx->x;
     auto step = [&](SlimStep what, const void* wt, const float* bias, const float* g, const float* b, const void* rows,
-                    void* out) {
+                    void* out, const void* w2 = nullptr, const float* bias2 = nullptr) {
       a.w = wt;
       a.bias = bias;
       a.ln_g = g;
       a.ln_b = b;
       a.rows = rows;
       a.out = out;
+      a.w2 = w2;
+      a.bias2 = bias2;
       return launch_slim(a, what, d, F, shape.rows, m_ptr, 0, m_cap, s);
     };
     for (size_t l = 0; l < (size_t)c.n_layers; ++l) {
@@ -367,14 +371,13 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
       CF_LAUNCH(CFDETR_K_ATTN,
                 launch_attention(ctx->qkv, ctx->vt, ctx->vt_ld, ctx->o, d, c.n_heads, ctx->items, ctx->cap8, ctx->queue_heads + 8 * l,
                                  shape.attn_grid, shape.block_q, bf, kv_len, s));
-      CF_LAUNCH(CFDETR_K_OUT, step(SlimStep::kOut, ctx->slim_o + l * d * d * 2, w.b_o + l * d, nullptr, nullptr, ctx->o,
-                                   nullptr));
-      CF_LAUNCH(CFDETR_K_FF1, step(SlimStep::kHidden, ctx->slim_ff1 + l * F * d * 2, w.b_ff1 + l * F, w.ln2_g + l * d,
-                                   w.ln2_b + l * d, nullptr, ctx->h));
+      CF_LAUNCH(CFDETR_K_FF1, step(SlimStep::kOutHidden, ctx->slim_o + l * d * d * 2, w.b_o + l * d, w.ln2_g + l * d,
+                                   w.ln2_b + l * d, ctx->o, ctx->h, ctx->slim_ff1 + l * F * d * 2, w.b_ff1 + l * F));
+      std::swap(a.x, a.x_new);
       CF_LAUNCH(CFDETR_K_FF2, step(SlimStep::kDown, ctx->slim_ff2 + l * F * d * 2, w.b_ff2 + l * d, nullptr, nullptr, ctx->h,
                                    nullptr));
     }
-    CF_LAUNCH(CFDETR_K_LN, launch_wide_norm(ctx->x_blocks, w.lnf_g, w.lnf_b, d, eps, y0, split_row, y1, m_ptr, 0, m_cap, s));
+    CF_LAUNCH(CFDETR_K_LN, launch_wide_norm(a.x, w.lnf_g, w.lnf_b, d, eps, y0, split_row, y1, m_ptr, 0, m_cap, s));
     return CFDETR_OK;
   }
   if (ctx->wide_layer) {
@@ -844,7 +847,7 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   const uint64_t Tm = c->tok_cap, d = cfg->d_model, F = cfg->d_ffn;
   const uint64_t Bm = cfg->max_batch, D = d / 2;
   Carver cv;
-  const uint64_t o_x = cv.take(Tm * d * 4), o_a = cv.take(Tm * d * c->esz);
+  const uint64_t o_x = cv.take((Tm + 31) / 32 * 32 * d * 4), o_a = cv.take(Tm * d * c->esz);
   const uint64_t o_qkv = cv.take(Tm * 3 * d * c->esz), o_o = cv.take(Tm * d * c->esz);
   const uint64_t o_h = cv.take((Tm + 31) * F * c->esz), o_x0 = cv.take(Bm * c->n0 * d * 4);
   c->vt_ld = (int)((Tm + 64 * 2 * Bm + 63) & ~uint64_t(63));

@@ -8,22 +8,28 @@
 // workgroup share, skip the LDS: packed 1 KB per MFMA operand they stream through a ring of
 // 24 registers a lane, all of them asked for before the first row is looked at.
 #pragma once
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace cfdetr {
 
 // Which tiles a workgroup does.  Every XCD has an L2 of its own, and with few rows a good part
 // of what a launch takes is its operands' way into the eight of them, so an XCD gets a
-// rectangle of tiles: the row tiles are cut in row_groups (1, 2, 4 or 8), the 128-column parts
-// in 8 / row_groups.
+// rectangle of tiles: the row tiles are cut in 2^row_bits groups (1, 2, 4 or 8), the 128-column parts
+// in 8 / that.  The grid (few_rows_grid) is a workgroup per row tile of a group, times eight, by the parts of
+// a group; a workgroup has part `part` (none: part_end and beyond) of row tiles r, r + step, .. below r_end.
+// (Shifts, no division: 150 dependent scalar instructions in front of a kernel's first load are 0.7 us.)
 struct XcdTiles {
-  int r0, rows, p0, count;
-  __device__ __forceinline__ XcdTiles(int mtiles, int parts, int row_groups) {
-    const int x = blockIdx.x & 7, rg = x & (row_groups - 1), pgs = 8 / row_groups, pg = x / row_groups;
-    r0 = mtiles * rg / row_groups;
-    rows = mtiles * (rg + 1) / row_groups - r0;
-    p0 = parts * pg / pgs;
-    count = rows * (parts * (pg + 1) / pgs - p0);
+  int r, r_end, step, part;
+  bool none;
+  __device__ __forceinline__ XcdTiles(int mtiles, int parts, int row_bits) {
+    const int x = blockIdx.x & 7, rg = x & ((1 << row_bits) - 1), pg = x >> row_bits, part_bits = 3 - row_bits;
+    r = ((mtiles * rg) >> row_bits) + (int)(blockIdx.x >> 3);
+    r_end = (mtiles * (rg + 1)) >> row_bits;
+    step = (int)(gridDim.x >> 3);
+    part = ((parts * pg) >> part_bits) + (int)blockIdx.y;
+    none = part >= (parts * (pg + 1)) >> part_bits;
   }
 };
 
@@ -71,56 +77,89 @@ __device__ __forceinline__ void few_rows_product(const bf16_t* rows, int K, int 
   };
   for (int s = 0; s < 3; ++s) stage(s);
   __builtin_amdgcn_sched_barrier(0);
+  // weight block i of a round, the base of every fourth one in scalar registers: no vector arithmetic
+  typedef const __attribute__((address_space(1))) unsigned char* gptr;
+  gptr wq = (gptr)wp;
+  auto weights = [&](int i) {
+    if (i % 4 == 0) {
+      wq = (gptr)wp + i * 1024;
+      asm volatile("" : "+s"(wq));
+    }
+    return *reinterpret_cast<const __attribute__((address_space(1))) bf16x8*>(wq + (i % 4) * 1024 + voff);
+  };
   bf16x8 wr[kRing];
 #pragma unroll
-  for (int i = 0; i < kRing; ++i) wr[i] = *reinterpret_cast<const bf16x8*>(wp + i * 1024 + voff);
+  for (int i = 0; i < kRing; ++i) wr[i] = weights(i);
   __builtin_amdgcn_sched_barrier(0);
   begin();
-#pragma nounroll
-  for (int s0 = 0; s0 < NS; s0 += 3) {
+  auto round = [&](int s0, auto last_tag) {
+    constexpr bool kLastRound = decltype(last_tag)::value;   // nothing is asked for any more
     wp += kRing * 1024;
 #pragma unroll
     for (int h = 0; h < 3; ++h) {
       const int s = s0 + h;
       // stage s has arrived: its loads are older than the ring's, and loads return in order;
       // so has everybody's behind the barrier, where the place of stage s - 1 is free
-      asm volatile("s_waitcnt vmcnt(%0)" : : "n"(kRing) : "memory");
+      asm volatile("s_waitcnt vmcnt(%0)" : : "n"(kLastRound ? kRing - 8 * h : kRing) : "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" : : : "memory");
-      if (s + 3 < NS) stage(s + 3);
+      if (!kLastRound) {
+        if (s + 3 < NS) stage(s + 3);
+      }
+      // operands are asked for kAhead k-steps ahead: one by one in front of their MFMAs, as the
+      // compiler has them otherwise, each is a wait for the LDS (900 clocks a stage against 400)
+      constexpr int kAhead = MT == 1 ? 6 : 2;
       const unsigned char* ap = smem + (s & 3) * kStage;
+      bf16x8 a[kAhead + 1][MT];
+      auto operands = [&](int k) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i) a[k % (kAhead + 1)][i] = *reinterpret_cast<const bf16x8*>(ap + ao[k] + i * 8192);
+      };
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) operands(k);
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
+        if (k + kAhead < 8) operands(k + kAhead);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(ap + ao[k] + i * 8192);
-          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[h * 8 + k], a, acc[i], 0, 0, 0);
-        }
-        wr[h * 8 + k] = *reinterpret_cast<const bf16x8*>(wp + (h * 8 + k) * 1024 + voff);
+        for (int i = 0; i < MT; ++i)
+          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[h * 8 + k], a[k % (kAhead + 1)][i], acc[i], 0, 0, 0);
+        if (!kLastRound) wr[h * 8 + k] = weights(h * 8 + k);
       }
       asm volatile("" : : : "memory");
     }
-  }
+  };
+  int s0 = 0;
+#pragma nounroll
+  for (; s0 + 3 < NS; s0 += 3) round(s0, std::false_type{});
+  round(s0, std::true_type{});
 }
 
 // Grid for the rows expected (a quarter more workgroups, and they go on to further tiles if
-// there are more rows after all), and the row_groups that go with it: a launch costs about the
-// bytes into the XCDs at 5 TB/s and, per CU, its tiles' operands at 110 GB/s.
-inline dim3 few_rows_grid(int rows, int m_capacity, int parts, int K, int mt, int* row_groups) {
-  const int bm = 32 * mt, m = rows > 0 && rows < m_capacity ? rows : m_capacity, t = (m + bm - 1) / bm;
-  const double row_bytes = 2.0 * t * bm * K, w_bytes = 256.0 * parts * K, tile_bytes = 2.0 * K * (128 + bm);
+// there are more rows after all), and the row_bits that go with it: a launch costs about the
+// bytes into the XCDs at 5 TB/s and, per CU, its tiles' operands at 110 GB/s.  tiles(rows): row tiles;
+// row_bytes, part_bytes: operands of a row tile and of a part, tile_bytes: of a workgroup.
+template <typename Tiles>
+inline dim3 few_rows_grid(int rows, int m_capacity, int parts, Tiles tiles, double row_bytes, double part_bytes,
+                          double tile_bytes, int* row_bits) {
+  const int m = rows > 0 && rows < m_capacity ? rows : m_capacity, t = tiles(m);
   double best = 0;
-  for (int rg = 1; rg <= 8; rg *= 2) {
-    const int pg = 8 / rg;
+  for (int bits = 0; bits <= 3; ++bits) {
+    const int rg = 1 << bits, pg = 8 >> bits;
     const long most = (long)((t + rg - 1) / rg) * ((parts + pg - 1) / pg);
-    const double us = (pg * row_bytes + rg * w_bytes) / 5e6 + (most + 31) / 32 * tile_bytes / 110e3;
-    if (rg == 1 || us < best) {
+    const double us = (pg * t * row_bytes + rg * parts * part_bytes) / 5e6 + (most + 31) / 32 * tile_bytes / 110e3;
+    if (bits == 0 || us < best) {
       best = us;
-      *row_groups = rg;
+      *row_bits = bits;
     }
   }
-  const int rg = *row_groups, pg = 8 / rg, more = m + m / 4 < m_capacity ? m + m / 4 : m_capacity;
-  return dim3(8 * (((more + bm - 1) / bm + rg - 1) / rg) * ((parts + pg - 1) / pg));
+  const int rg = 1 << *row_bits, pg = 8 >> *row_bits, more = m + m / 4 < m_capacity ? m + m / 4 : m_capacity;
+  return dim3(8 * ((tiles(more) + rg - 1) / rg), (parts + pg - 1) / pg);
+}
+inline dim3 few_rows_grid(int rows, int m_capacity, int parts, int K, int mt, int* row_bits) {
+  const int bm = 32 * mt;
+  return few_rows_grid(rows, m_capacity, parts, [=](int m) { return (m + bm - 1) / bm; }, 2.0 * bm * K, 256.0 * K,
+                       2.0 * K * (128 + bm), row_bits);
 }
 
 }  // namespace cfdetr

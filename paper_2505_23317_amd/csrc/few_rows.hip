@@ -1,6 +1,6 @@
 // Layers of width 384 when there are few rows: wide_layer_kernel (layer.hip) gives every row to
 // one CU, which streams all the weights of the layer past it; below some two thousand rows most
-// CUs would have none.  Here a layer is four launches, each spread over the chip, with the same
+// CUs would have none.  Here a layer is three launches, each spread over the chip, with the same
 // arithmetic in the same order (sums that start at the bias or at the residual's low part, its
 // LayerNorm), so that a row's result does not depend on how many others there are.
 #include "few_rows.h"
@@ -11,20 +11,28 @@ namespace cfdetr {
 namespace {
 
 constexpr int kSlimPad = 32;   // blocks of 1 KB the weight rings read ahead of the end
+constexpr int kAhead = 5;         // k-steps that operands are asked for ahead of their MFMAs (few_rows.h)
+constexpr int kSlimMaxN = 2048;   // widest second matrix of slim_out_norm_kernel (its bias is in LDS)
 
 struct SlimArgs {
   const bf16_t* rows;        // slim_residual_kernel's operand
-  const float* x0;           // first layer: the rows as the embedding left them
+  const float* x0;           // first layer: the rows as the embedding left them, or x0_rows rows over and over
+  int x0_rows;
   float* x;                  // residual blocks (wide_row.h)
   const float *ln_g, *ln_b;
   float eps;
   const unsigned char* w;    // launch_slim_pack's
   const float* bias;
+  float* x_new;              // slim_out_norm_kernel: the new residual rows, its second matrix, its shares of a row tile
+  const unsigned char* w2;
+  const float* bias2;
+  int shares, per_share;
   int parts;                 // 128-column parts of the result
   int K;
-  int row_groups;            // XcdTiles
+  int row_bits;              // XcdTiles
   float q_scale;
-  bf16_t* out;               // q/k/v [M, 3D], or hidden blocks
+  bf16_t* out;               // q/k/v [M, 3D], other rows [M, D], or hidden blocks
+  bf16_t* z;
   bf16_t* vt;
   int vt_ld;
   int32_t* vt_pos;
@@ -40,16 +48,30 @@ __device__ __forceinline__ float* x_block(float* x, int m0, int c, int q, int la
   return x + (((size_t)(m0 >> 5) * (D / 32) + (c >> 5)) * 4 + q) * 256 + lane * 4;
 }
 
-// kFirst: q/k/v of the first layer (reads x0, writes x and vt_pos); kQkv: of another one;
-// kHidden: first feed-forward matrix and activation, as operands of the second.
-constexpr int kFirst = 0, kQkv = 1, kHidden = 2;
+// The activation of a wavefront's 32 rows x 32 columns, as operands of the next contraction: k-step
+// n / 16 of it, the row's lane in that.
+__device__ __forceinline__ void hidden_store(const SlimArgs& p, int m0, int n0, int l32, int g, const f32x16& r) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const size_t blk = (size_t)(m0 >> 5) * (p.parts * 8) + (n0 >> 4) + (q >> 1);
+    *reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(p.out) + blk * 1024 + (l32 + 32 * (q & 1)) * 16 + g * 8) =
+        make_uint2(pack_bf16x2(gelu_fast(r[4 * q]), gelu_fast(r[4 * q + 1])),
+                   pack_bf16x2(gelu_fast(r[4 * q + 2]), gelu_fast(r[4 * q + 3])));
+  }
+}
+
+// What a kernel's contraction is.  kFirst: q/k/v of the first layer (reads x0, writes x and vt_pos); kQkv: of
+// another one; kRelu: a square matrix with its activation (the normalised rows themselves go to z);
+// kHidden: first feed-forward matrix and activation, as operands of the second; kQuery: the decoder's
+// query projection.
+constexpr int kFirst = 0, kQkv = 1, kRelu = 2, kHidden = 3, kQuery = 4;
 
 // LayerNorm and the contraction behind it, 32 rows x 128 columns a workgroup.  Every workgroup
 // of the same rows does their LayerNorm again, which costs 1.4 us in each and no launch (4.5 us).
 // All loads of the rows are issued first, then all those of the weights (K = 384 is one ring of
 // 24 blocks), which arrive while the rows are normalised.
-// 920 rows: 8.5 us for q/k/v, 9.8 us for the hidden units, of which 3 us are the launch, 2 us
-// the way of rows and weights into the XCDs; LayerNorm and 64 x 64 tiles took 4.5 and 8 us each.
+// 920 rows: 8.5 us for q/k/v, of which 3 us are the launch, 2 us the way of rows and weights into the
+// XCDs; LayerNorm and 64 x 64 tiles took 4.5 and 8 us.
 template <int D, int kOut>
 __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
   constexpr int KS = D / 16, NT = D / 128, ROWB = D * 2;
@@ -58,17 +80,18 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
   __shared__ float s_red[256], s_vec[2 * D];
 
   const int M = p.m_ptr ? *p.m_ptr : p.m_host;
-  const XcdTiles tiles((M + 31) >> 5, p.parts, p.row_groups);
+  const XcdTiles tiles((M + 31) >> 5, p.parts, p.row_bits);
+  if (tiles.none) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
   const float4 vg = *reinterpret_cast<const float4*>(p.ln_g + min(tid * 4, D - 4));
   const float4 vb = *reinterpret_cast<const float4*>(p.ln_b + min(tid * 4, D - 4));
 
-  for (int t = blockIdx.x >> 3; t < tiles.count; t += gridDim.x >> 3) {
-    const int part = tiles.p0 + t / tiles.rows, m0 = (tiles.r0 + t % tiles.rows) * 32;
-    const int m = min(m0 + l32, M - 1), n0 = part * 128 + wave * 32;
-    const bool v_cols = kOut != kHidden && n0 >= 2 * D;
+  const int part = tiles.part, n0 = part * 128 + wave * 32;
+  for (int t = tiles.r; t < tiles.r_end; t += tiles.step) {
+    const int m0 = t * 32, m = min(m0 + l32, M - 1);
+    const bool v_cols = kOut != kRelu && n0 >= 2 * D;
     int vpos = 0;
     if (kOut == kFirst && (v_cols || part == 0)) {
       const int f = frame_of_token(p.cu, p.nseq, m);
@@ -78,12 +101,13 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
       vpos = p.vt_pos[m];
     }
     f32x16 xa[NT][1];   // the wavefront's quarter of the rows' columns
+    const int m0_row = kOut == kFirst && p.x0_rows > 0 ? m % p.x0_rows : m;
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int c = wave * (D / 4) + j * 32;
-        const float4 v = *reinterpret_cast<const float4*>(kOut == kFirst ? p.x0 + (size_t)m * D + c + 8 * q + 4 * g
+        const float4 v = *reinterpret_cast<const float4*>(kOut == kFirst ? p.x0 + (size_t)m0_row * D + c + 8 * q + 4 * g
                                                                          : x_block<D>(p.x, m0, c, q, lane));
         xa[j][0][4 * q] = v.x;
         xa[j][0][4 * q + 1] = v.y;
@@ -116,60 +140,251 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
     wide_stats<4>(xa, s_red, l32, g, wave, p.eps, mean, rstd);
     wide_norm_to_lds<4>(xa, mean, rstd, s_vec, s_vec + D, sA, l32, g, wave);
 
-    f32x16 acc;
+    if (kOut == kRelu && part == 0) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc[4 * q] = b[q].x;
-      acc[4 * q + 1] = b[q].y;
-      acc[4 * q + 2] = b[q].z;
-      acc[4 * q + 3] = b[q].w;
+      for (int u0 = 0; u0 < 32 * (ROWB / 16); u0 += 256) {
+        const int u = u0 + tid, row = u / (ROWB / 16), pos = u % (ROWB / 16);
+        const int c = (pos & ~15) | ((pos ^ row) & 15);
+        if (m0 + row < M)
+          *reinterpret_cast<uint4*>(p.z + (size_t)(m0 + row) * D + c * 8) = *reinterpret_cast<const uint4*>(sA + u * 16);
+      }
     }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-          wr[ks], *reinterpret_cast<const bf16x8*>(sA + l32 * ROWB + (((2 * ks + g) ^ (l32 & 15)) << 4)), acc, 0, 0, 0);
-
-    const bool in = m0 + l32 < M;
+    f32x16 acc;   // (kRelu: the bias is added to the sum, as the tiled contraction does)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int n = n0 + 8 * q + 4 * g;
-      const float r0 = acc[4 * q], r1 = acc[4 * q + 1], r2 = acc[4 * q + 2], r3 = acc[4 * q + 3];
-      if (kOut == kHidden) {
-        // k-step n / 16 of the next contraction, the row's lane in it
-        const size_t blk = (size_t)(m0 >> 5) * (p.parts * 8) + (n0 >> 4) + (q >> 1);
-        *reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(p.out) + blk * 1024 + (l32 + 32 * (q & 1)) * 16 + g * 8) =
-            make_uint2(pack_bf16x2(gelu_fast(r0), gelu_fast(r1)), pack_bf16x2(gelu_fast(r2), gelu_fast(r3)));
-      } else if (v_cols) {
-        if (in) {
-          bf16_t* vp = p.vt + (size_t)(n - 2 * D) * p.vt_ld + vpos;
-          vp[0] = f32_to_bf16(r0);
-          vp[(size_t)p.vt_ld] = f32_to_bf16(r1);
-          vp[(size_t)2 * p.vt_ld] = f32_to_bf16(r2);
-          vp[(size_t)3 * p.vt_ld] = f32_to_bf16(r3);
+      acc[4 * q] = kOut == kRelu ? 0.f : b[q].x;
+      acc[4 * q + 1] = kOut == kRelu ? 0.f : b[q].y;
+      acc[4 * q + 2] = kOut == kRelu ? 0.f : b[q].z;
+      acc[4 * q + 3] = kOut == kRelu ? 0.f : b[q].w;
+    }
+    bf16x8 a[kAhead + 1];
+    uint32_t ao[8];
+    int lx = l32;
+    work_out_here(lx);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) ao[k] = lx * ROWB + (((2 * k + g) ^ (lx & 15)) << 4);
+    auto operand = [&](int ks) {
+      a[ks % (kAhead + 1)] = *reinterpret_cast<const bf16x8*>(sA + ao[ks & 7] + (ks >> 3) * 256);
+    };
+#pragma unroll
+    for (int ks = 0; ks < kAhead; ++ks) operand(ks);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks + kAhead < KS) operand(ks + kAhead);
+      __builtin_amdgcn_sched_barrier(0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[ks], a[ks % (kAhead + 1)], acc, 0, 0, 0);
+    }
+
+    if (m0 + l32 < M) {
+      if (v_cols) {
+        bf16_t* vp = p.vt + (size_t)(n0 + 4 * g - 2 * D) * p.vt_ld + vpos;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          *vp = f32_to_bf16(acc[r]);
+          vp += (size_t)((r & 3) == 3 ? 5 : 1) * p.vt_ld;
         }
-      } else if (in) {
-        const float sc = n0 < D ? p.q_scale : 1.0f;
-        *reinterpret_cast<uint2*>(p.out + (size_t)m * (3 * D) + n) =
-            make_uint2(pack_bf16x2(r0 * sc, r1 * sc), pack_bf16x2(r2 * sc, r3 * sc));
+      } else {
+        const float sc = kOut != kRelu && n0 < D ? p.q_scale : 1.0f;
+        bf16_t* const op = p.out + (size_t)m * (kOut == kRelu ? D : 3 * D) + n0 + 4 * g;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float r0 = acc[4 * q] * sc, r1 = acc[4 * q + 1] * sc, r2 = acc[4 * q + 2] * sc, r3 = acc[4 * q + 3] * sc;
+          if (kOut == kRelu) {
+            r0 = fmaxf(acc[4 * q] + b[q].x, 0.f);
+            r1 = fmaxf(acc[4 * q + 1] + b[q].y, 0.f);
+            r2 = fmaxf(acc[4 * q + 2] + b[q].z, 0.f);
+            r3 = fmaxf(acc[4 * q + 3] + b[q].w, 0.f);
+          }
+          *reinterpret_cast<uint2*>(op + 8 * q) = make_uint2(pack_bf16x2(r0, r1), pack_bf16x2(r2, r3));
+        }
       }
     }
     __syncthreads();   // the rows' place is free
   }
 }
 
-// x += operand . W^T + bias: attention rows times the output projection, or (kBlocks) the
-// hidden blocks times the second feed-forward matrix.  920 rows: 5.2 and 9.5 us (64 x 64 tiles
-// took 9.5 and 17 us), the latter the K = 1536 of a wavefront at what a CU's vector-memory path
-// gives.
-template <int D, bool kBlocks>
+// x_new = x + rows . W^T + bias (the attention's rows, the output projection), LayerNorm, and a
+// contraction behind that: the first feed-forward matrix with its activation (kHidden) or the
+// decoder's query projection (kQuery).  32 rows and one of p.shares equal runs of the second
+// matrix's 128-column parts a workgroup: each of them projects the rows again (D x D weights, 0.3 MB at
+// D = 384, against a launch of its own), and the first writes x_new, which is not x because the
+// others may not have read that yet.
+// Wavefront w has columns [w D/4, (w + 1) D/4) of the projection, then 32 columns of every part; one ring
+// of D/16 weight blocks serves both, refilled behind each MFMA.
+template <int D, int kOut>
+__global__ __launch_bounds__(256, 2) void slim_out_norm_kernel(SlimArgs p) {
+  constexpr int KS = D / 16, NT = D / 128, ROWB = D * 2, UN = KS / NT;
+  static_assert(UN == 8, "eight k-steps of the projection a ring round");
+  __shared__ __attribute__((aligned(1024))) unsigned char sA[32 * ROWB];
+  __shared__ float s_red[256], s_vec[3 * D], s_bias[kSlimMaxN];
+
+  const int M = p.m_ptr ? *p.m_ptr : p.m_host;
+  const XcdTiles tiles((M + 31) >> 5, p.shares, p.row_bits);
+  if (tiles.none) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t voff;
+  // 16 bytes a lane of block i at `base`, whose address is worked out in scalar registers and where it
+  // is used: no vector arithmetic, and nothing kept
+  typedef __attribute__((address_space(1))) unsigned char* gptr;
+  auto at = [&](const void* base, int i) {
+    gptr q = (gptr)base;
+    asm volatile("" : "+s"(q));
+    return q + i * 1024 + voff;
+  };
+  auto block = [&](const void* base, int i) { return *reinterpret_cast<const __attribute__((address_space(1))) bf16x8*>(at(base, i)); };
+  const int share = tiles.part, part0 = share * p.per_share, part1 = min(part0 + p.per_share, p.parts);
+  for (int t = tiles.r; t < tiles.r_end; t += tiles.step) {
+    const int m0 = t * 32;
+    int tid = threadIdx.x;
+    work_out_here(tid);   // (or the addresses of a row tile are kept from tile to tile, in scratch memory)
+    const int lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    voff = lane * 16;
+    const int vat = min(tid * 4, D - 4);
+    const float4 vo = *reinterpret_cast<const float4*>(p.bias + vat);
+    const float4 vg = *reinterpret_cast<const float4*>(p.ln_g + vat);
+    const float4 vb = *reinterpret_cast<const float4*>(p.ln_b + vat);
+    static_assert(kSlimMaxN == 2048, "two pieces");   // the share's biases
+    const float4 vc0 = *reinterpret_cast<const float4*>(p.bias2 + min(part0 * 128 + tid * 4, p.parts * 128 - 4));
+    const float4 vc1 = *reinterpret_cast<const float4*>(p.bias2 + min(part0 * 128 + 1024 + tid * 4, p.parts * 128 - 4));
+    // the rows into LDS: 128 columns by 128, 32 rows of 256 bytes each, chunks XORed by the row
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = (wave * 2 + i) * 4 + (lane >> 4);
+      const unsigned char* src = reinterpret_cast<const unsigned char*>(p.rows + (size_t)min(m0 + row, M - 1) * D) +
+                                 (((lane & 15) ^ (row & 15)) << 4);
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                     : : "s"((uint32_t)(uintptr_t)sA + j * 8192 + (wave * 2 + i) * 1024), "v"(src + j * 256) : "memory");
+    }
+    f32x16 acc[NT][1];
+    u32x8 hi[NT];
+    const size_t x0 = ((size_t)(m0 >> 5) * (D / 32) + wave * NT) * 1024;   // residual blocks of the wavefront
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 v = *reinterpret_cast<const __attribute__((address_space(1))) f32x4*>(at(p.x + x0, j * 4 + q));
+        acc[j][0][4 * q] = v[0];
+        acc[j][0][4 * q + 1] = v[1];
+        acc[j][0][4 * q + 2] = v[2];
+        acc[j][0][4 * q + 3] = v[3];
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    // block ks NT + j of the ring: column tile j of k-step ks
+    const unsigned char* const wo = p.w + (size_t)(wave * NT) * (KS * 1024);
+    const unsigned char* w2 = p.w2 + (size_t)(part0 * 4 + wave) * (KS * 1024);
+    bf16x8 wr[KS];
+#pragma unroll
+    for (int i = 0; i < KS; ++i) wr[i] = block(wo, (i % NT) * KS + i / NT);
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < D / 4) {
+      *reinterpret_cast<float4*>(s_vec + tid * 4) = vo;
+      *reinterpret_cast<float4*>(s_vec + D + tid * 4) = vg;
+      *reinterpret_cast<float4*>(s_vec + 2 * D + tid * 4) = vb;
+    }
+    *reinterpret_cast<float4*>(s_bias + tid * 4) = vc0;
+    *reinterpret_cast<float4*>(s_bias + 1024 + tid * 4) = vc1;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) residual_split(acc[j][0], hi[j]);
+    // the rows' loads are older than the ring's
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(KS) : "memory");
+    __syncthreads();
+    bf16x8 a[kAhead + 1];
+    uint32_t ao[8];
+    auto operand = [&](int ks, int next_8) {
+      a[ks % (kAhead + 1)] = *reinterpret_cast<const bf16x8*>(sA + ao[ks & 7] + (ks >> 3) * next_8);
+    };
+    auto operand_addresses = [&](int row_bytes) {
+      int lx = l32;
+      work_out_here(lx);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) ao[k] = lx * row_bytes + (((2 * k + g) ^ (lx & 15)) << 4);
+    };
+    operand_addresses(256);
+#pragma unroll
+    for (int ks = 0; ks < kAhead; ++ks) operand(ks, 8192);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks + kAhead < KS) operand(ks + kAhead, 8192);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const int i = (ks % UN) * NT + j;
+        acc[j][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[i], a[ks % (kAhead + 1)], acc[j][0], 0, 0, 0);
+        wr[i] = ks + UN < KS ? block(wo, j * KS + ks + UN) : block(w2, i);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        residual_join(acc[j][0], hi[j], q, *reinterpret_cast<const float4*>(s_vec + wave * (D / 4) + j * 32 + 8 * q + 4 * g));
+    if (share == 0) {
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<__attribute__((address_space(1))) f32x4*>(at(p.x_new + x0, j * 4 + q)) =
+              f32x4{acc[j][0][4 * q], acc[j][0][4 * q + 1], acc[j][0][4 * q + 2], acc[j][0][4 * q + 3]};
+    }
+    float mean[1], rstd[1];
+    wide_stats<4>(acc, s_red, l32, g, wave, p.eps, mean, rstd);
+    wide_norm_to_lds<4>(acc, mean, rstd, s_vec + D, s_vec + 2 * D, sA, l32, g, wave);
+
+    operand_addresses(ROWB);
+    auto one_part = [&](int part, auto more_tag) {
+      constexpr bool kMore = decltype(more_tag)::value;   // another part's weights are asked for
+      const int n0 = part * 128 + wave * 32;
+      f32x16 r;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 b = *reinterpret_cast<const float4*>(s_bias + n0 - part0 * 128 + 8 * q + 4 * g);
+        r[4 * q] = b.x;
+        r[4 * q + 1] = b.y;
+        r[4 * q + 2] = b.z;
+        r[4 * q + 3] = b.w;
+      }
+      w2 += 4 * KS * 1024;
+#pragma unroll
+      for (int ks = 0; ks < kAhead; ++ks) operand(ks, 256);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks + kAhead < KS) operand(ks + kAhead, 256);
+        __builtin_amdgcn_sched_barrier(0);
+        r = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[ks], a[ks % (kAhead + 1)], r, 0, 0, 0);
+        if (kMore) wr[ks] = block(w2, ks);
+      }
+      if (kOut == kHidden) {
+        hidden_store(p, m0, n0, l32, g, r);
+      } else if (m0 + l32 < M) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<uint2*>(p.out + (size_t)(m0 + l32) * D + n0 + 8 * q + 4 * g) =
+              make_uint2(pack_bf16x2(r[4 * q] * p.q_scale, r[4 * q + 1] * p.q_scale),
+                         pack_bf16x2(r[4 * q + 2] * p.q_scale, r[4 * q + 3] * p.q_scale));
+      }
+    };
+#pragma nounroll
+    for (int part = part0; part + 1 < part1; ++part) one_part(part, std::true_type{});
+    one_part(part1 - 1, std::false_type{});
+    __syncthreads();   // the rows' place is free
+  }
+}
+
+// x += hidden blocks . W^T + bias, the second feed-forward matrix.  920 rows: 9.5 us (64 x 64 tiles
+// took 17 us), the K = 1536 of a wavefront at what a CU's vector-memory path gives.
+template <int D>
 __global__ __launch_bounds__(256, 2) void slim_residual_kernel(SlimArgs p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int M = p.m_ptr ? *p.m_ptr : p.m_host;
-  const XcdTiles tiles((M + 31) >> 5, D / 128, p.row_groups);
+  const XcdTiles tiles((M + 31) >> 5, D / 128, p.row_bits);
+  if (tiles.none) return;
   const int lane = threadIdx.x & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int t = blockIdx.x >> 3; t < tiles.count; t += gridDim.x >> 3) {
-    const int part = tiles.p0 + t / tiles.rows, m0 = (tiles.r0 + t % tiles.rows) * 32, n0 = part * 128 + wave * 32;
+  const int part = tiles.part, n0 = part * 128 + wave * 32;
+  for (int t = tiles.r; t < tiles.r_end; t += tiles.step) {
+    const int m0 = t * 32;
     float4 b[4];
     f32x16 x, acc[1];
     u32x8 hi;
@@ -182,7 +397,7 @@ __global__ __launch_bounds__(256, 2) void slim_residual_kernel(SlimArgs p) {
       x[4 * q + 2] = v.z;
       x[4 * q + 3] = v.w;
     }
-    few_rows_product<1, kBlocks>(p.rows, p.K, M, m0, p.w + (size_t)(part * 4 + wave) * (p.K >> 4) * 1024, smem, acc, [&]() {
+    few_rows_product<1, true>(p.rows, p.K, M, m0, p.w + (size_t)(part * 4 + wave) * (p.K >> 4) * 1024, smem, acc, [&]() {
       acc[0] = x;
       residual_split(acc[0], hi);
     });
@@ -248,6 +463,26 @@ __global__ __launch_bounds__(256) void slim_pack_kernel(const bf16_t* __restrict
 
 }  // namespace
 
+namespace {
+
+// Parts of a workgroup of slim_out_norm_kernel.  It streams the D x D weights of the projection and those
+// of its parts; what counts is what the busiest CU streams, and fewer workgroups where that is the same.
+int parts_of_a_share(int rows, int m_capacity, int parts, int d) {
+  const int m = rows > 0 && rows < m_capacity ? rows : m_capacity, tiles = (m + 31) / 32, cus = 256;
+  int per = parts;
+  long least = 0;
+  for (int n = parts; n >= 1; --n) {
+    const long most = ((long)tiles * ((parts + n - 1) / n) + cus - 1) / cus * (d + n * 128);
+    if (n == parts || most < least) {
+      least = most;
+      per = n;
+    }
+  }
+  return per;
+}
+
+}  // namespace
+
 bool few_rows_supported(int N, int K) { return N % 128 == 0 && K % (16 * kFewRing) == 0; }
 
 uint64_t slim_packed_bytes(uint64_t N, uint64_t K) { return N * K * 2 + kSlimPad * 1024; }
@@ -261,20 +496,26 @@ hipError_t launch_slim_pack(const void* W, uint64_t N, int K, void* packed, hipS
 
 hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int rows, const int32_t* m_ptr, int m_host,
                        int m_capacity, hipStream_t s) {
-  if (d != 384 || !few_rows_supported(F, F)) return hipErrorInvalidValue;
+  const bool pair = step == SlimStep::kOutHidden || step == SlimStep::kOutQuery;
+  if (!(d == 384 && few_rows_supported(F, F)) && !(d == 256 && step == SlimStep::kOutQuery)) return hipErrorInvalidValue;
   SlimArgs p{};
   p.rows = static_cast<const bf16_t*>(a.rows);
   p.x0 = a.x0;
+  p.x0_rows = a.x0_rows;
   p.x = a.x;
+  p.x_new = a.x_new;
   p.ln_g = a.ln_g;
   p.ln_b = a.ln_b;
   p.eps = a.eps;
   p.w = static_cast<const unsigned char*>(a.w);
   p.bias = a.bias;
-  p.parts = step == SlimStep::kHidden ? F / 128 : step == SlimStep::kOut || step == SlimStep::kDown ? d / 128 : 3 * d / 128;
+  p.w2 = static_cast<const unsigned char*>(a.w2);
+  p.bias2 = a.bias2;
+  p.parts = step == SlimStep::kOutHidden ? F / 128 : step == SlimStep::kFirstQkv || step == SlimStep::kQkv ? 3 * d / 128 : d / 128;
   p.K = step == SlimStep::kDown ? F : d;
   p.q_scale = a.q_scale;
   p.out = static_cast<bf16_t*>(a.out);
+  p.z = static_cast<bf16_t*>(a.z);
   p.vt = static_cast<bf16_t*>(a.vt);
   p.vt_ld = a.vt_ld;
   p.vt_pos = a.vt_pos;
@@ -283,33 +524,27 @@ hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int 
   p.nseq = a.nseq;
   p.m_ptr = m_ptr;
   p.m_host = m_host;
-  const dim3 grid = few_rows_grid(rows, m_capacity, p.parts, p.K, 1, &p.row_groups);
+  if (pair && p.parts * 128 > kSlimMaxN) return hipErrorInvalidValue;
+  dim3 grid;
+  if (pair) {
+    p.per_share = parts_of_a_share(rows, m_capacity, p.parts, d);
+    p.shares = (p.parts + p.per_share - 1) / p.per_share;
+    grid = few_rows_grid(rows, m_capacity, p.shares, [](int m) { return (m + 31) / 32; }, 6.0 * 32 * d,
+                         256.0 * d * p.per_share, 2.0 * d * (d + 128.0 * p.per_share), &p.row_bits);
+  } else {
+    grid = few_rows_grid(rows, m_capacity, p.parts, p.K, 1, &p.row_bits);
+  }
+  auto launch = [&](auto kern, int lds) { hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, p); };
   switch (step) {
-    case SlimStep::kFirstQkv: {
-      constexpr auto kern = slim_norm_kernel<384, kFirst>;
-      hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p);
+    case SlimStep::kFirstQkv: launch(slim_norm_kernel<384, kFirst>, 0); break;
+    case SlimStep::kQkv: launch(slim_norm_kernel<384, kQkv>, 0); break;
+    case SlimStep::kRelu: launch(slim_norm_kernel<384, kRelu>, 0); break;
+    case SlimStep::kOutHidden: launch(slim_out_norm_kernel<384, kHidden>, 0); break;
+    case SlimStep::kOutQuery:
+      if (d == 256) launch(slim_out_norm_kernel<256, kQuery>, 0);
+      else launch(slim_out_norm_kernel<384, kQuery>, 0);
       break;
-    }
-    case SlimStep::kQkv: {
-      constexpr auto kern = slim_norm_kernel<384, kQkv>;
-      hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p);
-      break;
-    }
-    case SlimStep::kHidden: {
-      constexpr auto kern = slim_norm_kernel<384, kHidden>;
-      hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p);
-      break;
-    }
-    case SlimStep::kOut: {
-      constexpr auto kern = slim_residual_kernel<384, false>;
-      hipLaunchKernelGGL(kern, grid, dim3(256), few_rows_lds(1), s, p);
-      break;
-    }
-    case SlimStep::kDown: {
-      constexpr auto kern = slim_residual_kernel<384, true>;
-      hipLaunchKernelGGL(kern, grid, dim3(256), few_rows_lds(1), s, p);
-      break;
-    }
+    case SlimStep::kDown: launch(slim_residual_kernel<384>, few_rows_lds(1)); break;
   }
   return hipGetLastError();
 }

@@ -1036,14 +1036,16 @@ __device__ __forceinline__ float row16_sum(float v) {
 template <int MT, typename EP>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_few_kernel(const bf16_t* __restrict__ A, const unsigned char* W, int N, int K,
                                                                EP ep, const int32_t* __restrict__ m_ptr, int m_host,
-                                                               int row_groups) {
+                                                               int row_bits) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int M = m_ptr ? *m_ptr : m_host;
-  const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), N / 128, row_groups);
+  const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), N / 128, row_bits);
+  if (tiles.none) return;
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int t = blockIdx.x >> 3; t < tiles.count; t += gridDim.x >> 3) {
-    const int part = tiles.p0 + t / tiles.rows, m0 = (tiles.r0 + t % tiles.rows) * (32 * MT), n0 = part * 128 + wave * 32;
+  const int part = tiles.part, n0 = part * 128 + wave * 32;
+  for (int r = tiles.r; r < tiles.r_end; r += tiles.step) {
+    const int m0 = r * (32 * MT);
     int32_t info[MT];
     float4 b[4], x[MT][4];
 #pragma unroll
@@ -2346,11 +2348,11 @@ hipError_t launch_persist_tile(const DenseRows& a, const bf16_t* w, int N, int K
 template <int MT, typename EP>
 hipError_t launch_few(const bf16_t* a, const void* packed, int N, int K, const EP& ep, const int32_t* m_ptr, int m_host,
                       int m_capacity, hipStream_t s) {
-  int row_groups = 1;
-  const dim3 grid = few_rows_grid(m_host, m_capacity, N / 128, K, MT, &row_groups);
+  int row_bits = 0;
+  const dim3 grid = few_rows_grid(m_host, m_capacity, N / 128, K, MT, &row_bits);
   constexpr auto kern = gemm_bf16_few_kernel<MT, EP>;
   hipLaunchKernelGGL(kern, grid, dim3(256), few_rows_lds(MT), s, a, static_cast<const unsigned char*>(packed), N, K, ep, m_ptr,
-                     m_host, row_groups);
+                     m_host, row_bits);
   return hipSuccess;
 }
 

@@ -280,24 +280,30 @@ hipError_t launch_slim_pack(const void* W, uint64_t N, int K, void* packed, hipS
 
 // A step of a layer of width 384 where there are few rows, with the results of
 // wide_layer_kernel and on the same residual blocks (few_rows.hip):
-//   kFirstQkv  LayerNorm of x0 and q/k/v; writes x and vt_pos, which the others read
-//   kQkv       the same of x
-//   kOut       x += rows . W^T + bias (rows: the attention's)
-//   kHidden    LayerNorm of x, first feed-forward matrix and activation, to `out` as operand
-//              blocks: tiles of 32 rows, F x 64 bytes each
-//   kDown      x += blocks (rows) . W^T + bias
-// `rows`: those expected (0: unknown).
-enum class SlimStep { kFirstQkv, kQkv, kOut, kHidden, kDown };
+//   kFirstQkv   LayerNorm of x0 and q/k/v; writes x and vt_pos, which the others read
+//   kQkv        the same of x
+//   kOutHidden  x_new = x + rows . W^T + bias (rows: the attention's), its LayerNorm, first feed-forward
+//               matrix (w2, bias2) and activation, to `out` as operand blocks: tiles of 32 rows, F x 64
+//               bytes each
+//   kOutQuery   the same with the decoder's query projection behind it (widths 256 and 384): rows
+//               (LayerNorm . W2^T + bias2) q_scale to `out`
+//   kDown       x += blocks (rows) . W^T + bias
+//   kRelu       LayerNorm of x to z [M, d], and max(0, that . W^T + bias) to `out` [M, d]
+// `rows` of launch_slim: those expected (0: unknown).
+enum class SlimStep { kFirstQkv, kQkv, kOutHidden, kOutQuery, kDown, kRelu };
 struct SlimLayerArgs {
   const void* rows;
   const float* x0;
-  float* x;
+  int x0_rows;          // x0 has that many rows, over and over (0: a row for each)
+  float *x, *x_new;     // x_new: not x
   const float *ln_g, *ln_b;
   float eps;
   const void* w;        // launch_slim_pack's
   const float* bias;
+  const void* w2;
+  const float* bias2;
   float q_scale;
-  void* out;
+  void *out, *z;
   void* vt;
   int vt_ld;
   int32_t* vt_pos;
