@@ -337,9 +337,9 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
   const bool fused_ln = gemm_residual_ln_supported(d, bf);
   const bool fused_tail = fused_ln && ctx->tail_packed_layer != 0;
   // width 384, few rows: four launches a layer over all CUs instead of one over the CUs that the
-  // rows fill.  Passes of 12 layers in us, spread / fused: 64 rows 375 / 575, 920 rows 552 / 667,
-  // 1,840 rows 655 / 671, 2,760 rows 835 / 690.
-  if (ctx->wide_layer && ctx->slim_qkv && shape.rows > 0 && shape.rows <= 7 * ctx->cus) {
+  // rows fill.  Passes of 12 layers in us, spread / fused: 128 rows 352 / 585, 920 rows 473 / 656,
+  // 2,048 rows 525 / 660, 2,760 rows 622 / 679, 3,680 rows 652 / 689, 4,600 rows 774 / 708.
+  if (ctx->wide_layer && ctx->slim_qkv && shape.rows > 0 && shape.rows <= 15 * ctx->cus) {
     SlimLayerArgs a{};
     a.x0 = ctx->x;
     a.x = ctx->x_blocks;
@@ -366,8 +366,8 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
       return launch_slim(a, what, d, F, shape.rows, m_ptr, 0, m_cap, s);
     };
     for (size_t l = 0; l < (size_t)c.n_layers; ++l) {
-      CF_LAUNCH(CFDETR_K_QKV, step(l == 0 ? SlimStep::kFirstQkv : SlimStep::kQkv, ctx->slim_qkv + l * 3 * d * d * 2,
-                                   w.b_qkv + l * 3 * d, w.ln1_g + l * d, w.ln1_b + l * d, nullptr, ctx->qkv));
+      CF_LAUNCH(CFDETR_K_QKV, step(l == 0 ? SlimStep::kFirstQkv : SlimStep::kQkv, nullptr, nullptr, w.ln1_g + l * d, w.ln1_b + l * d,
+                                   nullptr, ctx->qkv, ctx->slim_qkv + l * 3 * d * d * 2, w.b_qkv + l * 3 * d));
       CF_LAUNCH(CFDETR_K_ATTN,
                 launch_attention(ctx->qkv, ctx->vt, ctx->vt_ld, ctx->o, d, c.n_heads, ctx->items, ctx->cap8, ctx->queue_heads + 8 * l,
                                  shape.attn_grid, shape.block_q, bf, kv_len, s));
@@ -847,7 +847,7 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   const uint64_t Tm = c->tok_cap, d = cfg->d_model, F = cfg->d_ffn;
   const uint64_t Bm = cfg->max_batch, D = d / 2;
   Carver cv;
-  const uint64_t o_x = cv.take((Tm + 31) / 32 * 32 * d * 4), o_a = cv.take(Tm * d * c->esz);
+  const uint64_t o_x = cv.take((Tm + 63) / 64 * 64 * d * 4), o_a = cv.take(Tm * d * c->esz);
   const uint64_t o_qkv = cv.take(Tm * 3 * d * c->esz), o_o = cv.take(Tm * d * c->esz);
   const uint64_t o_h = cv.take((Tm + 31) * F * c->esz), o_x0 = cv.take(Bm * c->n0 * d * 4);
   c->vt_ld = (int)((Tm + 64 * 2 * Bm + 63) & ~uint64_t(63));

@@ -12,7 +12,7 @@ namespace {
 
 constexpr int kSlimPad = 32;   // blocks of 1 KB the weight rings read ahead of the end
 constexpr int kAhead = 5;         // k-steps that operands are asked for ahead of their MFMAs (few_rows.h)
-constexpr int kSlimMaxN = 2048;   // widest second matrix of slim_out_norm_kernel (its bias is in LDS)
+constexpr int kSlimMaxN = 2048;   // widest second matrix of slim_norm_kernel (its bias is in LDS)
 
 struct SlimArgs {
   const bf16_t* rows;        // slim_residual_kernel's operand
@@ -23,7 +23,7 @@ struct SlimArgs {
   float eps;
   const unsigned char* w;    // launch_slim_pack's
   const float* bias;
-  float* x_new;              // slim_out_norm_kernel: the new residual rows, its second matrix, its shares of a row tile
+  float* x_new;              // slim_norm_kernel: the new residual rows, its second matrix, its shares of a row tile
   const unsigned char* w2;
   const float* bias2;
   int shares, per_share;
@@ -66,153 +66,20 @@ __device__ __forceinline__ void hidden_store(const SlimArgs& p, int m0, int n0, 
 // query projection.
 constexpr int kFirst = 0, kQkv = 1, kRelu = 2, kHidden = 3, kQuery = 4;
 
-// LayerNorm and the contraction behind it, 32 rows x 128 columns a workgroup.  Every workgroup
-// of the same rows does their LayerNorm again, which costs 1.4 us in each and no launch (4.5 us).
-// All loads of the rows are issued first, then all those of the weights (K = 384 is one ring of
-// 24 blocks), which arrive while the rows are normalised.
-// 920 rows: 8.5 us for q/k/v, of which 3 us are the launch, 2 us the way of rows and weights into the
-// XCDs; LayerNorm and 64 x 64 tiles took 4.5 and 8 us.
+// LayerNorm of the residual rows and a contraction behind it.  kHidden and kQuery project the attention's
+// rows first: x_new = x + rows . W^T + bias, and the LayerNorm is of x_new.  32 rows and a run of p.per_share
+// 128-column parts of the contraction a workgroup: every workgroup of the same rows does their projection
+// (D x D weights, 0.3 MB at D = 384) and their LayerNorm (1.4 us) again, which costs less than a launch
+// of its own and rows that go through memory.  The first share writes x_new, which is not x because
+// the others may not have read that yet.
+// Wavefront w has columns [w D/4, (w + 1) D/4) of the rows, then 32 columns of every part; one ring of D/16
+// weight blocks serves projection and parts, refilled behind each MFMA.
+// Bounds: the chain launch (2.5 us) - first loads (1.5) - ring rounds at a CU's 64 B/clk (0.8 each; the projection
+// is three) - LayerNorm (1.4) - stores, over 920 rows 7.3 us for q/k/v and 11.5 us for projection and
+// hidden units.  Before, a launch each and an LDS wait in front of every MFMA: 8, 5.5 and 9.6 us.
 template <int D, int kOut>
 __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
-  constexpr int KS = D / 16, NT = D / 128, ROWB = D * 2;
-  static_assert(KS == kFewRing, "one ring of weights");
-  __shared__ __attribute__((aligned(1024))) unsigned char sA[32 * ROWB];
-  __shared__ float s_red[256], s_vec[2 * D];
-
-  const int M = p.m_ptr ? *p.m_ptr : p.m_host;
-  const XcdTiles tiles((M + 31) >> 5, p.parts, p.row_bits);
-  if (tiles.none) return;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, g = lane >> 5;
-  const float4 vg = *reinterpret_cast<const float4*>(p.ln_g + min(tid * 4, D - 4));
-  const float4 vb = *reinterpret_cast<const float4*>(p.ln_b + min(tid * 4, D - 4));
-
-  const int part = tiles.part, n0 = part * 128 + wave * 32;
-  for (int t = tiles.r; t < tiles.r_end; t += tiles.step) {
-    const int m0 = t * 32, m = min(m0 + l32, M - 1);
-    const bool v_cols = kOut != kRelu && n0 >= 2 * D;
-    int vpos = 0;
-    if (kOut == kFirst && (v_cols || part == 0)) {
-      const int f = frame_of_token(p.cu, p.nseq, m);
-      vpos = p.pcu[f] + (m - p.cu[f]);
-      if (part == 0 && wave == 0 && g == 0) p.vt_pos[m] = vpos;
-    } else if (v_cols) {
-      vpos = p.vt_pos[m];
-    }
-    f32x16 xa[NT][1];   // the wavefront's quarter of the rows' columns
-    const int m0_row = kOut == kFirst && p.x0_rows > 0 ? m % p.x0_rows : m;
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int c = wave * (D / 4) + j * 32;
-        const float4 v = *reinterpret_cast<const float4*>(kOut == kFirst ? p.x0 + (size_t)m0_row * D + c + 8 * q + 4 * g
-                                                                         : x_block<D>(p.x, m0, c, q, lane));
-        xa[j][0][4 * q] = v.x;
-        xa[j][0][4 * q + 1] = v.y;
-        xa[j][0][4 * q + 2] = v.z;
-        xa[j][0][4 * q + 3] = v.w;
-      }
-    float4 b[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) b[q] = *reinterpret_cast<const float4*>(p.bias + n0 + 8 * q + 4 * g);
-    __builtin_amdgcn_sched_barrier(0);
-    const unsigned char* wp = p.w + (size_t)(part * 4 + wave) * (KS * 1024) + lane * 16;
-    bf16x8 wr[KS];
-#pragma unroll
-    for (int i = 0; i < KS; ++i) wr[i] = *reinterpret_cast<const bf16x8*>(wp + i * 1024);
-    __builtin_amdgcn_sched_barrier(0);
-
-    if (tid < D / 4) {
-      *reinterpret_cast<float4*>(s_vec + tid * 4) = vg;
-      *reinterpret_cast<float4*>(s_vec + D + tid * 4) = vb;
-    }
-    if (kOut == kFirst && part == 0) {
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<float4*>(x_block<D>(p.x, m0, wave * (D / 4) + j * 32, q, lane)) =
-              make_float4(xa[j][0][4 * q], xa[j][0][4 * q + 1], xa[j][0][4 * q + 2], xa[j][0][4 * q + 3]);
-    }
-    float mean[1], rstd[1];
-    wide_stats<4>(xa, s_red, l32, g, wave, p.eps, mean, rstd);
-    wide_norm_to_lds<4>(xa, mean, rstd, s_vec, s_vec + D, sA, l32, g, wave);
-
-    if (kOut == kRelu && part == 0) {
-#pragma unroll
-      for (int u0 = 0; u0 < 32 * (ROWB / 16); u0 += 256) {
-        const int u = u0 + tid, row = u / (ROWB / 16), pos = u % (ROWB / 16);
-        const int c = (pos & ~15) | ((pos ^ row) & 15);
-        if (m0 + row < M)
-          *reinterpret_cast<uint4*>(p.z + (size_t)(m0 + row) * D + c * 8) = *reinterpret_cast<const uint4*>(sA + u * 16);
-      }
-    }
-    f32x16 acc;   // (kRelu: the bias is added to the sum, as the tiled contraction does)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc[4 * q] = kOut == kRelu ? 0.f : b[q].x;
-      acc[4 * q + 1] = kOut == kRelu ? 0.f : b[q].y;
-      acc[4 * q + 2] = kOut == kRelu ? 0.f : b[q].z;
-      acc[4 * q + 3] = kOut == kRelu ? 0.f : b[q].w;
-    }
-    bf16x8 a[kAhead + 1];
-    uint32_t ao[8];
-    int lx = l32;
-    work_out_here(lx);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) ao[k] = lx * ROWB + (((2 * k + g) ^ (lx & 15)) << 4);
-    auto operand = [&](int ks) {
-      a[ks % (kAhead + 1)] = *reinterpret_cast<const bf16x8*>(sA + ao[ks & 7] + (ks >> 3) * 256);
-    };
-#pragma unroll
-    for (int ks = 0; ks < kAhead; ++ks) operand(ks);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (ks + kAhead < KS) operand(ks + kAhead);
-      __builtin_amdgcn_sched_barrier(0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[ks], a[ks % (kAhead + 1)], acc, 0, 0, 0);
-    }
-
-    if (m0 + l32 < M) {
-      if (v_cols) {
-        bf16_t* vp = p.vt + (size_t)(n0 + 4 * g - 2 * D) * p.vt_ld + vpos;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          *vp = f32_to_bf16(acc[r]);
-          vp += (size_t)((r & 3) == 3 ? 5 : 1) * p.vt_ld;
-        }
-      } else {
-        const float sc = kOut != kRelu && n0 < D ? p.q_scale : 1.0f;
-        bf16_t* const op = p.out + (size_t)m * (kOut == kRelu ? D : 3 * D) + n0 + 4 * g;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float r0 = acc[4 * q] * sc, r1 = acc[4 * q + 1] * sc, r2 = acc[4 * q + 2] * sc, r3 = acc[4 * q + 3] * sc;
-          if (kOut == kRelu) {
-            r0 = fmaxf(acc[4 * q] + b[q].x, 0.f);
-            r1 = fmaxf(acc[4 * q + 1] + b[q].y, 0.f);
-            r2 = fmaxf(acc[4 * q + 2] + b[q].z, 0.f);
-            r3 = fmaxf(acc[4 * q + 3] + b[q].w, 0.f);
-          }
-          *reinterpret_cast<uint2*>(op + 8 * q) = make_uint2(pack_bf16x2(r0, r1), pack_bf16x2(r2, r3));
-        }
-      }
-    }
-    __syncthreads();   // the rows' place is free
-  }
-}
-
-// x_new = x + rows . W^T + bias (the attention's rows, the output projection), LayerNorm, and a
-// contraction behind that: the first feed-forward matrix with its activation (kHidden) or the
-// decoder's query projection (kQuery).  32 rows and one of p.shares equal runs of the second
-// matrix's 128-column parts a workgroup: each of them projects the rows again (D x D weights, 0.3 MB at
-// D = 384, against a launch of its own), and the first writes x_new, which is not x because the
-// others may not have read that yet.
-// Wavefront w has columns [w D/4, (w + 1) D/4) of the projection, then 32 columns of every part; one ring
-// of D/16 weight blocks serves both, refilled behind each MFMA.
-template <int D, int kOut>
-__global__ __launch_bounds__(256, 2) void slim_out_norm_kernel(SlimArgs p) {
+  constexpr bool kProject = kOut == kHidden || kOut == kQuery;
   constexpr int KS = D / 16, NT = D / 128, ROWB = D * 2, UN = KS / NT;
   static_assert(UN == 8, "eight k-steps of the projection a ring round");
   __shared__ __attribute__((aligned(1024))) unsigned char sA[32 * ROWB];
@@ -232,64 +99,77 @@ __global__ __launch_bounds__(256, 2) void slim_out_norm_kernel(SlimArgs p) {
     return q + i * 1024 + voff;
   };
   auto block = [&](const void* base, int i) { return *reinterpret_cast<const __attribute__((address_space(1))) bf16x8*>(at(base, i)); };
+
   const int share = tiles.part, part0 = share * p.per_share, part1 = min(part0 + p.per_share, p.parts);
   for (int t = tiles.r; t < tiles.r_end; t += tiles.step) {
     const int m0 = t * 32;
     int tid = threadIdx.x;
     work_out_here(tid);   // (or the addresses of a row tile are kept from tile to tile, in scratch memory)
-    const int lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+    const int lane = tid & 63, l32 = lane & 31, g = lane >> 5, m = min(m0 + l32, M - 1);
     voff = lane * 16;
+    int vpos = 0;   // place of the row in vt
+    if ((kOut == kFirst || kOut == kQkv) && (part1 * 128 > 2 * D || share == 0)) {
+      if (kOut == kQkv) {
+        vpos = p.vt_pos[m];
+      } else {
+        const int f = frame_of_token(p.cu, p.nseq, m);
+        vpos = p.pcu[f] + (m - p.cu[f]);
+        if (share == 0 && wave == 0 && g == 0) p.vt_pos[m] = vpos;
+      }
+    }
     const int vat = min(tid * 4, D - 4);
-    const float4 vo = *reinterpret_cast<const float4*>(p.bias + vat);
+    float4 vo;
+    if (kProject) vo = *reinterpret_cast<const float4*>(p.bias + vat);
     const float4 vg = *reinterpret_cast<const float4*>(p.ln_g + vat);
     const float4 vb = *reinterpret_cast<const float4*>(p.ln_b + vat);
     static_assert(kSlimMaxN == 2048, "two pieces");   // the share's biases
     const float4 vc0 = *reinterpret_cast<const float4*>(p.bias2 + min(part0 * 128 + tid * 4, p.parts * 128 - 4));
     const float4 vc1 = *reinterpret_cast<const float4*>(p.bias2 + min(part0 * 128 + 1024 + tid * 4, p.parts * 128 - 4));
-    // the rows into LDS: 128 columns by 128, 32 rows of 256 bytes each, chunks XORed by the row
+    // the attention's rows into LDS: 128 columns by 128, 32 rows of 256 bytes each, chunks XORed by the row
+    if (kProject) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int row = (wave * 2 + i) * 4 + (lane >> 4);
-      const unsigned char* src = reinterpret_cast<const unsigned char*>(p.rows + (size_t)min(m0 + row, M - 1) * D) +
-                                 (((lane & 15) ^ (row & 15)) << 4);
+      for (int i = 0; i < 2; ++i) {
+        const int row = (wave * 2 + i) * 4 + (lane >> 4);
+        const unsigned char* src = reinterpret_cast<const unsigned char*>(p.rows + (size_t)min(m0 + row, M - 1) * D) +
+                                   (((lane & 15) ^ (row & 15)) << 4);
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                     : : "s"((uint32_t)(uintptr_t)sA + j * 8192 + (wave * 2 + i) * 1024), "v"(src + j * 256) : "memory");
+        for (int j = 0; j < NT; ++j)
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                       : : "s"((uint32_t)(uintptr_t)sA + j * 8192 + (wave * 2 + i) * 1024), "v"(src + j * 256) : "memory");
+      }
     }
     f32x16 acc[NT][1];
     u32x8 hi[NT];
     const size_t x0 = ((size_t)(m0 >> 5) * (D / 32) + wave * NT) * 1024;   // residual blocks of the wavefront
+    const int row0 = kOut == kFirst && p.x0_rows > 0 ? m % p.x0_rows : m;
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const f32x4 v = *reinterpret_cast<const __attribute__((address_space(1))) f32x4*>(at(p.x + x0, j * 4 + q));
+        const f32x4 v = kOut == kFirst
+                            ? *reinterpret_cast<const f32x4*>(p.x0 + (size_t)row0 * D + wave * (D / 4) + j * 32 + 8 * q + 4 * g)
+                            : *reinterpret_cast<const __attribute__((address_space(1))) f32x4*>(at(p.x + x0, j * 4 + q));
         acc[j][0][4 * q] = v[0];
         acc[j][0][4 * q + 1] = v[1];
         acc[j][0][4 * q + 2] = v[2];
         acc[j][0][4 * q + 3] = v[3];
       }
     __builtin_amdgcn_sched_barrier(0);
-    // block ks NT + j of the ring: column tile j of k-step ks
+    // block ks NT + j of the ring: column tile j of k-step ks of the projection, then k-step ks of a part
     const unsigned char* const wo = p.w + (size_t)(wave * NT) * (KS * 1024);
     const unsigned char* w2 = p.w2 + (size_t)(part0 * 4 + wave) * (KS * 1024);
     bf16x8 wr[KS];
 #pragma unroll
-    for (int i = 0; i < KS; ++i) wr[i] = block(wo, (i % NT) * KS + i / NT);
+    for (int i = 0; i < KS; ++i) wr[i] = kProject ? block(wo, (i % NT) * KS + i / NT) : block(w2, i);
     __builtin_amdgcn_sched_barrier(0);
     if (tid < D / 4) {
-      *reinterpret_cast<float4*>(s_vec + tid * 4) = vo;
+      if (kProject) *reinterpret_cast<float4*>(s_vec + tid * 4) = vo;
       *reinterpret_cast<float4*>(s_vec + D + tid * 4) = vg;
       *reinterpret_cast<float4*>(s_vec + 2 * D + tid * 4) = vb;
     }
     *reinterpret_cast<float4*>(s_bias + tid * 4) = vc0;
     *reinterpret_cast<float4*>(s_bias + 1024 + tid * 4) = vc1;
-#pragma unroll
-    for (int j = 0; j < NT; ++j) residual_split(acc[j][0], hi[j]);
-    // the rows' loads are older than the ring's
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(KS) : "memory");
-    __syncthreads();
+
     bf16x8 a[kAhead + 1];
     uint32_t ao[8];
     auto operand = [&](int ks, int next_8) {
@@ -301,49 +181,67 @@ __global__ __launch_bounds__(256, 2) void slim_out_norm_kernel(SlimArgs p) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) ao[k] = lx * row_bytes + (((2 * k + g) ^ (lx & 15)) << 4);
     };
-    operand_addresses(256);
+    if (kProject) {
 #pragma unroll
-    for (int ks = 0; ks < kAhead; ++ks) operand(ks, 8192);
+      for (int j = 0; j < NT; ++j) residual_split(acc[j][0], hi[j]);
+      // the rows' loads are older than the ring's
+      asm volatile("s_waitcnt vmcnt(%0)" : : "n"(KS) : "memory");
+      __syncthreads();
+      operand_addresses(256);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (ks + kAhead < KS) operand(ks + kAhead, 8192);
+      for (int ks = 0; ks < kAhead; ++ks) operand(ks, 8192);
 #pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const int i = (ks % UN) * NT + j;
-        acc[j][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[i], a[ks % (kAhead + 1)], acc[j][0], 0, 0, 0);
-        wr[i] = ks + UN < KS ? block(wo, j * KS + ks + UN) : block(w2, i);
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks + kAhead < KS) operand(ks + kAhead, 8192);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          const int i = (ks % UN) * NT + j;
+          acc[j][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[i], a[ks % (kAhead + 1)], acc[j][0], 0, 0, 0);
+          wr[i] = ks + UN < KS ? block(wo, j * KS + ks + UN) : block(w2, i);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        residual_join(acc[j][0], hi[j], q, *reinterpret_cast<const float4*>(s_vec + wave * (D / 4) + j * 32 + 8 * q + 4 * g));
-    if (share == 0) {
 #pragma unroll
       for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<__attribute__((address_space(1))) f32x4*>(at(p.x_new + x0, j * 4 + q)) =
+          residual_join(acc[j][0], hi[j], q, *reinterpret_cast<const float4*>(s_vec + wave * (D / 4) + j * 32 + 8 * q + 4 * g));
+    }
+    if ((kProject || kOut == kFirst) && share == 0) {
+      float* const xo = (kProject ? p.x_new : p.x) + x0;
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<__attribute__((address_space(1))) f32x4*>(at(xo, j * 4 + q)) =
               f32x4{acc[j][0][4 * q], acc[j][0][4 * q + 1], acc[j][0][4 * q + 2], acc[j][0][4 * q + 3]};
     }
     float mean[1], rstd[1];
     wide_stats<4>(acc, s_red, l32, g, wave, p.eps, mean, rstd);
     wide_norm_to_lds<4>(acc, mean, rstd, s_vec + D, s_vec + 2 * D, sA, l32, g, wave);
+    if (kOut == kRelu && share == 0) {
+#pragma unroll
+      for (int u0 = 0; u0 < 32 * (ROWB / 16); u0 += 256) {
+        const int u = u0 + tid, row = u / (ROWB / 16), pos = u % (ROWB / 16);
+        const int c = (pos & ~15) | ((pos ^ row) & 15);
+        if (m0 + row < M)
+          *reinterpret_cast<uint4*>(p.z + (size_t)(m0 + row) * D + c * 8) = *reinterpret_cast<const uint4*>(sA + u * 16);
+      }
+    }
 
     operand_addresses(ROWB);
     auto one_part = [&](int part, auto more_tag) {
       constexpr bool kMore = decltype(more_tag)::value;   // another part's weights are asked for
       const int n0 = part * 128 + wave * 32;
-      f32x16 r;
+      const float* const bias = s_bias + n0 - part0 * 128 + 4 * g;
+      f32x16 r;   // (kRelu: the bias is added to the sum, as the tiled contraction does)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const float4 b = *reinterpret_cast<const float4*>(s_bias + n0 - part0 * 128 + 8 * q + 4 * g);
-        r[4 * q] = b.x;
-        r[4 * q + 1] = b.y;
-        r[4 * q + 2] = b.z;
-        r[4 * q + 3] = b.w;
+        const float4 b = *reinterpret_cast<const float4*>(bias + 8 * q);
+        r[4 * q] = kOut == kRelu ? 0.f : b.x;
+        r[4 * q + 1] = kOut == kRelu ? 0.f : b.y;
+        r[4 * q + 2] = kOut == kRelu ? 0.f : b.z;
+        r[4 * q + 3] = kOut == kRelu ? 0.f : b.w;
       }
       w2 += 4 * KS * 1024;
 #pragma unroll
@@ -358,11 +256,29 @@ __global__ __launch_bounds__(256, 2) void slim_out_norm_kernel(SlimArgs p) {
       if (kOut == kHidden) {
         hidden_store(p, m0, n0, l32, g, r);
       } else if (m0 + l32 < M) {
+        if ((kOut == kFirst || kOut == kQkv) && n0 >= 2 * D) {
+          bf16_t* vp = p.vt + (size_t)(n0 + 4 * g - 2 * D) * p.vt_ld + vpos;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<uint2*>(p.out + (size_t)(m0 + l32) * D + n0 + 8 * q + 4 * g) =
-              make_uint2(pack_bf16x2(r[4 * q] * p.q_scale, r[4 * q + 1] * p.q_scale),
-                         pack_bf16x2(r[4 * q + 2] * p.q_scale, r[4 * q + 3] * p.q_scale));
+          for (int e = 0; e < 16; ++e) {
+            *vp = f32_to_bf16(r[e]);
+            vp += (size_t)((e & 3) == 3 ? 5 : 1) * p.vt_ld;
+          }
+        } else {
+          const float sc = kOut == kQuery || (kOut != kRelu && n0 < D) ? p.q_scale : 1.0f;
+          bf16_t* const op = p.out + (size_t)m * (kOut == kFirst || kOut == kQkv ? 3 * D : D) + n0 + 4 * g;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if (kOut == kRelu) {
+              const float4 b = *reinterpret_cast<const float4*>(bias + 8 * q);
+              r[4 * q] = fmaxf(r[4 * q] + b.x, 0.f);
+              r[4 * q + 1] = fmaxf(r[4 * q + 1] + b.y, 0.f);
+              r[4 * q + 2] = fmaxf(r[4 * q + 2] + b.z, 0.f);
+              r[4 * q + 3] = fmaxf(r[4 * q + 3] + b.w, 0.f);
+            }
+            *reinterpret_cast<uint2*>(op + 8 * q) = make_uint2(pack_bf16x2(r[4 * q] * sc, r[4 * q + 1] * sc),
+                                                               pack_bf16x2(r[4 * q + 2] * sc, r[4 * q + 3] * sc));
+          }
+        }
       }
     };
 #pragma nounroll
@@ -372,40 +288,47 @@ __global__ __launch_bounds__(256, 2) void slim_out_norm_kernel(SlimArgs p) {
   }
 }
 
-// x += hidden blocks . W^T + bias, the second feed-forward matrix.  920 rows: 9.5 us (64 x 64 tiles
-// took 17 us), the K = 1536 of a wavefront at what a CU's vector-memory path gives.
-template <int D>
+// x += hidden blocks . W^T + bias, the second feed-forward matrix: 32 MT rows x 128 columns a workgroup.
+// 920 rows: 7.0 us, the K = 1536 of a wavefront at what a CU's vector-memory path gives.
+template <int D, int MT>
 __global__ __launch_bounds__(256, 2) void slim_residual_kernel(SlimArgs p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int M = p.m_ptr ? *p.m_ptr : p.m_host;
-  const XcdTiles tiles((M + 31) >> 5, D / 128, p.row_bits);
+  const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), D / 128, p.row_bits);
   if (tiles.none) return;
   const int lane = threadIdx.x & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int part = tiles.part, n0 = part * 128 + wave * 32;
   for (int t = tiles.r; t < tiles.r_end; t += tiles.step) {
-    const int m0 = t * 32;
+    const int m0 = t * (32 * MT);
     float4 b[4];
-    f32x16 x, acc[1];
-    u32x8 hi;
+    f32x16 acc[MT];
+    u32x8 hi[MT];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       b[q] = *reinterpret_cast<const float4*>(p.bias + n0 + 8 * q + 4 * g);
-      const float4 v = *reinterpret_cast<const float4*>(x_block<D>(p.x, m0, n0, q, lane));
-      x[4 * q] = v.x;
-      x[4 * q + 1] = v.y;
-      x[4 * q + 2] = v.z;
-      x[4 * q + 3] = v.w;
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const float4 v = *reinterpret_cast<const float4*>(x_block<D>(p.x, m0 + i * 32, n0, q, lane));
+        acc[i][4 * q] = v.x;
+        acc[i][4 * q + 1] = v.y;
+        acc[i][4 * q + 2] = v.z;
+        acc[i][4 * q + 3] = v.w;
+      }
     }
-    few_rows_product<1, true>(p.rows, p.K, M, m0, p.w + (size_t)(part * 4 + wave) * (p.K >> 4) * 1024, smem, acc, [&]() {
-      acc[0] = x;
-      residual_split(acc[0], hi);
+    few_rows_product<MT, true>(p.rows, p.K, M, m0, p.w + (size_t)(part * 4 + wave) * (p.K >> 4) * 1024, smem, acc, [&]() {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) residual_split(acc[i], hi[i]);
     });
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      residual_join(acc[0], hi, q, b[q]);
-      *reinterpret_cast<float4*>(x_block<D>(p.x, m0, n0, q, lane)) =
-          make_float4(acc[0][4 * q], acc[0][4 * q + 1], acc[0][4 * q + 2], acc[0][4 * q + 3]);
+    for (int i = 0; i < MT; ++i) {
+      if (m0 + i * 32 >= M) break;   // (what is behind the last tile of 32 rows is not a residual row)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        residual_join(acc[i], hi[i], q, b[q]);
+        *reinterpret_cast<float4*>(x_block<D>(p.x, m0 + i * 32, n0, q, lane)) =
+            make_float4(acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]);
+      }
     }
     __syncthreads();
   }
@@ -465,14 +388,14 @@ __global__ __launch_bounds__(256) void slim_pack_kernel(const bf16_t* __restrict
 
 namespace {
 
-// Parts of a workgroup of slim_out_norm_kernel.  It streams the D x D weights of the projection and those
-// of its parts; what counts is what the busiest CU streams, and fewer workgroups where that is the same.
-int parts_of_a_share(int rows, int m_capacity, int parts, int d) {
-  const int m = rows > 0 && rows < m_capacity ? rows : m_capacity, tiles = (m + 31) / 32, cus = 256;
+// Parts of a workgroup of slim_norm_kernel.  It streams the weights of the projection (project of its D rows) and
+// those of its parts, and is some 200 columns' worth of stream late at the start; what counts is what the
+// busiest CU has, and fewer workgroups where that is the same.
+int parts_of_a_share(int tiles, int parts, int project) {
   int per = parts;
   long least = 0;
   for (int n = parts; n >= 1; --n) {
-    const long most = ((long)tiles * ((parts + n - 1) / n) + cus - 1) / cus * (d + n * 128);
+    const long most = ((long)tiles * ((parts + n - 1) / n) + 255) / 256 * (project + 200 + n * 128);
     if (n == parts || most < least) {
       least = most;
       per = n;
@@ -496,7 +419,6 @@ hipError_t launch_slim_pack(const void* W, uint64_t N, int K, void* packed, hipS
 
 hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int rows, const int32_t* m_ptr, int m_host,
                        int m_capacity, hipStream_t s) {
-  const bool pair = step == SlimStep::kOutHidden || step == SlimStep::kOutQuery;
   if (!(d == 384 && few_rows_supported(F, F)) && !(d == 256 && step == SlimStep::kOutQuery)) return hipErrorInvalidValue;
   SlimArgs p{};
   p.rows = static_cast<const bf16_t*>(a.rows);
@@ -511,8 +433,6 @@ hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int 
   p.bias = a.bias;
   p.w2 = static_cast<const unsigned char*>(a.w2);
   p.bias2 = a.bias2;
-  p.parts = step == SlimStep::kOutHidden ? F / 128 : step == SlimStep::kFirstQkv || step == SlimStep::kQkv ? 3 * d / 128 : d / 128;
-  p.K = step == SlimStep::kDown ? F : d;
   p.q_scale = a.q_scale;
   p.out = static_cast<bf16_t*>(a.out);
   p.z = static_cast<bf16_t*>(a.z);
@@ -524,27 +444,35 @@ hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int 
   p.nseq = a.nseq;
   p.m_ptr = m_ptr;
   p.m_host = m_host;
-  if (pair && p.parts * 128 > kSlimMaxN) return hipErrorInvalidValue;
-  dim3 grid;
-  if (pair) {
-    p.per_share = parts_of_a_share(rows, m_capacity, p.parts, d);
-    p.shares = (p.parts + p.per_share - 1) / p.per_share;
-    grid = few_rows_grid(rows, m_capacity, p.shares, [](int m) { return (m + 31) / 32; }, 6.0 * 32 * d,
-                         256.0 * d * p.per_share, 2.0 * d * (d + 128.0 * p.per_share), &p.row_bits);
-  } else {
-    grid = few_rows_grid(rows, m_capacity, p.parts, p.K, 1, &p.row_bits);
+  const int m = rows > 0 && rows < m_capacity ? rows : m_capacity;
+  if (step == SlimStep::kDown) {
+    p.K = F;
+    // 64 rows a workgroup where 32 would give CUs a second one (3,520 rows: 14 -> 9 us)
+    const int mt = (m + 31) / 32 * (d / 128) > 256 ? 2 : 1;
+    const dim3 grid = few_rows_grid(rows, m_capacity, d / 128, F, mt, &p.row_bits);
+    if (mt == 2) hipLaunchKernelGGL((slim_residual_kernel<384, 2>), grid, dim3(256), few_rows_lds(2), s, p);
+    else hipLaunchKernelGGL((slim_residual_kernel<384, 1>), grid, dim3(256), few_rows_lds(1), s, p);
+    return hipGetLastError();
   }
-  auto launch = [&](auto kern, int lds) { hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, p); };
+  const bool qkv = step == SlimStep::kFirstQkv || step == SlimStep::kQkv;
+  const bool project = step == SlimStep::kOutHidden || step == SlimStep::kOutQuery;
+  p.parts = (step == SlimStep::kOutHidden ? F : qkv ? 3 * d : d) / 128;
+  if (p.parts * 128 > kSlimMaxN) return hipErrorInvalidValue;
+  p.per_share = parts_of_a_share((m + 31) / 32, p.parts, project ? d : 0);
+  p.shares = (p.parts + p.per_share - 1) / p.per_share;
+  const dim3 grid = few_rows_grid(rows, m_capacity, p.shares, [](int r) { return (r + 31) / 32; }, (project ? 6.0 : 4.0) * 32 * d,
+                                  256.0 * d * p.per_share, 2.0 * d * ((project ? d : 0) + 128.0 * p.per_share), &p.row_bits);
+  auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p); };
   switch (step) {
-    case SlimStep::kFirstQkv: launch(slim_norm_kernel<384, kFirst>, 0); break;
-    case SlimStep::kQkv: launch(slim_norm_kernel<384, kQkv>, 0); break;
-    case SlimStep::kRelu: launch(slim_norm_kernel<384, kRelu>, 0); break;
-    case SlimStep::kOutHidden: launch(slim_out_norm_kernel<384, kHidden>, 0); break;
+    case SlimStep::kFirstQkv: launch(slim_norm_kernel<384, kFirst>); break;
+    case SlimStep::kQkv: launch(slim_norm_kernel<384, kQkv>); break;
+    case SlimStep::kRelu: launch(slim_norm_kernel<384, kRelu>); break;
+    case SlimStep::kOutHidden: launch(slim_norm_kernel<384, kHidden>); break;
     case SlimStep::kOutQuery:
-      if (d == 256) launch(slim_out_norm_kernel<256, kQuery>, 0);
-      else launch(slim_out_norm_kernel<384, kQuery>, 0);
+      if (d == 256) launch(slim_norm_kernel<256, kQuery>);
+      else launch(slim_norm_kernel<384, kQuery>);
       break;
-    case SlimStep::kDown: launch(slim_residual_kernel<384>, few_rows_lds(1)); break;
+    default: break;
   }
   return hipGetLastError();
 }

@@ -280,15 +280,15 @@ hipError_t launch_slim_pack(const void* W, uint64_t N, int K, void* packed, hipS
 
 // A step of a layer of width 384 where there are few rows, with the results of
 // wide_layer_kernel and on the same residual blocks (few_rows.hip):
-//   kFirstQkv   LayerNorm of x0 and q/k/v; writes x and vt_pos, which the others read
+//   kFirstQkv   LayerNorm of x0, and q/k/v: that . W2^T + bias2; writes x and vt_pos, which the others read
 //   kQkv        the same of x
+//   kRelu       LayerNorm of x to z [M, d], and max(0, that . W2^T + bias2) to `out` [M, d]
 //   kOutHidden  x_new = x + rows . W^T + bias (rows: the attention's), its LayerNorm, first feed-forward
 //               matrix (w2, bias2) and activation, to `out` as operand blocks: tiles of 32 rows, F x 64
 //               bytes each
 //   kOutQuery   the same with the decoder's query projection behind it (widths 256 and 384): rows
 //               (LayerNorm . W2^T + bias2) q_scale to `out`
 //   kDown       x += blocks (rows) . W^T + bias
-//   kRelu       LayerNorm of x to z [M, d], and max(0, that . W^T + bias) to `out` [M, d]
 // `rows` of launch_slim: those expected (0: unknown).
 enum class SlimStep { kFirstQkv, kQkv, kOutHidden, kOutQuery, kDown, kRelu };
 struct SlimLayerArgs {
