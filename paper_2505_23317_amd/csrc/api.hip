@@ -74,6 +74,10 @@ struct cfdetr_ctx {
   cfdetr_decoder_weights dw;
   void* dec_arena = nullptr;
   float* dx = nullptr;        // residual stream of the queries [Bmax*Q, d] fp32
+  float* dx2 = nullptr;       // widths 256 and 384: dx and dx2 hold residual blocks in turn
+  char *dwide_packed = nullptr, *dwide_head = nullptr;   // wide_layer_kernel's copies of the matrices
+  uint64_t dwide_layer = 0;   // bytes a layer of the first (0: another path)
+  int32_t* dvt_pos = nullptr; // place of a query in dvt
   void* da = nullptr;         // LayerNorm output / head input [Bmax*Q, d] bf16
   void* dqkv = nullptr;       // [Bmax*Q, 3d] bf16 (self-attention), first third reused for
                               // the cross-attention queries
@@ -275,6 +279,11 @@ struct RunShape {
   int block_q = 128, attn_grid = 0;
 };
 
+// Rows a CU up to which layers of width 384 are spread over the chip (few_rows.hip).  Passes of 12
+// layers in us, spread / one kernel a layer, on 256 CUs: 128 rows 352 / 585, 920 rows 473 / 656, 2,048
+// rows 525 / 660, 2,760 rows 622 / 679, 3,680 rows 652 / 689, 4,600 rows 774 / 708.
+constexpr int kSpreadRows = 15;
+
 enum class RunKind { kMerged = 0, kFine = 1, kExact = 2 };
 
 // Between the coarse grids alone (m_least) and the capacity, before any run has been counted: a
@@ -336,10 +345,8 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
   // LayerNorm that follows them, and only the very first one is a launch of its own.
   const bool fused_ln = gemm_residual_ln_supported(d, bf);
   const bool fused_tail = fused_ln && ctx->tail_packed_layer != 0;
-  // width 384, few rows: four launches a layer over all CUs instead of one over the CUs that the
-  // rows fill.  Passes of 12 layers in us, spread / fused: 128 rows 352 / 585, 920 rows 473 / 656,
-  // 2,048 rows 525 / 660, 2,760 rows 622 / 679, 3,680 rows 652 / 689, 4,600 rows 774 / 708.
-  if (ctx->wide_layer && ctx->slim_qkv && shape.rows > 0 && shape.rows <= 15 * ctx->cus) {
+  // width 384, few rows: four launches a layer over all CUs instead of one over the CUs that the rows fill
+  if (ctx->wide_layer && ctx->slim_qkv && shape.rows > 0 && shape.rows <= kSpreadRows * ctx->cus) {
     SlimLayerArgs a{};
     a.x0 = ctx->x;
     a.x = ctx->x_blocks;
@@ -603,6 +610,117 @@ cfdetr_status padded_impl(cfdetr_ctx* ctx, const void* images, int B, const int3
   return run_encoder(ctx, B, shape, B * t_pad, y_padded, 0, nullptr, s, ctx->kv_len);
 }
 
+// The decoder's layers at widths 256 and 384: the encoder's kernels of those widths on the query rows, and
+// slim_norm_kernel between the two attentions.  Few rows of width 384 take the spread kernels
+// (run_encoder), the others one kernel behind the cross-attention, with the same bits.
+cfdetr_status decode_wide(cfdetr_ctx* ctx, int B, float* queries, int dblock_q, int dgrid, hipStream_t s) {
+  const cfdetr_config& c = ctx->cfg;
+  const cfdetr_decoder_weights& w = ctx->dw;
+  const size_t d = c.d_model, F = c.d_ffn;
+  const int Q = w.n_queries, L = w.n_layers, Mq = B * Q;
+  const bool spread = ctx->dslim_qkv != nullptr && Mq <= kSpreadRows * ctx->cus;
+  const size_t k_stride = (size_t)c.max_tokens_total * d, v_stride = d * ctx->vt_ld;
+  SlimLayerArgs a{};
+  a.x0 = w.query_embed;
+  a.x0_rows = Q;
+  a.x = ctx->dx;
+  a.x_new = ctx->dx2;
+  a.eps = c.ln_eps;
+  a.q_scale = attention_q_scale(c.d_model / c.n_heads);
+  a.vt = ctx->dvt;
+  a.vt_ld = ctx->dvt_ld;
+  a.vt_pos = ctx->dvt_pos;
+  a.cu = ctx->dcu_all;
+  a.pcu = ctx->dpcu;
+  a.nseq = B;
+  auto step = [&](SlimStep what, const float* g, const float* b, void* out, const void* w2, const float* bias2,
+                  const void* rows = nullptr, const void* wt = nullptr, const float* bias = nullptr) {
+    a.w = wt;
+    a.bias = bias;
+    a.w2 = w2;
+    a.bias2 = bias2;
+    a.ln_g = g;
+    a.ln_b = b;
+    a.rows = rows;
+    a.out = out;
+    const hipError_t e = launch_slim(a, what, (int)d, (int)F, Mq, nullptr, Mq, Mq, s);
+    if (what == SlimStep::kOutHidden || what == SlimStep::kOutQuery) std::swap(a.x, a.x_new);
+    return e;
+  };
+  const int mt = wide_layer_tiles((int)d, Mq, ctx->cus);
+  WideLayerArgs wa{};
+  wa.x0 = a.x0;
+  wa.x0_rows = Q;
+  wa.eps = a.eps;
+  wa.q_scale = a.q_scale;
+  wa.qk = ctx->dqkv;
+  wa.vt = a.vt;
+  wa.vt_ld = a.vt_ld;
+  wa.vt_pos = a.vt_pos;
+  wa.cu = a.cu;
+  wa.pcu = a.pcu;
+  wa.B = B;
+  wa.out = ctx->dz;
+  for (int l = 0; l < L; ++l) {
+    // self-attention among the queries of a frame
+    if (spread) {
+      CF_LAUNCH(CFDETR_K_QKV, step(l == 0 ? SlimStep::kFirstQkv : SlimStep::kQkv, w.ln1_g + l * d, w.ln1_b + l * d, ctx->dqkv,
+                                   ctx->dslim_qkv + l * 3 * d * d * 2, w.b_qkv + l * 3 * d));
+    } else if (l == 0) {
+      wa.packed = ctx->dwide_head;
+      wa.resid = a.x;
+      wa.ln_g = w.ln1_g;
+      wa.ln_b = w.ln1_b;
+      wa.b_qkv = w.b_qkv;
+      CF_LAUNCH(CFDETR_K_QKV, launch_wide_layer(wa, (int)d, (int)F, mt, nullptr, Mq, Mq, s));
+    }
+    CF_LAUNCH(CFDETR_K_ATTN,
+              launch_attention(ctx->dqkv, ctx->dvt, ctx->dvt_ld, ctx->d_o, (int)d, c.n_heads, ctx->ditems, ctx->dcap8,
+                               ctx->dqueue + 16 * l, dgrid, dblock_q, true, nullptr, s));
+    CF_LAUNCH(CFDETR_K_OUT, step(SlimStep::kOutQuery, w.ln2_g + l * d, w.ln2_b + l * d, ctx->dh, ctx->dslim_q + l * d * d * 2,
+                                 w.b_q + l * d, ctx->d_o, ctx->dslim_o + l * d * d * 2, w.b_o + l * d));
+    // cross-attention: the queries read the tokens of their frame
+    CF_LAUNCH(CFDETR_K_ATTN,
+              launch_cross_attention(ctx->dh, static_cast<const bf16_t*>(ctx->dk_all) + l * k_stride,
+                                     static_cast<const bf16_t*>(ctx->dvt_all) + l * v_stride, ctx->vt_ld, ctx->d_o,
+                                     ctx->cu_all, ctx->pcu, (int)d, c.n_heads, ctx->ditems, ctx->dcap8,
+                                     ctx->dqueue + 16 * l + 8, dgrid, dblock_q, s));
+    if (spread) {
+      CF_LAUNCH(CFDETR_K_FF1, step(SlimStep::kOutHidden, w.ln3_g + l * d, w.ln3_b + l * d, ctx->dh, ctx->dslim_ff1 + l * F * d * 2,
+                                   w.b_ff1 + l * F, ctx->d_o, ctx->dslim_o2 + l * d * d * 2, w.b_o2 + l * d));
+      CF_LAUNCH(CFDETR_K_FF2, step(SlimStep::kDown, nullptr, nullptr, nullptr, nullptr, nullptr, ctx->dh,
+                                   ctx->dslim_ff2 + l * F * d * 2, w.b_ff2 + l * d));
+      continue;
+    }
+    wa.O = ctx->d_o;
+    wa.resid = a.x;
+    wa.last = l + 1 == L;
+    wa.packed = ctx->dwide_packed + l * ctx->dwide_layer;
+    wa.b_o = w.b_o2 + l * d;
+    wa.ln2_g = w.ln3_g + l * d;
+    wa.ln2_b = w.ln3_b + l * d;
+    wa.b_ff1 = w.b_ff1 + l * F;
+    wa.b_ff2 = w.b_ff2 + l * d;
+    wa.ln_g = wa.last ? w.lnf_g : w.ln1_g + (l + 1) * d;
+    wa.ln_b = wa.last ? w.lnf_b : w.ln1_b + (l + 1) * d;
+    wa.b_qkv = wa.last ? nullptr : w.b_qkv + (l + 1) * 3 * d;
+    CF_LAUNCH(CFDETR_K_FF2, launch_wide_layer(wa, (int)d, (int)F, mt, nullptr, Mq, Mq, s));
+  }
+  // heads: z = final LayerNorm in da; the box perceptron's hidden rows in dqkv, then in d_o
+  if (spread) {
+    a.z = ctx->da;
+    CF_LAUNCH(CFDETR_K_DEC, step(SlimStep::kRelu, w.lnf_g, w.lnf_b, ctx->dqkv, ctx->dslim_box1, w.b_box1));
+  } else {
+    CF_LAUNCH(CFDETR_K_DEC, launch_cast_bf16(ctx->dz, ctx->da, (int)d, ctx->dm_all, Mq, s));
+    CF_LAUNCH(CFDETR_K_DEC, launch_gemm(ctx->da, w.w_box1, w.b_box1, (int)d, (int)d, Epilogue::kBiasRelu, ctx->dqkv, nullptr, true,
+                                        nullptr, Mq, Mq, s, 1.0f, ctx->dslim_box1));
+  }
+  CF_LAUNCH(CFDETR_K_DEC, launch_gemm(ctx->dqkv, w.w_box2, w.b_box2, (int)d, (int)d, Epilogue::kBiasRelu, ctx->d_o, nullptr, true,
+                                      nullptr, Mq, Mq, s, 1.0f, ctx->dslim_box2));
+  CF_LAUNCH(CFDETR_K_DEC, launch_decoder_heads(ctx->da, ctx->d_o, w.w_cls, w.b_cls, w.w_box3, w.b_box3, (int)d, Mq, queries, s));
+  return CFDETR_OK;
+}
+
 // Decoder over the encoded tokens `memory` of B frames (Sec. II-A).  The token side (bf16
 // copy of the tokens, their keys and feature-major values) lives in the encoder's work
 // space, which is idle here; the query side has the decoder's own buffers.
@@ -640,7 +758,8 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
     p.queue_start = dgrid / 8;
     CF_LAUNCH(CFDETR_K_PLAN, launch_plan(ctx->dcu, B, p, s, 0, 0, nullptr, ctx->err_flag));
   }
-  CF_LAUNCH(CFDETR_K_DEC, launch_broadcast_rows(w.query_embed, ctx->dx, Q, d, B, s));
+  if (ctx->dwide_layer == 0)
+    CF_LAUNCH(CFDETR_K_DEC, launch_broadcast_rows(w.query_embed, ctx->dx, Q, d, B, s));
   // The tokens' keys and values for the cross-attention of every layer depend on the tokens
   // and the weights only: one contraction for all layers, ahead of the loop.
   const size_t k_stride = (size_t)cap_m * d, v_stride = (size_t)d * ctx->vt_ld;
@@ -648,6 +767,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
             launch_gemm_kv_layers(ctx->a, w.w_kv, w.b_kv, d, L, ctx->dk_all, k_stride, ctx->dvt_all,
                                   v_stride, ctx->vt_ld, ctx->cu_all, ctx->pcu, B, ctx->m_all, 0,
                                   cap_m, s));
+  if (ctx->dwide_layer != 0) return decode_wide(ctx, B, queries, dblock_q, dgrid, s);
   const char* wqkv = static_cast<const char*>(w.w_qkv);
   const char* wo = static_cast<const char*>(w.w_o);
   const char* wq = static_cast<const char*>(w.w_q);
@@ -1216,16 +1336,24 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
   if (ctx->dgrid[0] < 8 || ctx->dgrid[1] < 8) return fail(ctx, CFDETR_EDEVICE, "cannot size the attention grid");
   ctx->dvt_ld = (int)(Bm * ((Q + 63) & ~uint64_t(63)) + 64);
   Carver cv;
-  const uint64_t o_x = cv.take(Mq * d * 4), o_a = cv.take(Mq * d * 2), o_qkv = cv.take(Mq * 3 * d * 2);
-  const uint64_t o_o = cv.take(Mq * d * 2), o_h = cv.take(Mq * std::max(F, d) * 2);
+  // widths 256 and 384: residual rows as blocks, whole tiles of 32, 64 and 96 rows
+  const bool wide = wide_layer_supported((int)d, (int)F, true, Mq);
+  const uint64_t x_bytes = (wide ? (Mq + 191) / 192 * 192 : Mq) * d * 4;
+  const uint64_t o_x = cv.take(x_bytes), o_x2 = cv.take(wide ? x_bytes : 0), o_a = cv.take(Mq * d * 2);
+  const uint64_t o_qkv = cv.take(Mq * 3 * d * 2);
+  const uint64_t o_o = cv.take(Mq * d * 2), o_h = cv.take((Mq + 31) * std::max(F, d) * 2);
+  const uint64_t o_vtpos = cv.take(wide ? Mq * 4 : 0);
+  const uint64_t wide_bytes = wide ? wide_layer_packed_bytes((int)d, (int)F, false) : 0;
+  const uint64_t o_wide = cv.take(wide_bytes * w->n_layers);
+  const uint64_t o_whead = cv.take(wide ? wide_layer_packed_bytes((int)d, (int)F, true) : 0);
   const uint64_t o_vt = cv.take(d * (uint64_t)ctx->dvt_ld * 2);
   const uint64_t o_cu = cv.take((Bm + 1) * 4), o_cua = cv.take((Bm + 1) * 4), o_m = cv.take(4);
   const uint64_t o_pcu = cv.take((Bm + 1) * 4), o_items = cv.take((uint64_t)ctx->dcap8 * 8 * 16);
   const uint64_t o_q = cv.take((uint64_t)w->n_layers * 16 * 4);
-  const bool fused = layer_tail_supported((int)d, (int)F, true) && gemm_residual_ln_supported((int)d, true);
+  const bool fused = !wide && layer_tail_supported((int)d, (int)F, true) && gemm_residual_ln_supported((int)d, true);
   const uint64_t tail_bytes = fused ? layer_tail_packed_bytes((int)d, (int)F) : 0;
   const uint64_t o_tail = cv.take(tail_bytes * w->n_layers);
-  const uint64_t o_head = cv.take(fused ? 3 * d * d * 2 : 0), o_z = cv.take(fused ? Mq * d * 4 : 0);
+  const uint64_t o_head = cv.take(fused ? 3 * d * d * 2 : 0), o_z = cv.take(fused || wide ? Mq * d * 4 : 0);
   const uint64_t o_mid = cv.take(fused ? 2 * d * d * 2 * w->n_layers : 0);
   const bool slim = !fused && few_rows_supported((int)d, (int)d) && few_rows_supported((int)F, (int)F);
   struct Slim {
@@ -1240,14 +1368,22 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
              {&ctx->dslim_q, w->w_q, L * d, d, 0},         {&ctx->dslim_o2, w->w_o2, L * d, d, 0},
              {&ctx->dslim_ff1, w->w_ff1, L * F, d, 0},     {&ctx->dslim_ff2, w->w_ff2, L * d, F, 0},
              {&ctx->dslim_box1, w->w_box1, d, d, 0},       {&ctx->dslim_box2, w->w_box2, d, d, 0}};
-    for (Slim& m : slims) m.at = cv.take(slim_packed_bytes(m.N, m.K));
+  } else if (wide) {
+    // the matrices between the two attentions
+    const uint64_t L = w->n_layers;
+    slims = {{&ctx->dslim_o, w->w_o, L * d, d, 0}, {&ctx->dslim_q, w->w_q, L * d, d, 0}};
   }
+  for (Slim& m : slims) m.at = cv.take(slim_packed_bytes(m.N, m.K));
   const uint64_t k_bytes = (uint64_t)c.max_tokens_total * d * 2, v_bytes = d * (uint64_t)ctx->vt_ld * 2;
   const uint64_t o_kall = cv.take(k_bytes * w->n_layers), o_vall = cv.take(v_bytes * w->n_layers);
   hipError_t e = hipMalloc(&ctx->dec_arena, cv.off);
   if (e != hipSuccess) return fail(ctx, CFDETR_ENOMEM, "hipMalloc of the decoder work space");
   char* base = static_cast<char*>(ctx->dec_arena);
   ctx->dx = reinterpret_cast<float*>(base + o_x);
+  ctx->dx2 = reinterpret_cast<float*>(base + o_x2);
+  ctx->dvt_pos = reinterpret_cast<int32_t*>(base + o_vtpos);
+  ctx->dwide_packed = base + o_wide;
+  ctx->dwide_head = base + o_whead;
   ctx->da = base + o_a;
   ctx->dqkv = base + o_qkv;
   ctx->d_o = base + o_o;
@@ -1284,6 +1420,14 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
     *m.where = base + m.at;
     if (e == hipSuccess) e = launch_slim_pack(m.w, m.N, (int)m.K, *m.where, nullptr);
   }
+  for (int l = 0; l < w->n_layers && e == hipSuccess && wide; ++l)
+    e = launch_wide_pack(
+        static_cast<const char*>(w->w_o2) + (size_t)l * d * d * 2,
+        static_cast<const char*>(w->w_ff1) + (size_t)l * F * d * 2,
+        static_cast<const char*>(w->w_ff2) + (size_t)l * d * F * 2,
+        l + 1 < w->n_layers ? static_cast<const char*>(w->w_qkv) + (size_t)(l + 1) * 3 * d * d * 2 : nullptr,
+        (int)d, (int)F, ctx->dwide_packed + (size_t)l * wide_bytes, nullptr);
+  if (e == hipSuccess && wide) e = launch_wide_pack(nullptr, nullptr, nullptr, w->w_qkv, (int)d, (int)F, ctx->dwide_head, nullptr);
   if (e == hipSuccess && fused) e = launch_layer_head_pack(w->w_qkv, (int)d, ctx->dhead_packed, nullptr);
   for (int l = 0; l < w->n_layers && e == hipSuccess && fused; ++l)
     e = launch_layer_mid_pack(static_cast<const char*>(w->w_o) + (size_t)l * d * d * 2,
@@ -1298,6 +1442,7 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
   }
   ctx->dw = *w;
   ctx->dtail_packed_layer = tail_bytes;
+  ctx->dwide_layer = wide_bytes;
   ctx->has_dec = true;
   return CFDETR_OK;
 }

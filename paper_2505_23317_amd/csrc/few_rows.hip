@@ -419,7 +419,7 @@ hipError_t launch_slim_pack(const void* W, uint64_t N, int K, void* packed, hipS
 
 hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int rows, const int32_t* m_ptr, int m_host,
                        int m_capacity, hipStream_t s) {
-  if (!(d == 384 && few_rows_supported(F, F)) && !(d == 256 && step == SlimStep::kOutQuery)) return hipErrorInvalidValue;
+  if (step == SlimStep::kOutQuery ? d != 256 && d != 384 : d != 384 || !few_rows_supported(F, F)) return hipErrorInvalidValue;
   SlimArgs p{};
   p.rows = static_cast<const bf16_t*>(a.rows);
   p.x0 = a.x0;

@@ -246,6 +246,7 @@ struct WideLayerArgs {
   const void* packed;   // launch_wide_pack's
   const float *b_o, *ln2_g, *ln2_b, *b_ff1, *b_ff2;
   const float* x0;      // the embedded rows, which that first launch reads
+  int x0_rows;          // x0 has that many rows, over and over (0: a row for each)
   float* resid;         // residual blocks (wide_row.h) that it writes, rows up to a multiple of 192
   const float *ln_g, *ln_b;
   float eps;

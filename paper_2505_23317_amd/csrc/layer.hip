@@ -19,7 +19,8 @@ struct WideArgs {
   uint32_t stream;               // bytes of one of them
   const float *b_o, *ln2_g, *ln2_b, *b1, *b2;
   int F;
-  const float* x0;           // kHead: the rows as the embedding left them
+  const float* x0;           // kHead: the rows as the embedding left them, or x0_rows rows over and over
+  int x0_rows;
   float* x;                  // residual blocks (wide_row.h)
   const float *ln_g, *ln_b;
   float eps;
@@ -183,6 +184,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
   unsigned char* const xw = reinterpret_cast<unsigned char*>(p.x) + (size_t)(m0 >> 5) * (D * 128) + wave * (NT * 4096);
   f32x16 acc[NT][MT];
   u32x8 hi[NT][MT];
+  int row0[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    row0[i] = min(m0 + i * 32 + l32, M - 1);
+    if (kKind == kHead && p.x0_rows > 0) row0[i] %= p.x0_rows;
+  }
 #pragma unroll
   for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -191,7 +198,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
       for (int i = 0; i < MT; ++i) {
         const float4 v =
             kKind == kHead
-                ? *reinterpret_cast<const float4*>(p.x0 + (size_t)min(m0 + i * 32 + l32, M - 1) * D + c0 + j * 32 + 8 * q + 4 * g)
+                ? *reinterpret_cast<const float4*>(p.x0 + (size_t)row0[i] * D + c0 + j * 32 + 8 * q + 4 * g)
                 : *reinterpret_cast<const float4*>(xw + i * (D * 128) + j * 4096 + q * 1024 + voff);
         acc[j][i][4 * q] = v.x;
         acc[j][i][4 * q + 1] = v.y;
@@ -680,6 +687,7 @@ hipError_t launch_wide_layer(const WideLayerArgs& a, int d, int F, int mt, const
   p.b2 = a.b_ff2;
   p.F = F;
   p.x0 = a.x0;
+  p.x0_rows = a.x0_rows;
   p.x = a.resid;
   p.ln_g = a.ln_g;
   p.ln_b = a.ln_b;
