@@ -429,6 +429,51 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
     }
     return CFDETR_OK;
   }
+  if (small_layer_supported(d, F, bf)) {
+    // widths 64 and 128: the same two kernels a layer, on rows and the caller's matrices
+    const size_t dd = (size_t)d * d * 2, df = (size_t)d * F * 2;
+    auto at = [](const void* base, size_t bytes) { return static_cast<const void*>(static_cast<const char*>(base) + bytes); };
+    SmallLayerArgs a{};
+    a.eps = eps;
+    a.x = ctx->x;
+    a.out = y0;
+    a.out2 = y1;
+    a.split_row = split_row;
+    a.q_scale = attention_q_scale(d / c.n_heads);
+    a.qk = ctx->qkv;
+    a.vt = ctx->vt;
+    a.vt_ld = ctx->vt_ld;
+    a.vt_pos = ctx->vt_pos;
+    a.cu = cu_all;
+    a.pcu = ctx->pcu;
+    a.nseq = nseq;
+    a.w_qkv = w.w_qkv;
+    a.b_qkv = w.b_qkv;
+    a.ln_g = w.ln1_g;
+    a.ln_b = w.ln1_b;
+    CF_LAUNCH(CFDETR_K_QKV, launch_small_layer(a, d, F, m_ptr, 0, m_cap, s));
+    a.O = ctx->o;
+    for (size_t l = 0; l < (size_t)c.n_layers; ++l) {
+      CF_LAUNCH(CFDETR_K_ATTN,
+                launch_attention(ctx->qkv, ctx->vt, ctx->vt_ld, ctx->o, d, c.n_heads, ctx->items, ctx->cap8, ctx->queue_heads + 8 * l,
+                                 shape.attn_grid, shape.block_q, bf, kv_len, s));
+      const bool last = l + 1 == (size_t)c.n_layers;
+      a.w_o = at(w.w_o, l * dd);
+      a.w_ff1 = at(w.w_ff1, l * df);
+      a.w_ff2 = at(w.w_ff2, l * df);
+      a.w_qkv = last ? nullptr : at(w.w_qkv, (l + 1) * 3 * dd);
+      a.b_o = w.b_o + l * d;
+      a.ln2_g = w.ln2_g + l * d;
+      a.ln2_b = w.ln2_b + l * d;
+      a.b_ff1 = w.b_ff1 + l * F;
+      a.b_ff2 = w.b_ff2 + l * d;
+      a.ln_g = last ? w.lnf_g : w.ln1_g + (l + 1) * d;
+      a.ln_b = last ? w.lnf_b : w.ln1_b + (l + 1) * d;
+      a.b_qkv = last ? nullptr : w.b_qkv + (l + 1) * 3 * d;
+      CF_LAUNCH(CFDETR_K_FF2, launch_small_layer(a, d, F, m_ptr, 0, m_cap, s));
+    }
+    return CFDETR_OK;
+  }
   for (int l = 0; l < c.n_layers; ++l) {
     const char* wqkv = static_cast<const char*>(w.w_qkv) + (size_t)l * 3 * d * d * es;
     const char* wo = static_cast<const char*>(w.w_o) + (size_t)l * d * d * es;

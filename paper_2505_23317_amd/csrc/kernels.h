@@ -279,6 +279,27 @@ bool few_rows_supported(int N, int K);
 uint64_t slim_packed_bytes(uint64_t N, uint64_t K);
 hipError_t launch_slim_pack(const void* W, uint64_t N, int K, void* packed, hipStream_t s);
 
+// The same for widths 64 and 128 (small_layer.hip), on residual rows [M, d] and the caller's matrices: O null for
+// the launch ahead of the first layer (LayerNorm of x and q/k/v; it writes vt_pos, which the others
+// read), w_qkv null for the last layer, which ends in the final LayerNorm.
+struct SmallLayerArgs {
+  const void *O, *w_o, *w_ff1, *w_ff2, *w_qkv;
+  const float *b_o, *ln2_g, *ln2_b, *b_ff1, *b_ff2, *ln_g, *ln_b, *b_qkv;
+  float eps;
+  float* x;
+  float *out, *out2;
+  int split_row;
+  float q_scale;
+  void *qk, *vt;
+  int vt_ld;
+  int32_t* vt_pos;
+  const int32_t *cu, *pcu;
+  int nseq;
+};
+bool small_layer_supported(int d, int F, bool use_bf16);
+hipError_t launch_small_layer(const SmallLayerArgs& a, int d, int F, const int32_t* m_ptr, int m_host, int m_capacity,
+                              hipStream_t s);
+
 // A step of a layer of width 384 where there are few rows, with the results of
 // wide_layer_kernel and on the same residual blocks (few_rows.hip):
 //   kFirstQkv   LayerNorm of x0, and q/k/v: that . W2^T + bias2; writes x and vt_pos, which the others read
