@@ -56,7 +56,7 @@ constexpr int kActNone = 0, kActGelu = 1, kActRelu = 2;
 template <typename TAct, int kAct>
 struct EpiAct;
 
-// out = act((v + bias) * scale) in bf16
+// out = act(v + bias) in bf16, without an activation (v + bias) * scale
 template <int kAct>
 struct EpiAct<bf16_t, kAct> {
   const float* bias;
@@ -64,10 +64,9 @@ struct EpiAct<bf16_t, kAct> {
   int ldc;
   float scale;
   __device__ __forceinline__ float act(float r) const {
-    r *= scale;
     if (kAct == kActGelu) return gelu_fast(r);
     if (kAct == kActRelu) return fmaxf(r, 0.f);
-    return r;
+    return r * scale;
   }
   static constexpr bool kExtra = kNoExtra;
   __device__ __forceinline__ int32_t row_info(int) const { return 0; }
@@ -1019,6 +1018,226 @@ __global__ __launch_bounds__(64 * NWM * NWN, WPE) void gemm_bf16_persist_kernel(
   }
 #undef CFDETR_SET_TILE
 #undef CFDETR_ISSUE_SLAB
+}
+
+// ---------------------------------------------------------------------------
+// The same with the weights packed (launch_slim_pack): the form of the layer matrices wherever there are
+// more rows than few_rows.h is for.  Four wavefronts do 32 MT rows x 256 columns, each all rows by 64
+// columns, so no two share weights: those skip the LDS and come as whole operands into a ring of 16 or 32 KB
+// a workgroup, R k-steps ahead.  Only rows go through the LDS, in slabs of 64 elements and two places;
+// two workgroups a CU.  What bounds it on a full chip: the matrix units' clock under load (1,620 to 1,860
+// TFLOP/s with nothing but MFMAs, 2,450 on zeros) and, outside the main loop, the epilogue's vector work
+// (FF1: a quarter of the time) that other wavefronts' MFMAs cover only in part.
+//  - Between two MFMAs stands at most one other thing (an operand read, a load), and addresses are added up
+//    once a slab: 25 scalar instructions a k-step cost 90 clocks of its 256, the reads of a k-step ahead of
+//    all its MFMAs 250 of 770.
+//  - One barrier a slab, before its last k-step: its operands are in registers by then, so its place is free
+//    for the slab after the next, and the next slab's first operands are read under the last k-step's MFMAs.
+//  - Slabs and weights run on into the workgroup's next tile; its first two slabs are waited for before the
+//    epilogue's first store, behind which a wait in the (in-order) counter would last until that is done.
+//  - An epilogue with addends (the residual rows) asks for them a pass ahead.
+// us, tiles with the weights through the LDS (gemm_bf16_persist_kernel) / this, rows x N x K: 3,300 x 3072 x
+// 768 27.5 / 23.8, 17,500 x 3072 x 768 107 / 90, 17,500 x 2304 x 768 70 / 58, 17,500 x 768 x 3072 93 / 81,
+// 17,500 x 768 x 768 37.6 / 32.2, 23,000 x 768 x 3072 132 / 103, 6,100 x 3072 x 384 23.5 / 21.4.
+// ---------------------------------------------------------------------------
+template <int MT, typename EP>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_packed_kernel(const bf16_t* __restrict__ A, const unsigned char* W, int N, int K,
+                                                                  EP ep, const int32_t* __restrict__ m_ptr, int m_host) {
+  constexpr int R = MT <= 3 ? 8 : 4, BM = 32 * MT, kSlab = BM * 128, STRIDE = 144;
+  static_assert(EP::kStageElem == 2 || EP::kStageElem == 4, "staged epilogues only");
+  typedef const __attribute__((address_space(1))) unsigned char* gptr;
+  typedef const __attribute__((address_space(1))) bf16x8* goper;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_packed[];   // two slabs, staging rows, bias
+  const int M = m_ptr ? *m_ptr : m_host;
+  const int parts = N >> 8, total = ((M + BM - 1) / BM) * parts;
+  int v = blockIdx.x;
+  if (v >= total) return;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nk = K >> 6;
+  const uint32_t voff = lane * 16, lds0 = (uint32_t)(uintptr_t)smem_packed;
+  unsigned char* stg = smem_packed + 2 * kSlab + wave * (32 * STRIDE);
+  float* sbias = reinterpret_cast<float*>(smem_packed + 2 * kSlab + 4 * 32 * STRIDE) + wave * 64;
+
+  int m0, n0, m0_next = 0, n0_next = 0;
+  auto tile = [&](int at, int& m, int& n) {
+    const int pid = xcd_tile_order(at, total), r = pid / parts;
+    m = r * BM;
+    n = (pid - r * parts) * 256;
+  };
+  tile(v, m0, n0);
+  // loads of a slab: 8 rows of 128 bytes an instruction, MT of them a wavefront, chunks XORed by the row
+  uint32_t row[MT];
+  auto set_rows = [&](int m) {
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+      const int r = (wave * MT + j) * 8 + (lane >> 3);
+      row[j] = (uint32_t)min(m + r, M - 1) * (uint32_t)K * 2u + (((lane & 7) ^ lds_row_key<128>(r)) << 4);
+    }
+  };
+  set_rows(m0);
+  const unsigned char* rows = reinterpret_cast<const unsigned char*>(A);   // of the slab to be asked for next
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+#pragma unroll
+    for (int j = 0; j < MT; ++j) dma16_untracked_s(rows, row[j], lds0 + s * kSlab + (wave * MT + j) * 1024);
+    rows += 128;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const size_t column = (size_t)K * 64;   // bytes of 32 columns
+  auto weights_of = [&](int n) { return (gptr)W + ((size_t)(n >> 5) + wave * 2) * column; };
+  gptr w_next = weights_of(n0), wq = w_next;
+  bf16x8 wr[R][2];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    gptr q = wq + k * 1024, q1 = q + column;
+    asm volatile("" : "+s"(q), "+s"(q1));   // scalar bases: no vector arithmetic
+    wr[k][0] = *reinterpret_cast<goper>(q + voff);
+    wr[k][1] = *reinterpret_cast<goper>(q1 + voff);
+  }
+  wq += R * 1024;
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * R + MT) : "memory");   // slab 0
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" : : : "memory");
+  uint32_t at = 0;     // place of the slab in work
+  bool first = true;   // the workgroup's first tile
+  uint32_t ao[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) ao[k] = l32 * 128 + (((2 * k + g) ^ lds_row_key<128>(l32)) << 4);
+
+  for (;;) {
+    const int v_next = v + (int)gridDim.x;
+    const bool more = v_next < total;
+    if (more) {
+      tile(v_next, m0_next, n0_next);
+      w_next = weights_of(n0_next);
+    }
+    const float bias = ep.bias[n0 + wave * 64 + lane];
+    f32x16 acc[MT][2];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    bf16x8 a[2][MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) a[0][i] = *reinterpret_cast<const bf16x8*>(smem_packed + at + ao[0] + i * 4096);
+    __builtin_amdgcn_sched_barrier(0);
+    auto slab = [&](int it, auto half_tag) {
+      constexpr int r0 = R == 8 ? 4 * decltype(half_tag)::value : 0;   // ring places
+      const uint32_t other = at ^ (uint32_t)kSlab, dst = lds0 + at + wave * MT * 1024;
+      if (it == nk - R / 4) wq = w_next;
+      gptr q = wq, q1 = wq + column;
+      asm volatile("" : "+s"(q), "+s"(q1));
+      wq += 4096;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (k == 3) {
+          // The slab behind this one has arrived: younger than its loads are the weights of four k-steps.
+          // (A tile's second one was waited for before the last epilogue.)
+          if (it > 0 || first) asm volatile("s_waitcnt vmcnt(8)" : : : "memory");
+          __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this one's operands are in registers
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" : : : "memory");
+          if (it == nk - 2) {   // on to the next tile, or once more to this one's: in bounds, and not read
+            if (more) set_rows(m0_next);
+            rows = reinterpret_cast<const unsigned char*>(A);
+          }
+        }
+        const unsigned char* p = smem_packed + (k == 3 ? other : at) + ao[(k + 1) & 3];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          a[(k + 1) & 1][i] = *reinterpret_cast<const bf16x8*>(p + i * 4096);
+          __builtin_amdgcn_sched_barrier(0);
+          acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[r0 + k][0], a[k & 1][i], acc[i][0], 0, 0, 0);
+          if (k == 3) dma16_untracked_s(rows, row[i], dst + i * 1024);
+          __builtin_amdgcn_sched_barrier(0);
+          acc[i][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[r0 + k][1], a[k & 1][i], acc[i][1], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        wr[r0 + k][0] = *reinterpret_cast<goper>(q + k * 1024 + voff);
+        wr[r0 + k][1] = *reinterpret_cast<goper>(q1 + k * 1024 + voff);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      rows += 128;
+      at = other;
+    };
+#pragma nounroll
+    for (int it = 0; it < nk; it += 2) {
+      slab(it, std::integral_constant<int, 0>{});
+      slab(it + 1, std::integral_constant<int, 1>{});
+    }
+
+    // epilogue, as in gemm_bf16_persist_kernel: passes of 32 rows x 128 bytes through the wavefront's staging rows
+    constexpr int ES = EP::kStageElem, CPP = 128 / ES, NPASS = 64 / CPP, P = MT * NPASS;
+    const int nw0 = n0 + wave * 64;
+    sbias[lane] = bias;
+    if (ep.staged(nw0)) {
+      const int crow = lane >> 3, cchunk = lane & 7;
+      float4 xin[2][4];
+      auto ask = [&](int p) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          xin[p & 1][t] = ep.extra4(min(m0 + p / NPASS * 32 + t * 8 + crow, M - 1), nw0 + p % NPASS * CPP + cchunk * (16 / ES), 0);
+      };
+      if (EP::kExtra) ask(0);
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const int i = p / NPASS, ps = p % NPASS, mb = m0 + i * 32, nc0 = nw0 + ps * CPP;
+        if (EP::kExtra && p + 1 < P) ask(p + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int jj = 0; jj < CPP / 32; ++jj) {
+          const int j = ps * (CPP / 32) + jj;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int nl = jj * 32 + 8 * q + 4 * g;
+            const float v4[4] = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            ep.stage4(stg + l32 * STRIDE + nl * ES, nc0 + nl, v4, *reinterpret_cast<const float4*>(sbias + ps * CPP + nl));
+          }
+        }
+        if (p == 0)   // the next tile's second slab: younger are two weights and the addends of two passes
+          asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 + (EP::kExtra ? 8 : 0)) : "memory");
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int r = t * 8 + crow;
+          const uint4 dd = *reinterpret_cast<const uint4*>(stg + r * STRIDE + cchunk * 16);
+          if (mb + r < M) ep.copy16(mb + r, nc0 + cchunk * (16 / ES), dd, xin[p & 1][t]);
+        }
+      }
+    } else {
+      // columns that do not leave as rows: per-element stores
+      int32_t info[MT];
+#pragma unroll
+      for (int i = 0; i < MT; ++i) info[i] = ep.row_info(min(m0 + i * 32 + l32, M - 1));
+      asm volatile("s_waitcnt vmcnt(2)" : : : "memory");
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const int m = m0 + i * 32 + l32;
+        if (m < M && ep.row_ok(info[i])) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int nl = j * 32 + 8 * q + 4 * g;
+              const float v4[4] = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+              ep.store4(m, nw0 + nl, v4, *reinterpret_cast<const float4*>(sbias + nl), ep.extra4(m, nw0 + nl, info[i]), info[i]);
+            }
+        }
+      }
+    }
+    if (!more) break;
+    __builtin_amdgcn_sched_barrier(0);
+    v = v_next;
+    m0 = m0_next;
+    n0 = n0_next;
+    first = false;
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): nothing is on its way into the LDS any more
 }
 
 // Sum over each group of 16 consecutive lanes, delivered to all 16 (quad swaps, then the
@@ -2356,7 +2575,44 @@ hipError_t launch_few(const bf16_t* a, const void* packed, int N, int K, const E
   return hipSuccess;
 }
 
-// Tile choice by problem size: 256x256 (8 wavefronts, 128x64 each) or 192x256 (96x64
+// Launch of the form with packed weights, 64, 96 or 128 rows a tile.
+template <int MT, typename EP>
+hipError_t launch_packed_tile(const bf16_t* a, const void* packed, int N, int K, const EP& ep, const int32_t* m_ptr, int m_host,
+                              int m_capacity, hipStream_t s) {
+  constexpr auto kern = gemm_bf16_packed_kernel<MT, EP>;
+  constexpr size_t lds = 2 * 32 * MT * 128 + 4 * 32 * 144 + 4 * 256;
+  static_assert(lds <= 80 * 1024, "two workgroups a CU");
+  static DeviceOnce configured;
+  hipError_t e = allow_lds(kern, lds, &configured);
+  if (e != hipSuccess) return e;
+  const long tiles = (long)((m_capacity + 32 * MT - 1) / (32 * MT)) * (N / 256);
+  long grid = ((long)cu_count() * 2) & ~7L;
+  if (grid < 8) grid = 8;
+  if (tiles < grid) grid = tiles;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, s, a, static_cast<const unsigned char*>(packed), N, K, ep, m_ptr, m_host);
+  return hipSuccess;
+}
+
+// Rows of a tile: what the CU with the most tiles takes, and what all of them take together (the clock
+// under load), per tile 61 : 78 : 100 for 64, 96 and 128 rows.  us for 64 / 96 / 128 rows: 4,200 x 768 x 3072
+// 28.0 / 31.8 / 39.6, 8,700 x 768 x 3072 50.3 / 59.4 / 45.5, 12,150 x 768 x 3072 73.7 / 62.2 / 76.5,
+// 17,500 x 2304 x 768 71.3 / 61.6 / 57.9.
+template <typename EP>
+hipError_t launch_packed(const bf16_t* a, const void* packed, int N, int K, const EP& ep, const int32_t* m_ptr, int m_host,
+                         int m_capacity, int m, hipStream_t s) {
+  const long cus = cu_count();
+  auto cost = [&](int mt, int weight) {
+    const long tiles = (long)((m + 32 * mt - 1) / (32 * mt)) * (N / 256);
+    return weight * (14 * ((tiles + cus - 1) / cus) * cus + 10 * tiles);
+  };
+  const long c2 = cost(2, 61), c3 = cost(3, 78), c4 = cost(4, 100);
+  if (c2 <= c3 && c2 <= c4) return launch_packed_tile<2>(a, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+  if (c3 <= c4) return launch_packed_tile<3>(a, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+  return launch_packed_tile<4>(a, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+}
+
+// Contractions without packed weights or of a width that is no multiple of 256, over many rows: 256x256
+// (8 wavefronts, 128x64 each) or 192x256 (96x64
 // each) for wide outputs over many rows, 192x128 or 128x128 (4 wavefronts, 96x64 or 64x64
 // each, two workgroups per CU) while that still yields a workgroup per CU, else 64x64
 // (2 wavefronts, 32x64 each).  All are the staying-workgroup kernel.  The rows that count
@@ -2386,23 +2642,23 @@ hipError_t launch_direct(const void* A, const void* W, int N, int K, const EP& e
   const long rounds192 = (tiles192 + cus - 1) / cus, rounds192n = (tiles192n + 2 * cus - 1) / (2 * cus);
   const long t128 = 100 * rounds128, t192n = 150 * rounds192n;
   const bool narrow_ok = N % 128 == 0 && tiles128 >= cus;
-  // Few rows: 32 or 64 rows a workgroup as long as no CU gets two, and twice as many where K is
-  // so long that a tile's chain of slabs counts and not the number of tiles.  In us, 64 x 64 or
-  // 128 x 128 tiles / 32 rows / 64 rows, N x K = 768 x 3072: 1024 rows 26.7 / 14.3 / 18.8, 2048
-  // rows 36.3 / 28.9 / 21.9, 4800 rows 43.7 / 53.9 / 39.1; 768 x 768: 1024 rows 10.6 / 7.1 / 9.5,
-  // 2048 rows 12.5 / 11.7 / 9.8, 3072 rows 14.1 / 16.4 / 15.2; 2304 x 768: 256 rows 8.6 / 6.5 /
-  // 8.1, 512 rows 10.1 / 10.8 / 8.6, 1024 rows 11.8 / 14.1 / 12.8; 384 x 384: 256 rows 6.0 / 4.4
-  // / 5.8, 2400 rows 6.1 / 5.1 / 6.1.
+  // Few rows: 32 or 64 rows a workgroup as long as no CU gets two, then tiles of 64 rows and more by 256
+  // columns.  In us, 32 rows / 64 rows / those tiles, N x K = 768 x 3072: 1000 rows 12.9 / 15.5 / 24.2, 2000
+  // rows 22.7 / 16.9 / 24.6, 2700 rows 31.6 / 30.2 / 25.4; 768 x 768: 1000 rows 5.8 / 7.4 / 9.2, 2000 rows
+  // 9.0 / 7.9 / 9.7, 2700 rows 11.3 / 12.2 / 10.1; 2304 x 768: 257 rows 5.3 / 6.4 / 8.4, 700 rows 8.1 / 7.1 /
+  // 9.1, 1000 rows - / 10.6 / 9.2; 3072 x 768: 400 rows 8.3 / 7.0 / 10.7, 700 rows - / 10.9 / 12.3, 1000 rows
+  // - / 12.0 / 12.5.  Where those do not fit (a width of 384 over K >= 2048) 64 rows up to two a CU: 768 x
+  // 3072, 4800 rows 39.1, and 43.7 with the weights through the LDS.
   if (packed && few_rows_supported(N, K)) {
     const long few32 = (long)((m + 31) / 32) * (N / 128), few64 = (long)((m + 63) / 64) * (N / 128);
     if (few32 <= cus) return launch_few<1>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
-    if (few64 <= cus || (K >= 2048 && few64 <= 2 * cus))
+    if (few64 <= cus || (N % 256 != 0 && K >= 2048 && few64 <= 2 * cus))
       return launch_few<2>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
   }
+  if (packed && N % 256 == 0 && K % 128 == 0)
+    return launch_packed(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, m, s);
   // A deeper ring (3 or 4 buffers, also with slabs of 32) measured no faster for these tiles: the
-  // latency of the loads is not what bounds their main loops.  Nor is LDS traffic (weights straight
-  // from memory into registers: 106 -> 109 us at N = 3072, K = 768): matrix and vector phases of the
-  // wavefronts of a SIMD alternate, with both units busy 2.7 % of the time.
+  // latency of the loads is not what bounds their main loops.
   if (N % 256 == 0 && m >= 8192) {
     const long t256 = 180 * rounds256, t192 = 145 * rounds192;
     const long tn = t192n < t128 ? t192n : t128;
