@@ -11,7 +11,7 @@ namespace cfdetr {
 
 namespace {
 
-constexpr int kRingMax = 24;    // most weight blocks of 1 KB a wavefront holds in registers
+constexpr int kRingMax = 16;    // most weight blocks of 1 KB a wavefront holds in registers
 
 struct WideArgs {
   const bf16_t* O;
@@ -79,7 +79,7 @@ constexpr int kHead = 0, kMid = 1, kLast = 2;
 // pair against 32), and the CU's vector-memory path: 64 B/clk for 3.5 MB of weights per
 // workgroup, which is what taller tiles save.  Measured per layer at D = 384, F = 1536
 // against q/k/v, out-projection, two LayerNorms and the two feed-forward matrices as kernels
-// of their own: 22,400 rows 168 -> 109 us, 64,000 rows 430 -> 260 us, 3,520 rows 54 -> 43 us,
+// of their own: 22,400 rows 168 -> 99 us, 64,000 rows 430 -> 260 us, 3,520 rows 54 -> 43 us,
 // 920 rows 45 -> 42 us (few_rows.hip takes those).  Of that the residual's two parts are 1 % of a pass
 // (summed on top of it: eight frames of up to 8,000 tokens 8,262 us, so 8,349); the whole residual
 // in memory would be 4 %.
@@ -94,10 +94,11 @@ constexpr int kHead = 0, kMid = 1, kLast = 2;
 template <int D, int NW, int MT, int kKind>
 __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer_kernel(WideArgs p) {
   using L = WideLds<D, NW, MT>;
-  // what the registers of one or two workgroups per CU hold
-  constexpr int kRing = NW == 8 ? 16 : MT > 2 ? 24 : 12;
+  // (96 rows of width 384, alone on a CU: a ring of 12 leaves registers for the residual's high parts.
+  // 22,400 rows 105 us a layer with a ring of 24 and those in memory, 100 with 12 and 99 like this.)
+  constexpr int kRing = NW == 8 ? 16 : 12;
   constexpr int kFC = L::kFC, kThreads = 64 * NW;
-  constexpr bool kKeep = NW == 8 || MT == 1;
+  constexpr bool kKeep = NW == 8 || MT == 1 || (MT == 3 && kKind != kLast);
   constexpr int NT = D / (32 * NW), KS = D / 16, BM = 32 * MT, ROWB = D * 2, HROWB = kFC * 2;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* const sA = smem;
