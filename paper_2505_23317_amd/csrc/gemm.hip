@@ -2241,9 +2241,9 @@ constexpr size_t gather_lds_bytes() {
 // LDS rows, contract a quarter of K each for the same tile; the quarters are added in their
 // order by all forms, so that a token has the same bits in each.  Launches before / after:
 // 16 tokens of width 64 23.4 / 14.4 us, up to 80 of 16 x 16 pixels 9.8 / 8.0 us, 920 tokens of width
-// 384 37.1 / 20.8 us.
+// 384 37.1 / 20.8 us.  A group of one wavefront (32 x 32 tiles) meets no barrier: it reads what it wrote.
 template <int BM, int BN, int NWM, int NWN, int KS, typename TPix>
-__global__ __launch_bounds__(64 * NWM * NWN * KS, KS == 4 ? 4 : BM == 128 ? 2 : 1) void gemm_bf16_gather_kernel(
+__global__ __launch_bounds__(64 * NWM * NWN * KS, KS == 4 ? (BM == 64 ? 4 : BN == 64 ? 2 : 1) : BM == 128 ? 2 : 1) void gemm_bf16_gather_kernel(
     PatchRows<TPix> al, const bf16_t* __restrict__ W, int N, int K, EpiEmbed ep,
     const int32_t* __restrict__ m_ptr, int m_host) {
   constexpr int THREADS = 64 * NWM * NWN;   // of a group
@@ -2357,7 +2357,8 @@ __global__ __launch_bounds__(64 * NWM * NWN * KS, KS == 4 ? 4 : BM == 128 ? 2 : 
         *reinterpret_cast<uint4*>(qa + PASS_ROWS * j * LDS_LD) = PatchRows<TPix>::as_bf16(ra[OUT_][j]);           \
     _Pragma("unroll") for (int j = 0; j < B_LOADS; ++j)                                                           \
         *reinterpret_cast<u32x4*>(qb + PASS_ROWS * j * LDS_LD) = rb[OUT_][j];                                     \
-    __syncthreads();                                                                                              \
+    if (NWM * NWN > 1) __syncthreads();                                                                           \
+    else asm volatile("" : : : "memory");   /* its own LDS rows: served in order */                               \
   } while (0)
 
   if constexpr (KS == 1) {
@@ -2679,17 +2680,22 @@ template <int BM, int BN, int KS, typename TPix>
 hipError_t launch_gather_tile(const PatchRows<TPix>& al, const bf16_t* w, int N, int K,
                               const EpiEmbed& ep, const int32_t* m_ptr, int m_host,
                               int m_capacity, hipStream_t s) {
-  auto kern = gemm_bf16_gather_kernel<BM, BN, 2, 2, KS, TPix>;
+  constexpr int NWM = BM >= 64 ? 2 : 1, NWN = BN >= 64 ? 2 : 1;
+  auto kern = gemm_bf16_gather_kernel<BM, BN, NWM, NWN, KS, TPix>;
   constexpr size_t lds = gather_lds_bytes<BM, BN, KS>();
   static DeviceOnce configured;
   hipError_t e = allow_lds(kern, lds, &configured);
   if (e != hipSuccess) return e;
   dim3 grid(((m_capacity + BM - 1) / BM) * (N / BN));
-  hipLaunchKernelGGL(kern, grid, dim3(256 * KS), lds, s, al, w, N, K, ep, m_ptr, m_host);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * NWM * NWN * KS), lds, s, al, w, N, K, ep, m_ptr, m_host);
   return hipSuccess;
 }
 
-// 128 x 128 tiles as long as they fill the chip, else 64 x 64.  Four groups of wavefronts share
+// 128 x 128 tiles as long as they fill the chip, else 64 x 64, and 32 x 64 or 32 x 32 as long as no CU
+// gets two: a tile is bound by its operands' way into the CU (64 x 64 of patches of 32 x 32: 1.2 MB, 11 us), which
+// smaller ones spread over more of them.  16 tokens of width 64 14.4 -> 8.6 us, up to 80 of 16 x 16 pixels 8.0 ->
+// 6.0 us, 920 tokens of width 384 20.8 -> 15.6 us.  (Three or four slabs on the way instead of two: 9.2 and 12.3 us
+// for the first, which the compiler's moves between its registers take.)  Four groups of wavefronts share
 // a tile where no CU gets two (a workgroup of 16 wavefronts is slower than four of four: 338 tiles
 // 83 against 64 us) and K has quarters of whole slabs (patches from 16 x 16 on).
 template <typename TPix>
@@ -2700,6 +2706,11 @@ hipError_t launch_gather(const PatchRows<TPix>& al, const void* W, int N, int K,
   const long tiles128 = (long)((m_capacity + 127) / 128) * (N / 128);
   if (N % 128 == 0 && tiles128 >= 256)
     return launch_gather_tile<128, 128, 1>(al, w, N, K, ep, m_ptr, m_host, m_capacity, s);
+  const long tiles32 = (long)((m_capacity + 31) / 32) * (N / 32), tiles32w = (long)((m_capacity + 31) / 32) * (N / 64);
+  if (K % (4 * BK) == 0 && tiles32 <= cu_count())
+    return launch_gather_tile<32, 32, 4>(al, w, N, K, ep, m_ptr, m_host, m_capacity, s);
+  if (K % (4 * BK) == 0 && tiles32w <= cu_count())
+    return launch_gather_tile<32, 64, 4>(al, w, N, K, ep, m_ptr, m_host, m_capacity, s);
   const long tiles64 = (long)((m_capacity + 63) / 64) * (N / 64);
   if (K % (4 * BK) == 0 && tiles64 <= cu_count())
     return launch_gather_tile<64, 64, 4>(al, w, N, K, ep, m_ptr, m_host, m_capacity, s);
@@ -2856,7 +2867,15 @@ hipError_t launch_embed(const EmbedArgs& a, const void* w, const float* bias, in
     const int m_likely = m_ptr ? m_capacity : m_host;
     const long tiles128 = (long)((m_likely + 127) / 128) * (d / 128);
     const long tiles64 = (long)((m_likely + 63) / 64) * (d / 64);
-    if (d % 128 == 0 && tiles128 >= 256)
+    const long tiles32 = (long)((m_likely + 31) / 32) * (d / 32), tiles32w = (long)((m_likely + 31) / 32) * (d / 64);
+    // the smallest tiles as long as no CU gets two: what a tile takes is its operands' way into the CU (64 x 64 with
+    // patches of 32 x 32: 786 KB, 7 us).  400 tokens of 32 x 32 and width 256 13.0 -> 10.5 us, 1,600 of 16 x 16 at most
+    // 6.5 -> 5.9 us, 405 of 64 x 64 and width 768 46.5 -> 42.5 us
+    if (K % 128 == 0 && tiles32 <= cu_count())
+      e = launch_direct_tile<32, 32, 1, 1, 4, 64, 2>(rows, wb, d, K, ep, m_ptr, m_host, m_capacity, s);
+    else if (K % 128 == 0 && tiles32w <= cu_count())
+      e = launch_direct_tile<32, 64, 1, 2, 4, 64, 2>(rows, wb, d, K, ep, m_ptr, m_host, m_capacity, s);
+    else if (d % 128 == 0 && tiles128 >= 256)
       e = launch_direct_tile<128, 128, 2, 2, 2, 64>(rows, wb, d, K, ep, m_ptr, m_host, m_capacity, s);
     else if (d % 128 == 0 && K >= 6144 && tiles64 > 2 * cu_count())
       // patches of 64 x 64 and three rounds of small tiles: one round of 128 x 128 with a deep ring

@@ -55,3 +55,19 @@ def test_bf16_frames_with_large_patches(frames):
     for n in frames[1:]:
         x = _embed(synth.replace(cfg, B=n), w, images[:n])
         assert torch.equal(x[0], few[0]) and torch.isfinite(x).all(), n
+
+
+# 221 tokens a frame: 32 x 32 tiles for one and four frames, 32 x 64 for eight, 64 x 64 for sixteen and forty
+@pytest.mark.parametrize("patch", [16, 32])
+def test_bf16_frames_by_tile(patch):
+    import torch
+
+    cfg = synth.Config("bf16", 40, 13 * patch, 17 * patch, (patch,), 256, 8, 1, 256, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 23)
+    images = synth.bf16_round(np.random.default_rng(10).random((40, 3, cfg.H, cfg.W), dtype=np.float32))
+    few = _embed(synth.replace(cfg, B=1), w, images[:1])
+    ref = np.asarray(O.coarse_encode(images[:1], cfg.patch, w, cfg.heads)[0]).reshape(-1, cfg.d)
+    assert float(np.abs(few[0].cpu().numpy() - ref).max() / np.abs(ref).max()) <= 2.0 ** -8
+    for n in (4, 8, 16, 40):
+        x = _embed(synth.replace(cfg, B=n), w, images[:n])
+        assert torch.equal(x[0], few[0]) and torch.isfinite(x).all(), n
