@@ -127,12 +127,12 @@ def hbm_traffic(cfg_id, family):
 # kernel family -> pattern of its kernel names in the rocprofv3 kernel statistics
 STATS_FAMILY = {
     "attention": r"attention_bf16_kernel",
-    "qkv": r"EpiQkv|layer_head_kernel|wide_layer_kernel<\d+, \d, ., 0>|slim_norm_kernel<384, [01]>",
-    "ffn1": r"EpiAct<unsigned short, (true|1)>|slim_norm_kernel<384, 2>",
-    "out_proj": r"EpiResidual|slim_residual_kernel<384, false>",
-    "ffn2": r"layer_tail_kernel|wide_layer_kernel<\d+, \d, ., [12]>|slim_residual_kernel<384, true>|EpiResidual",
+    "qkv": r"EpiQkv|layer_head_kernel|wide_layer_kernel<\d+, \d, ., 0>|slim_norm_kernel<384, [01]>|small_layer_kernel<\d+, 0>",
+    "ffn1": r"EpiAct<unsigned short, (true|1)>|slim_norm_kernel<384, 3>",
+    "out_proj": r"EpiResidual",
+    "ffn2": r"layer_tail_kernel|wide_layer_kernel<\d+, \d, ., [12]>|slim_residual_kernel|small_layer_kernel<\d+, [12]>|EpiResidual",
     "layernorm": r"layernorm|wide_norm_kernel",
-    "embed": r"EpiEmbed|gemm_bf16_gather_kernel",
+    "embed": r"EpiEmbed|gemm_bf16_(gather|patch)_kernel",
     "gather": r"gather_coarse_kernel",
     "select": r"select_",
 }

@@ -148,8 +148,10 @@ typedef enum {
  * In bf16 it also copies w_qkv, w_o, w_ff1, w_ff2 into the order in which its
  * kernels read them (the weights are read once, here): d_model 256 with d_ffn a
  * multiple of 128 up to 2048, one copy; d_model 384 or 768 with d_ffn a multiple
- * of 384, one for passes of few rows; d_model 384 with d_ffn a multiple of 128 up
- * to 2048, one (more) for the others.  cfdetr_workspace_bytes counts them.
+ * of 384, one (d_model 384: for passes of few rows); d_model 384 with d_ffn a
+ * multiple of 128 up to 2048, one (more) for the others.  With frames in bf16 and
+ * d_model a multiple of 128 also w_embed, of levels whose patches are 16 pixels wide
+ * or more.  cfdetr_workspace_bytes counts them.
  * On failure *out is NULL. */
 CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_weights* w,
                             cfdetr_ctx** out);

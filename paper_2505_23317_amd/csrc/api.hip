@@ -61,6 +61,7 @@ struct cfdetr_ctx {
   uint64_t tail_packed_layer = 0;   // bytes per layer; 0: the shape has no fused kernel
   void* head_packed = nullptr;      // w_qkv of the first layer in the same layout
   void* wide_packed = nullptr;      // the same in layer.hip's order
+  void* embed_packed[kMaxLevels] = {};   // w_embed as gemm_bf16_patch_kernel reads it (frames in bf16)
   uint64_t wide_layer = 0;
   void* wide_head = nullptr;
   float* x_blocks = nullptr;        // and its residual rows
@@ -263,6 +264,7 @@ cfdetr_status embed_level(cfdetr_ctx* ctx, const void* images, int level,
   a.pe_col = ctx->pe_col[level];
   a.out = out;
   a.out2 = out2;
+  a.packed = ctx->embed_packed[level];
   CF_LAUNCH(CFDETR_K_EMBED, launch_embed(a, ctx->w.w_embed[level], ctx->w.b_embed[level],
                                          ctx->cfg.d_model, ctx->bf16, m_ptr, m_host, m_cap, s));
   return CFDETR_OK;
@@ -1049,6 +1051,10 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   const uint64_t Lw = cfg->n_layers;
   const uint64_t o_sq = cv.take(slim ? slim_packed_bytes(Lw * 3 * d, d) : 0), o_so = cv.take(slim ? slim_packed_bytes(Lw * d, d) : 0);
   const uint64_t o_s1 = cv.take(slim ? slim_packed_bytes(Lw * F, d) : 0), o_s2 = cv.take(slim ? slim_packed_bytes(Lw * d, F) : 0);
+  uint64_t o_embed[kMaxLevels] = {};
+  auto embed_k = [&](int l) { return 3 * (uint64_t)p.patch[l] * p.patch[l]; };
+  auto embed_packs = [&](int l) { return c->bf16 && cfg->image_dtype == CFDETR_BF16 && patch_embed_supported((int)d, (int)embed_k(l)); };
+  for (int l = 0; l < cfg->n_levels; ++l) o_embed[l] = cv.take(embed_packs(l) ? slim_packed_bytes(d, embed_k(l)) : 0);
   c->arena_bytes = cv.off;
   e = hipMalloc(&c->arena, c->arena_bytes);
   if (e != hipSuccess) {
@@ -1141,6 +1147,11 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
         (int)d, (int)F, static_cast<char*>(c->wide_packed) + (size_t)l * c->wide_layer, nullptr);
   if (e == hipSuccess && c->wide_layer)
     e = launch_wide_pack(nullptr, nullptr, nullptr, w->w_qkv, (int)d, (int)F, c->wide_head, nullptr);
+  for (int l = 0; l < cfg->n_levels && e == hipSuccess; ++l) {
+    if (!embed_packs(l)) continue;
+    c->embed_packed[l] = base + o_embed[l];
+    e = launch_slim_pack(w->w_embed[l], d, (int)embed_k(l), c->embed_packed[l], nullptr);
+  }
   if (e == hipSuccess && slim) e = launch_slim_pack(w->w_qkv, Lw * 3 * d, (int)d, c->slim_qkv, nullptr);
   if (e == hipSuccess && slim) e = launch_slim_pack(w->w_o, Lw * d, (int)d, c->slim_o, nullptr);
   if (e == hipSuccess && slim) e = launch_slim_pack(w->w_ff1, Lw * F, (int)d, c->slim_ff1, nullptr);

@@ -1240,6 +1240,160 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_packed_kernel(const bf16_t* 
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): nothing is on its way into the LDS any more
 }
 
+// ---------------------------------------------------------------------------
+// Patch embedding with the weights packed (launch_slim_pack), for more tokens than the small tiles of
+// gemm_bf16_direct_kernel are for: 64 rows x 128 columns, two groups of four wavefronts, one for each half of K
+// (the halves that every form adds), a wavefront all rows by 32 columns.  The main loop is that of packed_tiles:
+// weights into a register ring, rows through the LDS in slabs of 64 elements and two places for each group.  At the
+// end a group gives the other half its sums of 32 rows and finishes the other 32.  Two workgroups a CU: what
+// a tile waits for, five loads one behind the other before its first pixel and the position tables behind
+// its last, is as long as the loop for small patches.  Bound by the operands' way into the CU for large ones (a tile of
+// 64 x 64 patches 4.7 MB, 43 us).  128 x 128 tiles with the weights through the LDS / this: 3,072 tokens of 64 x 64
+// and width 768 120 / 117 us, some 4,600 of 32 x 32 there 81 / 49, 51,200 of 16 x 16 and width 384 107 / 71,
+// 12,800 of 32 x 32 there 86 / 64; 64 x 64 tiles / this: 16,000 of 16 x 16 and width 384 54 / 37, some 3,000 and
+// width 256 11.4 / 9.1.  256 columns 51 -> 57 us for the second; a wavefront for both halves, in workgroups of four,
+// 64 us for the third but 12.2 for the last.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(512, 4) void gemm_bf16_patch_kernel(PatchPixelRows arows, const unsigned char* W, int N, int K,
+                                                                  EpiEmbed ep, const int32_t* __restrict__ m_ptr, int m_host) {
+  constexpr int R = 8, kSlab = 64 * 128, STRIDE = 144, kSums = 32 * STRIDE;
+  typedef const __attribute__((address_space(1))) unsigned char* gptr;
+  typedef const __attribute__((address_space(1))) bf16x8* goper;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_patch[];   // two slabs a group, sums a wavefront
+  const int M = m_ptr ? *m_ptr : m_host;
+  const int parts = N >> 7, total = ((M + 63) / 64) * parts;
+  if ((int)blockIdx.x >= total) return;
+  const int pid = xcd_tile_order(blockIdx.x, total), m0 = pid / parts * 64, n0 = pid % parts * 128;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
+  const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const int nk = K >> 7, k0 = grp * (K >> 1);   // slabs of the group, its first element
+  const uint32_t voff = lane * 16, lds0 = (uint32_t)(uintptr_t)smem_patch + grp * (2 * kSlab);
+  const unsigned char* const ring = smem_patch + grp * (2 * kSlab);
+
+  // loads of a slab: 8 rows of 128 bytes an instruction, two of them a wavefront, chunks XORed by the row
+  uint32_t row[2];
+  bool any_row = false;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int r = (wave * 2 + j) * 8 + (lane >> 3);
+    bool ok;
+    row[j] = arows.row_off(m0 + r, M, ok) + arows.lane_off(((lane & 7) ^ lds_row_key<128>(r)) * 8);
+    any_row |= ok;
+  }
+  if (!__syncthreads_or(any_row)) return;   // no token of the level
+  auto fill = [&](int it, int place, int j) {
+    dma16_untracked_s(arows.base() + arows.slab_off(k0 + it * 64), row[j], lds0 + place * kSlab + (wave * 2 + j) * 1024);
+  };
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) fill(s, s, j);
+  __builtin_amdgcn_sched_barrier(0);
+  const size_t column = (size_t)K * 64;   // bytes of 32 columns
+  const gptr w0 = (gptr)W + ((size_t)(n0 >> 5) + wave) * column + (size_t)(k0 >> 4) * 1024;
+  gptr wq = w0;
+  bf16x8 wr[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    gptr q = wq + k * 1024;
+    asm volatile("" : "+s"(q));   // scalar bases: no vector arithmetic
+    wr[k] = *reinterpret_cast<goper>(q + voff);
+  }
+  wq += R * 1024;
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(R + 2) : "memory");   // slab 0
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" : : : "memory");
+  f32x16 acc[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+  uint32_t ao[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) ao[k] = l32 * 128 + (((2 * k + g) ^ lds_row_key<128>(l32)) << 4);
+  bf16x8 a[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) a[0][i] = *reinterpret_cast<const bf16x8*>(ring + ao[0] + i * 4096);
+  __builtin_amdgcn_sched_barrier(0);
+  auto slab = [&](int it, auto half_tag) {
+    constexpr int H = decltype(half_tag)::value;   // LDS place, and ring places 4 H ..
+    if (it == nk - 2) wq = w0;   // past the end: in bounds, and not used
+    gptr q = wq;
+    asm volatile("" : "+s"(q));
+    wq += 4096;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k == 3) {
+        // the next slab has arrived: younger than its loads are the weights of four k-steps
+        asm volatile("s_waitcnt vmcnt(4)" : : : "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this one's operands are in registers
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" : : : "memory");
+      }
+      const unsigned char* p = ring + (k == 3 ? 1 - H : H) * kSlab + ao[(k + 1) & 3];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        a[(k + 1) & 1][i] = *reinterpret_cast<const bf16x8*>(p + i * 4096);
+        __builtin_amdgcn_sched_barrier(0);
+        if (k == 3 && it + 2 < nk) fill(it + 2, H, i);
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[4 * H + k], a[k & 1][i], acc[i], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wr[4 * H + k] = *reinterpret_cast<goper>(q + k * 1024 + voff);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+#pragma nounroll
+  for (int it = 0; it < nk; it += 2) {
+    slab(it, std::integral_constant<int, 0>{});
+    slab(it + 1, std::integral_constant<int, 1>{});
+  }
+
+  // Group g finishes rows 32 g ..: the other group's sums of them cross the LDS; then rows leave as runs of 128
+  // bytes through the same place.
+  const int mb = m0 + grp * 32, crow = lane >> 3, cchunk = lane & 7, n = n0 + wave * 32 + cchunk * 4;
+  int32_t desc[4];
+  float4 e[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int m = mb + t * 8 + crow;
+    desc[t] = m < M ? ep.row_info(m) : -1;
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) e[t] = ep.extra4(0, n, max(desc[t], 0));
+  const float4 b = ep.bias4(n);
+  unsigned char* const sums = smem_patch + 4 * kSlab;
+  float4* const give = reinterpret_cast<float4*>(sums + ((1 - grp) * 4 + wave) * kSums) + lane;
+  unsigned char* const take = sums + (grp * 4 + wave) * kSums;
+  const f32x16 other = grp == 0 ? acc[1] : acc[0];
+  f32x16 sum = grp == 0 ? acc[0] : acc[1];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) give[q * 64] = make_float4(other[4 * q], other[4 * q + 1], other[4 * q + 2], other[4 * q + 3]);
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 o = reinterpret_cast<const float4*>(take)[q * 64 + lane];
+    sum[4 * q] += o.x;
+    sum[4 * q + 1] += o.y;
+    sum[4 * q + 2] += o.z;
+    sum[4 * q + 3] += o.w;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    *reinterpret_cast<float4*>(take + l32 * STRIDE + (8 * q + 4 * g) * 4) =
+        make_float4(sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const float4 o = *reinterpret_cast<const float4*>(take + (t * 8 + crow) * STRIDE + cchunk * 16);
+    const float v[4] = {o.x, o.y, o.z, o.w};
+    if (ep.row_ok(desc[t])) ep.store4(mb + t * 8 + crow, n, v, b, e[t], desc[t]);
+  }
+}
+
 // Sum over each group of 16 consecutive lanes, delivered to all 16 (quad swaps, then the
 // mirror of each half-row and of the row: a fixed order, no LDS).
 __device__ __forceinline__ float row16_sum(float v) {
@@ -2612,6 +2766,19 @@ hipError_t launch_packed(const bf16_t* a, const void* packed, int N, int K, cons
   return launch_packed_tile<4>(a, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
 }
 
+// Launch of the patch embedding with packed weights.
+hipError_t launch_patch(const PatchPixelRows& rows, const void* packed, int N, int K, const EpiEmbed& ep, const int32_t* m_ptr,
+                        int m_host, int m_capacity, hipStream_t s) {
+  constexpr auto kern = gemm_bf16_patch_kernel;
+  constexpr size_t lds = 4 * 64 * 128 + 8 * 32 * 144;
+  static DeviceOnce configured;
+  hipError_t e = allow_lds(kern, lds, &configured);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(((m_capacity + 63) / 64) * (N / 128)), dim3(512), lds, s, rows,
+                     static_cast<const unsigned char*>(packed), N, K, ep, m_ptr, m_host);
+  return hipSuccess;
+}
+
 // Contractions without packed weights or of a width that is no multiple of 256, over many rows: 256x256
 // (8 wavefronts, 128x64 each) or 192x256 (96x64
 // each) for wide outputs over many rows, 192x128 or 128x128 (4 wavefronts, 96x64 or 64x64
@@ -2845,6 +3012,9 @@ hipError_t launch_layer_tail(const LayerTailArgs& a, int d, int F, const int32_t
   return hipGetLastError();
 }
 
+// whole slabs in both halves of K, two at a time
+bool patch_embed_supported(int d, int K) { return d % 128 == 0 && K % 256 == 0; }
+
 hipError_t launch_embed(const EmbedArgs& a, const void* w, const float* bias, int d,
                         bool use_bf16, const int32_t* m_ptr, int m_host, int m_capacity,
                         hipStream_t s) {
@@ -2875,12 +3045,12 @@ hipError_t launch_embed(const EmbedArgs& a, const void* w, const float* bias, in
       e = launch_direct_tile<32, 32, 1, 1, 4, 64, 2>(rows, wb, d, K, ep, m_ptr, m_host, m_capacity, s);
     else if (K % 128 == 0 && tiles32w <= cu_count())
       e = launch_direct_tile<32, 64, 1, 2, 4, 64, 2>(rows, wb, d, K, ep, m_ptr, m_host, m_capacity, s);
+    else if (a.packed && tiles64 > cu_count())
+      // more 64 x 64 tiles than CUs: 64 x 128 with packed weights (2,400 tokens of 32 x 32 and width 256, 152 tiles:
+      // 15.3 us, and 20.2 so)
+      e = launch_patch(rows, a.packed, d, K, ep, m_ptr, m_host, m_capacity, s);
     else if (d % 128 == 0 && tiles128 >= 256)
       e = launch_direct_tile<128, 128, 2, 2, 2, 64>(rows, wb, d, K, ep, m_ptr, m_host, m_capacity, s);
-    else if (d % 128 == 0 && K >= 6144 && tiles64 > 2 * cu_count())
-      // patches of 64 x 64 and three rounds of small tiles: one round of 128 x 128 with a deep ring
-      // (3,072 tokens of width 768: 158 -> 126 us; two rounds are 101)
-      e = launch_direct_tile<128, 128, 2, 2, 4, 64>(rows, wb, d, K, ep, m_ptr, m_host, m_capacity, s);
     else if ((tiles64 <= cu_count() || K >= 6144) && K % 128 == 0)
       // a workgroup per CU at most, or a very long contraction (patches of 64 x 64): two
       // groups of wavefronts share the contraction of a tile

@@ -149,9 +149,11 @@ struct EmbedArgs {
   const float* pe_col;    // [cols, d/2]
   float* out;             // [M, d] fp32
   float* out2;            // optional second copy (may be nullptr)
+  const void* packed;     // launch_slim_pack's copy of w, or null: bf16, where patch_embed_supported
 };
 // Patch gather + projection + bias + position for the tokens of one level.
 // w [d, 3*patch^2] in bf16 (use_bf16) or fp32.
+bool patch_embed_supported(int d, int K);
 hipError_t launch_embed(const EmbedArgs& a, const void* w, const float* bias, int d,
                         bool use_bf16, const int32_t* m_ptr, int m_host, int m_capacity,
                         hipStream_t s);
