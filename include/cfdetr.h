@@ -127,7 +127,8 @@ typedef struct {
 /* Kernel families, for cfdetr_profile_end. */
 typedef enum {
   CFDETR_K_SELECT = 0, /* A2 cell tests, compaction, offsets                   */
-  CFDETR_K_PLAN = 1,   /* attention work list from the sequence offsets        */
+  CFDETR_K_PLAN = 1,   /* attention work list from the sequence offsets; of the
+                          decoder also the tokens in bf16                      */
   CFDETR_K_EMBED = 2,  /* patch gather + projection + position                 */
   CFDETR_K_GATHER = 3, /* reuse of cached coarse tokens                        */
   CFDETR_K_LN = 4,     /* LayerNorm                                            */
@@ -139,7 +140,7 @@ typedef enum {
                           everything of a layer after attention, that kernel      */
   CFDETR_K_ROI = 10,   /* difficulty test and region proposal                  */
   CFDETR_K_DEC = 11,   /* decoder kernels that are not one of the families above
-                          (cast, query broadcast, key/value projection, heads)   */
+                          (query broadcast, key/value projection, heads)   */
   CFDETR_K_COUNT = 12
 } cfdetr_kernel_id;
 

@@ -86,7 +86,6 @@ struct cfdetr_ctx {
   void* dh = nullptr;         // FFN hidden [Bmax*Q, F]; also the box head's hidden rows
   void* dvt = nullptr;        // V of the queries, feature-major
   int dvt_ld = 0;
-  int32_t* dcu = nullptr;     // i * Q
   int32_t* dcu_all = nullptr; // plan outputs for the query sequences
   int32_t* dm_all = nullptr;
   int32_t* dpcu = nullptr;
@@ -586,7 +585,7 @@ cfdetr_status coarse_impl(cfdetr_ctx* ctx, const void* images, int B, float* x0_
                                  x0_out, nullptr, M, M, s);
   if (st != CFDETR_OK) return st;
   const RunShape shape = run_shape(ctx, RunKind::kExact, M, M);
-  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(ctx->coarse_cu, B, encoder_plan(ctx, 0, shape), s, M, 0, ctx->err_flag));
+  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(ctx->coarse_cu, B, encoder_plan(ctx, 0, shape), s, M, ctx->err_flag));
   return run_encoder(ctx, B, shape, M, y_coarse, 0, nullptr, s);
 }
 
@@ -633,7 +632,7 @@ cfdetr_status fine_impl(cfdetr_ctx* ctx, const void* images, int B, const int32_
   // the embedding included, reads the checked copy.
   const int cap = ctx->cfg.max_tokens_total;
   const RunShape shape = run_shape(ctx, RunKind::kFine, min(B * ctx->n0, cap), cap);
-  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, encoder_plan(ctx, 0, shape), s, cap, 0, ctx->err_flag));
+  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, encoder_plan(ctx, 0, shape), s, cap, ctx->err_flag));
   cfdetr_status st = fine_embed(ctx, images, B, tok_desc, ctx->cu_all, x0_cache, 0, s);
   if (st != CFDETR_OK) return st;
   return run_encoder(ctx, B, shape, cap, y_mixed, 0, nullptr, s);
@@ -648,12 +647,12 @@ cfdetr_status padded_impl(cfdetr_ctx* ctx, const void* images, int B, const int3
   // the caller's offsets are checked first (as in fine_impl); the padding reads the checked copy
   const RunShape shape = run_shape(ctx, RunKind::kExact, B * t_pad, B * t_pad);
   const PlanArgs plan = encoder_plan(ctx, 0, shape);
-  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, plan, s, ctx->cfg.max_tokens_total, 0, ctx->err_flag));
+  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, plan, s, ctx->cfg.max_tokens_total, ctx->err_flag));
   CF_LAUNCH(CFDETR_K_SELECT, launch_pad_tokens(tok_desc, ctx->cu_all, B, t_pad, ctx->tok_pad,
                                                ctx->cu_pad, ctx->kv_len, ctx->err_flag, s));
   cfdetr_status st = fine_embed(ctx, images, B, ctx->tok_pad, ctx->cu_pad, x0_cache, 0, s);
   if (st != CFDETR_OK) return st;
-  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(ctx->cu_pad, B, plan, s, B * t_pad, 0, ctx->err_flag));
+  CF_LAUNCH(CFDETR_K_PLAN, launch_plan(ctx->cu_pad, B, plan, s, B * t_pad, ctx->err_flag));
   return run_encoder(ctx, B, shape, B * t_pad, y_padded, 0, nullptr, s, ctx->kv_len);
 }
 
@@ -781,18 +780,11 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
   const float qs = attention_q_scale(d / c.n_heads);
   const int dblock_q = attention_block_q(d / c.n_heads, true, Mq, c.n_heads);
   const int dgrid = ctx->dgrid[dblock_q == 256];
-  // token sequences: offsets, total and padded offsets (the work list is not used).  The
-  // offsets are the caller's: the plan checks them, and after an error the second plan
-  // hands the attention kernels no work.
   {
-    PlanArgs p = encoder_plan(ctx, 0, RunShape{});
-    p.n_heads_q = 8;
-    CF_LAUNCH(CFDETR_K_PLAN, launch_plan(cu, B, p, s, cap_m, 1, ctx->err_flag, nullptr));
-  }
-  CF_LAUNCH(CFDETR_K_DEC, launch_cast_bf16(memory, ctx->a, d, ctx->m_all, cap_m, s));
-  // query sequences: B times Q rows, work list for both attentions of every layer
-  {
-    PlanArgs p{};
+    // token sequences: offsets, total and padded offsets (the work list is not used); query sequences: B
+    // times Q rows, work list for both attentions of every layer
+    PlanArgs t = encoder_plan(ctx, 0, RunShape{}), p{};
+    t.n_heads_q = 8;
     p.block_q = dblock_q;
     p.heads = c.n_heads;
     p.items = ctx->ditems;
@@ -803,7 +795,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
     p.queue_heads = ctx->dqueue;
     p.n_heads_q = 16 * L;
     p.queue_start = dgrid / 8;
-    CF_LAUNCH(CFDETR_K_PLAN, launch_plan(ctx->dcu, B, p, s, 0, 0, nullptr, ctx->err_flag));
+    CF_LAUNCH(CFDETR_K_PLAN, launch_decode_plan(cu, B, t, p, Q, cap_m, ctx->err_flag, memory, ctx->a, d, s));
   }
   if (ctx->dwide_layer == 0)
     CF_LAUNCH(CFDETR_K_DEC, launch_broadcast_rows(w.query_embed, ctx->dx, Q, d, B, s));
@@ -1403,7 +1395,7 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
   const uint64_t o_wide = cv.take(wide_bytes * w->n_layers);
   const uint64_t o_whead = cv.take(wide ? wide_layer_packed_bytes((int)d, (int)F, true) : 0);
   const uint64_t o_vt = cv.take(d * (uint64_t)ctx->dvt_ld * 2);
-  const uint64_t o_cu = cv.take((Bm + 1) * 4), o_cua = cv.take((Bm + 1) * 4), o_m = cv.take(4);
+  const uint64_t o_cua = cv.take((Bm + 1) * 4), o_m = cv.take(4);
   const uint64_t o_pcu = cv.take((Bm + 1) * 4), o_items = cv.take((uint64_t)ctx->dcap8 * 8 * 16);
   const uint64_t o_q = cv.take((uint64_t)w->n_layers * 16 * 4);
   const bool fused = !wide && layer_tail_supported((int)d, (int)F, true) && gemm_residual_ln_supported((int)d, true);
@@ -1445,7 +1437,6 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
   ctx->d_o = base + o_o;
   ctx->dh = base + o_h;
   ctx->dvt = base + o_vt;
-  ctx->dcu = reinterpret_cast<int32_t*>(base + o_cu);
   ctx->dcu_all = reinterpret_cast<int32_t*>(base + o_cua);
   ctx->dm_all = reinterpret_cast<int32_t*>(base + o_m);
   ctx->dpcu = reinterpret_cast<int32_t*>(base + o_pcu);
@@ -1457,11 +1448,8 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
   ctx->dmid_packed = base + o_mid;
   ctx->dk_all = base + o_kall;
   ctx->dvt_all = base + o_vall;
-  std::vector<int32_t> cu(Bm + 1);
-  for (uint64_t b = 0; b <= Bm; ++b) cu[b] = (int32_t)(b * Q);
-  e = hipMemcpy(ctx->dcu, cu.data(), cu.size() * 4, hipMemcpyHostToDevice);
   // padding positions of the feature-major V are read (with probability 0): keep them finite
-  if (e == hipSuccess) e = hipMemset(ctx->dvt, 0, d * (uint64_t)ctx->dvt_ld * 2);
+  e = hipMemset(ctx->dvt, 0, d * (uint64_t)ctx->dvt_ld * 2);
   if (e == hipSuccess) e = hipMemset(ctx->dvt_all, 0, v_bytes * w->n_layers);
   // the weights the fused layer kernels stream, in their order
   for (int l = 0; l < w->n_layers && e == hipSuccess && fused; ++l)

@@ -89,14 +89,15 @@ hipError_t launch_pad_tokens(const int32_t* tok_desc, const int32_t* cu_seqlens,
 // that follow (eight per launch), to queue_start = (attention grid) / 8: the entries
 // before that are handed out by workgroup index; or to -1 for a queue with no entries
 // beyond those.
-// max_total > 0 checks offsets that a caller wrote: a length below min_len, or a total above
+// max_total > 0 checks offsets that a caller wrote: a negative length, or a total above
 // max_total, gives every one of the B sequences length 0 (the run then computes and writes
-// nothing for them) and sets *err_flag.  gate (may be null): if
-// *gate is not 0 the work list comes out empty, so that the attention launches that
-// follow do nothing after an earlier kernel has raised the error flag.
+// nothing for them) and sets *err_flag.
 hipError_t launch_plan(const int32_t* cu_seqlens, int B, const PlanArgs& plan, hipStream_t s,
-                       int max_total = 0, int min_len = 0, int32_t* err_flag = nullptr,
-                       const int32_t* gate = nullptr);
+                       int max_total = 0, int32_t* err_flag = nullptr);
+// The plans of a decoder run and its tokens in bf16 (decode_plan_kernel): `tokens` for the B sequences of
+// cu_seqlens, checked (lengths from 1 on), `queries` for Q rows of every frame, without work after an error.
+hipError_t launch_decode_plan(const int32_t* cu_seqlens, int B, const PlanArgs& tokens, const PlanArgs& queries, int Q,
+                              int max_total, int32_t* err_flag, const float* memory, void* out, int d, hipStream_t s);
 
 // ---- row-wise kernels (rowwise.hip) ----------------------------------------
 // Position tables of one level: pe_row [rows, d/2], pe_col [cols, d/2] (fp32).
