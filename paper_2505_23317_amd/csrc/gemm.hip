@@ -1244,22 +1244,23 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_packed_kernel(const bf16_t* 
 // Patch embedding with the weights packed (launch_slim_pack), for more tokens than the small tiles of
 // gemm_bf16_direct_kernel are for: 64 rows x 128 columns, two groups of four wavefronts, one for each half of K
 // (the halves that every form adds), a wavefront all rows by 32 columns.  The main loop is that of packed_tiles:
-// weights into a register ring, rows through the LDS in slabs of 64 elements and two places for each group.  At the
+// weights into a register ring, rows through the LDS in slabs of 64 elements and three places for each group.  At the
 // end a group gives the other half its sums of 32 rows and finishes the other 32.  Two workgroups a CU: what
 // a tile waits for, five loads one behind the other before its first pixel and the position tables behind
 // its last, is as long as the loop for small patches.  Bound by the operands' way into the CU for large ones (a tile of
 // 64 x 64 patches 4.7 MB, 43 us).  128 x 128 tiles with the weights through the LDS / this: 3,072 tokens of 64 x 64
-// and width 768 120 / 117 us, some 4,600 of 32 x 32 there 81 / 49, 51,200 of 16 x 16 and width 384 107 / 71,
+// and width 768 120 / 117 us, some 4,600 of 32 x 32 there 81 / 46, 51,200 of 16 x 16 and width 384 107 / 68,
 // 12,800 of 32 x 32 there 86 / 64; 64 x 64 tiles / this: 16,000 of 16 x 16 and width 384 54 / 37, some 3,000 and
-// width 256 11.4 / 9.1.  256 columns 51 -> 57 us for the second; a wavefront for both halves, in workgroups of four,
+// width 256 11.4 / 8.9.  (With two places 49, 72 and 9.1; with four and 16 weight blocks spills, or one workgroup a CU: 90 for
+// the third.  128 rows: 58 us for the second.)  256 columns 51 -> 57 us for the second; a wavefront for both halves, in workgroups of four,
 // 64 us for the third but 12.2 for the last.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(512, 4) void gemm_bf16_patch_kernel(PatchPixelRows arows, const unsigned char* W, int N, int K,
                                                                   EpiEmbed ep, const int32_t* __restrict__ m_ptr, int m_host) {
-  constexpr int R = 8, kSlab = 64 * 128, STRIDE = 144, kSums = 32 * STRIDE;
+  constexpr int R = 8, S = 3, kSlab = 64 * 128, STRIDE = 144, kSums = 32 * STRIDE;
   typedef const __attribute__((address_space(1))) unsigned char* gptr;
   typedef const __attribute__((address_space(1))) bf16x8* goper;
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_patch[];   // two slabs a group, sums a wavefront
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_patch[];   // S slabs a group, then sums a wavefront
   const int M = m_ptr ? *m_ptr : m_host;
   const int parts = N >> 7, total = ((M + 63) / 64) * parts;
   if ((int)blockIdx.x >= total) return;
@@ -1268,8 +1269,8 @@ __global__ __launch_bounds__(512, 4) void gemm_bf16_patch_kernel(PatchPixelRows 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
   const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
   const int nk = K >> 7, k0 = grp * (K >> 1);   // slabs of the group, its first element
-  const uint32_t voff = lane * 16, lds0 = (uint32_t)(uintptr_t)smem_patch + grp * (2 * kSlab);
-  const unsigned char* const ring = smem_patch + grp * (2 * kSlab);
+  const uint32_t voff = lane * 16, lds0 = (uint32_t)(uintptr_t)smem_patch + grp * (S * kSlab);
+  const unsigned char* const ring = smem_patch + grp * (S * kSlab);
 
   // loads of a slab: 8 rows of 128 bytes an instruction, two of them a wavefront, chunks XORed by the row
   uint32_t row[2];
@@ -1286,7 +1287,7 @@ __global__ __launch_bounds__(512, 4) void gemm_bf16_patch_kernel(PatchPixelRows 
     dma16_untracked_s(arows.base() + arows.slab_off(k0 + it * 64), row[j], lds0 + place * kSlab + (wave * 2 + j) * 1024);
   };
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
+  for (int s = 0; s < S; ++s)
 #pragma unroll
     for (int j = 0; j < 2; ++j) fill(s, s, j);
   __builtin_amdgcn_sched_barrier(0);
@@ -1302,7 +1303,7 @@ __global__ __launch_bounds__(512, 4) void gemm_bf16_patch_kernel(PatchPixelRows 
   }
   wq += R * 1024;
   __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(R + 2) : "memory");   // slab 0
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(R + 2 * (S - 1)) : "memory");   // slab 0
   __builtin_amdgcn_s_barrier();
   asm volatile("" : : : "memory");
   f32x16 acc[2];
@@ -1317,40 +1318,45 @@ __global__ __launch_bounds__(512, 4) void gemm_bf16_patch_kernel(PatchPixelRows 
 #pragma unroll
   for (int i = 0; i < 2; ++i) a[0][i] = *reinterpret_cast<const bf16x8*>(ring + ao[0] + i * 4096);
   __builtin_amdgcn_sched_barrier(0);
-  auto slab = [&](int it, auto half_tag) {
-    constexpr int H = decltype(half_tag)::value;   // LDS place, and ring places 4 H ..
-    if (it == nk - 2) wq = w0;   // past the end: in bounds, and not used
-    gptr q = wq;
+  auto slab = [&](int it, auto place_tag) {
+    constexpr int H = decltype(place_tag)::value;   // LDS place, and ring places 4 H ..
+    gptr q = it + R / 4 < nk ? wq : w0;   // past the end: in bounds, and not used
     asm volatile("" : "+s"(q));
     wq += 4096;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       if (k == 3) {
-        // the next slab has arrived: younger than its loads are the weights of four k-steps
-        asm volatile("s_waitcnt vmcnt(4)" : : : "memory");
+        // the next slab has arrived: younger than its loads are the weights of S - 1 slabs, and the rows of
+        // S - 2 as long as there are any to be asked for
+        if (it + S - 1 < nk) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * (S - 1) + 2 * (S - 2)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" : : "n"(4 * (S - 1)) : "memory");
         __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this one's operands are in registers
         __builtin_amdgcn_s_barrier();
         asm volatile("" : : : "memory");
       }
-      const unsigned char* p = ring + (k == 3 ? 1 - H : H) * kSlab + ao[(k + 1) & 3];
+      const unsigned char* p = ring + (k == 3 ? (H + 1) % S : H % S) * kSlab + ao[(k + 1) & 3];
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         a[(k + 1) & 1][i] = *reinterpret_cast<const bf16x8*>(p + i * 4096);
         __builtin_amdgcn_sched_barrier(0);
-        if (k == 3 && it + 2 < nk) fill(it + 2, H, i);
-        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[4 * H + k], a[k & 1][i], acc[i], 0, 0, 0);
+        if (k == 3 && it + S < nk) fill(it + S, H % S, i);
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[(4 * H + k) % R], a[k & 1][i], acc[i], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
-      wr[4 * H + k] = *reinterpret_cast<goper>(q + k * 1024 + voff);
+      wr[(4 * H + k) % R] = *reinterpret_cast<goper>(q + k * 1024 + voff);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
 #pragma nounroll
-  for (int it = 0; it < nk; it += 2) {
+  for (int it = 0; it < nk; it += 6) {   // LDS and ring places as constants
     slab(it, std::integral_constant<int, 0>{});
     slab(it + 1, std::integral_constant<int, 1>{});
+    slab(it + 2, std::integral_constant<int, 2>{});
+    slab(it + 3, std::integral_constant<int, 3>{});
+    slab(it + 4, std::integral_constant<int, 4>{});
+    slab(it + 5, std::integral_constant<int, 5>{});
   }
 
   // Group g finishes rows 32 g ..: the other group's sums of them cross the LDS; then rows leave as runs of 128
@@ -1366,11 +1372,13 @@ __global__ __launch_bounds__(512, 4) void gemm_bf16_patch_kernel(PatchPixelRows 
 #pragma unroll
   for (int t = 0; t < 4; ++t) e[t] = ep.extra4(0, n, max(desc[t], 0));
   const float4 b = ep.bias4(n);
-  unsigned char* const sums = smem_patch + 4 * kSlab;
+  unsigned char* const sums = smem_patch;   // the slabs' place
+  static_assert(8 * kSums <= 2 * S * kSlab, "sums of eight wavefronts");
   float4* const give = reinterpret_cast<float4*>(sums + ((1 - grp) * 4 + wave) * kSums) + lane;
   unsigned char* const take = sums + (grp * 4 + wave) * kSums;
   const f32x16 other = grp == 0 ? acc[1] : acc[0];
   f32x16 sum = grp == 0 ? acc[0] : acc[1];
+  __syncthreads();   // the slabs have been read
 #pragma unroll
   for (int q = 0; q < 4; ++q) give[q * 64] = make_float4(other[4 * q], other[4 * q + 1], other[4 * q + 2], other[4 * q + 3]);
   __syncthreads();
@@ -2770,7 +2778,7 @@ hipError_t launch_packed(const bf16_t* a, const void* packed, int N, int K, cons
 hipError_t launch_patch(const PatchPixelRows& rows, const void* packed, int N, int K, const EpiEmbed& ep, const int32_t* m_ptr,
                         int m_host, int m_capacity, hipStream_t s) {
   constexpr auto kern = gemm_bf16_patch_kernel;
-  constexpr size_t lds = 4 * 64 * 128 + 8 * 32 * 144;
+  constexpr size_t lds = 2 * 3 * 64 * 128;
   static DeviceOnce configured;
   hipError_t e = allow_lds(kern, lds, &configured);
   if (e != hipSuccess) return e;
@@ -3012,8 +3020,8 @@ hipError_t launch_layer_tail(const LayerTailArgs& a, int d, int F, const int32_t
   return hipGetLastError();
 }
 
-// whole slabs in both halves of K, two at a time
-bool patch_embed_supported(int d, int K) { return d % 128 == 0 && K % 256 == 0; }
+// whole slabs in both halves of K, six at a time (K is 3 patch^2: patches of 16 x 16 pixels and larger)
+bool patch_embed_supported(int d, int K) { return d % 128 == 0 && K % 768 == 0; }
 
 hipError_t launch_embed(const EmbedArgs& a, const void* w, const float* bias, int d,
                         bool use_bf16, const int32_t* m_ptr, int m_host, int m_capacity,
