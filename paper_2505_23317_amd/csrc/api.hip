@@ -284,6 +284,13 @@ struct RunShape {
 // layers in us, spread / one kernel a layer, on 256 CUs: 128 rows 352 / 585, 920 rows 473 / 656, 2,048
 // rows 525 / 660, 2,760 rows 622 / 679, 3,680 rows 652 / 689, 4,600 rows 774 / 708.
 constexpr int kSpreadRows = 15;
+// Rows a CU up to which the weights behind an attention launch are asked for during it (read_ahead, attention.hip).
+// Without / with, in us, three contexts in turn, so that each finds its weights in memory: queries of four cameras 497 /
+// 458, the two-stage detector of six 889 / 843, one high-resolution fine pass 953 / 900.  One context over and over, its
+// weights in the cache: 425 / 424, 785 / 787, 880 / 884, the two stages of one camera 703 / 706.  32 to 128 workgroups do
+// the same.  Not in encoders of width 256 (one camera 207 / 208.5) or 768 (three small frames 1,024 / 1,028), nor with
+// more rows, whose attention fills the chip (six cameras, 29 rows a CU, 256.5 / 257.9).
+constexpr int kAheadRows = 16;
 
 enum class RunKind { kMerged = 0, kFine = 1, kExact = 2 };
 
@@ -326,6 +333,13 @@ PlanArgs encoder_plan(const cfdetr_ctx* ctx, int n_prefix, const RunShape& shape
 }
 
 const void* packed(const char* base, size_t elements) { return base ? base + elements * 2 : nullptr; }
+
+// Weights to be read during an attention launch, if there are any.
+void ask_for(ReadAhead& ahead, int i, const void* at, size_t bytes) {
+  if (at == nullptr || bytes >= (size_t)1 << 32) return;
+  ahead.at[i] = at;
+  ahead.bytes[i] = (uint32_t)bytes;
+}
 
 // All layers + final LayerNorm over the tokens in ctx->x.  The sequences are
 // n_prefix coarse grids (n0 tokens each) followed by B sequences of the caller's; the
@@ -376,9 +390,16 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
     for (size_t l = 0; l < (size_t)c.n_layers; ++l) {
       CF_LAUNCH(CFDETR_K_QKV, step(l == 0 ? SlimStep::kFirstQkv : SlimStep::kQkv, nullptr, nullptr, w.ln1_g + l * d, w.ln1_b + l * d,
                                    nullptr, ctx->qkv, ctx->slim_qkv + l * 3 * d * d * 2, w.b_qkv + l * 3 * d));
+      ReadAhead ahead;
+      if (shape.rows <= kAheadRows * ctx->cus) {
+        ask_for(ahead, 0, ctx->slim_o + l * d * d * 2, (size_t)d * d * 2);
+        ask_for(ahead, 1, ctx->slim_ff1 + l * F * d * 2, (size_t)F * d * 2);
+        ask_for(ahead, 2, ctx->slim_ff2 + l * F * d * 2, (size_t)F * d * 2);
+        if (l + 1 < (size_t)c.n_layers) ask_for(ahead, 3, ctx->slim_qkv + (l + 1) * 3 * d * d * 2, (size_t)3 * d * d * 2);
+      }
       CF_LAUNCH(CFDETR_K_ATTN,
                 launch_attention(ctx->qkv, ctx->vt, ctx->vt_ld, ctx->o, d, c.n_heads, ctx->items, ctx->cap8, ctx->queue_heads + 8 * l,
-                                 shape.attn_grid, shape.block_q, bf, kv_len, s));
+                                 shape.attn_grid, shape.block_q, bf, kv_len, s, ahead));
       CF_LAUNCH(CFDETR_K_FF1, step(SlimStep::kOutHidden, ctx->slim_o + l * d * d * 2, w.b_o + l * d, w.ln2_g + l * d,
                                    w.ln2_b + l * d, ctx->o, ctx->h, ctx->slim_ff1 + l * F * d * 2, w.b_ff1 + l * F));
       std::swap(a.x, a.x_new);
@@ -413,9 +434,12 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
     wa.split_row = split_row;
     wa.out2 = y1;
     for (int l = 0; l < c.n_layers; ++l) {
+      ReadAhead ahead;
+      if (d == 384 && shape.rows <= kAheadRows * ctx->cus)
+        ask_for(ahead, 0, static_cast<const char*>(ctx->wide_packed) + (size_t)l * ctx->wide_layer, ctx->wide_layer);
       CF_LAUNCH(CFDETR_K_ATTN,
                 launch_attention(ctx->qkv, ctx->vt, ctx->vt_ld, ctx->o, d, c.n_heads, ctx->items, ctx->cap8, ctx->queue_heads + 8 * l,
-                                 shape.attn_grid, shape.block_q, bf, kv_len, s));
+                                 shape.attn_grid, shape.block_q, bf, kv_len, s, ahead));
       wa.last = l + 1 == c.n_layers;
       wa.packed = static_cast<const char*>(ctx->wide_packed) + (size_t)l * ctx->wide_layer;
       wa.b_o = w.b_o + (size_t)l * d;
@@ -720,9 +744,22 @@ cfdetr_status decode_wide(cfdetr_ctx* ctx, int B, float* queries, int dblock_q, 
       wa.b_qkv = w.b_qkv;
       CF_LAUNCH(CFDETR_K_QKV, launch_wide_layer(wa, (int)d, (int)F, mt, nullptr, Mq, Mq, s));
     }
+    ReadAhead ahead, behind_cross;
+    if (Mq <= kAheadRows * ctx->cus) {
+      ask_for(ahead, 0, ctx->dslim_o + l * d * d * 2, d * d * 2);
+      ask_for(ahead, 1, ctx->dslim_q + l * d * d * 2, d * d * 2);
+      if (spread) {
+        ask_for(behind_cross, 0, ctx->dslim_o2 + l * d * d * 2, d * d * 2);
+        ask_for(behind_cross, 1, ctx->dslim_ff1 + l * F * d * 2, F * d * 2);
+        ask_for(behind_cross, 2, ctx->dslim_ff2 + l * F * d * 2, F * d * 2);
+        if (l + 1 < L) ask_for(behind_cross, 3, ctx->dslim_qkv + (l + 1) * 3 * d * d * 2, 3 * d * d * 2);
+      } else {
+        ask_for(behind_cross, 0, ctx->dwide_packed + l * ctx->dwide_layer, ctx->dwide_layer);
+      }
+    }
     CF_LAUNCH(CFDETR_K_ATTN,
               launch_attention(ctx->dqkv, ctx->dvt, ctx->dvt_ld, ctx->d_o, (int)d, c.n_heads, ctx->ditems, ctx->dcap8,
-                               ctx->dqueue + 16 * l, dgrid, dblock_q, true, nullptr, s));
+                               ctx->dqueue + 16 * l, dgrid, dblock_q, true, nullptr, s, ahead));
     CF_LAUNCH(CFDETR_K_OUT, step(SlimStep::kOutQuery, w.ln2_g + l * d, w.ln2_b + l * d, ctx->dh, ctx->dslim_q + l * d * d * 2,
                                  w.b_q + l * d, ctx->d_o, ctx->dslim_o + l * d * d * 2, w.b_o + l * d));
     // cross-attention: the queries read the tokens of their frame
@@ -730,7 +767,7 @@ cfdetr_status decode_wide(cfdetr_ctx* ctx, int B, float* queries, int dblock_q, 
               launch_cross_attention(ctx->dh, static_cast<const bf16_t*>(ctx->dk_all) + l * k_stride,
                                      static_cast<const bf16_t*>(ctx->dvt_all) + l * v_stride, ctx->vt_ld, ctx->d_o,
                                      ctx->cu_all, ctx->pcu, (int)d, c.n_heads, ctx->ditems, ctx->dcap8,
-                                     ctx->dqueue + 16 * l + 8, dgrid, dblock_q, s));
+                                     ctx->dqueue + 16 * l + 8, dgrid, dblock_q, s, behind_cross));
     if (spread) {
       CF_LAUNCH(CFDETR_K_FF1, step(SlimStep::kOutHidden, w.ln3_g + l * d, w.ln3_b + l * d, ctx->dh, ctx->dslim_ff1 + l * F * d * 2,
                                    w.b_ff1 + l * F, ctx->d_o, ctx->dslim_o2 + l * d * d * 2, w.b_o2 + l * d));

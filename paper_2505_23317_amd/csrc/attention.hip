@@ -124,8 +124,9 @@ __device__ __attribute__((noinline)) void clear_v_padding(unsigned char* wV, int
 // The exact walk of 32 queries per wavefront (see above), for an item whose sums left the safe
 // range: the largest logit of every query, then the probabilities relative to it; only the
 // queries with `redo` set are written.  Everything is fetched again; this is the rare path and
-// it is a function of its own, so that the registers of the fast path are not its business.
-template <int DH>
+// it is a function of its own, so that the registers of the fast path are not its business (one for
+// each kernel: a second caller at head width 32 took 32 bytes of scratch and 36 instructions more).
+template <int DH, typename... Extra>
 __device__ __attribute__((noinline)) void exact_queries(
     const bf16_t* q_row, const bf16_t* kbase, int k_ld, const bf16_t* vbase, int vt_ld, int TK,
     bf16_t* orow, bool redo, unsigned char* smem) {
@@ -224,15 +225,42 @@ __device__ __attribute__((noinline)) void exact_queries(
   }
 }
 
+// Few rows leave CUs without work in an attention launch, and the kernels behind it wait for weights that other
+// work has driven out of the chip's memory-side cache.  kAheadGroups workgroups behind the others read them.  A
+// kernel of its own (with Ahead), because the arguments and the branch cost the others 0.3 us a launch.
+constexpr int kAheadGroups = 64;
+struct Ahead {
+  ReadAhead what;
+  int from;  // the first of those workgroups
+};
+__device__ __forceinline__ void read_ahead(const ReadAhead& ahead, int group) {
+  uint32_t sink = 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const uint4* const p = static_cast<const uint4*>(ahead.at[r]);
+    const uint32_t units = ahead.bytes[r] / 16;
+#pragma unroll 8
+    for (uint32_t u = group * (64 * kWavesPerGroup) + threadIdx.x; u < units; u += kAheadGroups * 64 * kWavesPerGroup) sink ^= p[u].x;
+  }
+  asm volatile("" : : "v"(sink));
+}
+
 // QB: blocks of 32 queries per wavefront.  The second launch bound holds the compiler to the
 // registers of two (64 queries), three or (head width 32) four wavefronts per SIMD.
-template <int DH, int QB>
+template <int DH, int QB, typename... Extra>
 __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4) void attention_bf16_kernel(
     const bf16_t* __restrict__ qbuf, int q_ld, const bf16_t* __restrict__ kbuf, int k_ld,
     const bf16_t* __restrict__ vt, int vt_ld, bf16_t* __restrict__ out,
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ pcu_k, int d,
     const int4* __restrict__ items, int cap8, int32_t* __restrict__ queue_heads,
-    const int32_t* __restrict__ kv_len) {
+    const int32_t* __restrict__ kv_len, Extra... extra) {
+  if constexpr (sizeof...(Extra) != 0) {
+    const Ahead& ahead = (extra, ...);
+    if ((int)blockIdx.x >= ahead.from) {
+      read_ahead(ahead.what, blockIdx.x - ahead.from);
+      return;
+    }
+  }
   constexpr int NW = kWavesPerGroup;
   constexpr int BQ = 32 * QB * NW;
   constexpr int KS = DH / 16;          // k-steps of Q.K^T
@@ -548,7 +576,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup, QB == 2 ? 2 : DH == 64 ? 3 : 4
       for (int qb = 0; qb < QB; ++qb) {
         const int q_local = qt * BQ + (wave * QB + qb) * 32 + l32;
         const bool again = QB == 1 ? redo[0] : (qb == 0 ? redo[0] : redo[QB - 1]);
-        exact_queries<DH>(qbase + (size_t)min(q_local, T - 1) * q_ld, kbase, k_ld, vbase, vt_ld, TK,
+        exact_queries<DH, Extra...>(qbase + (size_t)min(q_local, T - 1) * q_ld, kbase, k_ld, vbase, vt_ld, TK,
                               out + (size_t)(seq0 + min(q_local, T - 1)) * d + head * DH,
                               again && q_local < T, smem);
       }
@@ -679,17 +707,23 @@ namespace {
 bool launch_bf16(int dh, int block_q, int grid_size, hipStream_t s, const bf16_t* q, int q_ld,
                  const bf16_t* k, int k_ld, const bf16_t* v, int vt_ld, bf16_t* out,
                  const int32_t* cu_k, const int32_t* pcu_k, int d, const int4* recs, int cap8,
-                 int32_t* queue_heads, const int32_t* kv_len) {
-  const dim3 grid(grid_size), block(64 * kWavesPerGroup);
-  if (dh == 64 && block_q == 256)
-    hipLaunchKernelGGL((attention_bf16_kernel<64, 2>), grid, block, 0, s, q, q_ld, k, k_ld, v, vt_ld,
-                       out, cu_k, pcu_k, d, recs, cap8, queue_heads, kv_len);
+                 int32_t* queue_heads, const int32_t* kv_len, const ReadAhead& ahead) {
+  const dim3 block(64 * kWavesPerGroup);
+  auto go = [&](auto kernel, int groups, auto... extra) {
+    hipLaunchKernelGGL(kernel, dim3(groups), block, 0, s, q, q_ld, k, k_ld, v, vt_ld, out, cu_k, pcu_k, d, recs, cap8,
+                       queue_heads, kv_len, extra...);
+  };
+  const bool any = ahead.bytes[0] != 0;
+  if (dh == 64 && block_q == 256)  // rows enough to fill the chip
+    go(attention_bf16_kernel<64, 2>, grid_size);
+  else if (dh == 64 && block_q == 128 && any)
+    go(attention_bf16_kernel<64, 1, Ahead>, grid_size + kAheadGroups, Ahead{ahead, grid_size});
   else if (dh == 64 && block_q == 128)
-    hipLaunchKernelGGL((attention_bf16_kernel<64, 1>), grid, block, 0, s, q, q_ld, k, k_ld, v, vt_ld,
-                       out, cu_k, pcu_k, d, recs, cap8, queue_heads, kv_len);
+    go(attention_bf16_kernel<64, 1>, grid_size);
+  else if (dh == 32 && block_q == 128 && any)
+    go(attention_bf16_kernel<32, 1, Ahead>, grid_size + kAheadGroups, Ahead{ahead, grid_size});
   else if (dh == 32 && block_q == 128)
-    hipLaunchKernelGGL((attention_bf16_kernel<32, 1>), grid, block, 0, s, q, q_ld, k, k_ld, v, vt_ld,
-                       out, cu_k, pcu_k, d, recs, cap8, queue_heads, kv_len);
+    go(attention_bf16_kernel<32, 1>, grid_size);
   else
     return false;
   return true;
@@ -699,7 +733,7 @@ bool launch_bf16(int dh, int block_q, int grid_size, hipStream_t s, const bf16_t
 
 hipError_t launch_attention(const void* qkv, const void* vt, int vt_ld, void* out, int d, int heads,
                             const int32_t* items, int cap8, int32_t* queue_heads, int grid_size,
-                            int block_q, bool use_bf16, const int32_t* kv_len, hipStream_t s) {
+                            int block_q, bool use_bf16, const int32_t* kv_len, hipStream_t s, const ReadAhead& ahead) {
   if (grid_size < 8 || grid_size % 8 != 0 || grid_size > 8 * cap8) return hipErrorInvalidValue;
   const int dh = d / heads;
   const int4* recs = reinterpret_cast<const int4*>(items);
@@ -708,7 +742,7 @@ hipError_t launch_attention(const void* qkv, const void* vt, int vt_ld, void* ou
     const bf16_t* in = static_cast<const bf16_t*>(qkv);
     if (!launch_bf16(dh, block_q, grid_size, s, in, 3 * d, in + d, 3 * d, static_cast<const bf16_t*>(vt),
                      vt_ld, static_cast<bf16_t*>(out), nullptr, nullptr, d, recs, cap8, queue_heads,
-                     kv_len))
+                     kv_len, ahead))
       return hipErrorInvalidValue;
   } else {
     if (block_q != 128) return hipErrorInvalidValue;
@@ -732,12 +766,12 @@ hipError_t launch_cross_attention(const void* q, const void* k, const void* vt, 
                                   void* out, const int32_t* cu_k,
                                   const int32_t* pcu_k, int d, int heads, const int32_t* items,
                                   int cap8, int32_t* queue_heads, int grid_size, int block_q,
-                                  hipStream_t s) {
+                                  hipStream_t s, const ReadAhead& ahead) {
   if (grid_size < 8 || grid_size % 8 != 0 || grid_size > 8 * cap8) return hipErrorInvalidValue;
   if (!launch_bf16(d / heads, block_q, grid_size, s, static_cast<const bf16_t*>(q), d,
                    static_cast<const bf16_t*>(k), d, static_cast<const bf16_t*>(vt), vt_ld,
                    static_cast<bf16_t*>(out), cu_k, pcu_k, d, reinterpret_cast<const int4*>(items), cap8,
-                   queue_heads, nullptr))
+                   queue_heads, nullptr, ahead))
     return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -366,6 +366,13 @@ hipError_t launch_gemm_qkv(const void* A, const void* W, const float* bias, int 
 // log2(e) / sqrt(d_head): the factor the bf16 attention kernel expects folded into q.
 float attention_q_scale(int d_head);
 
+// What the kernels behind an attention launch will read (their weights), multiples of 16 bytes: workgroups of
+// their own ask for it meanwhile.
+struct ReadAhead {
+  const void* at[4] = {};
+  uint32_t bytes[4] = {};
+};
+
 // ---- attention (attention.hip) -----------------------------------------------
 // qkv [M, 3d] (q | k | v, head h at columns h*dh), out [M, d], both in the activation
 // dtype.  The bf16 kernel takes v from vt (see launch_gemm_qkv) instead of the last
@@ -380,7 +387,7 @@ float attention_q_scale(int d_head);
 // The sequences' offsets come with the work items (launch_plan).
 hipError_t launch_attention(const void* qkv, const void* vt, int vt_ld, void* out, int d, int heads,
                             const int32_t* items, int cap8, int32_t* queue_heads, int grid_size,
-                            int block_q, bool use_bf16, const int32_t* kv_len, hipStream_t s);
+                            int block_q, bool use_bf16, const int32_t* kv_len, hipStream_t s, const ReadAhead& ahead = {});
 // bf16 attention of query rows over the keys and values of another set of rows (the
 // decoder's cross-attention): q [Mq, d] and k [Mk, d] (head h at columns h*dh, q
 // pre-multiplied by attention_q_scale), v feature-major in vt at the padded offsets pcu_k
@@ -390,7 +397,7 @@ hipError_t launch_cross_attention(const void* q, const void* k, const void* vt, 
                                   void* out, const int32_t* cu_k,
                                   const int32_t* pcu_k, int d, int heads, const int32_t* items,
                                   int cap8, int32_t* queue_heads, int grid_size, int block_q,
-                                  hipStream_t s);
+                                  hipStream_t s, const ReadAhead& ahead = {});
 // Queries per work item (plan and kernels), for about that many query rows: 128 or 256.  A
 // query's result is the same, bit for bit, either way.
 int attention_block_q(int d_head, bool use_bf16, int64_t rows, int heads);

@@ -74,3 +74,20 @@ def test_decoders_alone_and_in_a_batch(d, heads, ffn, queries):
     print("decoder against the oracle:", err, flush=True)
     assert err <= BAR
     enc.close()
+
+
+# weights asked for during attention (up to 16 rows a CU: 4,096 rows on 256 CUs): spread (2 x 1,024), the fused form
+# (4 x 1,024, the last count) and without (5 x 1,024), for both head widths
+@pytest.mark.parametrize("heads, ffn", [(6, 384), (12, 768)])
+def test_weights_asked_for_during_attention(heads, ffn):
+    import torch
+
+    cfg = synth.Config("ahead", 5, 8 * 32, 8 * 32, (8,), 384, heads, 3, ffn, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 17)
+    images = synth.bf16_round(np.random.default_rng(9).normal(0.5, 0.25, (5, 3, cfg.H, cfg.W)).astype(np.float32))
+    many = _coarse(cfg, w, images)
+    ref = np.asarray(O.coarse_encode(images[:1], cfg.patch, w, cfg.heads)[-1]).reshape(-1, cfg.d)
+    assert float(np.abs(many[0].cpu().numpy() - ref).max() / np.abs(ref).max()) <= BAR
+    for n in (2, 4):
+        few = _coarse(synth.replace(cfg, B=n), w, images[:n])
+        assert torch.equal(few, many[:n]), n
