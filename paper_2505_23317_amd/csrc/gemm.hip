@@ -3106,6 +3106,7 @@ hipError_t launch_gemm(const void* A, const void* W, const float* bias, int N, i
                        Epilogue epi, void* out_act, float* resid, bool use_bf16,
                        const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s,
                        float scale, const void* packed) {
+  if (scale != 1.0f && !(use_bf16 && epi == Epilogue::kBias)) return hipErrorInvalidValue;   // nothing else applies it
   hipError_t e = hipSuccess;
   if (use_bf16) {
     bf16_t* o = static_cast<bf16_t*>(out_act);
@@ -3115,11 +3116,11 @@ hipError_t launch_gemm(const void* A, const void* W, const float* bias, int N, i
                           m_capacity, s, packed);
         break;
       case Epilogue::kBiasGelu:
-        e = launch_direct(A, W, N, K, EpiAct<bf16_t, kActGelu>{bias, o, N, scale}, m_ptr, m_host,
+        e = launch_direct(A, W, N, K, EpiAct<bf16_t, kActGelu>{bias, o, N, 1.0f}, m_ptr, m_host,
                           m_capacity, s, packed);
         break;
       case Epilogue::kBiasRelu:
-        e = launch_direct(A, W, N, K, EpiAct<bf16_t, kActRelu>{bias, o, N, scale}, m_ptr, m_host,
+        e = launch_direct(A, W, N, K, EpiAct<bf16_t, kActRelu>{bias, o, N, 1.0f}, m_ptr, m_host,
                           m_capacity, s, packed);
         break;
       case Epilogue::kBiasResidual:

@@ -160,11 +160,12 @@ hipError_t launch_embed(const EmbedArgs& a, const void* w, const float* bias, in
                         hipStream_t s);
 
 enum class Epilogue { kBias, kBiasGelu, kBiasRelu, kBiasResidual };
-// C = (A[M,K] . W[N,K]^T + bias) * scale (scale: bf16 path only), then per `epi`:
-//   kBias         -> out_act (activation dtype)
+// C = A[M,K] . W[N,K]^T + bias, then per `epi`:
+//   kBias         -> C * scale, out_act (activation dtype)
 //   kBiasGelu     -> GELU, out_act
 //   kBiasRelu     -> max(., 0), out_act (bf16 path only)
-//   kBiasResidual -> resid[M,N] (fp32) += result, in place (no scale)
+//   kBiasResidual -> resid[M,N] (fp32) += result, in place
+// A scale other than 1 is refused but for kBias of the bf16 path.
 hipError_t launch_gemm(const void* A, const void* W, const float* bias, int N, int K,
                        Epilogue epi, void* out_act, float* resid, bool use_bf16,
                        const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s,
