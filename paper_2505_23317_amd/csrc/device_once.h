@@ -1,5 +1,5 @@
-// Something to be done once for every device of the process (no HIP here: the tests build it
-// for the host).
+// Something to be done, or found out, once for every device of the process (no HIP here: the
+// tests build it for the host).
 #pragma once
 #include <atomic>
 #include <cstdint>
@@ -22,6 +22,24 @@ class DeviceOnce {
 
  private:
   std::atomic<uint64_t> done_{0};
+};
+
+// get(device, f): what f() returned for that device, a positive number; one that is not is returned and
+// asked for again the next time.  Threads and devices as above.
+class DeviceNumber {
+ public:
+  template <typename F>
+  int get(int device, F f) {
+    const bool known = device >= 0 && device < 64;
+    if (known)
+      if (const int n = of_[device].load(std::memory_order_relaxed); n > 0) return n;
+    const int n = f();
+    if (known && n > 0) of_[device].store(n, std::memory_order_relaxed);
+    return n;
+  }
+
+ private:
+  std::atomic<int> of_[64] = {};
 };
 
 }  // namespace cfdetr

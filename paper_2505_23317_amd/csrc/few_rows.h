@@ -140,16 +140,16 @@ __device__ __forceinline__ void few_rows_product(const bf16_t* rows, int K, int 
 // Grid for the rows expected (a quarter more workgroups, and they go on to further tiles if
 // there are more rows after all), and the row_bits that go with it: a launch costs about the
 // bytes into the XCDs at 5 TB/s and, per CU, its tiles' operands at 110 GB/s.  tiles(rows): row tiles;
-// row_bytes, part_bytes: operands of a row tile and of a part, tile_bytes: of a workgroup.
+// row_bytes, part_bytes: operands of a row tile and of a part, tile_bytes: of a workgroup; cus: of the device.
 template <typename Tiles>
 inline dim3 few_rows_grid(int rows, int m_capacity, int parts, Tiles tiles, double row_bytes, double part_bytes,
-                          double tile_bytes, int* row_bits) {
+                          double tile_bytes, int cus, int* row_bits) {
   const int m = rows > 0 && rows < m_capacity ? rows : m_capacity, t = tiles(m);
   double best = 0;
   for (int bits = 0; bits <= 3; ++bits) {
     const int rg = 1 << bits, pg = 8 >> bits;
     const long most = (long)((t + rg - 1) / rg) * ((parts + pg - 1) / pg);
-    const double us = (pg * t * row_bytes + rg * parts * part_bytes) / 5e6 + (most + 31) / 32 * tile_bytes / 110e3;
+    const double us = (pg * t * row_bytes + rg * parts * part_bytes) / 5e6 + (most + cus / 8 - 1) / (cus / 8) * tile_bytes / 110e3;
     if (bits == 0 || us < best) {
       best = us;
       *row_bits = bits;
@@ -159,10 +159,10 @@ inline dim3 few_rows_grid(int rows, int m_capacity, int parts, Tiles tiles, doub
   const int rows_x = (tiles(more) + rg - 1) / rg, parts_x = (parts + pg - 1) / pg;
   return dim3(8 * parts_x, rows_x);
 }
-inline dim3 few_rows_grid(int rows, int m_capacity, int parts, int K, int mt, int* row_bits) {
+inline dim3 few_rows_grid(int rows, int m_capacity, int parts, int K, int mt, int cus, int* row_bits) {
   const int bm = 32 * mt;
   return few_rows_grid(rows, m_capacity, parts, [=](int m) { return (m + bm - 1) / bm; }, 2.0 * bm * K, 256.0 * K,
-                       2.0 * K * (128 + bm), row_bits);
+                       2.0 * K * (128 + bm), cus, row_bits);
 }
 
 }  // namespace cfdetr

@@ -2691,19 +2691,6 @@ hipError_t launch_direct_tile(const AROWS& a, const bf16_t* w, int N, int K, con
   return hipSuccess;
 }
 
-int cu_count() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-      cus = n;
-    else
-      cus = 256;
-  }
-  return cus;
-}
-
 // Launch of the staying-workgroup form: the grid is `per_cu` workgroups per CU (what the
 // tile's LDS ring allows), a multiple of 8, and no more than the tiles the capacity yields.
 template <int BM, int BN, int NWM, int NWN, int WPE = 1, typename EP>
@@ -2731,7 +2718,7 @@ template <int MT, typename EP>
 hipError_t launch_few(const bf16_t* a, const void* packed, int N, int K, const EP& ep, const int32_t* m_ptr, int m_host,
                       int m_capacity, hipStream_t s) {
   int row_bits = 0;
-  const dim3 grid = few_rows_grid(m_host, m_capacity, N / 128, K, MT, &row_bits);
+  const dim3 grid = few_rows_grid(m_host, m_capacity, N / 128, K, MT, cu_count(), &row_bits);
   constexpr auto kern = gemm_bf16_few_kernel<MT, EP>;
   hipLaunchKernelGGL(kern, grid, dim3(256), few_rows_lds(MT), s, a, static_cast<const unsigned char*>(packed), N, K, ep, m_ptr,
                      m_host, row_bits);
@@ -2879,7 +2866,7 @@ hipError_t launch_gather(const PatchRows<TPix>& al, const void* W, int N, int K,
                          hipStream_t s) {
   const bf16_t* w = static_cast<const bf16_t*>(W);
   const long tiles128 = (long)((m_capacity + 127) / 128) * (N / 128);
-  if (N % 128 == 0 && tiles128 >= 256)
+  if (N % 128 == 0 && tiles128 >= cu_count())
     return launch_gather_tile<128, 128, 1>(al, w, N, K, ep, m_ptr, m_host, m_capacity, s);
   const long tiles32 = (long)((m_capacity + 31) / 32) * (N / 32), tiles32w = (long)((m_capacity + 31) / 32) * (N / 64);
   if (K % (4 * BK) == 0 && tiles32 <= cu_count())
@@ -2903,6 +2890,17 @@ hipError_t launch_f32(const AL& al, const void* W, int N, int K, const EP& ep,
 }
 
 }  // namespace
+
+int cu_count() {
+  static DeviceNumber cus;
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  const int n = cus.get(dev, [&] {
+    int v = 0;
+    return hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? v : 0;
+  });
+  return n > 0 ? n : 256;
+}
 
 // Width 384 would fit too (three ring buffers), but a workgroup then streams 48 KB of
 // weights per 32 rows and slab, and the pair of separate kernels is faster (measured).
@@ -3057,7 +3055,7 @@ hipError_t launch_embed(const EmbedArgs& a, const void* w, const float* bias, in
       // more 64 x 64 tiles than CUs: 64 x 128 with packed weights (2,400 tokens of 32 x 32 and width 256, 152 tiles:
       // 15.3 us, and 20.2 so)
       e = launch_patch(rows, a.packed, d, K, ep, m_ptr, m_host, m_capacity, s);
-    else if (d % 128 == 0 && tiles128 >= 256)
+    else if (d % 128 == 0 && tiles128 >= cu_count())
       e = launch_direct_tile<128, 128, 2, 2, 2, 64>(rows, wb, d, K, ep, m_ptr, m_host, m_capacity, s);
     else if ((tiles64 <= cu_count() || K >= 6144) && K % 128 == 0)
       // a workgroup per CU at most, or a very long contraction (patches of 64 x 64): two

@@ -18,6 +18,10 @@ inline hipError_t allow_lds(Kern kern, size_t bytes, DeviceOnce* once) {
   });
 }
 
+// Compute units of the current device (256 where that cannot be read): grids and tiles are chosen by them, results
+// do not depend on it.
+int cu_count();
+
 // What launch_plan writes and how (see there); also accepted by launch_select, whose last
 // workgroup then makes the plan for the run that follows (the n_prefix prefix sequences plus
 // the B token sets it has just counted).

@@ -48,3 +48,38 @@ def test_no_launcher_goes_by_a_flag_of_the_process():
     for path in glob.glob(os.path.join(CSRC, "*.hip")):
         with open(path) as f:
             assert not re.search(r"\bstatic bool\s+\w+\s*=", f.read()), path
+
+
+NUMBERS = """
+#include "device_once.h"
+#include <cstdio>
+#include <initializer_list>
+int main() {
+  static cfdetr::DeviceNumber number;
+  int calls = 0;
+  auto tell = [&](int device, int answer) {
+    const int got = number.get(device, [&] { ++calls; return answer; });
+    std::printf("%d:%d ", got, calls);
+  };
+  for (int device : {0, 0, 3, 0, 3, 63, 63}) tell(device, 100 + device);
+  for (int answer : {0, -1, 5, 6}) tell(7, answer);
+  for (int device : {64, 64, -1}) tell(device, 9);
+}
+"""
+
+
+def test_a_number_of_every_device(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no host compiler")
+    (tmp_path / "driver.cc").write_text(NUMBERS)
+    exe = str(tmp_path / "driver")
+    subprocess.run([gxx, "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(tmp_path / "driver.cc"), "-o", exe], check=True)
+    got = subprocess.run([exe], capture_output=True, text=True, check=True).stdout.split()
+    assert got == ["100:1", "100:1", "103:2", "100:2", "103:2", "163:3", "163:3", "0:4", "-1:5", "5:6", "5:6", "9:7", "9:8", "9:9"]
+
+
+def test_no_launcher_goes_by_a_number_of_the_process():
+    for path in glob.glob(os.path.join(CSRC, "*.hip")):
+        with open(path) as f:
+            assert not re.search(r"^\s+static (int|long|unsigned)\s+\w+\s*=", f.read(), re.M), path
