@@ -137,25 +137,43 @@ __device__ __forceinline__ void few_rows_product(const bf16_t* rows, int K, int 
   round(s0, std::true_type{});
 }
 
-// Grid for the rows expected (a quarter more workgroups, and they go on to further tiles if
-// there are more rows after all), and the row_bits that go with it: a launch costs about the
-// bytes into the XCDs at 5 TB/s and, per CU, its tiles' operands at 110 GB/s.  tiles(rows): row tiles;
-// row_bytes, part_bytes: operands of a row tile and of a part, tile_bytes: of a workgroup; cus: of the device.
-template <typename Tiles>
-inline dim3 few_rows_grid(int rows, int m_capacity, int parts, Tiles tiles, double row_bytes, double part_bytes,
-                          double tile_bytes, int cus, int* row_bits) {
-  const int m = rows > 0 && rows < m_capacity ? rows : m_capacity, t = tiles(m);
+// How `t` row tiles of `parts` column parts are cut for the XCDs (XcdTiles): row_bits, and the tiles of the XCD
+// with the most.  A launch costs about the bytes into the XCDs at 5 TB/s and, per CU, its tiles' operands at
+// 110 GB/s.  row_bytes, part_bytes: operands of a row tile and of a part, tile_bytes: of a workgroup; cus: of
+// the device.
+struct FewCut {
+  int row_bits;
+  long most;
+};
+inline FewCut few_rows_cut(int t, int parts, double row_bytes, double part_bytes, double tile_bytes, int cus) {
+  const int per_xcd = cus < 8 ? 1 : cus / 8;
+  FewCut cut{};
   double best = 0;
   for (int bits = 0; bits <= 3; ++bits) {
     const int rg = 1 << bits, pg = 8 >> bits;
     const long most = (long)((t + rg - 1) / rg) * ((parts + pg - 1) / pg);
-    const double us = (pg * t * row_bytes + rg * parts * part_bytes) / 5e6 + (most + cus / 8 - 1) / (cus / 8) * tile_bytes / 110e3;
+    const double us = (pg * t * row_bytes + rg * parts * part_bytes) / 5e6 + (most + per_xcd - 1) / per_xcd * tile_bytes / 110e3;
     if (bits == 0 || us < best) {
       best = us;
-      *row_bits = bits;
+      cut = {bits, most};
     }
   }
-  const int rg = 1 << *row_bits, pg = 8 >> *row_bits, more = m + m / 4 < m_capacity ? m + m / 4 : m_capacity;
+  return cut;
+}
+// Of a contraction N x K, 32 mt rows a tile.
+inline FewCut few_rows_cut(int m, int N, int K, int mt, int cus) {
+  const int bm = 32 * mt;
+  return few_rows_cut((m + bm - 1) / bm, N / 128, 2.0 * bm * K, 256.0 * K, 2.0 * K * (128 + bm), cus);
+}
+
+// Grid for the rows expected: a quarter more workgroups, and they go on to further tiles if there are more
+// rows after all.  tiles(rows): row tiles.
+template <typename Tiles>
+inline dim3 few_rows_grid(int rows, int m_capacity, int parts, Tiles tiles, double row_bytes, double part_bytes,
+                          double tile_bytes, int cus, int* row_bits) {
+  const int m = rows > 0 && rows < m_capacity ? rows : m_capacity, more = m + m / 4 < m_capacity ? m + m / 4 : m_capacity;
+  *row_bits = few_rows_cut(tiles(m), parts, row_bytes, part_bytes, tile_bytes, cus).row_bits;
+  const int rg = 1 << *row_bits, pg = 8 >> *row_bits;
   const int rows_x = (tiles(more) + rg - 1) / rg, parts_x = (parts + pg - 1) / pg;
   return dim3(8 * parts_x, rows_x);
 }
@@ -163,6 +181,32 @@ inline dim3 few_rows_grid(int rows, int m_capacity, int parts, int K, int mt, in
   const int bm = 32 * mt;
   return few_rows_grid(rows, m_capacity, parts, [=](int m) { return (m + bm - 1) / bm; }, 2.0 * bm * K, 256.0 * K,
                        2.0 * K * (128 + bm), cus, row_bits);
+}
+
+// Row tiles of 32 that a workgroup of gemm_bf16_few_kernel takes for m rows of an N x K contraction (`gelu`: with that
+// activation behind it), or 0: the kernels for more rows.  32 rows as long as no CU gets two workgroups, else 64 as long as none
+// does, else 32 with two.  What counts is the fullest XCD: with fewer tiles than CUs it may still have more than
+// its share (41 tiles of 6 parts are 33 at best).  In us, 32 rows / 64 rows / packed tiles (gemm_bf16_packed_kernel),
+// N x K = 768 x 3072: 1,200 rows 13.5 / 15.7 / 24.1, 1,300 rows 20.0 / 15.9 / 24.2, 2,200 rows 22.5 / 19.0 / 24.7, 2,600
+// rows 23.6 / 28.9 / 25.1, 2,700 rows 31.0 / 30.4 / 25.4; 768 x 768: 1,200 rows 5.6 / 7.1 / 9.0, 2,200 rows 8.5 / 7.7 /
+// 9.4, 2,600 rows 9.1 / 12.6 / 9.8, 2,700 rows 11.1 / 12.2 / 10.0; 2304 x 768: 300 rows 5.1 / 6.2 / 8.2, 700 rows
+// 7.7 / 6.8 / 8.3, 800 rows 7.8 / 9.4 / 8.7, 900 rows 10.5 / 10.4 / 8.8.
+// Then 64 rows with two workgroups a CU
+//  - where the activation is behind it, which a tile of 64 x 256 does with half as many wavefronts: 3072 x 768 (packed weights
+//    past an XCD's 4 MB of L2, too): 700 rows 10.6 / 10.5 / 12.1, 1,000 rows 11.3 / 11.6 / 12.3, 1,300 rows 14.9 /
+//    12.2 / 14.9, 1,400 rows 17.2 / 15.5 / 14.8; 6144 x 768: 530 rows 13.3 / 12.0 / 17.2; 2304 x 384: 1,420
+//    rows 9.9 / 8.2 / 11.6; even at 2304 x 768, and 1536 x 768, 2,000 rows, 11.3 / 11.2 / 10.9;
+//  - where the packed tiles do not fit (N no multiple of 256; the third figure is then for tiles with the weights through the LDS)
+//    over a long K and the CUs are three quarters full: 384 x 3072: 6,400 rows 31.9 / 31.4 / 28.7, 8,500 rows
+//    42.1 / 31.6 / 36.1, 10,700 rows 46.0 / 34.6 / 39.6, 10,900 rows 51.3 / 44.5 / 39.5.
+inline int few_rows_tiles(int m, int N, int K, bool gelu, int cus) {
+  const long per_xcd = cus < 8 ? 1 : cus / 8;
+  const long most1 = few_rows_cut(m, N, K, 1, cus).most, most2 = few_rows_cut(m, N, K, 2, cus).most;
+  if (most1 <= per_xcd) return 1;
+  if (most2 <= per_xcd) return 2;
+  if (most1 <= 2 * per_xcd) return 1;
+  if (most2 <= 2 * per_xcd && ((gelu && N >= 2304) || (N % 256 != 0 && K >= 2048 && 2 * most2 > 3 * per_xcd))) return 2;
+  return 0;
 }
 
 }  // namespace cfdetr

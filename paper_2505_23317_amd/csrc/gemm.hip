@@ -2805,18 +2805,10 @@ hipError_t launch_direct(const void* A, const void* W, int N, int K, const EP& e
   const long rounds192 = (tiles192 + cus - 1) / cus, rounds192n = (tiles192n + 2 * cus - 1) / (2 * cus);
   const long t128 = 100 * rounds128, t192n = 150 * rounds192n;
   const bool narrow_ok = N % 128 == 0 && tiles128 >= cus;
-  // Few rows: 32 or 64 rows a workgroup as long as no CU gets two, then tiles of 64 rows and more by 256
-  // columns.  In us, 32 rows / 64 rows / those tiles, N x K = 768 x 3072: 1000 rows 12.9 / 15.5 / 24.2, 2000
-  // rows 22.7 / 16.9 / 24.6, 2700 rows 31.6 / 30.2 / 25.4; 768 x 768: 1000 rows 5.8 / 7.4 / 9.2, 2000 rows
-  // 9.0 / 7.9 / 9.7, 2700 rows 11.3 / 12.2 / 10.1; 2304 x 768: 257 rows 5.3 / 6.4 / 8.4, 700 rows 8.1 / 7.1 /
-  // 9.1, 1000 rows - / 10.6 / 9.2; 3072 x 768: 400 rows 8.3 / 7.0 / 10.7, 700 rows - / 10.9 / 12.3, 1000 rows
-  // - / 12.0 / 12.5.  Where those do not fit (a width of 384 over K >= 2048) 64 rows up to two a CU: 768 x
-  // 3072, 4800 rows 39.1, and 43.7 with the weights through the LDS.
   if (packed && few_rows_supported(N, K)) {
-    const long few32 = (long)((m + 31) / 32) * (N / 128), few64 = (long)((m + 63) / 64) * (N / 128);
-    if (few32 <= cus) return launch_few<1>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
-    if (few64 <= cus || (N % 256 != 0 && K >= 2048 && few64 <= 2 * cus))
-      return launch_few<2>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+    const int tiles = few_rows_tiles(m, N, K, std::is_same_v<EP, EpiAct<bf16_t, kActGelu>>, (int)cus);
+    if (tiles == 1) return launch_few<1>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+    if (tiles == 2) return launch_few<2>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
   }
   if (packed && N % 256 == 0 && K % 128 == 0)
     return launch_packed(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, m, s);

@@ -1,4 +1,5 @@
-"""Host side of the kernels' launchers, without a GPU: arguments that no kernel applies are refused."""
+"""Host side of the kernels' launchers, without a GPU: arguments that no kernel applies are refused; which kernel
+contractions of few rows go to."""
 import os
 import subprocess
 
@@ -7,7 +8,7 @@ import pytest
 from paper_2505_23317_amd import build
 
 DRIVER = """
-#include "kernels.h"
+#include "few_rows.h"
 #include <cstdio>
 using namespace cfdetr;
 int main() {
@@ -16,8 +17,19 @@ int main() {
       if (!(bf16 && epi == Epilogue::kBias))
         std::printf("scale %d\\n", (int)launch_gemm(nullptr, nullptr, nullptr, 64, 64, epi, nullptr, nullptr, bf16 != 0, nullptr,
                                                    64, 64, nullptr, 0.5f));
+  const int shapes[][3] = {SHAPES};
+  for (const auto& n : shapes)
+    for (int m = 1; m <= 12000; m += m % 10 == 0 ? 1 : 9)
+      for (int cus : {256, 64}) {
+        const FewCut one = few_rows_cut(m, n[0], n[1], 1, cus), two = few_rows_cut(m, n[0], n[1], 2, cus);
+        std::printf("tiles %d %d %d %d %d %d %d %d\\n", n[0], n[1], n[2], m, cus, one.row_bits, two.row_bits,
+                    few_rows_tiles(m, n[0], n[1], n[2] != 0, cus));
+      }
 }
 """
+# N, K, GELU behind it
+SHAPES = [(768, 768, 0), (768, 3072, 0), (2304, 768, 0), (3072, 768, 1), (1536, 768, 1), (768, 1536, 0), (384, 3072, 0),
+          (2304, 384, 1), (1152, 384, 0)]
 
 
 @pytest.fixture(scope="module")
@@ -27,7 +39,7 @@ def lines(tmp_path_factory):
     if not all(os.path.exists(o) for o in objects):
         pytest.skip("the library has not been built here")
     at = tmp_path_factory.mktemp("rules")
-    (at / "driver.hip").write_text(DRIVER)
+    (at / "driver.hip").write_text(DRIVER.replace("SHAPES", ", ".join("{%d, %d, %d}" % s for s in SHAPES)))
     hipcc = [build._hipcc(), "--offload-arch=gfx950"]
     for cmd in ([*hipcc, "-std=c++17", "-I", build.CSRC, "-c", str(at / "driver.hip"), "-o", str(at / "driver.o")],
                 [*hipcc, str(at / "driver.o"), *objects, "-o", str(at / "driver")]):
@@ -41,3 +53,39 @@ def lines(tmp_path_factory):
 def test_a_factor_that_nothing_applies_is_refused(lines):
     """The activations, the residual form and the fp32 path have no factor: 1 is hipErrorInvalidValue."""
     assert [v for k, *v in lines if k == "scale"] == [["1"]] * 7
+
+
+def _fullest(m, N, height, bits):
+    """Tiles of the XCD with the most, as XcdTiles deals them: workgroup by workgroup."""
+    tiles, parts, most = -(-m // height), N // 128, 0
+    for xcd in range(8):
+        rg, pg, part_bits = xcd & ((1 << bits) - 1), xcd >> bits, 3 - bits
+        rows = ((tiles * (rg + 1)) >> bits) - ((tiles * rg) >> bits)
+        most = max(most, rows * (((parts * (pg + 1)) >> part_bits) - ((parts * pg) >> part_bits)))
+    return most
+
+
+def test_few_rows_go_where_no_cu_gets_two(lines):
+    """32 rows a workgroup, else 64, as long as no CU of any XCD gets a second workgroup; two only by the rules that
+    the comment at few_rows_tiles has figures for."""
+    seen = set()
+    for k, *v in lines:
+        if k != "tiles":
+            continue
+        N, K, gelu, m, cus, bits1, bits2, got = map(int, v)
+        share = cus // 8
+        one, two = _fullest(m, N, 32, bits1), _fullest(m, N, 64, bits2)
+        want = 1 if one <= share else 2 if two <= share else 1 if one <= 2 * share else 0
+        if want == 0 and two <= 2 * share and (gelu and N >= 2304 or N % 256 and K >= 2048 and 2 * two > 3 * share):
+            want = 2
+        assert got == want, (N, K, gelu, m, cus, one, two)
+        seen.add((got, one <= share, two <= share))
+    assert seen == {(1, True, True), (2, False, True), (1, False, False), (2, False, False), (0, False, False)}
+
+
+# rows at which one of the forms is the fastest by a tenth and more, of those that do not fit into one workgroup a CU
+@pytest.mark.parametrize("N, K, gelu, m, tiles", [
+    (768, 3072, 0, 1300, 2), (768, 3072, 0, 2700, 0), (768, 768, 0, 2700, 0), (2304, 768, 0, 900, 0), (3072, 768, 1, 700, 2),
+    (3072, 768, 1, 1300, 2), (2304, 384, 1, 1420, 2), (384, 3072, 0, 8500, 2), (384, 3072, 0, 10900, 0)])
+def test_few_rows_by_the_figures(lines, N, K, gelu, m, tiles):
+    assert ["tiles", *map(str, (N, K, gelu, m, 256))] + [str(tiles)] in [v[:6] + v[8:] for v in lines]
