@@ -32,8 +32,15 @@ struct SmallArgs {
 // last layer (which ends in the final LayerNorm).
 constexpr int kHead = 0, kMid = 1, kLast = 2;
 
+// Rows, hidden rows, statistics, and the vectors: b_o, ln2_g, ln2_b, b2, b1, and ln_g, ln_b, b_qkv, which at width 128
+// take b1's place when the hidden units are done.  With a place of their own F = 1024 left room for one
+// workgroup a CU there (83,456 bytes against 80,896).  At width 64 there is room, and writing them that late costs 0.2 us.
+constexpr bool small_shares(int D) { return D == 128; }
 template <int D>
-constexpr int small_lds(int F) { return 32 * D * 2 + 32 * F * 2 + 32 * 8 * 4 + (9 * D + F) * 4; }
+constexpr int small_lds(int F) {
+  return 32 * D * 2 + 32 * F * 2 + 32 * 8 * 4 + (4 * D + (!small_shares(D) ? F + 5 * D : F > 5 * D ? F : 5 * D)) * 4;
+}
+static_assert(small_lds<64>(kSmallMaxF) <= 80 * 1024 && small_lds<128>(kSmallMaxF) <= 80 * 1024, "two workgroups a CU");
 
 // 16-byte chunks of an LDS row of `bytes` bytes are XORed by this, so that operand reads of 16
 // rows hit disjoint banks.
@@ -84,6 +91,9 @@ __device__ __forceinline__ void small_stats(const f32x16& x, float* s_red, int l
 // start: rows, residual, vectors, and the first eight weight operands a wavefront needs of each of
 // the four matrices (all there are at width 64 and F = 128); what is left of larger ones follows
 // behind the MFMAs.  80 rows of width 64, F = 128: 11 launches -> 3 an encoder of one layer, 29 -> 16 us.
+// No row limit: encoders of six layers in us, seven kernels a layer / this, 960 rows: width 64, F = 128 177 / 101, F = 1024
+// 216 / 142, width 128, F = 128 193 / 121, F = 1024 238 / 199; 65,536 rows: 657 / 462, 944 / 751, 961 / 769, 1,332 /
+// 1,339 (with one workgroup a CU 1,503); width 128, F = 512 1,123 / 1,017, F = 768 1,229 / 1,178.
 // A row's result does not depend on the others, so no other form has to match this one's bits.
 template <int D, int kKind>
 __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
@@ -93,8 +103,9 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
   unsigned char* const sA = smem;
   unsigned char* const sH = smem + 32 * ROWB;
   float* const s_red = reinterpret_cast<float*>(sH + 32 * HROWB);
-  float* const s_vec = s_red + 32 * 8;   // [ln_g][ln_b][b_qkv: 3 D] [b_o][ln2_g][ln2_b][b2][b1: F]
-  float* const v_mid = s_vec + 5 * D;
+  constexpr bool kLate = small_shares(D) && kKind != kHead;
+  float* const s_vec = s_red + 32 * 8 + (small_shares(D) ? 4 * D : 0);   // [ln_g][ln_b][b_qkv: 3 D]
+  float* const v_mid = small_shares(D) ? s_vec - 4 * D : s_vec + 5 * D;  // [b_o][ln2_g][ln2_b][b2][b1: F]
 
   const int M = p.m_ptr ? *p.m_ptr : p.m_host;
   const int m0 = blockIdx.x * 32;
@@ -166,8 +177,10 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
     vpos = p.vt_pos[m];
   }
   if (tid < D / 4) {
-    *reinterpret_cast<float4*>(s_vec + tid * 4) = vg;
-    *reinterpret_cast<float4*>(s_vec + D + tid * 4) = vb;
+    if (!kLate) {
+      *reinterpret_cast<float4*>(s_vec + tid * 4) = vg;
+      *reinterpret_cast<float4*>(s_vec + D + tid * 4) = vb;
+    }
     if (kKind != kHead) {
       *reinterpret_cast<float4*>(v_mid + tid * 4) = vo;
       *reinterpret_cast<float4*>(v_mid + D + tid * 4) = vg2;
@@ -175,7 +188,7 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
       *reinterpret_cast<float4*>(v_mid + 3 * D + tid * 4) = vd;
     }
   }
-  if (kKind != kLast && tid < 3 * D / 4) *reinterpret_cast<float4*>(s_vec + 2 * D + tid * 4) = vq;
+  if (!kLate && kKind != kLast && tid < 3 * D / 4) *reinterpret_cast<float4*>(s_vec + 2 * D + tid * 4) = vq;
   if (kKind != kHead && tid < F / 4) *reinterpret_cast<float4*>(v_mid + 4 * D + tid * 4) = v1;
 
   auto operand = [&](const unsigned char* rows, int bytes, int ks) {
@@ -256,7 +269,7 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
                        pack_bf16x2(gelu_fast(r[4 * q + 2]), gelu_fast(r[4 * q + 3])));
     });
     residual_split(x, hi);
-    __syncthreads();
+    __syncthreads();   // hidden units are complete, and their biases have been read
     if (holds) {
 #pragma nounroll
       for (int k0 = 0; k0 < F / 16; k0 += 8) {
@@ -270,6 +283,13 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
           for (int i = 0; i < 8; ++i) r2[i] = weights(p.w2, F, xw * 32, k0 + 8 + i);
         }
       }
+    }
+    if (kLate) {   // (a barrier of small_stats is in front of their readers)
+      if (tid < D / 4) {
+        *reinterpret_cast<float4*>(s_vec + tid * 4) = vg;
+        *reinterpret_cast<float4*>(s_vec + D + tid * 4) = vb;
+      }
+      if (kKind != kLast && tid < 3 * D / 4) *reinterpret_cast<float4*>(s_vec + 2 * D + tid * 4) = vq;
     }
     join(v_mid + 3 * D);
     if (kKind == kMid && holds && in) {

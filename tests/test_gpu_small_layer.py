@@ -40,3 +40,20 @@ def test_rows_alone_and_in_a_batch(d, heads, ffn, cells):
         assert torch.equal(_coarse(synth.replace(cfg, B=1), w, images[f:f + 1])[0], many[f]), f
     ref = np.asarray(O.coarse_encode(images[frames - 1:], cfg.patch, w, cfg.heads)[-1]).reshape(-1, d)
     assert float(np.abs(many[-1].cpu().numpy() - ref).max() / np.abs(ref).max()) <= BAR
+
+
+# the largest hidden block there is, two workgroups a CU: 32,000 rows are two rounds of them and more
+@pytest.mark.parametrize("d, heads", [(64, 2), (128, 4)])
+def test_largest_hidden_block_over_many_rows(d, heads):
+    import torch
+
+    frames = 32
+    cfg = synth.Config("small", frames, 8 * 8, 8 * 125, (8,), d, heads, 2, 1024, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 29)
+    images = synth.bf16_round(np.random.default_rng(7).normal(0.5, 0.25, (frames, 3, cfg.H, cfg.W)).astype(np.float32))
+    many = _coarse(cfg, w, images)
+    assert torch.isfinite(many).all()
+    for f in (0, frames // 2, frames - 1):
+        assert torch.equal(_coarse(synth.replace(cfg, B=1), w, images[f:f + 1])[0], many[f]), f
+    ref = np.asarray(O.coarse_encode(images[frames - 1:], cfg.patch, w, cfg.heads)[-1]).reshape(-1, d)
+    assert float(np.abs(many[-1].cpu().numpy() - ref).max() / np.abs(ref).max()) <= BAR
