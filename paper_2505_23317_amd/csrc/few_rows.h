@@ -166,6 +166,35 @@ inline FewCut few_rows_cut(int m, int N, int K, int mt, int cus) {
   return few_rows_cut((m + bm - 1) / bm, N / 128, 2.0 * bm * K, 256.0 * K, 2.0 * K * (128 + bm), cus);
 }
 
+// Operands of slim_norm_kernel in bytes: of a row tile, of a workgroup's `per` parts, and of both, with the
+// projection's weights where there is one (few_rows_cut).
+struct SlimBytes {
+  double row, part, tile;
+};
+inline SlimBytes slim_bytes(int d, int per, bool project) {
+  return {(project ? 6.0 : 4.0) * 32 * d, 256.0 * d * per, 2.0 * d * ((project ? d : 0) + 128.0 * per)};
+}
+
+// Parts of a workgroup of slim_norm_kernel.  It streams the weights of the projection (a matrix of D rows) and
+// those of its parts, and is some 200 columns' worth of stream late at the start; what counts is what the
+// busiest CU of the fullest XCD has, and fewer workgroups where that is the same.  (With tiles shared out over all CUs
+// instead, encoder passes of width 384, 8 layers, F = 1536: 660 rows 287 and 267 us, 1,300 rows 325 and 297, 2,600 rows
+// 418 and 378, the last with slim_residual_kernel's 64 rows by the same count.)
+inline int parts_of_a_share(int tiles, int parts, int d, bool project, int cus) {
+  int per = parts;
+  long least = 0;
+  for (int n = parts; n >= 1; --n) {
+    const SlimBytes b = slim_bytes(d, n, project);
+    const long cut = few_rows_cut(tiles, (parts + n - 1) / n, b.row, b.part, b.tile, cus).most, per_xcd = cus < 8 ? 1 : cus / 8;
+    const long most = (cut + per_xcd - 1) / per_xcd * ((project ? d : 0) + 200 + n * 128);
+    if (n == parts || most < least) {
+      least = most;
+      per = n;
+    }
+  }
+  return per;
+}
+
 // Grid for the rows expected: a quarter more workgroups, and they go on to further tiles if there are more
 // rows after all.  tiles(rows): row tiles.
 template <typename Tiles>

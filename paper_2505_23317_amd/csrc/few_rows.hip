@@ -386,26 +386,6 @@ __global__ __launch_bounds__(256) void slim_pack_kernel(const bf16_t* __restrict
 
 }  // namespace
 
-namespace {
-
-// Parts of a workgroup of slim_norm_kernel.  It streams the weights of the projection (project of its D rows) and
-// those of its parts, and is some 200 columns' worth of stream late at the start; what counts is what the
-// busiest CU has, and fewer workgroups where that is the same.
-int parts_of_a_share(int tiles, int parts, int project, int cus) {
-  int per = parts;
-  long least = 0;
-  for (int n = parts; n >= 1; --n) {
-    const long most = ((long)tiles * ((parts + n - 1) / n) + cus - 1) / cus * (project + 200 + n * 128);
-    if (n == parts || most < least) {
-      least = most;
-      per = n;
-    }
-  }
-  return per;
-}
-
-}  // namespace
-
 bool few_rows_supported(int N, int K) { return N % 128 == 0 && K % (16 * kFewRing) == 0; }
 
 uint64_t slim_packed_bytes(uint64_t N, uint64_t K) { return N * K * 2 + kSlimPad * 1024; }
@@ -448,7 +428,7 @@ hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int 
   if (step == SlimStep::kDown) {
     p.K = F;
     // 64 rows a workgroup where 32 would give CUs a second one (3,520 rows: 14 -> 9 us)
-    const int mt = (m + 31) / 32 * (d / 128) > cus ? 2 : 1;
+    const int mt = few_rows_cut(m, d, F, 1, cus).most > cus / 8 ? 2 : 1;
     const dim3 grid = few_rows_grid(rows, m_capacity, d / 128, F, mt, cus, &p.row_bits);
     if (mt == 2) hipLaunchKernelGGL((slim_residual_kernel<384, 2>), grid, dim3(256), few_rows_lds(2), s, p);
     else hipLaunchKernelGGL((slim_residual_kernel<384, 1>), grid, dim3(256), few_rows_lds(1), s, p);
@@ -458,10 +438,10 @@ hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int 
   const bool project = step == SlimStep::kOutHidden || step == SlimStep::kOutQuery;
   p.parts = (step == SlimStep::kOutHidden ? F : qkv ? 3 * d : d) / 128;
   if (p.parts * 128 > kSlimMaxN) return hipErrorInvalidValue;
-  p.per_share = parts_of_a_share((m + 31) / 32, p.parts, project ? d : 0, cus);
+  p.per_share = parts_of_a_share((m + 31) / 32, p.parts, d, project, cus);
   p.shares = (p.parts + p.per_share - 1) / p.per_share;
-  const dim3 grid = few_rows_grid(rows, m_capacity, p.shares, [](int r) { return (r + 31) / 32; }, (project ? 6.0 : 4.0) * 32 * d,
-                                  256.0 * d * p.per_share, 2.0 * d * ((project ? d : 0) + 128.0 * p.per_share), cus, &p.row_bits);
+  const SlimBytes b = slim_bytes(d, p.per_share, project);
+  const dim3 grid = few_rows_grid(rows, m_capacity, p.shares, [](int r) { return (r + 31) / 32; }, b.row, b.part, b.tile, cus, &p.row_bits);
   auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p); };
   switch (step) {
     case SlimStep::kFirstQkv: launch(slim_norm_kernel<384, kFirst>); break;

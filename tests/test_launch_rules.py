@@ -25,6 +25,16 @@ int main() {
         std::printf("tiles %d %d %d %d %d %d %d %d\\n", n[0], n[1], n[2], m, cus, one.row_bits, two.row_bits,
                     few_rows_tiles(m, n[0], n[1], n[2] != 0, cus));
       }
+  for (int project = 0; project < 2; ++project)
+    for (int parts = 1; parts <= 16; ++parts)
+      for (int tiles = 1; tiles <= 120; ++tiles) {
+        std::printf("share %d %d %d %d", project, parts, tiles, parts_of_a_share(tiles, parts, 384, project != 0, 256));
+        for (int n = 1; n <= parts; ++n) {
+          const SlimBytes b = slim_bytes(384, n, project != 0);
+          std::printf(" %d", few_rows_cut(tiles, (parts + n - 1) / n, b.row, b.part, b.tile, 256).row_bits);
+        }
+        std::printf("\\n");
+      }
 }
 """
 # N, K, GELU behind it
@@ -81,6 +91,17 @@ def test_few_rows_go_where_no_cu_gets_two(lines):
         assert got == want, (N, K, gelu, m, cus, one, two)
         seen.add((got, one <= share, two <= share))
     assert seen == {(1, True, True), (2, False, True), (1, False, False), (2, False, False), (0, False, False)}
+
+
+def test_shares_of_a_row_tile(lines):
+    """Of all splits of the parts the one that leaves the busiest CU the least, its columns and a start of 200."""
+    for k, *v in lines:
+        if k != "share":
+            continue
+        project, parts, tiles, got, *bits = map(int, v)
+        cost = [-(-_fullest(32 * tiles, 128 * -(-parts // n), 32, bits[n - 1]) // 32) * (384 * project + 200 + 128 * n)
+                for n in range(1, parts + 1)]
+        assert cost[got - 1] == min(cost), (project, parts, tiles)
 
 
 # rows at which one of the forms is the fastest by a tenth and more, of those that do not fit into one workgroup a CU
