@@ -1,6 +1,6 @@
 // Layers of width 384 when there are few rows: wide_layer_kernel (layer.hip) gives every row to
-// one CU, which streams all the weights of the layer past it; below some two thousand rows most
-// CUs would have none.  Here a layer is three launches, each spread over the chip, with the same
+// one CU, which streams all the weights of the layer past it; up to 15 rows a CU (3,840 rows on 256 CUs) half of the
+// CUs and more would have none.  Here a layer is three launches, each spread over the chip, with the same
 // arithmetic in the same order (sums that start at the bias or at the residual's low part, its
 // LayerNorm), so that a row's result does not depend on how many others there are.
 #include "few_rows.h"
@@ -10,7 +10,6 @@ namespace cfdetr {
 
 namespace {
 
-constexpr int kSlimPad = 32;   // blocks of 1 KB the weight rings read ahead of the end
 constexpr int kAhead = 5;         // k-steps that operands are asked for ahead of their MFMAs (few_rows.h)
 constexpr int kSlimMaxN = 2048;   // widest second matrix of slim_norm_kernel (its bias is in LDS)
 
@@ -388,7 +387,7 @@ __global__ __launch_bounds__(256) void slim_pack_kernel(const bf16_t* __restrict
 
 bool few_rows_supported(int N, int K) { return N % 128 == 0 && K % (16 * kFewRing) == 0; }
 
-uint64_t slim_packed_bytes(uint64_t N, uint64_t K) { return N * K * 2 + kSlimPad * 1024; }
+uint64_t slim_packed_bytes(uint64_t N, uint64_t K) { return N * K * 2; }
 
 hipError_t launch_slim_pack(const void* W, uint64_t N, int K, void* packed, hipStream_t s) {
   const long units = (long)(N * K / 8);
