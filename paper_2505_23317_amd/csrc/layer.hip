@@ -645,18 +645,19 @@ hipError_t launch_wide_pack(const void* Wo, const void* W1, const void* W2, cons
 // that; a workgroup of 96 rows has a CU to itself, one of 64 shares it with a second one,
 // whose vector work then runs under its MFMAs, and is the best where CUs get several.
 // Encoder passes of 4 layers over frames of 1,024 tokens in us, at 32 / 64 / 96 rows, F = 1536:
-// 8,192 rows 309 / 348 / 444; 16,384 rows 519 / 470 / 561; 24,576 rows 775 / 697 / 692; 32,768 rows
-// 1003 / 857 / 1077.  The same with F from 256 to 2048, but for 96 rows up to F = 512 (24,576 rows
-// 573 / 541 / 555).
+// 8,192 rows 309 / 348 / 444; 16,384 rows 519 / 470 / 561; 24,576 rows 762 / 690 / 654; 32,768 rows
+// 1003 / 857 / 1077.  The same with F from 256 to 2048: 24,576 rows at F = 256 520 / 498 / 488, at 512 552 / 526 / 518, at
+// 768 599 / 567 / 550; 18,432 rows at 512 478 / 460 / 444.
 //
 // Width 256: a workgroup of eight wavefronts fills a CU at every height, so the rounds of the
 // busiest CU times what one costs decide.  A layer costs 19, 26 and 37 us at F = 1024, 12, 17 and 24
 // at 256, 29, 39 and 55 at 2048: 1 : 1.4 : 1.95 at all of them, and only the ratio counts.  Passes as
 // above, F = 1024: 8,192 rows 200 / 220 / 257; 16,384 rows 347 / 306 / 340; 24,576 rows 501 / 490 /
-// 438; 32,768 rows 660 / 592 / 657.  At F = 256, 512, 1536 and 2048 the same heights win.
+// 438; 32,768 rows 660 / 592 / 657; 102,400 rows 2,238 / 2,001 / 2,014; 112,896 rows 2,524 / 2,217 / 2,228.  At F =
+// 256, 512, 1536 and 2048 the same heights win.
 int wide_layer_tiles(int d, int rows, int cus) {
   if (d == 256) {
-    const int cost[3] = {19, 26, 36};
+    const int cost[3] = {19, 26, 37};
     int best = 1;
     long least = 0;
     for (int mt = 1; mt <= 3; ++mt) {

@@ -25,6 +25,9 @@ int main() {
         std::printf("tiles %d %d %d %d %d %d %d %d\\n", n[0], n[1], n[2], m, cus, one.row_bits, two.row_bits,
                     few_rows_tiles(m, n[0], n[1], n[2] != 0, cus));
       }
+  for (int d : {256, 384})
+    for (int rows : {8192, 16384, 18432, 24576, 32768, 102400, 112896})
+      std::printf("height %d %d %d\\n", d, rows, wide_layer_tiles(d, rows, 256));
   for (int project = 0; project < 2; ++project)
     for (int parts = 1; parts <= 16; ++parts)
       for (int tiles = 1; tiles <= 120; ++tiles) {
@@ -110,3 +113,13 @@ def test_shares_of_a_row_tile(lines):
     (3072, 768, 1, 1300, 2), (2304, 384, 1, 1420, 2), (384, 3072, 0, 8500, 2), (384, 3072, 0, 10900, 0)])
 def test_few_rows_by_the_figures(lines, N, K, gelu, m, tiles):
     assert ["tiles", *map(str, (N, K, gelu, m, 256))] + [str(tiles)] in [v[:6] + v[8:] for v in lines]
+
+
+def test_rows_of_a_layer_workgroup_by_the_figures(lines):
+    """The fastest of 32, 64 and 96 rows at the row counts that the comment at wide_layer_tiles has figures for."""
+    got = {(int(d), int(rows)): int(mt) for k, *v in lines if k == "height" for d, rows, mt in [v]}
+    want = {256: {8192: 1, 16384: 2, 24576: 3, 32768: 2, 102400: 2, 112896: 2},
+            384: {8192: 1, 16384: 2, 18432: 3, 24576: 3, 32768: 2}}
+    for d, heights in want.items():
+        for rows, mt in heights.items():
+            assert got[d, rows] == mt, (d, rows)
