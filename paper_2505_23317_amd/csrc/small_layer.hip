@@ -57,12 +57,15 @@ __device__ __forceinline__ void small_stats(const f32x16& x, float* s_red, int l
 #pragma unroll
     for (int q = 0; q < 4; ++q) s += (x[4 * q] + x[4 * q + 1]) + (x[4 * q + 2] + x[4 * q + 3]);
     s += __shfl_xor(s, 32, kWave);
-    float v = 0.f;
+    // in pairs, as layernorm4_kernel has them: one after the other the sixteen squares leave a row 3 % more of rounding
+    float v4[4];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float e = fmaf(s, -1.0f / 32, x[r]);
-      v = fmaf(e, e, v);
+    for (int q = 0; q < 4; ++q) {
+      const float e0 = fmaf(s, -1.0f / 32, x[4 * q]), e1 = fmaf(s, -1.0f / 32, x[4 * q + 1]);
+      const float e2 = fmaf(s, -1.0f / 32, x[4 * q + 2]), e3 = fmaf(s, -1.0f / 32, x[4 * q + 3]);
+      v4[q] = fmaf(e0, e0, e1 * e1) + fmaf(e2, e2, e3 * e3);
     }
+    float v = (v4[0] + v4[1]) + (v4[2] + v4[3]);
     v += __shfl_xor(v, 32, kWave);
     if (g == 0) {
       s_red[l32 * 8 + wave] = s;
@@ -70,19 +73,23 @@ __device__ __forceinline__ void small_stats(const f32x16& x, float* s_red, int l
     }
   }
   __syncthreads();
-  float sum = 0.f, within = 0.f, between = 0.f;
+  // The parts' squares in pairs, and what their last sum is rounded by with the distances of the means: as few
+  // roundings at the sum's magnitude as layernorm4_kernel has.
+  float s[NP], v[NP], between = 0.f;
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
-    sum += s_red[l32 * 8 + k];
-    within += s_red[l32 * 8 + 4 + k];
+    s[k] = s_red[l32 * 8 + k];
+    v[k] = s_red[l32 * 8 + 4 + k];
   }
-  mean = sum / D;
+  mean = (NP == 2 ? s[0] + s[1] : (s[0] + s[1]) + (s[NP - 2] + s[NP - 1])) / D;
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
-    const float d = fmaf(mean, -32.0f, s_red[l32 * 8 + k]);
+    const float d = fmaf(mean, -32.0f, s[k]);
     between = fmaf(d, d, between);
   }
-  rstd = rsqrtf(fmaf(fmaf(between, 1.0f / 32, within), 1.0f / D, eps));
+  const float a = NP == 2 ? v[0] : v[0] + v[1], b = NP == 2 ? v[1] : v[NP - 2] + v[NP - 1];
+  const float sq = a + b, b_in = sq - a, rest = (a - (sq - b_in)) + (b - b_in);
+  rstd = rsqrtf(fmaf(sq, 1.0f / D, fmaf(fmaf(between, 1.0f / 32, rest), 1.0f / D, eps)));
 }
 
 // 32 complete rows a workgroup of four wavefronts.  At these widths nothing is a rate: as kernels of
