@@ -41,7 +41,7 @@ def test_every_form_gives_the_same_bits(patch, rows, cols, d, frames):
         assert torch.equal(_embed(synth.replace(cfg, B=n), w, images[:n])[0], few[0]), n
 
 
-# 2 x 12 small tiles, two rounds and three of them on 256 CUs (there 128 x 128 tiles)
+# few tokens: 2 x 12 tiles of 64 x 64 and smaller; 35 and 40 frames: the kernel with packed weights (gemm_bf16_patch_kernel)
 @pytest.mark.parametrize("frames", [(1, 35, 40)])
 def test_bf16_frames_with_large_patches(frames):
     import torch
@@ -57,7 +57,8 @@ def test_bf16_frames_with_large_patches(frames):
         assert torch.equal(x[0], few[0]) and torch.isfinite(x).all(), n
 
 
-# 221 tokens a frame: 32 x 32 tiles for one and four frames, 32 x 64 for eight, 64 x 64 for sixteen and forty
+# 221 tokens a frame: 32 x 32 tiles for one and four frames, 32 x 64 for eight, 64 x 64 for sixteen, 64 x 128 with packed
+# weights (gemm_bf16_patch_kernel) for forty
 @pytest.mark.parametrize("patch", [16, 32])
 def test_bf16_frames_by_tile(patch):
     import torch
@@ -71,3 +72,41 @@ def test_bf16_frames_by_tile(patch):
     for n in (4, 8, 16, 40):
         x = _embed(synth.replace(cfg, B=n), w, images[:n])
         assert torch.equal(x[0], few[0]) and torch.isfinite(x).all(), n
+
+
+# Levels in between each other: a tile of 64 tokens holds some of its level, none, or nothing else.  Room for 20,480 tokens
+# sends both levels to gemm_bf16_patch_kernel (more 64 x 64 tiles than CUs), a context of its own a frame to the small tiles.
+@pytest.mark.parametrize("fractions", [(0.0, 1.0, 0.3), (0.05, 0.6, 0.0)])
+def test_levels_in_one_tile(fractions):
+    import torch
+    from paper_2505_23317_amd import cfdetr as K
+
+    cfg = synth.Config("levels", 3, 32 * 13, 32 * 17, (32, 16), 256, 8, 1, 256, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 29)
+    images = synth.bf16_round(np.random.default_rng(11).random((3, 3, cfg.H, cfg.W), dtype=np.float32))
+    tok = []
+    for f, part in enumerate(fractions):   # cells picked at random, each one token or its four children
+        fine = np.random.default_rng(40 + f).random((13, 17)) < part
+        tok.append([t for r in range(13) for c in range(17) for t in
+                    ([(1, 2 * r + i, 2 * c + j) for i in (0, 1) for j in (0, 1)] if fine[r, c] else [(0, r, c)])])
+    cu = np.concatenate([[0], np.cumsum([len(t) for t in tok])]).astype(np.int32)
+
+    def fine_pass(first, frames, room):
+        sub = synth.replace(cfg, B=frames)
+        enc = K.Encoder(sub, w, max_tokens_total=room)
+        desc = torch.from_numpy(O.pack_tok_desc(np.asarray(sum(tok[first:first + frames], [])))).cuda()
+        offs = torch.from_numpy(cu[first:first + frames + 1] - cu[first]).cuda()
+        y = torch.empty((int(offs[-1]), cfg.d), device="cuda")
+        full = torch.full((room, cfg.d), float("nan"), device="cuda")
+        enc.fine_encode(enc.upload_images(images[first:first + frames]), frames, desc, offs, None, full)
+        enc.sync_status()
+        y.copy_(full[:y.shape[0]])
+        enc.close()
+        return y
+
+    many = fine_pass(0, 3, 20480)
+    assert torch.isfinite(many).all()
+    for f in range(3):
+        assert torch.equal(fine_pass(f, 1, 884), many[cu[f]:cu[f + 1]]), f
+    ref = np.asarray(O.fine_encode(images, np.asarray(sum(tok, [])), cu, cfg.patch, w, cfg.heads))
+    assert float(np.abs(many.cpu().numpy() - ref).max() / np.abs(ref).max()) <= 2e-2
