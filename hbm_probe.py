@@ -11,8 +11,10 @@ Two steps, both on the GPU machine:
 
 `run` first copies a buffer of known size with a plain device-to-device copy kernel
 (the calibration: it reads and writes exactly COPY_BYTES), then runs a few
-cfdetr_multilevel_batch steps.  `report` scales each counter by what it read for the
-copy and prints bytes per launch for every kernel family.
+cfdetr_multilevel_batch steps, or with `--case NAME` passes of that case of perf/cases.py.
+`report` scales each counter by what it read for the copy and prints bytes per launch for
+every kernel family.  `stats` turns a kernel statistics file of `run` under
+`rocprofv3 --kernel-trace --stats` into a table.
 """
 from __future__ import annotations
 
@@ -37,6 +39,15 @@ FAMILIES = [
     ("layer_head", r"layer_head_kernel"),
     ("wide_head", r"wide_layer_kernel<\d+, \d, ., 0>"),
     ("wide_layer", r"wide_layer_kernel<\d+, \d, ., [12]>"),
+    ("wide_norm", r"wide_norm_kernel"),
+    ("slim_qkv", r"slim_norm_kernel<\d+, [01]>"),
+    ("slim_relu", r"slim_norm_kernel<\d+, 2>"),
+    ("slim_hidden", r"slim_norm_kernel<\d+, 3>"),
+    ("slim_query", r"slim_norm_kernel<\d+, 4>"),
+    ("slim_ffn2", r"slim_residual_kernel"),
+    ("small_layer", r"small_layer_kernel"),
+    ("decoder_kv", r"gemm_bf16_\w+_kernel.*EpiKvLayers"),
+    ("decoder_heads", r"decoder_heads_kernel"),
     ("embed", r"gemm_bf16_(gather|patch)_kernel|gemm_bf16_direct_kernel.*EpiEmbed"),
     ("layernorm", r"layernorm4?_kernel"),
     ("select", r"select_kernel"),
@@ -47,7 +58,7 @@ FAMILIES = [
 ]
 
 
-def run(cfg_id: int) -> None:
+def run(cfg_id: int, case: str = "", passes: int = STEPS) -> None:
     import torch
     from paper_2505_23317_amd import cfdetr, synth
     src = torch.empty(COPY_BYTES, dtype=torch.uint8, device="cuda")
@@ -56,6 +67,13 @@ def run(cfg_id: int) -> None:
     torch.cuda.synchronize()
     dst.copy_(src)                       # the calibration kernel (elementwise copy)
     torch.cuda.synchronize()
+    if case:
+        from perf import cases
+        state = cases.prepare(next(c for c in cases.listed() if c["name"] == case), 1)
+        for _ in range(passes):
+            cases.run(state)
+        torch.cuda.synchronize()
+        return
     cfg = synth.config(cfg_id)
     wl = synth.make_workload(cfg_id)
     enc = cfdetr.Encoder(cfg, wl["weights"])
@@ -177,11 +195,40 @@ def counters(csvs, cfg_id: int, names) -> None:
             print(line)
 
 
+def _short(name: str) -> str:
+    """A kernel's name without its return type, namespaces and arguments."""
+    name = re.sub(r"^void |cfdetr::|\(anonymous namespace\)::", "", name)
+    depth = 0
+    for i, ch in enumerate(name):
+        depth += (ch == "<") - (ch == ">")
+        if ch == "(" and depth == 0:
+            return name[:i]
+    return name
+
+
+def stats(path: str, case: str, passes: int) -> None:
+    """The library's kernels in a statistics file of `run --case`, as a table."""
+    print(f"# {case} of perf/cases.py: kernel statistics ({passes} passes, set-up included)\n")
+    print("Commands, from the repository root on the MI355X box (OUT: any scratch folder):\n")
+    print(f"    rocprofv3 --kernel-trace --stats --output-format csv -d OUT -o t -- python3 hbm_probe.py run --case {case} "
+          f"--passes {passes}")
+    print(f"    python3 hbm_probe.py stats OUT/t_kernel_stats.csv --case {case} --passes {passes}\n")
+    print("Durations in microseconds.\n")
+    print("| kernel | calls | total us | avg us | min us | max us |\n|---|---|---|---|---|---|")
+    with open(path) as f:
+        for r in csv.DictReader(f):
+            if "cfdetr::" in r["Name"]:
+                us = [float(r[c]) / 1e3 for c in ("TotalDurationNs", "AverageNs", "MinNs", "MaxNs")]
+                print(f"| `{_short(r['Name'])}` | {r['Calls']} | {us[0]:.1f} | {us[1]:.2f} | {us[2]:.2f} | {us[3]:.2f} |")
+
+
 def main() -> None:
     ap = argparse.ArgumentParser()
     sub = ap.add_subparsers(dest="cmd", required=True)
     r = sub.add_parser("run")
     r.add_argument("--config", type=int, default=3)
+    r.add_argument("--case", default="")
+    r.add_argument("--passes", type=int, default=STEPS, help="of a case")
     p = sub.add_parser("report")
     p.add_argument("fetch_csv")
     p.add_argument("write_csv")
@@ -193,12 +240,18 @@ def main() -> None:
                                                   "SQ_ACTIVE_INST_VALU", "SQ_ACTIVE_INST_LDS",
                                                   "SQ_ACTIVE_INST_VMEM", "SQ_INSTS_MFMA",
                                                   "SQ_INSTS_VALU", "SQ_WAIT_INST_ANY"])
+    k = sub.add_parser("stats")
+    k.add_argument("csv")
+    k.add_argument("--case", required=True)
+    k.add_argument("--passes", type=int, required=True)
     a = ap.parse_args()
     if a.cmd == "counters":
         counters(a.csv, a.config, a.names)
         return
-    if a.cmd == "run":
-        run(a.config)
+    if a.cmd == "stats":
+        stats(a.csv, a.case, a.passes)
+    elif a.cmd == "run":
+        run(a.config, a.case, a.passes)
     else:
         report(a.fetch_csv, a.write_csv, a.config)
 
