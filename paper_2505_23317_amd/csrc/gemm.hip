@@ -1023,8 +1023,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, WPE) void gemm_bf16_persist_kernel(
 // ---------------------------------------------------------------------------
 // The same with the weights packed (launch_slim_pack): the form of the layer matrices wherever there are
 // more rows than few_rows.h is for.  Four wavefronts do 32 MT rows x 256 columns, each all rows by 64
-// columns, so no two share weights: those skip the LDS and come as whole operands into a ring of 16 or 32 KB
-// a workgroup, R k-steps ahead.  Only rows go through the LDS, in slabs of 64 elements and two places;
+// columns, so no two share weights: those skip the LDS and come as whole operands into a ring of 32 or 64 KB
+// of registers a workgroup, R k-steps ahead.  Only rows go through the LDS, in slabs of 64 elements and two places;
 // two workgroups a CU.  What bounds it on a full chip: the matrix units' clock under load (1,620 to 1,860
 // TFLOP/s with nothing but MFMAs, 2,450 on zeros) and, outside the main loop, the epilogue's vector work
 // (FF1: a quarter of the time) that other wavefronts' MFMAs cover only in part.

@@ -382,12 +382,13 @@ __device__ __forceinline__ uint32_t twice(uint32_t x) {
 // and on memory's latency (a trip per 1024 cells).  Painting the boxes is cheap enough to do
 // in every workgroup instead: up to eight lanes a box, one row each, an OR per 32 cells into a bit
 // map in LDS.  Eight lanes halve the time of few boxes and do most of a box's work eight times, so
-// there are fewer the more boxes there are, and the next box is on its way while one is painted.  Counts are popcounts of words; the tokens of a level's word are the children of
+// there are fewer the more boxes the frame has, and the next box is on its way while one is painted.  Counts are popcounts of words; the tokens of a level's word are the children of
 // the parents' bits without the word's own, so one scan over the words of the frame gives
 // every token its place.
 // Measured, two kernels / this one: six frames of 640 x 640 10.4 / 7.8 us, twelve of three
 // levels at 1024 x 1024 with the plan 28 / 9 us; with 300 boxes a frame 64 frames of 640 x 640
-// 43.0 / 21.6 us (eight lanes a box throughout 76.7), of 320 x 320 32.4 / 21.0 (76.1).
+// 43.0 / 21.6 us (eight lanes a box throughout 76.7), of 320 x 320 32.4 / 21.0 (76.1).  What counts is the frame's own
+// number, for its own threads paint its boxes: 64 frames, 512 boxes in one of them, 22.0 us, and 90.1 by all frames' boxes.
 constexpr int kPaintTrips = 4;          // boxes a lane paints before a box gets fewer lanes
 constexpr int kSelectLds = 96 * 1024;   // most of its dynamic LDS (the plan's tables take 20 KB)
 
@@ -414,13 +415,13 @@ __global__ __launch_bounds__(kCompactThreads) void select_kernel(
     lo = box_offsets[pf];
     hi = box_offsets[pf + 1];
   }
-  const int boxes_all = min(max(box_offsets[B] - box_offsets[0], 0), 1 << 24);
   const bool easy = hard != nullptr && lane < B && hard[lane] == 0;
   for (int i = tid; i < B * frame_words; i += kCompactThreads) s_bits[i] = 0;
   for (int i = tid; i < kMaxBatch * kMaxLevels; i += kCompactThreads) (&s_split[0][0])[i] = 0;
   __syncthreads();
-  int log_lanes = 3;
-  while (log_lanes > 0 && (boxes_all << log_lanes) > kPaintTrips * kCompactThreads) --log_lanes;
+  // the most of eight, four, two and one with which the frame's boxes are kPaintTrips to a lane and fewer
+  const int log_share = 31 - __clz(kPaintTrips * per_frame), log_boxes = 32 - __clz(max(hi - lo, 1) - 1);
+  const int log_lanes = min(max(log_share - log_boxes, 0), 3);
   const int lanes = 1 << log_lanes, stride = per_frame >> log_lanes;
   int b = lo + ((tid & (per_frame - 1)) >> log_lanes);
   int4 next = make_int4(0, 0, 0, 0);

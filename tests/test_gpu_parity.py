@@ -166,6 +166,34 @@ def test_selection_of_many_boxes(K, frames, most):
     enc.close()
 
 
+# one frame has nearly all boxes: its own threads paint them, with as few lanes a box as its own number asks for
+@pytest.mark.parametrize("frames, most", [(12, 200), (33, 513), (64, 512)])
+def test_selection_with_one_full_frame(K, frames, most):
+    cfg = synth.Config("full", frames, 256, 320, (32, 16, 8), 64, 2, 1, 128, "f32")
+    rng = np.random.default_rng(most)
+    boxes, tier, offs = [], [], [0]
+    for f in range(frames):
+        n = most if f == frames - 2 else f % 3
+        side = rng.choice([1, 6, 12], n, p=[0.6, 0.3, 0.1])
+        x0, y0 = rng.integers(0, cfg.W, n), rng.integers(0, cfg.H, n)
+        boxes.append(np.stack([x0, y0, x0 + rng.integers(0, side + 1), y0 + rng.integers(0, side + 1)], 1))
+        tier.append(rng.choice([0, 1, 2], n, p=[0.3, 0.5, 0.2]))
+        offs.append(offs[-1] + n)
+    boxes = np.concatenate(boxes).astype(np.int32).reshape(-1, 4)
+    tier, offs = np.concatenate(tier).astype(np.uint8), np.asarray(offs, np.int32)
+    _say(f"[case] selection, {most} of {offs[-1]} boxes in one of {frames} frames")
+    enc = K.Encoder(cfg, synth.make_weights(cfg, 4))
+    b, t, o = enc.upload_boxes(boxes, tier, offs)
+    out = enc.alloc_outputs(frames)
+    tok, cu, counts = O.select_fine(boxes, tier, offs, frames, cfg.H, cfg.W, cfg.patch)
+    enc.select_fine(b, t, o, frames, out["tok_desc"], out["cu_seqlens"], out["level_counts"])
+    enc.sync_status()
+    np.testing.assert_array_equal(out["cu_seqlens"].cpu().numpy(), cu)
+    np.testing.assert_array_equal(out["level_counts"].cpu().numpy(), counts)
+    np.testing.assert_array_equal(out["tok_desc"].cpu().numpy()[:cu[-1]], O.pack_tok_desc(tok))
+    enc.close()
+
+
 def test_selection_with_changing_batch_size_on_one_context(K):
     # flags raised by a call with many frames must not leak into later, smaller or larger calls
     cfg = synth.Config("varb", 4, 128, 128, (64, 32, 16), 64, 2, 1, 128, "f32")
