@@ -74,3 +74,35 @@ def test_decoder_alone_and_in_a_batch(d, heads, ffn, queries):
         assert torch.isfinite(one).all()
         assert torch.equal(one[0], many[f]), f
     enc.close()
+
+
+# Attention to tokens of several tiles of 64 keys, the last one ragged, by items of 256 queries (64 frames) and of 128
+@pytest.mark.parametrize("d, heads, queries, tokens", [(768, 12, 155, 411), (256, 4, 449, 330)])
+def test_decoder_over_several_key_tiles(d, heads, queries, tokens):
+    import torch
+    from paper_2505_23317_amd import cfdetr as K
+
+    frames = 64
+    cfg = synth.Config("few_dec", frames, 352, 352, (32, 16), d, heads, 1, 512, "bf16", box_rule="poisson",
+                       box_lambda=2.0, side_lo=8, side_hi=40)
+    assert frames * queries * heads > 3500 * 32 >= queries * heads
+    enc = K.Encoder(cfg, synth.make_weights(cfg, 7))
+    dw = synth.make_decoder_weights(cfg, 3, n_queries=queries, layers=1)
+    for k in ("w_cls", "w_box3"):   # logits of a few units
+        dw[k] = synth.bf16_round((dw[k] * (4.0 / np.sqrt(d))).astype(np.float32))
+    for k in ("w_box1", "w_box2"):
+        dw[k] = synth.bf16_round((dw[k] * np.sqrt(256.0 / d)).astype(np.float32))
+    enc.attach_decoder(dw)
+    mem = torch.randn((frames * tokens, d), generator=torch.Generator().manual_seed(5)).cuda()
+    cu = torch.arange(frames + 1, dtype=torch.int32).cuda() * tokens
+    many = torch.empty((frames, queries, 5), device="cuda")
+    enc.decode(mem, cu, frames, many)
+    one = torch.empty((1, queries, 5), device="cuda")
+    for f in (0, frames - 1):
+        enc.decode(mem[f * tokens:(f + 1) * tokens].clone(), cu[:2].clone(), 1, one)
+        enc.sync_status()
+        assert torch.isfinite(one).all()
+        assert torch.equal(one[0], many[f]), f
+    enc.close()
+    ref = np.asarray(O.decode(mem[-tokens:].cpu().numpy(), np.array([0, tokens], np.int32), dw, heads))
+    assert float(np.abs(one.cpu().numpy() - ref.reshape(1, queries, 5)).max() / np.abs(ref).max()) <= BAR
