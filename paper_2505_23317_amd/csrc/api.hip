@@ -288,9 +288,10 @@ constexpr int kSpreadRows = 15;
 // Without / with, in us, three contexts in turn, so that each finds its weights in memory: queries of four cameras 497 /
 // 458, the two-stage detector of six 889 / 843, one high-resolution fine pass 953 / 900.  One context over and over, its
 // weights in the cache: 425 / 424, 785 / 787, 880 / 884, the two stages of one camera 703 / 706.  With one kernel a layer
-// (rows past kSpreadRows, or F no multiple of 384) 12 layers over 4,090 rows 726 / 643 and 634 / 637; F = 1024, 3,900 rows 595 /
-// 562 and 556 / 561, 1,000 to 3,000 rows, whose three contexts the cache holds, 0.5 % lost.  32 to 128 workgroups do the same.  Not in encoders of width 256 (one camera 207 / 208.5) or 768 (three small frames 1,024 / 1,028), nor with
-// more rows, whose attention fills the chip (six cameras, 29 rows a CU, 256.5 / 257.9).
+// (rows past kSpreadRows, or F no multiple of 384) 12 layers over 4,090 rows 726 / 643 and 634 / 637; F = 1024, 3,900
+// rows 595 / 562 and 556 / 561, 1,000 to 3,000 rows, whose three contexts the cache holds, 0.5 % lost.  32 to 128
+// workgroups do the same.  Not in encoders of width 256 (one camera 207 / 208.5) or 768 (three small frames 1,024 / 1,028),
+// nor with more rows, whose attention fills the chip (six cameras, 29 rows a CU, 256.5 / 257.9).
 constexpr int kAheadRows = 16;
 
 enum class RunKind { kMerged = 0, kFine = 1, kExact = 2 };
