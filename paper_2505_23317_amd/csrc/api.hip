@@ -1028,12 +1028,10 @@ CFDETR_API cfdetr_status cfdetr_create(const cfdetr_config* cfg, const cfdetr_we
   // Activation buffers hold one merged run: max_batch coarse grids + the mixed sets.
   c->tok_cap = (uint64_t)cfg->max_tokens_total + (uint64_t)cfg->max_batch * c->n0;
   {
-    // Query tiles of a whole run, and of its longest possible sequence; an XCD never
-    // gets more than (all items)/8 + (tiles of the longest sequence) work items.
+    // Query tiles of a whole run; an XCD gets an eighth of its work items, rounded up.
     const int bq = 128;   // the smallest items there are
     const int tiles_all = (int)((c->tok_cap + bq - 1) / bq) + 2 * cfg->max_batch;
-    const int longest = std::max(cfg->max_tokens_total, c->n0);
-    c->cap8 = (tiles_all * cfg->n_heads + 7) / 8 + (longest + bq - 1) / bq;
+    c->cap8 = (tiles_all * cfg->n_heads + 7) / 8;
   }
   for (int i = 0; i < 2; ++i)
     c->attn_grid[i] = attention_grid(cfg->d_model / cfg->n_heads, c->bf16, 128 << i, c->cap8);
@@ -1415,9 +1413,9 @@ CFDETR_API cfdetr_status cfdetr_decoder_attach(cfdetr_ctx* ctx, const cfdetr_dec
   const cfdetr_config& c = ctx->cfg;
   const uint64_t Bm = c.max_batch, Q = w->n_queries, d = c.d_model, F = c.d_ffn;
   const uint64_t Mq = Bm * Q;
-  // query tiles of a whole run; per queue at most all/8 + those of one sequence
+  // query tiles of a whole run, an eighth of them in every queue
   const int tiles_seq = (int)((Q + 127) / 128);
-  ctx->dcap8 = (int)((Bm * tiles_seq * c.n_heads + 7) / 8) + tiles_seq;
+  ctx->dcap8 = (int)((Bm * tiles_seq * c.n_heads + 7) / 8);
   for (int i = 0; i < 2; ++i)
     ctx->dgrid[i] = attention_grid(c.d_model / c.n_heads, true, 128 << i, ctx->dcap8);
   if (ctx->dgrid[0] < 8 || ctx->dgrid[1] < 8) return fail(ctx, CFDETR_EDEVICE, "cannot size the attention grid");

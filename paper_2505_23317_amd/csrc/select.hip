@@ -64,17 +64,19 @@ __global__ __launch_bounds__(kHitThreads) void select_hit_kernel(
 //                    tile (or -1: no item), then the sequence's offset, length and padded
 //                    offset, so that a workgroup gets all it needs to start in one load.
 // Workgroups are dealt to the 8 XCDs round-robin (workgroup w runs on XCD w % 8), and
-// every XCD has its own L2.  All query tiles of one (sequence, head) read the same
-// keys and values, so a whole group goes to one XCD: groups are ordered longest
-// sequence first and dealt round-robin, group G to XCD G % 8, whose workgroups
-// 8*j + G%8 take its tiles in order.  Costs fall with G, so the XCD loads differ by at
-// most one group, and no XCD gets more than total/8 + (tiles of the longest sequence)
-// items, which is what cap8 provides.
+// every XCD has its own L2.  Sequences come longest first, and the items of each, head by
+// head, are cut into eight runs of equal length, one for every XCD (whose workgroups
+// 8*j + x take its run in order): all XCDs get the same work of every length, and an XCD
+// reads the keys and values of an eighth of a sequence's heads and one or two more.  What
+// does not divide by eight goes to the XCDs in turn, so the queues differ by one entry in
+// all.  Whole (sequence, head) groups dealt to the XCDs read the least, but leave the fullest
+// of them with 1.2 times the average where lengths are mixed: attention over four coarse
+// grids of 1,600 tokens and sets of 5,803, 3,433, 4,612 and 2,257 (6 heads of 64) 132.5 us so,
+// 115.8 in runs; sets of 3,000 to 6,000 153 and 137, twelve of 1,200 to 4,000 88 and 82; eight
+// of 6,400, four of 6,400, eight of 3,200 or of 2,560 and 24 of 256 to 1,435 the same.
 // gated: no item at all.  The items are then not written (and not only counted as none): there
 // is no barrier between the two loops over the entries, so where both wrote one, either could
 // be the last, and an item that is left sends a workgroup to a sequence without keys.
-constexpr int kMaxHeads = 32;
-
 // Inclusive sum over the lanes of a wavefront: inside the rows of 16 lanes, then the last lane
 // of row 0 and 2 to the row behind, then that of row 1 to the upper half.
 __device__ __forceinline__ int wave_scan(int v) {
@@ -93,15 +95,20 @@ __device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readla
 // barrier); all threads of a workgroup of at least 2 * kMaxBatch threads call it.
 __device__ __forceinline__ void plan_body(const PlanArgs& p, int nseq, const int* s_len, bool gated) {
   __shared__ int s_order[2 * kMaxBatch];
-  __shared__ int s_gstart[2 * kMaxBatch * kMaxHeads];
+  __shared__ int s_turn[2 * kMaxBatch], s_start[2 * kMaxBatch * 8];
   __shared__ int s_count[8];
   __shared__ int s_cu[2 * kMaxBatch + 1], s_pcu[2 * kMaxBatch + 1];
   const int tid = threadIdx.x;
   // (no integer divisions: the kernel's time is latency, the way of its code to the CU included)
   const int heads = p.heads, cap8 = p.cap8, log_q = 31 - __clz(p.block_q);   // block_q: a power of two
-  const float per_head = 1.0f / heads;
-  auto sequence = [&](int G) { return s_order[(int)((G + 0.5f) * per_head)]; };   // (of at most 4096 groups)
   auto tiles = [&](int f) { return (s_len[f] + p.block_q - 1) >> log_q; };
+  // items of the sequence of that rank that XCD x gets: an eighth, and one more for each of the
+  // n % 8 XCDs from `turn` on; `first` is the number of those that the XCDs in front of it get
+  auto run_of = [&](int n, int turn, int x, int& first) {
+    const int rest = n & 7, end = turn + rest;
+    first = x * (n >> 3) + max(min(end, x) - turn, 0) + max(min(end - 8, x), 0);
+    return (n >> 3) + (((x - turn) & 7) < rest ? 1 : 0);
+  };
   int4* const items4 = reinterpret_cast<int4*>(p.items);
   if (tid < nseq) {
     const int len = s_len[tid];
@@ -113,15 +120,26 @@ __device__ __forceinline__ void plan_body(const PlanArgs& p, int nseq, const int
     s_order[rank] = tid;
   }
   __syncthreads();
-  const int ngroups = nseq * heads;
   const int lane = tid & (kWave - 1), wave = tid / kWave, waves = blockDim.x / kWave;
-  for (int x = wave; x < 8; x += waves) {   // XCD x: slots of its groups, 64 at a time
+  if (wave == 0) {
+    int turn = 0;
+    for (int i0 = 0; i0 < nseq; i0 += kWave) {
+      const int i = i0 + lane;
+      const int rest = i < nseq ? (heads * tiles(s_order[i])) & 7 : 0;
+      const int end = wave_scan(rest);
+      if (i < nseq) s_turn[i] = (turn + end - rest) & 7;
+      turn += last_lane(end);
+    }
+  }
+  __syncthreads();
+  for (int x = wave; x < 8; x += waves) {   // XCD x: places of its runs, 64 sequences at a time
     int pos = 0;
-    for (int G0 = x; G0 < ngroups; G0 += 8 * kWave) {
-      const int G = G0 + 8 * lane;
-      const int nt = G < ngroups ? tiles(sequence(G)) : 0;
-      const int end = wave_scan(nt);
-      if (G < ngroups) s_gstart[G] = pos + end - nt;
+    for (int i0 = 0; i0 < nseq; i0 += kWave) {
+      const int i = i0 + lane;
+      int first;
+      const int n = i < nseq ? run_of(heads * tiles(s_order[i]), s_turn[i], x, first) : 0;
+      const int end = wave_scan(n);
+      if (i < nseq) s_start[i * 8 + x] = pos + end - n;
       pos += last_lane(end);
     }
     if (lane == 0) s_count[x] = gated ? 0 : min(pos, cap8);
@@ -154,12 +172,20 @@ __device__ __forceinline__ void plan_body(const PlanArgs& p, int nseq, const int
     *p.m_all = s_cu[nseq];
     if (p.m_seen != nullptr) *p.m_seen = s_cu[nseq];
   }
-  for (int G = tid; !gated && G < ngroups; G += blockDim.x) {   // one thread per group
-    const int at = (int)((G + 0.5f) * per_head), f = s_order[at], h = G - at * heads, x = G & 7;
-    const int nt = tiles(f);
-    const int j0 = s_gstart[G];
-    for (int q = 0; q < nt && j0 + q < cap8; ++q)
-      items4[8 * (j0 + q) + x] = make_int4((f << 24) | (h << 19) | q, s_cu[f], s_len[f], s_pcu[f]);
+  for (int u = tid; !gated && u < nseq * 8; u += blockDim.x) {   // one thread per run
+    const int f = s_order[u >> 3], x = u & 7, nt = tiles(f), j0 = s_start[u];
+    int first;
+    const int n = run_of(heads * nt, s_turn[u >> 3], x, first);
+    int h = (int)(first * __builtin_amdgcn_rcpf((float)max(nt, 1)));   // first / nt, or one off
+    h += (h + 1) * nt <= first ? 1 : h * nt > first ? -1 : 0;
+    int q = first - h * nt;
+    for (int j = j0; j < min(j0 + n, cap8); ++j) {
+      items4[8 * j + x] = make_int4((f << 24) | (h << 19) | q, s_cu[f], s_len[f], s_pcu[f]);
+      if (++q == nt) {
+        q = 0;
+        ++h;
+      }
+    }
   }
   for (int i = tid; i < 8 * cap8; i += blockDim.x)
     if ((i >> 3) >= s_count[i & 7]) items4[i] = make_int4(-1, 0, 0, 0);
