@@ -32,9 +32,9 @@ STEPS = 3
 
 FAMILIES = [
     ("attention", r"attention_bf16_kernel"),
-    ("gemm_qkv", r"gemm_bf16_(direct|persist|packed|few)_kernel.*EpiQkv"),
-    ("gemm_ffn1_gelu", r"gemm_bf16_(direct|persist|packed|few)_kernel.*EpiAct<unsigned short, (true|1)>"),
-    ("gemm_residual", r"gemm_bf16_(direct|persist|packed|few)_kernel.*EpiResidual|gemm_bf16_rowln_kernel"),
+    ("gemm_qkv", r"gemm_bf16_(direct|persist|packed|few|norm)_kernel.*EpiQkv"),
+    ("gemm_ffn1_gelu", r"gemm_bf16_(direct|persist|packed|few|norm)_kernel.*EpiAct<unsigned short, (true|1)>"),
+    ("gemm_residual", r"gemm_bf16_(direct|persist|packed|few|norm)_kernel.*EpiResidual|gemm_bf16_rowln_kernel"),
     ("layer_tail", r"layer_tail_kernel"),
     ("layer_head", r"layer_head_kernel"),
     ("wide_head", r"wide_layer_kernel<\d+, \d, ., 0>"),

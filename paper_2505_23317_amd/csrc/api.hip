@@ -290,8 +290,10 @@ constexpr int kSpreadRows = 15;
 // weights in the cache: 425 / 424, 785 / 787, 880 / 884, the two stages of one camera 703 / 706.  With one kernel a layer
 // (rows past kSpreadRows, or F no multiple of 384) 12 layers over 4,090 rows 726 / 643 and 634 / 637; F = 1024, 3,900
 // rows 595 / 562 and 556 / 561, 1,000 to 3,000 rows, whose three contexts the cache holds, 0.5 % lost.  32 to 128
-// workgroups do the same.  Not in encoders of width 256 (one camera 207 / 208.5) or 768 (three small frames 1,024 / 1,028),
-// nor with more rows, whose attention fills the chip (six cameras, 29 rows a CU, 256.5 / 257.9).
+// workgroups do the same.  Not in encoders of width 256 (one camera 207 / 208.5), nor with more rows, whose attention fills
+// the chip (six cameras, 29 rows a CU, 256.5 / 257.9).  At width 768 where a LayerNorm and the contraction behind it are one
+// launch (norm_rows_fit): three small frames 1,136 / 1,022, and 1,096 with the launches apart, which gain nothing by it
+// (1,030 / 1,139, three contexts in turn each time).
 constexpr int kAheadRows = 16;
 
 enum class RunKind { kMerged = 0, kFine = 1, kExact = 2 };
@@ -501,6 +503,9 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
     }
     return CFDETR_OK;
   }
+  // width 768, few rows: a LayerNorm and the contraction behind it are one launch
+  const bool norm_qkv = bf && ctx->slim_qkv && norm_rows_fit(m_hint, 3 * d, d);
+  const bool norm_ff1 = bf && ctx->slim_ff1 && norm_rows_fit(m_hint, F, d);
   for (int l = 0; l < c.n_layers; ++l) {
     const char* wqkv = static_cast<const char*>(w.w_qkv) + (size_t)l * 3 * d * d * es;
     const char* wo = static_cast<const char*>(w.w_o) + (size_t)l * d * d * es;
@@ -513,7 +518,7 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
                 launch_layer_head(ctx->x, ctx->head_packed, w.ln1_g, w.ln1_b, eps, w.b_qkv,
                                   attention_q_scale(d / c.n_heads), ctx->qkv, ctx->vt, ctx->vt_ld,
                                   cu_all, ctx->pcu, nseq, d, m_ptr, 0, m_cap, s));
-    else if (!fused_ln || l == 0) {
+    else if (!norm_qkv && (!fused_ln || l == 0)) {
       // the first LayerNorm of a bf16 run also lists where every row goes in vt
       const RowPositions rp{ctx->vt_pos, cu_all, ctx->pcu, nseq};
       const bool list = bf && l == 0 && d % 4 == 0;
@@ -523,7 +528,12 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
     }
     if (fused_tail) {
       // q, k, v of this layer came out of the kernel before (the previous layer's last)
-    } else if (bf)
+    } else if (norm_qkv)
+      CF_LAUNCH(CFDETR_K_QKV,
+                launch_norm_qkv(ctx->x, w.ln1_g + (size_t)l * d, w.ln1_b + (size_t)l * d, eps, packed(ctx->slim_qkv, (size_t)l * 3 * d * d),
+                                w.b_qkv + (size_t)l * 3 * d, d, attention_q_scale(d / c.n_heads), ctx->qkv, ctx->vt, ctx->vt_ld,
+                                RowPositions{ctx->vt_pos, cu_all, ctx->pcu, nseq}, l == 0, m_ptr, m_hint, m_cap, s));
+    else if (bf)
       CF_LAUNCH(CFDETR_K_QKV,
                 launch_gemm_qkv(ctx->a, wqkv, w.b_qkv + (size_t)l * 3 * d, d,
                                 attention_q_scale(d / c.n_heads), ctx->qkv, ctx->vt,
@@ -533,9 +543,17 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
       CF_LAUNCH(CFDETR_K_QKV, launch_gemm(ctx->a, wqkv, w.b_qkv + (size_t)l * 3 * d, 3 * d, d,
                                           Epilogue::kBias, ctx->qkv, nullptr, bf, m_ptr, m_hint, m_cap,
                                           s));
+    ReadAhead ahead;
+    if (norm_qkv && shape.block_q == 128) {
+      const size_t dd = (size_t)d * d * 2, df = (size_t)F * d * 2;
+      ask_for(ahead, 0, ctx->slim_o + l * dd, dd);
+      ask_for(ahead, 1, ctx->slim_ff1 + l * df, df);
+      ask_for(ahead, 2, ctx->slim_ff2 + l * df, df);
+      if (!last) ask_for(ahead, 3, ctx->slim_qkv + (l + 1) * 3 * dd, 3 * dd);
+    }
     CF_LAUNCH(CFDETR_K_ATTN,
               launch_attention(ctx->qkv, ctx->vt, ctx->vt_ld, ctx->o, d, c.n_heads, ctx->items, ctx->cap8, ctx->queue_heads + 8 * l,
-                               shape.attn_grid, shape.block_q, bf, kv_len, s));
+                               shape.attn_grid, shape.block_q, bf, kv_len, s, ahead));
     if (fused_tail) {
       // out-projection, LayerNorm, feed-forward block and the LayerNorm after it (the next
       // layer's first one, or the final one) in one kernel
@@ -575,11 +593,17 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
       CF_LAUNCH(CFDETR_K_OUT, launch_gemm(ctx->o, wo, w.b_o + (size_t)l * d, d, d,
                                           Epilogue::kBiasResidual, nullptr, ctx->x, bf, m_ptr, m_hint,
                                           m_cap, s, 1.0f, packed(ctx->slim_o, (size_t)l * d * d)));
-      CF_LAUNCH(CFDETR_K_LN,
-                launch_layernorm(ctx->x, w.ln2_g + (size_t)l * d, w.ln2_b + (size_t)l * d, ctx->a,
-                                 bf, d, eps, m_ptr, 0, m_cap, 0, nullptr, s));
+      if (!norm_ff1)
+        CF_LAUNCH(CFDETR_K_LN,
+                  launch_layernorm(ctx->x, w.ln2_g + (size_t)l * d, w.ln2_b + (size_t)l * d, ctx->a,
+                                   bf, d, eps, m_ptr, 0, m_cap, 0, nullptr, s));
     }
-    CF_LAUNCH(CFDETR_K_FF1, launch_gemm(ctx->a, w1, w.b_ff1 + (size_t)l * F, F, d,
+    if (norm_ff1)
+      CF_LAUNCH(CFDETR_K_FF1, launch_norm_gemm(ctx->x, w.ln2_g + (size_t)l * d, w.ln2_b + (size_t)l * d, eps,
+                                               packed(ctx->slim_ff1, (size_t)l * F * d), w.b_ff1 + (size_t)l * F, F,
+                                               Epilogue::kBiasGelu, 1.0f, ctx->h, m_ptr, m_hint, m_cap, s));
+    else
+      CF_LAUNCH(CFDETR_K_FF1, launch_gemm(ctx->a, w1, w.b_ff1 + (size_t)l * F, F, d,
                                         Epilogue::kBiasGelu, ctx->h, nullptr, bf, m_ptr, m_hint, m_cap,
                                         s, 1.0f, packed(ctx->slim_ff1, (size_t)l * F * d)));
     if (fused_ln && !last)
@@ -857,14 +881,32 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
   // cross-attention, and one kernel for the second out-projection, the feed-forward block,
   // the LayerNorm after it and the next layer's q/k/v projection.
   const bool fused = ctx->dtail_packed_layer != 0;
+  // width 768, few rows: a LayerNorm and the contraction behind it are one launch
+  const bool norm_qkv = ctx->dslim_qkv && norm_rows_fit(Mq, 3 * d, d), norm_q = ctx->dslim_q && norm_rows_fit(Mq, d, d);
+  const bool norm_ff1 = ctx->dslim_ff1 && norm_rows_fit(Mq, F, d);
+  const size_t dd = (size_t)d * d * 2, df = (size_t)F * d * 2;
   for (int l = 0; l < L; ++l) {
     const bool last = l + 1 == L;
+    ReadAhead ahead, behind_cross;
+    if (norm_qkv && dblock_q == 128) {
+      ask_for(ahead, 0, ctx->dslim_o + l * dd, dd);
+      ask_for(ahead, 1, ctx->dslim_q + l * dd, dd);
+      ask_for(behind_cross, 0, ctx->dslim_o2 + l * dd, dd);
+      ask_for(behind_cross, 1, ctx->dslim_ff1 + l * df, df);
+      ask_for(behind_cross, 2, ctx->dslim_ff2 + l * df, df);
+      if (!last) ask_for(behind_cross, 3, ctx->dslim_qkv + (l + 1) * 3 * dd, 3 * dd);
+    }
     // self-attention among the queries of a frame
     if (fused && l == 0) {
       CF_LAUNCH(CFDETR_K_QKV,
                 launch_layer_head(ctx->dx, ctx->dhead_packed, w.ln1_g, w.ln1_b, eps, w.b_qkv, qs,
                                   ctx->dqkv, ctx->dvt, ctx->dvt_ld, ctx->dcu_all, ctx->dpcu, B, d,
                                   nullptr, Mq, Mq, s));
+    } else if (norm_qkv) {
+      CF_LAUNCH(CFDETR_K_QKV,
+                launch_norm_qkv(ctx->dx, w.ln1_g + (size_t)l * d, w.ln1_b + (size_t)l * d, eps, packed(ctx->dslim_qkv, (size_t)l * 3 * d * d),
+                                w.b_qkv + (size_t)l * 3 * d, d, qs, ctx->dqkv, ctx->dvt, ctx->dvt_ld,
+                                RowPositions{nullptr, ctx->dcu_all, ctx->dpcu, B}, false, nullptr, Mq, Mq, s));
     } else if (!fused) {
       CF_LAUNCH(CFDETR_K_LN, launch_layernorm(ctx->dx, w.ln1_g + (size_t)l * d, w.ln1_b + (size_t)l * d,
                                               ctx->da, true, d, eps, nullptr, Mq, Mq, 0, nullptr, s));
@@ -875,7 +917,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
     }
     CF_LAUNCH(CFDETR_K_ATTN,
               launch_attention(ctx->dqkv, ctx->dvt, ctx->dvt_ld, ctx->d_o, d, c.n_heads, ctx->ditems, ctx->dcap8, ctx->dqueue + 16 * l,
-                               dgrid, dblock_q, true, nullptr, s));
+                               dgrid, dblock_q, true, nullptr, s, ahead));
     // cross-attention: the queries read the tokens of their frame
     if (fused) {
       // first out-projection, LayerNorm and the query projection in one kernel
@@ -887,10 +929,15 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
       CF_LAUNCH(CFDETR_K_OUT, launch_gemm(ctx->d_o, wo + (size_t)l * d * d * 2, w.b_o + (size_t)l * d,
                                           d, d, Epilogue::kBiasResidual, nullptr, ctx->dx, true,
                                           nullptr, Mq, Mq, s, 1.0f, packed(ctx->dslim_o, (size_t)l * d * d)));
-      CF_LAUNCH(CFDETR_K_LN, launch_layernorm(ctx->dx, w.ln2_g + (size_t)l * d, w.ln2_b + (size_t)l * d,
-                                              ctx->da, true, d, eps, nullptr, Mq, Mq, 0, nullptr, s));
+      if (norm_q)
+        CF_LAUNCH(CFDETR_K_QKV, launch_norm_gemm(ctx->dx, w.ln2_g + (size_t)l * d, w.ln2_b + (size_t)l * d, eps,
+                                                 packed(ctx->dslim_q, (size_t)l * d * d), w.b_q + (size_t)l * d, d, Epilogue::kBias, qs,
+                                                 ctx->dh, nullptr, Mq, Mq, s));
+      else
+        CF_LAUNCH(CFDETR_K_LN, launch_layernorm(ctx->dx, w.ln2_g + (size_t)l * d, w.ln2_b + (size_t)l * d,
+                                                ctx->da, true, d, eps, nullptr, Mq, Mq, 0, nullptr, s));
     }
-    if (!fused)
+    if (!fused && !norm_q)
       CF_LAUNCH(CFDETR_K_QKV, launch_gemm(ctx->da, wq + (size_t)l * d * d * 2, w.b_q + (size_t)l * d, d,
                                           d, Epilogue::kBias, ctx->dh, nullptr, true, nullptr, Mq,
                                           Mq, s, qs, packed(ctx->dslim_q, (size_t)l * d * d)));
@@ -899,7 +946,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
                                      static_cast<const bf16_t*>(ctx->dvt_all) + l * v_stride,
                                      ctx->vt_ld, ctx->d_o,
                                      ctx->cu_all, ctx->pcu, d, c.n_heads, ctx->ditems,
-                                     ctx->dcap8, ctx->dqueue + 16 * l + 8, dgrid, dblock_q, s));
+                                     ctx->dcap8, ctx->dqueue + 16 * l + 8, dgrid, dblock_q, s, behind_cross));
     if (fused) {
       LayerTailArgs ta{};
       ta.O = ctx->d_o;
@@ -932,11 +979,17 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
                                         d, d, Epilogue::kBiasResidual, nullptr, ctx->dx, true,
                                         nullptr, Mq, Mq, s, 1.0f, packed(ctx->dslim_o2, (size_t)l * d * d)));
     // feed-forward
-    CF_LAUNCH(CFDETR_K_LN, launch_layernorm(ctx->dx, w.ln3_g + (size_t)l * d, w.ln3_b + (size_t)l * d,
-                                            ctx->da, true, d, eps, nullptr, Mq, Mq, 0, nullptr, s));
-    CF_LAUNCH(CFDETR_K_FF1, launch_gemm(ctx->da, w1 + (size_t)l * F * d * 2, w.b_ff1 + (size_t)l * F,
-                                        F, d, Epilogue::kBiasGelu, ctx->dh, nullptr, true, nullptr,
-                                        Mq, Mq, s, 1.0f, packed(ctx->dslim_ff1, (size_t)l * F * d)));
+    if (norm_ff1) {
+      CF_LAUNCH(CFDETR_K_FF1, launch_norm_gemm(ctx->dx, w.ln3_g + (size_t)l * d, w.ln3_b + (size_t)l * d, eps,
+                                               packed(ctx->dslim_ff1, (size_t)l * F * d), w.b_ff1 + (size_t)l * F, F,
+                                               Epilogue::kBiasGelu, 1.0f, ctx->dh, nullptr, Mq, Mq, s));
+    } else {
+      CF_LAUNCH(CFDETR_K_LN, launch_layernorm(ctx->dx, w.ln3_g + (size_t)l * d, w.ln3_b + (size_t)l * d,
+                                              ctx->da, true, d, eps, nullptr, Mq, Mq, 0, nullptr, s));
+      CF_LAUNCH(CFDETR_K_FF1, launch_gemm(ctx->da, w1 + (size_t)l * F * d * 2, w.b_ff1 + (size_t)l * F,
+                                          F, d, Epilogue::kBiasGelu, ctx->dh, nullptr, true, nullptr,
+                                          Mq, Mq, s, 1.0f, packed(ctx->dslim_ff1, (size_t)l * F * d)));
+    }
     CF_LAUNCH(CFDETR_K_FF2, launch_gemm(ctx->dh, w2 + (size_t)l * d * F * 2, w.b_ff2 + (size_t)l * d,
                                         d, F, Epilogue::kBiasResidual, nullptr, ctx->dx, true,
                                         nullptr, Mq, Mq, s, 1.0f, packed(ctx->dslim_ff2, (size_t)l * F * d)));

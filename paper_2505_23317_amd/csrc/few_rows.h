@@ -238,4 +238,47 @@ inline int few_rows_tiles(int m, int N, int K, bool gelu, int cus) {
   return 0;
 }
 
+// How a LayerNorm and the contraction behind it (gemm_bf16_norm_kernel, width 768) are cut for `rows` rows and N
+// columns: 32 mt rows by per_share strips of 32 columns a workgroup, the shares in 2^group_bits groups, each done by as
+// many XCDs as there are for a group, and there tile by tile in runs of equal length. A CU holds one workgroup, so one
+// round of them is all there may be (with a second one two launches are faster); eight strips are a round of a workgroup's
+// wavefronts and take 5 us with 32 rows, 6.5 with 64, behind 4 and 8.5 us of launch, rows and LayerNorm. In us, the cuts mt /
+// shares for 1,300 rows: q/k/v 1/4 13.8, 1/6 11.9, 2/9 14.4, 2/12 13.9; N = 3072 1/4 16.3, 1/6 14.1, 2/9 17.5, 2/12 14.8;
+// 2,600 rows: q/k/v 1/2 23.7, 1/3 19.9, 2/4 23.0, 2/6 19.6; N = 3072 1/3 24.4, 2/4 25.1, 2/6 22.4. Beyond four rounds it no
+// longer gains: 3,200 rows in two shares 24.9 and 32.0, and two launches 25.3 and 30.7.
+constexpr int kNormWidth = 768, kNormRounds = 4;
+struct NormCut {
+  int mt = 0;   // 0: no cut
+  int shares, per_share, group_bits;
+};
+// Workgroups of an XCD.
+inline int norm_units(int rows, int mt, int shares, int group_bits) {
+  const int g = 1 << group_bits, units = (rows + 32 * mt - 1) / (32 * mt) * ((shares + g - 1) / g);
+  return (units + (8 >> group_bits) - 1) / (8 >> group_bits);
+}
+inline NormCut norm_cut(int rows, int N, int cus) {
+  const int strips = N / 32, per_xcd = cus < 8 ? 1 : cus / 8;
+  NormCut best;
+  double least = 0;
+  for (int mt = 1; mt <= 2; ++mt)
+    for (int want = 1; want <= strips / 8; ++want) {
+      const int per = (strips + want - 1) / want, shares = (strips + per - 1) / per, rounds = (per + 7) / 8;
+      if (rounds > kNormRounds) continue;
+      for (int bits = 0; bits <= 3; ++bits) {
+        if (norm_units(rows, mt, shares, bits) > per_xcd) continue;
+        // operands into the XCDs: the matrix once for each XCD of a group, the rows once for each group
+        const double bytes = 2.0 * kNormWidth * N * (8 >> bits) + 4.0 * kNormWidth * rows * (1 << bits);
+        const double us = (mt == 1 ? 4 + 5 * rounds : 8.5 + 6.5 * rounds) + 0.1 * per + bytes / 50e6;
+        if (best.mt == 0 || us < least) {
+          least = us;
+          best.mt = mt;
+          best.shares = shares;
+          best.per_share = per;
+          best.group_bits = bits;
+        }
+      }
+    }
+  return best;
+}
+
 }  // namespace cfdetr

@@ -26,6 +26,7 @@
 // leave at once), and an all-fp32 kernel for the check mode complete the file.
 #include "few_rows.h"
 #include "kernels.h"
+#include "wide_row.h"
 
 namespace cfdetr {
 
@@ -1461,6 +1462,217 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_few_kernel(const bf16_t* __r
 }
 
 // ---------------------------------------------------------------------------
+// LayerNorm and the contraction behind it (a projection, or the first feed-forward matrix with its activation) for few
+// rows of width 768, weights packed: with the bits of layernorm4_kernel and of the other contractions.
+// A workgroup has 32 MT complete rows, normalised, in LDS, and a share of the columns; its eight wavefronts take
+// strips of 32 columns, each on its own: no two share weights, so those stream through a ring of 24 registers a
+// lane and skip the LDS, and behind the LayerNorm no wavefront waits for another. The rows of a tile are normalised
+// again for each share (1.5 us for 32 of them), which costs less than the launch and the rows' way through memory.
+// Bounds: a chain - launch 2.5 us, rows 1.5, LayerNorm, then 2.6 us at least for every eight strips (393 KB of weights
+// at a CU's 64 B/clk, or 64 rows' MFMAs), stores. us, LayerNorm and contraction as two launches / this: q/k/v (N = 2304)
+// 350 rows 9.0 / 7.8, 700 rows 11.2 / 9.1, 1,300 rows 16.3 / 11.9, 2,600 rows 24.1 / 19.6, 5,200 rows 32.9 / 30.4; N = 3072
+// with its activation 350 rows 10.4 / 8.0, 700 rows 15.0 / 9.9, 1,300 rows 18.4 / 14.1, 2,600 rows 26.6 / 22.4, 5,200 rows
+// 39.3 / 36.2. With more rows than one round of workgroups holds (norm_cut) it gains nothing: 8,200 rows 49.2 / 57.8
+// and 64.0 / 70.1, 16,063 rows 77.8 / 71.3 and 98.3 / 95.4.
+// ---------------------------------------------------------------------------
+struct NormArgs {
+  const float* x;
+  const float *ln_g, *ln_b;
+  float eps;
+  const unsigned char* w;   // launch_slim_pack's
+  int N;
+  int shares, per_share;    // shares of a row tile, strips of a share
+  int group_bits;           // the shares are cut in 2^group_bits groups, each for the same number of XCDs
+  RowPositions rp;          // out: list the rows' places in vt, too
+  const int32_t* m_ptr;
+  int m_host;
+};
+
+template <int D, int MT>
+struct NormLds {   // rows, a wavefront's staging rows and biases
+  static constexpr int kRows = 32 * MT * D * 2, kStride = 64 + 16, kStage = 8 * 32 * kStride, kBytes = kRows + kStage + 8 * 128;
+};
+
+template <int D, int MT, typename EP>
+__global__ __launch_bounds__(512, 2) void gemm_bf16_norm_kernel(NormArgs p, EP ep) {
+  using L = NormLds<D, MT>;
+  constexpr int KS = D / 16, ROWB = D * 2, NQ = D / 256, RW = 4 * MT, R = kFewRing, STRIDE = L::kStride;
+  static_assert(KS % R == 0 && R % 8 == 0 && D % 256 == 0 && EP::kStageElem == 2, "ring rounds");
+  typedef const __attribute__((address_space(1))) unsigned char* gptr;
+  typedef const __attribute__((address_space(1))) bf16x8* goper;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_norm[];
+  const int M = p.m_ptr ? *p.m_ptr : p.m_host;
+  const int mtiles = (M + 32 * MT - 1) / (32 * MT);
+  const int xcd = blockIdx.x & 7, group = xcd >> (3 - p.group_bits), xcds = 8 >> p.group_bits, nth = xcd & (xcds - 1);
+  const int share0 = (p.shares * group) >> p.group_bits, nshares = ((p.shares * (group + 1)) >> p.group_bits) - share0;
+  const int units = mtiles * nshares, u_end = (units * (nth + 1)) >> (3 - p.group_bits);
+  int unit = ((units * nth) >> (3 - p.group_bits)) + (int)(blockIdx.x >> 3);
+  if (unit >= u_end) return;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t voff = lane * 16;
+  unsigned char* const stg = smem_norm + L::kRows + wave * (32 * STRIDE);
+  float* const sbias = reinterpret_cast<float*>(smem_norm + L::kRows + L::kStage) + wave * 32;
+  const int strips = p.N / 32;
+  const size_t column = (size_t)KS * 1024;   // bytes of 32 columns
+  bf16x8 wr[R];
+  auto weights_of = [&](int s) { return (gptr)p.w + (size_t)s * column; };
+  auto ask = [&](gptr base, int k) {   // ring place k
+    gptr q = base + (k & ~3) * 1024;
+    asm volatile("" : "+s"(q));   // scalar bases: no vector arithmetic
+    wr[k] = *reinterpret_cast<goper>(q + (k & 3) * 1024 + voff);
+  };
+  for (; unit < u_end; unit += (int)(gridDim.x >> 3)) {
+    int t = (int)((float)unit * __builtin_amdgcn_rcpf((float)nshares));   // unit / nshares, or one off
+    t += (t + 1) * nshares <= unit ? 1 : t * nshares > unit ? -1 : 0;
+    t = __builtin_amdgcn_readfirstlane(t);
+    const int share = share0 + unit - t * nshares, m0 = t * (32 * MT);
+    const int s0 = share * p.per_share + wave, s1 = min((share + 1) * p.per_share, strips);
+    {
+      // rows of this wavefront, the second half on its way while the first is worked on
+      constexpr int HW = RW / 2;
+      float4 v[2][HW][NQ], gain[NQ], offs[NQ];
+      int ln = lane;
+      work_out_here(ln);
+      auto rows_of = [&](int h) {
+#pragma unroll
+        for (int r = 0; r < HW; ++r) {
+          const float4* const xr = reinterpret_cast<const float4*>(p.x + (size_t)min(m0 + wave * RW + h * HW + r, M - 1) * D);
+#pragma unroll
+          for (int j = 0; j < NQ; ++j) v[h][r][j] = xr[ln + 64 * j];
+        }
+      };
+      auto norm = [&](int h) {
+#pragma unroll
+        for (int r = 0; r < HW; ++r) {
+          const int row = wave * RW + h * HW + r;
+          float mean, rstd;
+          ln_quad_stats(v[h][r], 64 * NQ, ln, D, p.eps, mean, rstd);
+#pragma unroll
+          for (int j = 0; j < NQ; ++j) {
+            const float4 y = ln_quad(v[h][r][j], mean, rstd, gain[j], offs[j]);
+            const int c = (ln >> 1) + 32 * j;
+            *reinterpret_cast<uint2*>(smem_norm + row * ROWB + ((c ^ (row & 15)) << 4) + (ln & 1) * 8) =
+                make_uint2(pack_bf16x2(y.x, y.y), pack_bf16x2(y.z, y.w));
+          }
+        }
+      };
+#pragma unroll
+      for (int j = 0; j < NQ; ++j) {
+        gain[j] = reinterpret_cast<const float4*>(p.ln_g)[ln + 64 * j];
+        offs[j] = reinterpret_cast<const float4*>(p.ln_b)[ln + 64 * j];
+      }
+      rows_of(0);
+      rows_of(1);
+      __builtin_amdgcn_sched_barrier(0);
+      norm(0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (s0 < s1) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) ask(weights_of(s0), k);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      norm(1);
+    }
+    if (p.rp.out != nullptr && share == 0 && (int)threadIdx.x < 32 * MT && m0 + (int)threadIdx.x < M) {
+      const int m = m0 + threadIdx.x, f = frame_of_token(p.rp.cu, p.rp.nseq, m);
+      p.rp.out[m] = p.rp.pcu[f] + (m - p.rp.cu[f]);
+    }
+    int32_t info[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) info[i] = ep.row_info(min(m0 + i * 32 + l32, M - 1));
+    __syncthreads();
+    auto strip = [&](int s, auto more_tag) {
+      constexpr bool kMore = decltype(more_tag)::value;   // another strip's weights are asked for
+      const int n0 = s * 32;
+      const float bias = ep.bias[n0 + (lane & 31)];
+      const gptr w = weights_of(s), w_next = weights_of(s + 8);
+      int lx = lane;
+      work_out_here(lx);
+      uint32_t ao[8];   // operand of k-step k modulo 8: chunks XORed by the row
+#pragma unroll
+      for (int k = 0; k < 8; ++k) ao[k] = (lx & 31) * ROWB + (((2 * k + (lx >> 5)) ^ (lx & 15)) << 4);
+      f32x16 acc[MT];
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+      constexpr int kAhead = 2;
+      bf16x8 a[kAhead + 1][MT];
+      static_assert(R % (kAhead + 1) == 0, "operands of the next ring round");
+      const unsigned char* rows = smem_norm;
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) a[k][i] = *reinterpret_cast<const bf16x8*>(rows + ao[k] + i * (32 * ROWB));
+      // a ring round, each place refilled behind its MFMAs: from `next`
+      auto round = [&](gptr next, auto last_tag) {
+        constexpr bool kLast = decltype(last_tag)::value;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          __builtin_amdgcn_sched_barrier(0);
+          const int ka = k + kAhead;
+          if (!kLast || ka < R) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+              a[ka % (kAhead + 1)][i] = *reinterpret_cast<const bf16x8*>(rows + ao[ka & 7] + (ka >> 3) * 256 + i * (32 * ROWB));
+          }
+#pragma unroll
+          for (int i = 0; i < MT; ++i)
+            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[k], a[k % (kAhead + 1)][i], acc[i], 0, 0, 0);
+          if (!kLast || kMore) ask(next, k);
+        }
+        rows += (R / 8) * 256;
+      };
+#pragma unroll
+      for (int k0 = R; k0 < KS; k0 += R) round(w + k0 * 1024, std::false_type{});
+      round(w_next, std::true_type{});
+      __builtin_amdgcn_sched_barrier(0);
+      sbias[lane & 31] = bias;
+      work_out_here(lx);
+      const int l32 = lx & 31, g = lx >> 5;
+      if (ep.staged(n0)) {
+        const int crow = lx >> 2, cchunk = lx & 3;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          const int mb = m0 + i * 32;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int nl = 8 * q + 4 * g;
+            const float v4[4] = {acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+            ep.stage4(stg + l32 * STRIDE + nl * 2, n0 + nl, v4, *reinterpret_cast<const float4*>(sbias + nl));
+          }
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const int r = c * 16 + crow;
+            const uint4 dd = *reinterpret_cast<const uint4*>(stg + r * STRIDE + cchunk * 16);
+            if (mb + r < M) ep.copy16(mb + r, n0 + cchunk * 8, dd, make_float4(0.f, 0.f, 0.f, 0.f));
+          }
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+          const int m = m0 + i * 32 + l32;
+          if (m < M) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int nl = 8 * q + 4 * g;
+              const float v4[4] = {acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+              ep.store4(m, n0 + nl, v4, *reinterpret_cast<const float4*>(sbias + nl), make_float4(0.f, 0.f, 0.f, 0.f), info[i]);
+            }
+          }
+        }
+      }
+    };
+    int s = s0;
+#pragma nounroll
+    for (; s + 8 < s1; s += 8) strip(s, std::true_type{});
+    if (s < s1) strip(s, std::false_type{});
+    __syncthreads();   // the rows' place is free
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Residual contraction + LayerNorm of the new residual rows in one kernel.
 // ---------------------------------------------------------------------------
 // x[m, :] += A[m, :] . W^T + bias;  out[m, :] = LayerNorm(x[m, :]) * g + b.
@@ -2743,6 +2955,35 @@ hipError_t launch_packed_tile(const bf16_t* a, const void* packed, int N, int K,
   return hipSuccess;
 }
 
+template <int MT, typename EP>
+hipError_t launch_norm_tile(NormArgs p, const NormCut& cut, const EP& ep, int m_capacity, int m, hipStream_t s) {
+  constexpr int D = kNormWidth;
+  constexpr auto kern = gemm_bf16_norm_kernel<D, MT, EP>;
+  constexpr size_t lds = NormLds<D, MT>::kBytes;
+  static_assert(lds <= 160 * 1024, "LDS");
+  static DeviceOnce configured;
+  if (hipError_t e = allow_lds(kern, lds, &configured); e != hipSuccess) return e;
+  p.shares = cut.shares;
+  p.per_share = cut.per_share;
+  p.group_bits = cut.group_bits;
+  // workgroups for a quarter more rows than expected; they go on to further units if there are more after all
+  const int rows = m + m / 4 < m_capacity ? m + m / 4 : m_capacity;
+  hipLaunchKernelGGL(kern, dim3(8 * norm_units(rows, MT, cut.shares, cut.group_bits)), dim3(512), lds, s, p, ep);
+  return hipSuccess;
+}
+
+template <typename EP>
+hipError_t launch_norm(const float* x, const float* ln_g, const float* ln_b, float eps, const void* packed, int N, const EP& ep,
+                       const RowPositions* list, const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s) {
+  const int m = m_host > 0 && m_host < m_capacity ? m_host : m_capacity;
+  const NormCut cut = norm_cut(m, N, cu_count());
+  if (cut.mt == 0 || packed == nullptr) return hipErrorInvalidValue;
+  NormArgs p{x, ln_g, ln_b, eps, static_cast<const unsigned char*>(packed), N, 0, 0, 0, RowPositions{}, m_ptr, m_host};
+  if (list != nullptr) p.rp = *list;
+  const hipError_t e = cut.mt == 1 ? launch_norm_tile<1>(p, cut, ep, m_capacity, m, s) : launch_norm_tile<2>(p, cut, ep, m_capacity, m, s);
+  return e != hipSuccess ? e : hipGetLastError();
+}
+
 // Rows of a tile: what the CU with the most tiles takes, and what all of them take together (the clock
 // under load), per tile 61 : 78 : 100 for 64, 96 and 128 rows.  us for 64 / 96 / 128 rows: 4,200 x 768 x 3072
 // 28.0 / 31.8 / 39.6, 8,700 x 768 x 3072 50.3 / 59.4 / 45.5, 12,150 x 768 x 3072 73.7 / 62.2 / 76.5,
@@ -3078,6 +3319,26 @@ hipError_t launch_gemm_qkv(const void* A, const void* W, const float* bias, int 
   hipError_t e = launch_direct(A, W, 3 * d, d, ep, m_ptr, m_host, m_capacity, s, packed);
   if (e != hipSuccess) return e;
   return hipGetLastError();
+}
+
+bool norm_rows_fit(int rows, int N, int d) { return d == kNormWidth && rows > 0 && few_rows_supported(N, d) && norm_cut(rows, N, cu_count()).mt != 0; }
+
+hipError_t launch_norm_qkv(const float* x, const float* ln_g, const float* ln_b, float eps, const void* packed, const float* bias, int d,
+                           float q_scale, void* qk, void* vt, int vt_ld, const RowPositions& positions, bool list,
+                           const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s) {
+  const EpiQkv ep{bias, static_cast<bf16_t*>(qk), 3 * d, 2 * d, d, q_scale, static_cast<bf16_t*>(vt), vt_ld,
+                  positions.cu, positions.pcu, positions.nseq, list ? nullptr : positions.out};
+  return launch_norm(x, ln_g, ln_b, eps, packed, 3 * d, ep, list ? &positions : nullptr, m_ptr, m_host, m_capacity, s);
+}
+
+hipError_t launch_norm_gemm(const float* x, const float* ln_g, const float* ln_b, float eps, const void* packed, const float* bias,
+                            int N, Epilogue epi, float scale, void* out, const int32_t* m_ptr, int m_host, int m_capacity,
+                            hipStream_t s) {
+  bf16_t* const o = static_cast<bf16_t*>(out);
+  if (epi == Epilogue::kBias)
+    return launch_norm(x, ln_g, ln_b, eps, packed, N, EpiAct<bf16_t, kActNone>{bias, o, N, scale}, nullptr, m_ptr, m_host, m_capacity, s);
+  if (epi != Epilogue::kBiasGelu || scale != 1.0f) return hipErrorInvalidValue;
+  return launch_norm(x, ln_g, ln_b, eps, packed, N, EpiAct<bf16_t, kActGelu>{bias, o, N, 1.0f}, nullptr, m_ptr, m_host, m_capacity, s);
 }
 
 hipError_t launch_gemm_kv_layers(const void* A, const void* W, const float* bias, int d, int layers,

@@ -1,0 +1,66 @@
+"""LayerNorm and the contraction behind it in one launch (width 768, few rows): at every height and split of the launch
+a frame's result is the same bit for bit as in a batch that is too large for it, and with more rows than were expected
+as with the right number."""
+import numpy as np
+import pytest
+
+from paper_2505_23317_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _coarse(cfg, w, images):
+    from paper_2505_23317_amd import cfdetr as K
+    enc = K.Encoder(cfg, w)
+    n = images.shape[0]
+    out = enc.alloc_outputs(n)
+    enc.coarse_encode(enc.upload_images(images), n, out["x0_cache"], out["y_coarse"])
+    enc.sync_status()
+    y = out["y_coarse"].reshape(n, -1, cfg.d).clone()
+    enc.close()
+    return y
+
+
+# frames of 7 x 13 cells: 32 and 64 rows a workgroup in 2 to 12 shares (182 to 5,005 rows), against 5,824 rows;
+# hidden widths with uneven shares
+@pytest.mark.parametrize("ffn", [3072, 640, 1408])
+def test_every_height_and_split(ffn):
+    import torch
+
+    most = 64
+    cfg = synth.Config("norm", most, 56, 104, (8,), 768, 12, 1, ffn, "bf16", box_rule="poisson")
+    w = synth.make_weights(cfg, 13)
+    rng = np.random.default_rng(4)
+    images = synth.bf16_round(rng.normal(0.5, 0.25, (most, 3, cfg.H, cfg.W)).astype(np.float32))
+    many = _coarse(cfg, w, images)
+    assert torch.isfinite(many).all()
+    for frames in (2, 5, 9, 12, 15, 19, 23, 29, 39, 55):
+        assert torch.equal(_coarse(synth.replace(cfg, B=frames), w, images[:frames]), many[:frames]), frames
+
+
+def test_more_rows_than_expected():
+    """The launches are sized for the rows of the run before: a few tokens, then every cell refined."""
+    import torch
+    from paper_2505_23317_amd import cfdetr as K
+
+    cfg = synth.Config("norm2", 2, 384, 512, (32, 16), 768, 12, 2, 1536, "bf16", box_rule="poisson")
+    enc = K.Encoder(cfg, synth.make_weights(cfg, 5))
+    rng = np.random.default_rng(6)
+    img = enc.upload_images(synth.bf16_round(rng.normal(0.5, 0.25, (2, 3, cfg.H, cfg.W)).astype(np.float32)))
+    none = enc.upload_boxes([(0, 0, 8, 8)] * 2, [1, 1], np.array([0, 1, 2]))
+    full = enc.upload_boxes([(0, 0, cfg.W, cfg.H)] * 2, [1, 1], np.array([0, 1, 2]))
+    out = enc.alloc_outputs(2)
+
+    def run(boxes):
+        enc.multilevel_batch(img, 2, *boxes, out)
+        enc.sync_status()
+        return [out[k].clone() for k in ("y_coarse", "y_mixed")]
+
+    run(none)
+    first, second = run(full), run(full)
+    rows = int(out["cu_seqlens"][-1])
+    assert rows == 2 * 768
+    for a, b in zip(first, second):
+        assert torch.equal(a[:rows], b[:rows])
+        assert torch.isfinite(b[:rows]).all()
+    enc.close()

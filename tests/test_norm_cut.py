@@ -1,0 +1,63 @@
+"""How a LayerNorm with the contraction behind it is cut for few rows (norm_cut, few_rows.h), without a GPU."""
+import subprocess
+
+import pytest
+
+from paper_2505_23317_amd import build
+
+DRIVER = """
+#include "few_rows.h"
+#include <cstdio>
+using namespace cfdetr;
+int main() {
+  for (int N : {768, 1536, 2304, 3072, 640})
+    for (int rows = 1; rows <= 6000; rows += rows < 100 ? 1 : 37)
+      for (int cus : {256, 64}) {
+        const NormCut c = norm_cut(rows, N, cus);
+        std::printf("%d %d %d %d %d %d %d %d\\n", N, rows, cus, c.mt, c.mt ? c.shares : 0, c.mt ? c.per_share : 0,
+                    c.mt ? c.group_bits : 0, c.mt ? norm_units(rows, c.mt, c.shares, c.group_bits) : 0);
+      }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def cuts(tmp_path_factory):
+    at = tmp_path_factory.mktemp("cut")
+    (at / "driver.hip").write_text(DRIVER)
+    r = subprocess.run([build._hipcc(), "--offload-arch=gfx950", "-std=c++17", "-I", build.CSRC, str(at / "driver.hip"), "-o",
+                        str(at / "driver")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    out = subprocess.run([str(at / "driver")], capture_output=True, text=True, check=True).stdout
+    return [tuple(map(int, line.split())) for line in out.splitlines()]
+
+
+def test_every_tile_and_strip_once_and_a_workgroup_a_cu(cuts):
+    """The kernel's way from a workgroup to its units: XCD x has an equal run of the units of its group of shares."""
+    seen = set()
+    for N, rows, cus, mt, shares, per, bits, most in cuts:
+        if mt == 0:
+            seen.add(0)
+            continue
+        strips, tiles, xcds = N // 32, -(-rows // (32 * mt)), 8 >> bits
+        assert shares * per >= strips > (shares - 1) * per and per <= 32
+        assert most <= cus // 8
+        got = []
+        for xcd in range(8):
+            group, nth = xcd >> (3 - bits), xcd & (xcds - 1)
+            first = (shares * group) >> bits
+            n = ((shares * (group + 1)) >> bits) - first
+            lo, hi = (tiles * n * nth) >> (3 - bits), (tiles * n * (nth + 1)) >> (3 - bits)
+            assert hi - lo <= most
+            got += [(u // n, first + u % n) for u in range(lo, hi)]
+        assert sorted(got) == [(t, s) for t in range(tiles) for s in range(shares)]
+        seen.add(mt)
+    assert seen == {0, 1, 2}
+
+
+@pytest.mark.parametrize("N, rows, mt", [(2304, 1300, 1), (3072, 1300, 1), (3072, 2600, 2), (2304, 5200, 2), (3072, 5200, 2),
+                                         (2304, 8200, 0), (3072, 16063, 0)])
+def test_by_the_figures(cuts, N, rows, mt):
+    """Heights at the row counts that the comments at norm_cut and its kernel have figures for (the nearest below)."""
+    at = max((r for n, r, cus, *_ in cuts if n == N and cus == 256 and r <= rows))
+    assert [c[3] for c in cuts if c[:3] == (N, at, 256)] == [mt]
