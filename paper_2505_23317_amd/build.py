@@ -11,8 +11,11 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcfdetr.so")
 SOURCES = ["api.hip", "select.hip", "roi.hip", "rowwise.hip", "gemm.hip", "layer.hip", "small_layer.hip",
            "few_rows.hip", "attention.hip", "sched.hip"]
+# A kernel's first 14 words of arguments come in scalar registers with the launch, so that its first
+# loads need not wait for a load of their addresses (arguments that are structs are left in memory).
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-fvisibility=hidden",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 # Per-source extras.  The attention kernel reads every MFMA result back for the
 # softmax, so its accumulators should live in ordinary VGPRs (no AGPR copies); the
 # GEMMs only read theirs in the epilogue and are faster with AGPR accumulators.
