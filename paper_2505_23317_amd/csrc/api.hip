@@ -332,6 +332,7 @@ PlanArgs encoder_plan(const cfdetr_ctx* ctx, int n_prefix, const RunShape& shape
   p.queue_heads = ctx->queue_heads;
   p.n_heads_q = 8 * ctx->cfg.n_layers;
   p.queue_start = shape.attn_grid / 8;
+  p.round = ctx->cus / 8;
   p.m_seen = shape.m_seen;
   return p;
 }
@@ -858,6 +859,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
     p.queue_heads = ctx->dqueue;
     p.n_heads_q = 16 * L;
     p.queue_start = dgrid / 8;
+    p.round = ctx->cus / 8;
     CF_LAUNCH(CFDETR_K_PLAN, launch_decode_plan(cu, B, t, p, Q, cap_m, ctx->err_flag, memory, ctx->a, d, s));
   }
   if (ctx->dwide_layer == 0)

@@ -74,6 +74,11 @@ __global__ __launch_bounds__(kHitThreads) void select_hit_kernel(
 // grids of 1,600 tokens and sets of 5,803, 3,433, 4,612 and 2,257 (6 heads of 64) 132.5 us so,
 // 115.8 in runs; sets of 3,000 to 6,000 153 and 137, twelve of 1,200 to 4,000 88 and 82; eight
 // of 6,400, four of 6,400, eight of 3,200 or of 2,560 and 24 of 256 to 1,435 the same.
+// The first entries of a queue, one for each CU of its XCD (p.round), are in turned order where there are more: CUs take
+// a workgroup each before any takes a second, so the shortest of them share their CU with the longest of the next,
+// and of 53 entries for 32 CUs the 11 longest have one to themselves.  In us, longest first throughout / so: six cameras
+// (8 heads of 32, 640 to 1,300 tokens, 50 items an XCD) 262 / 254 a pass, one camera 205 / 203, two stages of six 836 /
+// 822; sets of equal or far more items the same.
 // gated: no item at all.  The items are then not written (and not only counted as none): there
 // is no barrier between the two loops over the entries, so where both wrote one, either could
 // be the last, and an item that is left sends a workgroup to a sequence without keys.
@@ -179,8 +184,9 @@ __device__ __forceinline__ void plan_body(const PlanArgs& p, int nseq, const int
     int h = (int)(first * __builtin_amdgcn_rcpf((float)max(nt, 1)));   // first / nt, or one off
     h += (h + 1) * nt <= first ? 1 : h * nt > first ? -1 : 0;
     int q = first - h * nt;
+    const int turned = s_count[x] > p.round ? p.round : 0;   // entries
     for (int j = j0; j < min(j0 + n, cap8); ++j) {
-      items4[8 * j + x] = make_int4((f << 24) | (h << 19) | q, s_cu[f], s_len[f], s_pcu[f]);
+      items4[8 * (j < turned ? turned - 1 - j : j) + x] = make_int4((f << 24) | (h << 19) | q, s_cu[f], s_len[f], s_pcu[f]);
       if (++q == nt) {
         q = 0;
         ++h;
