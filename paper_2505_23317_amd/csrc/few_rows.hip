@@ -13,22 +13,17 @@ namespace {
 constexpr int kAhead = 5;         // k-steps that operands are asked for ahead of their MFMAs (few_rows.h)
 constexpr int kSlimMaxN = 2048;   // widest second matrix of slim_norm_kernel (its bias is in LDS)
 
+// slim_norm_kernel's arguments behind those that it takes one by one: these are in scalar registers when a workgroup
+// starts (build.py), a structure is a trip to memory away.
 struct SlimArgs {
-  const bf16_t* rows;        // slim_residual_kernel's operand
   const float* x0;           // first layer: the rows as the embedding left them, or x0_rows rows over and over
   int x0_rows;
-  float* x;                  // residual blocks (wide_row.h)
   const float *ln_g, *ln_b;
   float eps;
-  const unsigned char* w;    // launch_slim_pack's
-  const float* bias;
-  float* x_new;              // slim_norm_kernel: the new residual rows, its second matrix, its shares of a row tile
-  const unsigned char* w2;
+  const float* bias;         // of the projection
+  float* x_new;              // the new residual rows
   const float* bias2;
-  int shares, per_share;
   int parts;                 // 128-column parts of the result
-  int K;
-  int row_bits;              // XcdTiles
   float q_scale;
   bf16_t* out;               // q/k/v [M, 3D], other rows [M, D], or hidden blocks
   bf16_t* z;
@@ -38,8 +33,6 @@ struct SlimArgs {
   const int32_t* cu;
   const int32_t* pcu;
   int nseq;
-  const int32_t* m_ptr;
-  int m_host;
 };
 
 template <int D>
@@ -65,6 +58,8 @@ __device__ __forceinline__ void hidden_store(const SlimArgs& p, int m0, int n0, 
 // query projection.
 constexpr int kFirst = 0, kQkv = 1, kRelu = 2, kHidden = 3, kQuery = 4;
 
+// x: residual blocks (wide_row.h); w_rows, w_parts: the matrices of the projection and of the contraction, as
+// launch_slim_pack leaves them; shares, per_share: shares of a row tile and parts of a share; row_bits: XcdTiles.
 // LayerNorm of the residual rows and a contraction behind it.  kHidden and kQuery project the attention's
 // rows first: x_new = x + rows . W^T + bias, and the LayerNorm is of x_new.  32 rows and a run of p.per_share
 // 128-column parts of the contraction a workgroup: every workgroup of the same rows does their projection
@@ -77,15 +72,17 @@ constexpr int kFirst = 0, kQkv = 1, kRelu = 2, kHidden = 3, kQuery = 4;
 // is three) - LayerNorm (1.4) - stores, over 920 rows 7.3 us for q/k/v and 11.5 us for projection and
 // hidden units.  Before, a launch each and an LDS wait in front of every MFMA: 8, 5.5 and 9.6 us.
 template <int D, int kOut>
-__global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
+__global__ __launch_bounds__(256, 2) void slim_norm_kernel(const int32_t* m_ptr, const unsigned char* w_rows, const unsigned char* w_parts,
+                                                            const bf16_t* rows, float* x, int m_host, int shares, int per_share,
+                                                            int row_bits, SlimArgs p) {
   constexpr bool kProject = kOut == kHidden || kOut == kQuery;
   constexpr int KS = D / 16, NT = D / 128, ROWB = D * 2, UN = KS / NT;
   static_assert(UN == 8, "eight k-steps of the projection a ring round");
   __shared__ __attribute__((aligned(1024))) unsigned char sA[32 * ROWB];
   __shared__ float s_red[256], s_vec[3 * D], s_bias[kSlimMaxN];
 
-  const int M = p.m_ptr ? *p.m_ptr : p.m_host;
-  const XcdTiles tiles((M + 31) >> 5, p.shares, p.row_bits);
+  const int M = m_ptr ? *m_ptr : m_host;
+  const XcdTiles tiles((M + 31) >> 5, shares, row_bits);
   if (tiles.none) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t voff;
@@ -99,7 +96,7 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
   };
   auto block = [&](const void* base, int i) { return *reinterpret_cast<const __attribute__((address_space(1))) bf16x8*>(at(base, i)); };
 
-  const int share = tiles.part, part0 = share * p.per_share, part1 = min(part0 + p.per_share, p.parts);
+  const int share = tiles.part, part0 = share * per_share, part1 = min(part0 + per_share, p.parts);
   for (int t = tiles.r; t < tiles.r_end; t += tiles.step) {
     const int m0 = t * 32;
     int tid = threadIdx.x;
@@ -129,7 +126,7 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int row = (wave * 2 + i) * 4 + (lane >> 4);
-        const unsigned char* src = reinterpret_cast<const unsigned char*>(p.rows + (size_t)min(m0 + row, M - 1) * D) +
+        const unsigned char* src = reinterpret_cast<const unsigned char*>(rows + (size_t)min(m0 + row, M - 1) * D) +
                                    (((lane & 15) ^ (row & 15)) << 4);
 #pragma unroll
         for (int j = 0; j < NT; ++j)
@@ -147,7 +144,7 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
       for (int q = 0; q < 4; ++q) {
         const f32x4 v = kOut == kFirst
                             ? *reinterpret_cast<const f32x4*>(p.x0 + (size_t)row0 * D + wave * (D / 4) + j * 32 + 8 * q + 4 * g)
-                            : *reinterpret_cast<const __attribute__((address_space(1))) f32x4*>(at(p.x + x0, j * 4 + q));
+                            : *reinterpret_cast<const __attribute__((address_space(1))) f32x4*>(at(x + x0, j * 4 + q));
         acc[j][0][4 * q] = v[0];
         acc[j][0][4 * q + 1] = v[1];
         acc[j][0][4 * q + 2] = v[2];
@@ -155,8 +152,8 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
       }
     __builtin_amdgcn_sched_barrier(0);
     // block ks NT + j of the ring: column tile j of k-step ks of the projection, then k-step ks of a part
-    const unsigned char* const wo = p.w + (size_t)(wave * NT) * (KS * 1024);
-    const unsigned char* w2 = p.w2 + (size_t)(part0 * 4 + wave) * (KS * 1024);
+    const unsigned char* const wo = w_rows + (size_t)(wave * NT) * (KS * 1024);
+    const unsigned char* w2 = w_parts + (size_t)(part0 * 4 + wave) * (KS * 1024);
     bf16x8 wr[KS];
 #pragma unroll
     for (int i = 0; i < KS; ++i) wr[i] = kProject ? block(wo, (i % NT) * KS + i / NT) : block(w2, i);
@@ -207,7 +204,7 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
           residual_join(acc[j][0], hi[j], q, *reinterpret_cast<const float4*>(s_vec + wave * (D / 4) + j * 32 + 8 * q + 4 * g));
     }
     if ((kProject || kOut == kFirst) && share == 0) {
-      float* const xo = (kProject ? p.x_new : p.x) + x0;
+      float* const xo = (kProject ? p.x_new : x) + x0;
 #pragma unroll
       for (int j = 0; j < NT; ++j)
 #pragma unroll
@@ -290,10 +287,11 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(SlimArgs p) {
 // x += hidden blocks . W^T + bias, the second feed-forward matrix: 32 MT rows x 128 columns a workgroup.
 // 920 rows: 7.0 us, the K = 1536 of a wavefront at what a CU's vector-memory path gives.
 template <int D, int MT>
-__global__ __launch_bounds__(256, 2) void slim_residual_kernel(SlimArgs p) {
+__global__ __launch_bounds__(256, 2) void slim_residual_kernel(const int32_t* m_ptr, const unsigned char* w, const bf16_t* rows, float* x,
+                                                                const float* bias, int m_host, int K, int row_bits) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  const int M = p.m_ptr ? *p.m_ptr : p.m_host;
-  const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), D / 128, p.row_bits);
+  const int M = m_ptr ? *m_ptr : m_host;
+  const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), D / 128, row_bits);
   if (tiles.none) return;
   const int lane = threadIdx.x & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -305,17 +303,17 @@ __global__ __launch_bounds__(256, 2) void slim_residual_kernel(SlimArgs p) {
     u32x8 hi[MT];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      b[q] = *reinterpret_cast<const float4*>(p.bias + n0 + 8 * q + 4 * g);
+      b[q] = *reinterpret_cast<const float4*>(bias + n0 + 8 * q + 4 * g);
 #pragma unroll
       for (int i = 0; i < MT; ++i) {
-        const float4 v = *reinterpret_cast<const float4*>(x_block<D>(p.x, m0 + i * 32, n0, q, lane));
+        const float4 v = *reinterpret_cast<const float4*>(x_block<D>(x, m0 + i * 32, n0, q, lane));
         acc[i][4 * q] = v.x;
         acc[i][4 * q + 1] = v.y;
         acc[i][4 * q + 2] = v.z;
         acc[i][4 * q + 3] = v.w;
       }
     }
-    few_rows_product<MT, true>(p.rows, p.K, M, m0, p.w + (size_t)(part * 4 + wave) * (p.K >> 4) * 1024, smem, acc, [&]() {
+    few_rows_product<MT, true>(rows, K, M, m0, w + (size_t)(part * 4 + wave) * (K >> 4) * 1024, smem, acc, [&]() {
 #pragma unroll
       for (int i = 0; i < MT; ++i) residual_split(acc[i], hi[i]);
     });
@@ -325,7 +323,7 @@ __global__ __launch_bounds__(256, 2) void slim_residual_kernel(SlimArgs p) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         residual_join(acc[i], hi[i], q, b[q]);
-        *reinterpret_cast<float4*>(x_block<D>(p.x, m0 + i * 32, n0, q, lane)) =
+        *reinterpret_cast<float4*>(x_block<D>(x, m0 + i * 32, n0, q, lane)) =
             make_float4(acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]);
       }
     }
@@ -400,17 +398,13 @@ hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int 
                        int m_capacity, hipStream_t s) {
   if (step == SlimStep::kOutQuery ? d != 256 && d != 384 : d != 384 || !few_rows_supported(F, F)) return hipErrorInvalidValue;
   SlimArgs p{};
-  p.rows = static_cast<const bf16_t*>(a.rows);
   p.x0 = a.x0;
   p.x0_rows = a.x0_rows;
-  p.x = a.x;
   p.x_new = a.x_new;
   p.ln_g = a.ln_g;
   p.ln_b = a.ln_b;
   p.eps = a.eps;
-  p.w = static_cast<const unsigned char*>(a.w);
   p.bias = a.bias;
-  p.w2 = static_cast<const unsigned char*>(a.w2);
   p.bias2 = a.bias2;
   p.q_scale = a.q_scale;
   p.out = static_cast<bf16_t*>(a.out);
@@ -421,27 +415,31 @@ hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int 
   p.cu = a.cu;
   p.pcu = a.pcu;
   p.nseq = a.nseq;
-  p.m_ptr = m_ptr;
-  p.m_host = m_host;
+  const bf16_t* const in = static_cast<const bf16_t*>(a.rows);
+  const unsigned char *const w = static_cast<const unsigned char*>(a.w), *const w2 = static_cast<const unsigned char*>(a.w2);
+  int row_bits = 0;
   const int m = rows > 0 && rows < m_capacity ? rows : m_capacity, cus = cu_count();
   if (step == SlimStep::kDown) {
-    p.K = F;
     // 64 rows a workgroup where 32 would give CUs a second one (3,520 rows: 14 -> 9 us)
     const int mt = few_rows_cut(m, d, F, 1, cus).most > cus / 8 ? 2 : 1;
-    const dim3 grid = few_rows_grid(rows, m_capacity, d / 128, F, mt, cus, &p.row_bits);
-    if (mt == 2) hipLaunchKernelGGL((slim_residual_kernel<384, 2>), grid, dim3(256), few_rows_lds(2), s, p);
-    else hipLaunchKernelGGL((slim_residual_kernel<384, 1>), grid, dim3(256), few_rows_lds(1), s, p);
+    const dim3 grid = few_rows_grid(rows, m_capacity, d / 128, F, mt, cus, &row_bits);
+    if (mt == 2) hipLaunchKernelGGL((slim_residual_kernel<384, 2>), grid, dim3(256), few_rows_lds(2), s, m_ptr, w, in, a.x,
+                                    a.bias, m_host, F, row_bits);
+    else hipLaunchKernelGGL((slim_residual_kernel<384, 1>), grid, dim3(256), few_rows_lds(1), s, m_ptr, w, in, a.x,
+                            a.bias, m_host, F, row_bits);
     return hipGetLastError();
   }
   const bool qkv = step == SlimStep::kFirstQkv || step == SlimStep::kQkv;
   const bool project = step == SlimStep::kOutHidden || step == SlimStep::kOutQuery;
   p.parts = (step == SlimStep::kOutHidden ? F : qkv ? 3 * d : d) / 128;
   if (p.parts * 128 > kSlimMaxN) return hipErrorInvalidValue;
-  p.per_share = parts_of_a_share((m + 31) / 32, p.parts, d, project, cus);
-  p.shares = (p.parts + p.per_share - 1) / p.per_share;
-  const SlimBytes b = slim_bytes(d, p.per_share, project);
-  const dim3 grid = few_rows_grid(rows, m_capacity, p.shares, [](int r) { return (r + 31) / 32; }, b.row, b.part, b.tile, cus, &p.row_bits);
-  auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, p); };
+  const int per_share = parts_of_a_share((m + 31) / 32, p.parts, d, project, cus);
+  const int shares = (p.parts + per_share - 1) / per_share;
+  const SlimBytes b = slim_bytes(d, per_share, project);
+  const dim3 grid = few_rows_grid(rows, m_capacity, shares, [](int r) { return (r + 31) / 32; }, b.row, b.part, b.tile, cus, &row_bits);
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, m_ptr, w, w2, in, a.x, m_host, shares, per_share, row_bits, p);
+  };
   switch (step) {
     case SlimStep::kFirstQkv: launch(slim_norm_kernel<384, kFirst>); break;
     case SlimStep::kQkv: launch(slim_norm_kernel<384, kQkv>); break;

@@ -1416,9 +1416,9 @@ __device__ __forceinline__ float row16_sum(float v) {
 // Few rows (few_rows.h): 32 MT rows x 128 columns a workgroup, weights packed.  The sums and
 // the epilogue are those of the other forms, so the results are the same bits.
 template <int MT, typename EP>
-__global__ __launch_bounds__(256, 2) void gemm_bf16_few_kernel(const bf16_t* __restrict__ A, const unsigned char* W, int N, int K,
-                                                               EP ep, const int32_t* __restrict__ m_ptr, int m_host,
-                                                               int row_bits) {
+__global__ __launch_bounds__(256, 2) void gemm_bf16_few_kernel(const int32_t* __restrict__ m_ptr, const unsigned char* W,
+                                                               const bf16_t* __restrict__ A, int m_host, int N, int K, int row_bits,
+                                                               EP ep) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int M = m_ptr ? *m_ptr : m_host;
   const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), N / 128, row_bits);
@@ -1476,16 +1476,9 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_few_kernel(const bf16_t* __r
 // and 64.0 / 70.1, 16,063 rows 77.8 / 71.3 and 98.3 / 95.4.
 // ---------------------------------------------------------------------------
 struct NormArgs {
-  const float* x;
-  const float *ln_g, *ln_b;
-  float eps;
-  const unsigned char* w;   // launch_slim_pack's
   int N;
-  int shares, per_share;    // shares of a row tile, strips of a share
-  int group_bits;           // the shares are cut in 2^group_bits groups, each for the same number of XCDs
+  float eps;
   RowPositions rp;          // out: list the rows' places in vt, too
-  const int32_t* m_ptr;
-  int m_host;
 };
 
 template <int D, int MT>
@@ -1493,20 +1486,24 @@ struct NormLds {   // rows, a wavefront's staging rows and biases
   static constexpr int kRows = 32 * MT * D * 2, kStride = 64 + 16, kStage = 8 * 32 * kStride, kBytes = kRows + kStage + 8 * 128;
 };
 
+// w_all: launch_slim_pack's; shares, per_share: shares of a row tile, strips of a share; group_bits: the shares are cut
+// in 2^group_bits groups, each for the same number of XCDs.
 template <int D, int MT, typename EP>
-__global__ __launch_bounds__(512, 2) void gemm_bf16_norm_kernel(NormArgs p, EP ep) {
+__global__ __launch_bounds__(512, 2) void gemm_bf16_norm_kernel(const int32_t* m_ptr, const float* x, const float* ln_g, const float* ln_b,
+                                                                const unsigned char* w_all, int m_host, int shares, int per_share,
+                                                                int group_bits, NormArgs p, EP ep) {
   using L = NormLds<D, MT>;
   constexpr int KS = D / 16, ROWB = D * 2, NQ = D / 256, RW = 4 * MT, R = kFewRing, STRIDE = L::kStride;
   static_assert(KS % R == 0 && R % 8 == 0 && D % 256 == 0 && EP::kStageElem == 2, "ring rounds");
   typedef const __attribute__((address_space(1))) unsigned char* gptr;
   typedef const __attribute__((address_space(1))) bf16x8* goper;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_norm[];
-  const int M = p.m_ptr ? *p.m_ptr : p.m_host;
+  const int M = m_ptr ? *m_ptr : m_host;
   const int mtiles = (M + 32 * MT - 1) / (32 * MT);
-  const int xcd = blockIdx.x & 7, group = xcd >> (3 - p.group_bits), xcds = 8 >> p.group_bits, nth = xcd & (xcds - 1);
-  const int share0 = (p.shares * group) >> p.group_bits, nshares = ((p.shares * (group + 1)) >> p.group_bits) - share0;
-  const int units = mtiles * nshares, u_end = (units * (nth + 1)) >> (3 - p.group_bits);
-  int unit = ((units * nth) >> (3 - p.group_bits)) + (int)(blockIdx.x >> 3);
+  const int xcd = blockIdx.x & 7, group = xcd >> (3 - group_bits), xcds = 8 >> group_bits, nth = xcd & (xcds - 1);
+  const int share0 = (shares * group) >> group_bits, nshares = ((shares * (group + 1)) >> group_bits) - share0;
+  const int units = mtiles * nshares, u_end = (units * (nth + 1)) >> (3 - group_bits);
+  int unit = ((units * nth) >> (3 - group_bits)) + (int)(blockIdx.x >> 3);
   if (unit >= u_end) return;
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1516,7 +1513,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_norm_kernel(NormArgs p, EP e
   const int strips = p.N / 32;
   const size_t column = (size_t)KS * 1024;   // bytes of 32 columns
   bf16x8 wr[R];
-  auto weights_of = [&](int s) { return (gptr)p.w + (size_t)s * column; };
+  auto weights_of = [&](int s) { return (gptr)w_all + (size_t)s * column; };
   auto ask = [&](gptr base, int k) {   // ring place k
     gptr q = base + (k & ~3) * 1024;
     asm volatile("" : "+s"(q));   // scalar bases: no vector arithmetic
@@ -1527,7 +1524,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_norm_kernel(NormArgs p, EP e
     t += (t + 1) * nshares <= unit ? 1 : t * nshares > unit ? -1 : 0;
     t = __builtin_amdgcn_readfirstlane(t);
     const int share = share0 + unit - t * nshares, m0 = t * (32 * MT);
-    const int s0 = share * p.per_share + wave, s1 = min((share + 1) * p.per_share, strips);
+    const int s0 = share * per_share + wave, s1 = min((share + 1) * per_share, strips);
     {
       // rows of this wavefront, the second half on its way while the first is worked on
       constexpr int HW = RW / 2;
@@ -1537,7 +1534,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_norm_kernel(NormArgs p, EP e
       auto rows_of = [&](int h) {
 #pragma unroll
         for (int r = 0; r < HW; ++r) {
-          const float4* const xr = reinterpret_cast<const float4*>(p.x + (size_t)min(m0 + wave * RW + h * HW + r, M - 1) * D);
+          const float4* const xr = reinterpret_cast<const float4*>(x + (size_t)min(m0 + wave * RW + h * HW + r, M - 1) * D);
 #pragma unroll
           for (int j = 0; j < NQ; ++j) v[h][r][j] = xr[ln + 64 * j];
         }
@@ -1559,8 +1556,8 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_norm_kernel(NormArgs p, EP e
       };
 #pragma unroll
       for (int j = 0; j < NQ; ++j) {
-        gain[j] = reinterpret_cast<const float4*>(p.ln_g)[ln + 64 * j];
-        offs[j] = reinterpret_cast<const float4*>(p.ln_b)[ln + 64 * j];
+        gain[j] = reinterpret_cast<const float4*>(ln_g)[ln + 64 * j];
+        offs[j] = reinterpret_cast<const float4*>(ln_b)[ln + 64 * j];
       }
       rows_of(0);
       rows_of(1);
@@ -2932,8 +2929,8 @@ hipError_t launch_few(const bf16_t* a, const void* packed, int N, int K, const E
   int row_bits = 0;
   const dim3 grid = few_rows_grid(m_host, m_capacity, N / 128, K, MT, cu_count(), &row_bits);
   constexpr auto kern = gemm_bf16_few_kernel<MT, EP>;
-  hipLaunchKernelGGL(kern, grid, dim3(256), few_rows_lds(MT), s, a, static_cast<const unsigned char*>(packed), N, K, ep, m_ptr,
-                     m_host, row_bits);
+  hipLaunchKernelGGL(kern, grid, dim3(256), few_rows_lds(MT), s, m_ptr, static_cast<const unsigned char*>(packed), a, m_host, N, K,
+                     row_bits, ep);
   return hipSuccess;
 }
 
@@ -2956,19 +2953,18 @@ hipError_t launch_packed_tile(const bf16_t* a, const void* packed, int N, int K,
 }
 
 template <int MT, typename EP>
-hipError_t launch_norm_tile(NormArgs p, const NormCut& cut, const EP& ep, int m_capacity, int m, hipStream_t s) {
+hipError_t launch_norm_tile(const NormArgs& p, const NormCut& cut, const EP& ep, const float* x, const float* ln_g, const float* ln_b,
+                            const void* packed, const int32_t* m_ptr, int m_host, int m_capacity, int m, hipStream_t s) {
   constexpr int D = kNormWidth;
   constexpr auto kern = gemm_bf16_norm_kernel<D, MT, EP>;
   constexpr size_t lds = NormLds<D, MT>::kBytes;
   static_assert(lds <= 160 * 1024, "LDS");
   static DeviceOnce configured;
   if (hipError_t e = allow_lds(kern, lds, &configured); e != hipSuccess) return e;
-  p.shares = cut.shares;
-  p.per_share = cut.per_share;
-  p.group_bits = cut.group_bits;
   // workgroups for a quarter more rows than expected; they go on to further units if there are more after all
   const int rows = m + m / 4 < m_capacity ? m + m / 4 : m_capacity;
-  hipLaunchKernelGGL(kern, dim3(8 * norm_units(rows, MT, cut.shares, cut.group_bits)), dim3(512), lds, s, p, ep);
+  hipLaunchKernelGGL(kern, dim3(8 * norm_units(rows, MT, cut.shares, cut.group_bits)), dim3(512), lds, s, m_ptr, x, ln_g, ln_b,
+                     static_cast<const unsigned char*>(packed), m_host, cut.shares, cut.per_share, cut.group_bits, p, ep);
   return hipSuccess;
 }
 
@@ -2978,9 +2974,10 @@ hipError_t launch_norm(const float* x, const float* ln_g, const float* ln_b, flo
   const int m = m_host > 0 && m_host < m_capacity ? m_host : m_capacity;
   const NormCut cut = norm_cut(m, N, cu_count());
   if (cut.mt == 0 || packed == nullptr) return hipErrorInvalidValue;
-  NormArgs p{x, ln_g, ln_b, eps, static_cast<const unsigned char*>(packed), N, 0, 0, 0, RowPositions{}, m_ptr, m_host};
+  NormArgs p{N, eps, RowPositions{}};
   if (list != nullptr) p.rp = *list;
-  const hipError_t e = cut.mt == 1 ? launch_norm_tile<1>(p, cut, ep, m_capacity, m, s) : launch_norm_tile<2>(p, cut, ep, m_capacity, m, s);
+  const hipError_t e = cut.mt == 1 ? launch_norm_tile<1>(p, cut, ep, x, ln_g, ln_b, packed, m_ptr, m_host, m_capacity, m, s)
+                                   : launch_norm_tile<2>(p, cut, ep, x, ln_g, ln_b, packed, m_ptr, m_host, m_capacity, m, s);
   return e != hipSuccess ? e : hipGetLastError();
 }
 

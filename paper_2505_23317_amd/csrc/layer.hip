@@ -13,15 +13,10 @@ namespace {
 
 constexpr int kRingMax = 16;    // most weight blocks of 1 KB a wavefront holds in registers
 
+// The arguments behind those that the kernel takes one by one: these are in scalar registers when a workgroup
+// starts (build.py), a structure is a trip to memory away.
 struct WideArgs {
-  const bf16_t* O;
-  const unsigned char* packed;   // weight streams, one per wavefront
-  uint32_t stream;               // bytes of one of them
   const float *b_o, *ln2_g, *ln2_b, *b1, *b2;
-  int F;
-  const float* x0;           // kHead: the rows as the embedding left them, or x0_rows rows over and over
-  int x0_rows;
-  float* x;                  // residual blocks (wide_row.h)
   const float *ln_g, *ln_b;
   float eps;
   float* out;
@@ -36,8 +31,6 @@ struct WideArgs {
   const int32_t* cu;
   const int32_t* pcu;
   int nseq;
-  const int32_t* m_ptr;
-  int m_host;
 };
 
 // LDS of a workgroup: operand rows, a hidden chunk (its place also serves the row sums and the
@@ -91,8 +84,13 @@ constexpr int kHead = 0, kMid = 1, kLast = 2;
 // of 6 layers against layer_tail_kernel (gemm.hip: 32 rows, a split of roles in the feed-forward
 // block): 1,200 rows 224 -> 191 us, 6,400 rows 283 -> 260 us, 11,200 rows 470 -> 344 us,
 // 24,000 rows 857 -> 676 us.
+// m_ptr or m_host: rows; packed: weight streams of `stream` bytes, one per wavefront; x: residual blocks (wide_row.h);
+// O: the attention's rows; x0 (kHead): the rows as the embedding left them, or x0_rows rows over and over.
 template <int D, int NW, int MT, int kKind>
-__global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer_kernel(WideArgs p) {
+__global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer_kernel(const int32_t* m_ptr, const unsigned char* packed,
+                                                                                float* x, const bf16_t* O, const float* x0,
+                                                                                int m_host, uint32_t stream, int F, int x0_rows,
+                                                                                WideArgs p) {
   using L = WideLds<D, NW, MT>;
   // (96 rows of width 384, alone on a CU: a ring of 12 leaves registers for the residual's high parts.
   // 22,400 rows 105 us a layer with a ring of 24 and those in memory, 100 with 12 and 99 like this.)
@@ -105,7 +103,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
   unsigned char* const sH = smem + L::kA;
   float* const s_red = reinterpret_cast<float*>(smem + L::kA);
 
-  const int M = p.m_ptr ? *p.m_ptr : p.m_host;
+  const int M = m_ptr ? *m_ptr : m_host;
   const int total = (M + BM - 1) / BM;
   if ((int)blockIdx.x >= total) return;
   const int m0 = tile_order(blockIdx.x, total) * BM;
@@ -114,7 +112,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
   const int l32 = lane & 31, g = lane >> 5;
   unsigned char* const stg = smem + L::kA + wave * (16 * L::kRow);
   float* const v_b1 = reinterpret_cast<float*>(smem + L::kVec);
-  float* const v_d = v_b1 + max(p.F, 3 * D);   // five vectors of D
+  float* const v_d = v_b1 + max(F, 3 * D);   // five vectors of D
   float* const v_qkv = NW == 8 ? v_d + 5 * D : v_b1;
   // (behind the row sums' place; the hidden chunk comes there later)
   float* const v_bo = reinterpret_cast<float*>(smem + L::kVec) - D;
@@ -134,7 +132,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
 
   // the vectors of the layer
   if (kKind != kHead) {
-    for (int i = tid * 4; i < p.F; i += 4 * kThreads) *reinterpret_cast<float4*>(v_b1 + i) = *reinterpret_cast<const float4*>(p.b1 + i);
+    for (int i = tid * 4; i < F; i += 4 * kThreads) *reinterpret_cast<float4*>(v_b1 + i) = *reinterpret_cast<const float4*>(p.b1 + i);
   }
   if (kKind == kHead || (NW == 8 && kKind == kMid)) {
     for (int i = tid * 4; i < 3 * D; i += 4 * kThreads) *reinterpret_cast<float4*>(v_qkv + i) = *reinterpret_cast<const float4*>(p.b_qkv + i);
@@ -150,7 +148,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
     *reinterpret_cast<float4*>(v_d + 4 * D + tid * 4) = *reinterpret_cast<const float4*>(p.ln_b + tid * 4);
   }
   // weight stream
-  const unsigned char* wp = p.packed + (size_t)wave * p.stream;
+  const unsigned char* wp = packed + (size_t)wave * stream;
   const uint32_t voff = lane * 16;
   bf16x8 wr[kRing];
   // block i of the ring's next round: the base of every fourth one in scalar registers, so
@@ -175,21 +173,21 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
       const int u = u0 + tid;
       const int row = u / (ROWB / 16), pos = u % (ROWB / 16);
       const int c = (pos & ~15) | ((pos ^ row) & 15);
-      const bf16_t* src = p.O + (size_t)min(m0 + row, M - 1) * D + c * 8;
+      const bf16_t* src = O + (size_t)min(m0 + row, M - 1) * D + c * 8;
       const uint32_t dst = (uint32_t)(uintptr_t)sA + (u0 + wave * 64) * 16;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                    : : "s"(dst), "v"(src) : "memory");
     }
   }
   // residual rows: into the accumulators, in two parts where something is added to them
-  unsigned char* const xw = reinterpret_cast<unsigned char*>(p.x) + (size_t)(m0 >> 5) * (D * 128) + wave * (NT * 4096);
+  unsigned char* const xw = reinterpret_cast<unsigned char*>(x) + (size_t)(m0 >> 5) * (D * 128) + wave * (NT * 4096);
   f32x16 acc[NT][MT];
   u32x8 hi[NT][MT];
   int row0[MT];
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     row0[i] = min(m0 + i * 32 + l32, M - 1);
-    if (kKind == kHead && p.x0_rows > 0) row0[i] %= p.x0_rows;
+    if (kKind == kHead && x0_rows > 0) row0[i] %= x0_rows;
   }
 #pragma unroll
   for (int j = 0; j < NT; ++j)
@@ -199,7 +197,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
       for (int i = 0; i < MT; ++i) {
         const float4 v =
             kKind == kHead
-                ? *reinterpret_cast<const float4*>(p.x0 + (size_t)row0[i] * D + c0 + j * 32 + 8 * q + 4 * g)
+                ? *reinterpret_cast<const float4*>(x0 + (size_t)row0[i] * D + c0 + j * 32 + 8 * q + 4 * g)
                 : *reinterpret_cast<const float4*>(xw + i * (D * 128) + j * 4096 + q * 1024 + voff);
         acc[j][i][4 * q] = v.x;
         acc[j][i][4 * q + 1] = v.y;
@@ -320,7 +318,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 && MT > 2 ? 1 : 2) void wide_layer
         for (int q = 0; q < 4; ++q)
           *reinterpret_cast<uint2*>(sH + (i * 32 + l32) * HROWB + (((wave * 4 + q) ^ (l32 & 15)) << 4) + g * 8) = pk[i][q];
     };
-    const int nc = p.F / kFC;
+    const int nc = F / kFC;
     hid_bias(0);
     WIDE_PRODUCT(hid, 1, KS, sA, ROWB, ao);
 #pragma unroll
@@ -598,14 +596,23 @@ __global__ __launch_bounds__(256) void wide_pack_kernel(const bf16_t* __restrict
   if (src) reinterpret_cast<uint4*>(out)[u] = *reinterpret_cast<const uint4*>(src);
 }
 
+int wide_waves(int d) { return d == 256 ? 8 : 4; }
+
+int wide_blocks(int d, int F, bool head) {
+  const int nw = wide_waves(d), nt = d / (32 * nw), ks = d / 16, nc = F / (32 * nw);
+  return (head ? 0 : ks * nt + nc * (ks + 2 * nw * nt)) + 3 * ks * nt;
+}
+
 template <int D, int NW, int MT, int kKind>
-hipError_t launch_wide(const WideArgs& p, int m_capacity, hipStream_t s) {
+hipError_t launch_wide(const WideLayerArgs& a, const WideArgs& p, int F, const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s) {
   auto kern = wide_layer_kernel<D, NW, MT, kKind>;
-  const size_t lds = WideLds<D, NW, MT>::bytes(p.F);
+  const size_t lds = WideLds<D, NW, MT>::bytes(F);
   static DeviceOnce configured;
   hipError_t e = allow_lds(kern, 160 * 1024, &configured);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((m_capacity + 32 * MT - 1) / (32 * MT)), dim3(64 * NW), lds, s, p);
+  hipLaunchKernelGGL(kern, dim3((m_capacity + 32 * MT - 1) / (32 * MT)), dim3(64 * NW), lds, s, m_ptr,
+                     static_cast<const unsigned char*>(a.packed), a.resid, static_cast<const bf16_t*>(a.O), a.x0, m_host,
+                     (uint32_t)wide_blocks(D, F, kKind == kHead) * 1024, F, a.x0_rows, p);
   return hipGetLastError();
 }
 
@@ -616,13 +623,6 @@ hipError_t launch_wide(const WideArgs& p, int m_capacity, hipStream_t s) {
 // kernel addresses rows of x and of q/k/v with 32-bit byte offsets.
 bool wide_layer_supported(int d, int F, bool use_bf16, uint64_t rows) {
   return use_bf16 && ((d == 256 && F % 256 == 0) || (d == 384 && F % 128 == 0)) && F <= 2048 && rows * 6 * d < (1ull << 32);
-}
-
-static int wide_waves(int d) { return d == 256 ? 8 : 4; }
-
-static int wide_blocks(int d, int F, bool head) {
-  const int nw = wide_waves(d), nt = d / (32 * nw), ks = d / 16, nc = F / (32 * nw);
-  return (head ? 0 : ks * nt + nc * (ks + 2 * nw * nt)) + 3 * ks * nt;
 }
 
 uint64_t wide_layer_packed_bytes(int d, int F, bool head) {
@@ -679,18 +679,11 @@ hipError_t launch_wide_layer(const WideLayerArgs& a, int d, int F, int mt, const
   if (!wide_layer_supported(d, F, true, m_capacity)) return hipErrorInvalidValue;
   WideArgs p{};
   const bool head = a.O == nullptr;
-  p.O = static_cast<const bf16_t*>(a.O);
-  p.packed = static_cast<const unsigned char*>(a.packed);
-  p.stream = (uint32_t)wide_blocks(d, F, head) * 1024;
   p.b_o = a.b_o;
   p.ln2_g = a.ln2_g;
   p.ln2_b = a.ln2_b;
   p.b1 = a.b_ff1;
   p.b2 = a.b_ff2;
-  p.F = F;
-  p.x0 = a.x0;
-  p.x0_rows = a.x0_rows;
-  p.x = a.resid;
   p.ln_g = a.ln_g;
   p.ln_b = a.ln_b;
   p.eps = a.eps;
@@ -706,15 +699,13 @@ hipError_t launch_wide_layer(const WideLayerArgs& a, int d, int F, int mt, const
   p.cu = a.cu;
   p.pcu = a.pcu;
   p.nseq = a.B;
-  p.m_ptr = m_ptr;
-  p.m_host = m_host;
   auto kind = [&](auto tiles) {
     constexpr int MT = decltype(tiles)::value;
     if (d == 256)
-      return head ? launch_wide<256, 8, MT, kHead>(p, m_capacity, s)
-                  : a.last ? launch_wide<256, 8, MT, kLast>(p, m_capacity, s) : launch_wide<256, 8, MT, kMid>(p, m_capacity, s);
-    return head ? launch_wide<384, 4, MT, kHead>(p, m_capacity, s)
-                : a.last ? launch_wide<384, 4, MT, kLast>(p, m_capacity, s) : launch_wide<384, 4, MT, kMid>(p, m_capacity, s);
+      return head ? launch_wide<256, 8, MT, kHead>(a, p, F, m_ptr, m_host, m_capacity, s)
+                  : a.last ? launch_wide<256, 8, MT, kLast>(a, p, F, m_ptr, m_host, m_capacity, s) : launch_wide<256, 8, MT, kMid>(a, p, F, m_ptr, m_host, m_capacity, s);
+    return head ? launch_wide<384, 4, MT, kHead>(a, p, F, m_ptr, m_host, m_capacity, s)
+                : a.last ? launch_wide<384, 4, MT, kLast>(a, p, F, m_ptr, m_host, m_capacity, s) : launch_wide<384, 4, MT, kMid>(a, p, F, m_ptr, m_host, m_capacity, s);
   };
   return mt >= 3 ? kind(std::integral_constant<int, 3>{})
                  : mt == 2 ? kind(std::integral_constant<int, 2>{}) : kind(std::integral_constant<int, 1>{});

@@ -10,12 +10,12 @@ namespace {
 
 constexpr int kSmallMaxF = 1024;
 
+// The arguments behind those that the kernel takes one by one: these are in scalar registers when a workgroup
+// starts (build.py), a structure is a trip to memory away.
 struct SmallArgs {
-  const bf16_t *O, *w_o, *w1, *w2, *w_qkv;   // rows of the attention; matrices [N, K]
+  const bf16_t* w_qkv;
   const float *b_o, *ln2_g, *ln2_b, *b1, *b2, *ln_g, *ln_b, *b_qkv;
-  int F;
   float eps;
-  float* x;                 // residual rows [M, D]
   float *out, *out2;
   int split_row;
   float q_scale;
@@ -24,8 +24,6 @@ struct SmallArgs {
   int32_t* vt_pos;
   const int32_t *cu, *pcu;
   int nseq;
-  const int32_t* m_ptr;
-  int m_host;
 };
 
 // What a launch does: the first layer's LayerNorm and projection only, a whole layer, or the
@@ -102,11 +100,14 @@ __device__ __forceinline__ void small_stats(const f32x16& x, float* s_red, int l
 // 216 / 142, width 128, F = 128 193 / 121, F = 1024 238 / 199; 65,536 rows: 657 / 462, 944 / 751, 961 / 769, 1,332 /
 // 1,339 (with one workgroup a CU 1,503); width 128, F = 512 1,123 / 1,017, F = 768 1,229 / 1,178.
 // A row's result does not depend on the others, so no other form has to match this one's bits.
+// m_ptr or m_host: rows; O: rows of the attention; x_rows: residual rows [M, D]; matrices [N, K].
 template <int D, int kKind>
-__global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
+__global__ __launch_bounds__(256, 2) void small_layer_kernel(const int32_t* m_ptr, const bf16_t* O, float* x_rows,
+                                                              const bf16_t* w_o, const bf16_t* w1, const bf16_t* w2, int m_host,
+                                                              int F, SmallArgs p) {
   constexpr int NP = D / 32, KS = D / 16, TPR = 8 / KS, ROWB = D * 2;   // TPR: column tiles a ring round
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  const int F = p.F, HROWB = F * 2;
+  const int HROWB = F * 2;
   unsigned char* const sA = smem;
   unsigned char* const sH = smem + 32 * ROWB;
   float* const s_red = reinterpret_cast<float*>(sH + 32 * HROWB);
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
   float* const s_vec = s_red + 32 * 8 + (small_shares(D) ? 4 * D : 0);   // [ln_g][ln_b][b_qkv: 3 D]
   float* const v_mid = small_shares(D) ? s_vec - 4 * D : s_vec + 5 * D;  // [b_o][ln2_g][ln2_b][b2][b1: F]
 
-  const int M = p.m_ptr ? *p.m_ptr : p.m_host;
+  const int M = m_ptr ? *m_ptr : m_host;
   const int m0 = blockIdx.x * 32;
   if (m0 >= M) return;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
@@ -129,14 +130,14 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
 #pragma unroll
     for (int i = 0; i < (INST + 3) / 4; ++i) {
       const int u = wave + 4 * i, row = u * RPI + lane / (ROWB / 16), c = (lane % (ROWB / 16)) ^ small_key(ROWB, row);
-      const bf16_t* src = p.O + (size_t)min(m0 + row, M - 1) * D + c * 8;
+      const bf16_t* src = O + (size_t)min(m0 + row, M - 1) * D + c * 8;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                    : : "s"((uint32_t)(uintptr_t)sA + u * 1024), "v"(src) : "memory");
     }
   }
   f32x16 x;
   u32x8 hi;
-  float* const xrow = p.x + (size_t)m * D + xw * 32 + 4 * g;
+  float* const xrow = x_rows + (size_t)m * D + xw * 32 + 4 * g;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const float4 v = *reinterpret_cast<const float4*>(xrow + 8 * q);
@@ -165,11 +166,11 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
   bf16x8 ro[KS], r1[8], r2[8], rq[8];
   if (kKind != kHead) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) ro[ks] = weights(p.w_o, D, xw * 32, ks);
+    for (int ks = 0; ks < KS; ++ks) ro[ks] = weights(w_o, D, xw * 32, ks);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r1[i] = weights(p.w1, D, min(wave + 4 * (i / KS), n_ff1 - 1) * 32, i % KS);
+    for (int i = 0; i < 8; ++i) r1[i] = weights(w1, D, min(wave + 4 * (i / KS), n_ff1 - 1) * 32, i % KS);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r2[i] = weights(p.w2, F, xw * 32, i);
+    for (int i = 0; i < 8; ++i) r2[i] = weights(w2, F, xw * 32, i);
   }
   if (kKind != kLast) {
 #pragma unroll
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
     for (int ks = 0; ks < KS; ++ks) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ro[ks], operand(sA, ROWB, ks), x, 0, 0, 0);
     join(v_mid);
     norm_to_lds(v_mid + D, v_mid + 2 * D);
-    contract(p.w1, n_ff1, r1, v_mid + 4 * D, [&](int tile, const f32x16& r) {
+    contract(w1, n_ff1, r1, v_mid + 4 * D, [&](int tile, const f32x16& r) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         *reinterpret_cast<uint2*>(sH + l32 * HROWB + (((tile * 4 + q) ^ small_key(HROWB, l32)) << 4) + g * 8) =
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
         for (int i = 0; i < 8; ++i) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(r2[i], a[i], x, 0, 0, 0);
         if (k0 + 8 < F / 16) {
 #pragma unroll
-          for (int i = 0; i < 8; ++i) r2[i] = weights(p.w2, F, xw * 32, k0 + 8 + i);
+          for (int i = 0; i < 8; ++i) r2[i] = weights(w2, F, xw * 32, k0 + 8 + i);
         }
       }
     }
@@ -339,13 +340,16 @@ __global__ __launch_bounds__(256, 2) void small_layer_kernel(SmallArgs p) {
 }
 
 template <int D, int kKind>
-hipError_t launch_small(const SmallArgs& p, int m_capacity, hipStream_t s) {
-  const size_t lds = small_lds<D>(p.F);
+hipError_t launch_small(const SmallLayerArgs& a, const SmallArgs& p, int F, const int32_t* m_ptr, int m_host, int m_capacity,
+                        hipStream_t s) {
+  const size_t lds = small_lds<D>(F);
+  auto w = [](const void* q) { return static_cast<const bf16_t*>(q); };
   if (lds > 64 * 1024) {
     static DeviceOnce configured;
     if (hipError_t e = allow_lds(small_layer_kernel<D, kKind>, small_lds<D>(kSmallMaxF), &configured); e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((small_layer_kernel<D, kKind>), dim3((m_capacity + 31) / 32), dim3(256), lds, s, p);
+  hipLaunchKernelGGL((small_layer_kernel<D, kKind>), dim3((m_capacity + 31) / 32), dim3(256), lds, s, m_ptr, w(a.O),
+                     a.x, w(a.w_o), w(a.w_ff1), w(a.w_ff2), m_host, F, p);
   return hipGetLastError();
 }
 
@@ -360,12 +364,7 @@ hipError_t launch_small_layer(const SmallLayerArgs& a, int d, int F, const int32
                               hipStream_t s) {
   if (!small_layer_supported(d, F, true)) return hipErrorInvalidValue;
   SmallArgs p{};
-  auto w = [](const void* q) { return static_cast<const bf16_t*>(q); };
-  p.O = w(a.O);
-  p.w_o = w(a.w_o);
-  p.w1 = w(a.w_ff1);
-  p.w2 = w(a.w_ff2);
-  p.w_qkv = w(a.w_qkv);
+  p.w_qkv = static_cast<const bf16_t*>(a.w_qkv);
   p.b_o = a.b_o;
   p.ln2_g = a.ln2_g;
   p.ln2_b = a.ln2_b;
@@ -374,9 +373,7 @@ hipError_t launch_small_layer(const SmallLayerArgs& a, int d, int F, const int32
   p.ln_g = a.ln_g;
   p.ln_b = a.ln_b;
   p.b_qkv = a.b_qkv;
-  p.F = F;
   p.eps = a.eps;
-  p.x = a.x;
   p.out = a.out;
   p.out2 = a.out2;
   p.split_row = a.split_row;
@@ -388,14 +385,12 @@ hipError_t launch_small_layer(const SmallLayerArgs& a, int d, int F, const int32
   p.cu = a.cu;
   p.pcu = a.pcu;
   p.nseq = a.nseq;
-  p.m_ptr = m_ptr;
-  p.m_host = m_host;
   const int kind = a.O == nullptr ? kHead : a.w_qkv == nullptr ? kLast : kMid;
   if (d == 64)
-    return kind == kHead ? launch_small<64, kHead>(p, m_capacity, s)
-                         : kind == kMid ? launch_small<64, kMid>(p, m_capacity, s) : launch_small<64, kLast>(p, m_capacity, s);
-  return kind == kHead ? launch_small<128, kHead>(p, m_capacity, s)
-                       : kind == kMid ? launch_small<128, kMid>(p, m_capacity, s) : launch_small<128, kLast>(p, m_capacity, s);
+    return kind == kHead ? launch_small<64, kHead>(a, p, F, m_ptr, m_host, m_capacity, s)
+                         : kind == kMid ? launch_small<64, kMid>(a, p, F, m_ptr, m_host, m_capacity, s) : launch_small<64, kLast>(a, p, F, m_ptr, m_host, m_capacity, s);
+  return kind == kHead ? launch_small<128, kHead>(a, p, F, m_ptr, m_host, m_capacity, s)
+                       : kind == kMid ? launch_small<128, kMid>(a, p, F, m_ptr, m_host, m_capacity, s) : launch_small<128, kLast>(a, p, F, m_ptr, m_host, m_capacity, s);
 }
 
 }  // namespace cfdetr
