@@ -36,18 +36,21 @@ struct XcdTiles {
 };
 
 constexpr int kFewRing = 24;       // weight blocks in flight per wavefront; K is a multiple of 16 kFewRing
-constexpr int few_rows_lds(int mt) { return 4 * mt * 8 * 1024; }
+constexpr int kDeepRing = 48;      // the same of a workgroup of two wavefronts
+constexpr int few_rows_lds(int mt, int waves = 4) { return (waves == 2 ? 8 : 4) * mt * 8 * 1024; }
 
 // acc[i] += rows m0 + 32 i .. of `rows` times the wavefront's 32 columns of weights (K / 16
 // blocks from wp).  `rows`: bf16 rows [M, K], or operand blocks (kBlocks): tiles of 32 rows, one
 // block of 1 KB per k-step.  They come through the LDS (few_rows_lds bytes) eight k-steps at a
-// time, in four places, three stages ahead.  begin() runs when all first loads have been
+// time, in four places, three stages ahead (two wavefronts, which have 48 blocks in flight: in eight, six ahead).  begin() runs when all first loads have been
 // issued and sets acc.  Ends in front of a barrier that the caller has to pass before the next
 // call.
-template <int MT, bool kBlocks, typename Begin>
+template <int MT, bool kBlocks, int NW = 4, typename Begin>
 __device__ __forceinline__ void few_rows_product(const bf16_t* rows, int K, int M, int m0, const unsigned char* wp,
                                                  unsigned char* smem, f32x16 (&acc)[MT], Begin begin) {
-  constexpr int kRing = kFewRing, kStage = MT * 8 * 1024, kLoads = 2 * MT;
+  constexpr int kRing = NW == 2 ? kDeepRing : kFewRing, kStage = MT * 8 * 1024, kLoads = 8 * MT / NW;
+  constexpr int kStages = kRing / 8, kPlaces = NW == 2 ? 8 : 4;   // of a ring round, and in the LDS
+  static_assert(kStages < kPlaces, "a stage's place is free before it is asked for");
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int NK = K >> 4, NS = NK >> 3;
@@ -72,12 +75,12 @@ __device__ __forceinline__ void few_rows_product(const bf16_t* rows, int K, int 
   auto stage = [&](int s) {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
-      const uint32_t dst = (uint32_t)(uintptr_t)smem + (s & 3) * kStage + (wave * kLoads + i) * 1024;
+      const uint32_t dst = (uint32_t)(uintptr_t)smem + (s & (kPlaces - 1)) * kStage + (wave * kLoads + i) * 1024;
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
                    : : "s"(dst), "v"(src[i] + (size_t)s * (kBlocks ? 8192 : 256)) : "memory");
     }
   };
-  for (int s = 0; s < 3; ++s) stage(s);
+  for (int s = 0; s < kStages; ++s) stage(s);
   __builtin_amdgcn_sched_barrier(0);
   // weight block i of a round, the base of every fourth one in scalar registers: no vector arithmetic
   typedef const __attribute__((address_space(1))) unsigned char* gptr;
@@ -98,7 +101,7 @@ __device__ __forceinline__ void few_rows_product(const bf16_t* rows, int K, int 
     constexpr bool kLastRound = decltype(last_tag)::value;   // nothing is asked for any more
     wp += kRing * 1024;
 #pragma unroll
-    for (int h = 0; h < 3; ++h) {
+    for (int h = 0; h < kStages; ++h) {
       const int s = s0 + h;
       // stage s has arrived: its loads are older than the ring's, and loads return in order;
       // so has everybody's behind the barrier, where the place of stage s - 1 is free
@@ -106,12 +109,12 @@ __device__ __forceinline__ void few_rows_product(const bf16_t* rows, int K, int 
       __builtin_amdgcn_s_barrier();
       asm volatile("" : : : "memory");
       if (!kLastRound) {
-        if (s + 3 < NS) stage(s + 3);
+        if (s + kStages < NS) stage(s + kStages);
       }
       // operands are asked for kAhead k-steps ahead: one by one in front of their MFMAs, as the
       // compiler has them otherwise, each is a wait for the LDS (900 clocks a stage against 400)
       constexpr int kAhead = MT == 1 ? 6 : 2;
-      const unsigned char* ap = smem + (s & 3) * kStage;
+      const unsigned char* ap = smem + (s & (kPlaces - 1)) * kStage;
       bf16x8 a[kAhead + 1][MT];
       auto operands = [&](int k) {
 #pragma unroll
@@ -133,7 +136,7 @@ __device__ __forceinline__ void few_rows_product(const bf16_t* rows, int K, int 
   };
   int s0 = 0;
 #pragma nounroll
-  for (; s0 + 3 < NS; s0 += 3) round(s0, std::false_type{});
+  for (; s0 + kStages < NS; s0 += kStages) round(s0, std::false_type{});
   round(s0, std::true_type{});
 }
 
@@ -210,6 +213,21 @@ inline dim3 few_rows_grid(int rows, int m_capacity, int parts, int K, int mt, in
   const int bm = 32 * mt;
   return few_rows_grid(rows, m_capacity, parts, [=](int m) { return (m + bm - 1) / bm; }, 2.0 * bm * K, 256.0 * K,
                        2.0 * K * (128 + bm), cus, row_bits);
+}
+
+// Tiles of slim_residual_kernel for m rows of N columns: 32 mt rows by 32 `waves` columns. 64 columns as long as no CU
+// gets two workgroups: a workgroup's operands are half as much to bring into its CU, and two wavefronts have the registers
+// for 48 blocks on the way each (with 24 that would be lost again). In us, 128 / 64 columns: K = 1536, 920 rows 7.3 / 6.1 (a
+// pass of 12 layers 457 / 442), 1,200 rows 7.7 / 6.4 (a decoder of 6 layers 438.7 / 431.0). Else 64 rows where 32 would give CUs a
+// second workgroup (3,520 rows: 14 -> 9 us).
+struct FewDown {
+  int mt, waves;
+};
+inline FewDown few_rows_down(int m, int N, int K, int cus) {
+  const int per_xcd = cus < 8 ? 1 : cus / 8;
+  const double row = 64.0 * K, part = 128.0 * K;   // bytes of 32 rows and of 64 columns
+  if (K % (16 * kDeepRing) == 0 && few_rows_cut((m + 31) / 32, N / 64, row, part, row + part, cus).most <= per_xcd) return {1, 2};
+  return {few_rows_cut(m, N, K, 1, cus).most > per_xcd ? 2 : 1, 4};
 }
 
 // Row tiles of 32 that a workgroup of gemm_bf16_few_kernel takes for m rows of an N x K contraction (`gelu`: with that

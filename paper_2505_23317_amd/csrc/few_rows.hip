@@ -284,18 +284,19 @@ __global__ __launch_bounds__(256, 2) void slim_norm_kernel(const int32_t* m_ptr,
   }
 }
 
-// x += hidden blocks . W^T + bias, the second feed-forward matrix: 32 MT rows x 128 columns a workgroup.
-// 920 rows: 7.0 us, the K = 1536 of a wavefront at what a CU's vector-memory path gives.
-template <int D, int MT>
-__global__ __launch_bounds__(256, 2) void slim_residual_kernel(const int32_t* m_ptr, const unsigned char* w, const bf16_t* rows, float* x,
+// x += hidden blocks . W^T + bias, the second feed-forward matrix: 32 MT rows x 32 NW columns a workgroup.
+// 920 rows: 6.1 us (four wavefronts 7.3), the operands of a workgroup at what a CU's vector-memory path gives.  Two
+// wavefronts are one a SIMD: their ring of 48 blocks does not fit beside another's.
+template <int D, int MT, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 2 ? 1 : 2) void slim_residual_kernel(const int32_t* m_ptr, const unsigned char* w, const bf16_t* rows, float* x,
                                                                 const float* bias, int m_host, int K, int row_bits) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int M = m_ptr ? *m_ptr : m_host;
-  const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), D / 128, row_bits);
+  const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), D / (32 * NW), row_bits);
   if (tiles.none) return;
   const int lane = threadIdx.x & 63, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int part = tiles.part, n0 = part * 128 + wave * 32;
+  const int part = tiles.part, n0 = part * (32 * NW) + wave * 32;
   for (int t = tiles.r; t < tiles.r_end; t += tiles.step) {
     const int m0 = t * (32 * MT);
     float4 b[4];
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(256, 2) void slim_residual_kernel(const int32_t* m_
         acc[i][4 * q + 3] = v.w;
       }
     }
-    few_rows_product<MT, true>(rows, K, M, m0, w + (size_t)(part * 4 + wave) * (K >> 4) * 1024, smem, acc, [&]() {
+    few_rows_product<MT, true, NW>(rows, K, M, m0, w + (size_t)(part * NW + wave) * (K >> 4) * 1024, smem, acc, [&]() {
 #pragma unroll
       for (int i = 0; i < MT; ++i) residual_split(acc[i], hi[i]);
     });
@@ -420,13 +421,17 @@ hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int 
   int row_bits = 0;
   const int m = rows > 0 && rows < m_capacity ? rows : m_capacity, cus = cu_count();
   if (step == SlimStep::kDown) {
-    // 64 rows a workgroup where 32 would give CUs a second one (3,520 rows: 14 -> 9 us)
-    const int mt = few_rows_cut(m, d, F, 1, cus).most > cus / 8 ? 2 : 1;
-    const dim3 grid = few_rows_grid(rows, m_capacity, d / 128, F, mt, cus, &row_bits);
-    if (mt == 2) hipLaunchKernelGGL((slim_residual_kernel<384, 2>), grid, dim3(256), few_rows_lds(2), s, m_ptr, w, in, a.x,
-                                    a.bias, m_host, F, row_bits);
-    else hipLaunchKernelGGL((slim_residual_kernel<384, 1>), grid, dim3(256), few_rows_lds(1), s, m_ptr, w, in, a.x,
-                            a.bias, m_host, F, row_bits);
+    const FewDown down = few_rows_down(m, d, F, cus);
+    const int cols = 32 * down.waves, bm = 32 * down.mt;
+    const dim3 grid = few_rows_grid(rows, m_capacity, d / cols, [=](int r) { return (r + bm - 1) / bm; }, 2.0 * bm * F, 2.0 * cols * F,
+                                    2.0 * F * (cols + bm), cus, &row_bits);
+    auto launch = [&](auto kern) {
+      hipLaunchKernelGGL(kern, grid, dim3(64 * down.waves), few_rows_lds(down.mt, down.waves), s, m_ptr, w, in, a.x, a.bias, m_host, F,
+                         row_bits);
+    };
+    if (down.waves == 2) launch(slim_residual_kernel<384, 1, 2>);
+    else if (down.mt == 2) launch(slim_residual_kernel<384, 2, 4>);
+    else launch(slim_residual_kernel<384, 1, 4>);
     return hipGetLastError();
   }
   const bool qkv = step == SlimStep::kFirstQkv || step == SlimStep::kQkv;

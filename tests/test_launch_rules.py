@@ -38,6 +38,13 @@ int main() {
         }
         std::printf("\\n");
       }
+  for (int ffn : {384, 768, 1152, 1536, 1920})
+    for (int m = 1; m <= 4000; m += m % 10 == 0 ? 1 : 9)
+      for (int cus : {256, 64}) {
+        const FewDown down = few_rows_down(m, 384, ffn, cus);
+        std::printf("down %d %d %d %d %d %d\\n", ffn, m, cus, down.mt, down.waves,
+                    few_rows_cut((m + 31) / 32, 6, 64.0 * ffn, 128.0 * ffn, 192.0 * ffn, cus).row_bits);
+      }
 }
 """
 # N, K, GELU behind it
@@ -105,6 +112,22 @@ def test_shares_of_a_row_tile(lines):
         cost = [-(-_fullest(32 * tiles, 128 * -(-parts // n), 32, bits[n - 1]) // 32) * (384 * project + 200 + 128 * n)
                 for n in range(1, parts + 1)]
         assert cost[got - 1] == min(cost), (project, parts, tiles)
+
+
+def test_second_matrix_of_few_rows(lines):
+    """Width 384: 64 columns a workgroup where every one then has a CU of its own and K is whole rings of 48 blocks, else
+    128, and 64 rows where 32 would give a CU two."""
+    seen = set()
+    for k, *v in lines:
+        if k != "down":
+            continue
+        ffn, m, cus, mt, waves, bits = map(int, v)
+        narrow = _fullest(m, 768, 32, bits) <= cus // 8   # (parts of 64 of 384 columns, as many as of 128 of 768)
+        assert (waves == 2) == (narrow and ffn % 768 == 0), v
+        assert waves == 4 or mt == 2 or 3 * -(-m // 32) <= cus, v
+        assert waves == 4 or mt == 1, v
+        seen.add((mt, waves))
+    assert seen == {(1, 2), (1, 4), (2, 4)}
 
 
 # rows at which one of the forms is the fastest by a tenth and more, of those that do not fit into one workgroup a CU
