@@ -37,7 +37,7 @@ struct XcdTiles {
 
 constexpr int kFewRing = 24;       // weight blocks in flight per wavefront; K is a multiple of 16 kFewRing
 constexpr int kDeepRing = 48;      // the same of a workgroup of two wavefronts
-constexpr int few_rows_lds(int mt, int waves = 4) { return (waves == 2 ? 8 : 4) * mt * 8 * 1024; }
+constexpr int few_rows_lds(int mt, int waves) { return (waves == 2 ? 8 : 4) * mt * 8 * 1024; }
 
 // acc[i] += rows m0 + 32 i .. of `rows` times the wavefront's 32 columns of weights (K / 16
 // blocks from wp).  `rows`: bf16 rows [M, K], or operand blocks (kBlocks): tiles of 32 rows, one
@@ -209,12 +209,18 @@ inline dim3 few_rows_grid(int rows, int m_capacity, int parts, Tiles tiles, doub
   const int rows_x = (tiles(more) + rg - 1) / rg, parts_x = (parts + pg - 1) / pg;
   return dim3(8 * parts_x, rows_x);
 }
-inline dim3 few_rows_grid(int rows, int m_capacity, int parts, int K, int mt, int cus, int* row_bits) {
-  const int bm = 32 * mt;
-  return few_rows_grid(rows, m_capacity, parts, [=](int m) { return (m + bm - 1) / bm; }, 2.0 * bm * K, 256.0 * K,
-                       2.0 * K * (128 + bm), cus, row_bits);
+inline dim3 few_rows_grid(int rows, int m_capacity, int N, int K, int mt, int waves, int cus, int* row_bits) {
+  const int bm = 32 * mt, bn = 32 * waves;
+  return few_rows_grid(rows, m_capacity, N / bn, [=](int m) { return (m + bm - 1) / bm; }, 2.0 * bm * K, 2.0 * bn * K,
+                       2.0 * K * (bn + bm), cus, row_bits);
 }
 
+// Do workgroups of 32 rows x 64 columns leave every CU with one at most? (And is K whole rings of theirs.)
+inline bool few_rows_narrow(int m, int N, int K, int cus) {
+  const double row = 64.0 * K, part = 128.0 * K;   // bytes of a tile's rows and columns
+  return K % (16 * kDeepRing) == 0 &&
+         few_rows_cut((m + 31) / 32, N / 64, row, part, row + part, cus).most <= (cus < 8 ? 1 : cus / 8);
+}
 // Tiles of slim_residual_kernel for m rows of N columns: 32 mt rows by 32 `waves` columns. 64 columns as long as no CU
 // gets two workgroups: a workgroup's operands are half as much to bring into its CU, and two wavefronts have the registers
 // for 48 blocks on the way each (with 24 that would be lost again). In us, 128 / 64 columns: K = 1536, 920 rows 7.3 / 6.1 (a
@@ -224,12 +230,12 @@ struct FewDown {
   int mt, waves;
 };
 inline FewDown few_rows_down(int m, int N, int K, int cus) {
-  const int per_xcd = cus < 8 ? 1 : cus / 8;
-  const double row = 64.0 * K, part = 128.0 * K;   // bytes of 32 rows and of 64 columns
-  if (K % (16 * kDeepRing) == 0 && few_rows_cut((m + 31) / 32, N / 64, row, part, row + part, cus).most <= per_xcd) return {1, 2};
-  return {few_rows_cut(m, N, K, 1, cus).most > per_xcd ? 2 : 1, 4};
+  if (few_rows_narrow(m, N, K, cus)) return {1, 2};
+  return {few_rows_cut(m, N, K, 1, cus).most > (cus < 8 ? 1 : cus / 8) ? 2 : 1, 4};
 }
 
+// (gemm_bf16_few_kernel takes 64 columns by the same rule. Width 768, F = 3072, passes with some 200, 350 and 700 rows: 684 / 642
+// us, 727 / 699 and 762 / 745, decoders of 300 and 600 queries 475 / 450 and 494 / 469.)
 // Row tiles of 32 that a workgroup of gemm_bf16_few_kernel takes for m rows of an N x K contraction (`gelu`: with that
 // activation behind it), or 0: the kernels for more rows.  32 rows as long as no CU gets two workgroups, else 64 as long as none
 // does, else 32 with two.  What counts is the fullest XCD: with fewer tiles than CUs it may still have more than

@@ -422,9 +422,7 @@ hipError_t launch_slim(const SlimLayerArgs& a, SlimStep step, int d, int F, int 
   const int m = rows > 0 && rows < m_capacity ? rows : m_capacity, cus = cu_count();
   if (step == SlimStep::kDown) {
     const FewDown down = few_rows_down(m, d, F, cus);
-    const int cols = 32 * down.waves, bm = 32 * down.mt;
-    const dim3 grid = few_rows_grid(rows, m_capacity, d / cols, [=](int r) { return (r + bm - 1) / bm; }, 2.0 * bm * F, 2.0 * cols * F,
-                                    2.0 * F * (cols + bm), cus, &row_bits);
+    const dim3 grid = few_rows_grid(rows, m_capacity, d, F, down.mt, down.waves, cus, &row_bits);
     auto launch = [&](auto kern) {
       hipLaunchKernelGGL(kern, grid, dim3(64 * down.waves), few_rows_lds(down.mt, down.waves), s, m_ptr, w, in, a.x, a.bias, m_host, F,
                          row_bits);

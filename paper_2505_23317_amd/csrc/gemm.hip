@@ -1413,19 +1413,19 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
-// Few rows (few_rows.h): 32 MT rows x 128 columns a workgroup, weights packed.  The sums and
+// Few rows (few_rows.h): 32 MT rows x 32 NW columns a workgroup, weights packed.  The sums and
 // the epilogue are those of the other forms, so the results are the same bits.
-template <int MT, typename EP>
-__global__ __launch_bounds__(256, 2) void gemm_bf16_few_kernel(const int32_t* __restrict__ m_ptr, const unsigned char* W,
+template <int MT, int NW, typename EP>
+__global__ __launch_bounds__(64 * NW, NW == 2 ? 1 : 2) void gemm_bf16_few_kernel(const int32_t* __restrict__ m_ptr, const unsigned char* W,
                                                                const bf16_t* __restrict__ A, int m_host, int N, int K, int row_bits,
                                                                EP ep) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int M = m_ptr ? *m_ptr : m_host;
-  const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), N / 128, row_bits);
+  const XcdTiles tiles((M + 32 * MT - 1) / (32 * MT), N / (32 * NW), row_bits);
   if (tiles.none) return;
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int part = tiles.part, n0 = part * 128 + wave * 32;
+  const int part = tiles.part, n0 = part * (32 * NW) + wave * 32;
   for (int r = tiles.r; r < tiles.r_end; r += tiles.step) {
     const int m0 = r * (32 * MT);
     int32_t info[MT];
@@ -1440,7 +1440,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_few_kernel(const int32_t* __
 #pragma unroll
     for (int q = 0; q < 4; ++q) b[q] = ep.bias4(n0 + 8 * q + 4 * g);
     f32x16 acc[MT];
-    few_rows_product<MT, false>(A, K, M, m0, W + (size_t)(part * 4 + wave) * (K >> 4) * 1024, smem, acc, [&]() {
+    few_rows_product<MT, false, NW>(A, K, M, m0, W + (size_t)(part * NW + wave) * (K >> 4) * 1024, smem, acc, [&]() {
 #pragma unroll
       for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -2923,13 +2923,13 @@ hipError_t launch_persist_tile(const DenseRows& a, const bf16_t* w, int N, int K
   return hipSuccess;
 }
 
-template <int MT, typename EP>
+template <int MT, int NW, typename EP>
 hipError_t launch_few(const bf16_t* a, const void* packed, int N, int K, const EP& ep, const int32_t* m_ptr, int m_host,
                       int m_capacity, hipStream_t s) {
   int row_bits = 0;
-  const dim3 grid = few_rows_grid(m_host, m_capacity, N / 128, K, MT, cu_count(), &row_bits);
-  constexpr auto kern = gemm_bf16_few_kernel<MT, EP>;
-  hipLaunchKernelGGL(kern, grid, dim3(256), few_rows_lds(MT), s, m_ptr, static_cast<const unsigned char*>(packed), a, m_host, N, K,
+  const dim3 grid = few_rows_grid(m_host, m_capacity, N, K, MT, NW, cu_count(), &row_bits);
+  constexpr auto kern = gemm_bf16_few_kernel<MT, NW, EP>;
+  hipLaunchKernelGGL(kern, grid, dim3(64 * NW), few_rows_lds(MT, NW), s, m_ptr, static_cast<const unsigned char*>(packed), a, m_host, N, K,
                      row_bits, ep);
   return hipSuccess;
 }
@@ -3045,8 +3045,9 @@ hipError_t launch_direct(const void* A, const void* W, int N, int K, const EP& e
   const bool narrow_ok = N % 128 == 0 && tiles128 >= cus;
   if (packed && few_rows_supported(N, K)) {
     const int tiles = few_rows_tiles(m, N, K, std::is_same_v<EP, EpiAct<bf16_t, kActGelu>>, (int)cus);
-    if (tiles == 1) return launch_few<1>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
-    if (tiles == 2) return launch_few<2>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+    if (tiles == 1 && few_rows_narrow(m, N, K, (int)cus)) return launch_few<1, 2>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+    if (tiles == 1) return launch_few<1, 4>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+    if (tiles == 2) return launch_few<2, 4>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
   }
   if (packed && N % 256 == 0 && K % 128 == 0)
     return launch_packed(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, m, s);
