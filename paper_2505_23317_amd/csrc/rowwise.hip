@@ -1,4 +1,6 @@
 // Row-wise kernels: position tables, LayerNorm, reuse of cached coarse tokens.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace cfdetr {
@@ -77,9 +79,13 @@ __global__ __launch_bounds__(256) void layernorm_kernel(
 }
 
 // The same with four elements per lane and step (16-byte loads, 8- or 16-byte stores), for
-// widths that are a multiple of four.  (Two rows per wavefront, both requested before either
-// is reduced, measured no faster.)
+// widths that are a multiple of four.  The grid is what the chip holds at most, and a wavefront goes on to further rows,
+// the next one on its way while it works: with a workgroup for every four rows of the capacity (52,224, of which 16,063
+// were there) 15.7 us a launch at width 768, so 12.9 (5.7 TB/s; 4 workgroups a CU the same, rows in runs for the
+// XCDs too).
 constexpr int kLnMaxQuads = kLnMaxPairs / 2;
+// Workgroups of four wavefronts that a CU holds.
+constexpr int kRowGroups = 8;
 
 __device__ __forceinline__ void store_quad(float* p, float a, float b, float c, float d) {
   *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
@@ -94,36 +100,45 @@ __global__ __launch_bounds__(256) void layernorm4_kernel(
     TOut* __restrict__ out, int d, float eps, const int32_t* __restrict__ m_ptr, int m_host,
     int split_row, TOut* __restrict__ out2, RowPositions rp) {
   const int M = m_ptr ? *m_ptr : m_host;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= M) return;
-  const int lane = threadIdx.x & 63;
-  if (rp.out != nullptr && lane == 0) {
-    // position of the row in the feature-major copy of V, for the projections that follow
-    const int f = frame_of_token(rp.cu, rp.nseq, row);
-    rp.out[row] = rp.pcu[f] + (row - rp.cu[f]);
-  }
+  const int lane = threadIdx.x & 63, step = gridDim.x * 4;
   const int quads = d >> 2;
-  const float4* xr = reinterpret_cast<const float4*>(x + (size_t)row * d);
-  float4 v[kLnMaxQuads];
+  float4 v[kLnMaxQuads], next[kLnMaxQuads], gain[kLnMaxQuads], offs[kLnMaxQuads];
+  auto load = [&](float4(&to)[kLnMaxQuads], const float* from) {
 #pragma unroll
-  for (int j = 0; j < kLnMaxQuads; ++j) {
-    const int i = lane + 64 * j;
-    v[j] = (i < quads) ? xr[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  float mean, rstd;
-  ln_quad_stats(v, quads, lane, d, eps, mean, rstd);
-  TOut* orow = (out2 != nullptr && row >= split_row) ? out2 + (size_t)(row - split_row) * d
-                                                     : out + (size_t)row * d;
-  const float4* g4 = reinterpret_cast<const float4*>(g);
-  const float4* b4 = reinterpret_cast<const float4*>(b);
-#pragma unroll
-  for (int j = 0; j < kLnMaxQuads; ++j) {
-    const int i = lane + 64 * j;
-    if (i < quads) {
-      const float4 gg = g4[i], bb = b4[i];
-      const float4 y = ln_quad(v[j], mean, rstd, gg, bb);
-      store_quad(orow + 4 * i, y.x, y.y, y.z, y.w);
+    for (int j = 0; j < kLnMaxQuads; ++j) {
+      const int i = lane + 64 * j;
+      to[j] = (i < quads) ? reinterpret_cast<const float4*>(from)[i] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
+  };
+  load(v, x + (size_t)row * d);
+  load(gain, g);
+  load(offs, b);
+  for (;;) {
+    const int behind = row + step;
+    if (behind < M) load(next, x + (size_t)behind * d);
+    if (rp.out != nullptr && lane == 0) {
+      // position of the row in the feature-major copy of V, for the projections that follow
+      const int f = frame_of_token(rp.cu, rp.nseq, row);
+      rp.out[row] = rp.pcu[f] + (row - rp.cu[f]);
+    }
+    float mean, rstd;
+    ln_quad_stats(v, quads, lane, d, eps, mean, rstd);
+    TOut* orow = (out2 != nullptr && row >= split_row) ? out2 + (size_t)(row - split_row) * d
+                                                       : out + (size_t)row * d;
+#pragma unroll
+    for (int j = 0; j < kLnMaxQuads; ++j) {
+      const int i = lane + 64 * j;
+      if (i < quads) {
+        const float4 y = ln_quad(v[j], mean, rstd, gain[j], offs[j]);
+        store_quad(orow + 4 * i, y.x, y.y, y.z, y.w);
+      }
+    }
+    if (behind >= M) break;
+#pragma unroll
+    for (int j = 0; j < kLnMaxQuads; ++j) v[j] = next[j];
+    row = behind;
   }
 }
 
@@ -231,6 +246,7 @@ hipError_t launch_layernorm(const float* x, const float* g, const float* b, void
   dim3 grid((m_capacity + 3) / 4);
   const RowPositions none{nullptr, nullptr, nullptr, 0};
   if (d % 4 == 0) {
+    grid.x = std::min<int>(grid.x, kRowGroups * cu_count());
     const RowPositions rp = positions ? *positions : none;
     if (out_is_bf16)
       hipLaunchKernelGGL(layernorm4_kernel<bf16_t>, grid, dim3(256), 0, s, x, g, b,
