@@ -64,10 +64,10 @@ __global__ __launch_bounds__(kHitThreads) void select_hit_kernel(
 //                    tile (or -1: no item), then the sequence's offset, length and padded
 //                    offset, so that a workgroup gets all it needs to start in one load.
 // Workgroups are dealt to the 8 XCDs round-robin (workgroup w runs on XCD w % 8), and
-// every XCD has its own L2.  Sequences come longest first, and the items of each, head by
-// head, are cut into eight runs of equal length, one for every XCD (whose workgroups
-// 8*j + x take its run in order): all XCDs get the same work of every length, and an XCD
-// reads the keys and values of an eighth of a sequence's heads and one or two more.  What
+// every XCD has its own L2.  Sequences come longest first, and the items of those of as many
+// tiles, sequence by sequence and head by head, are cut into eight runs of equal length, one for every XCD (whose
+// workgroups 8*j + x take its run in order): all XCDs get the same work of every length, and an XCD
+// reads the keys and values of an eighth of the heads and one or two more.  What
 // does not divide by eight goes to the XCDs in turn, so the queues differ by one entry in
 // all.  Whole (sequence, head) groups dealt to the XCDs read the least, but leave the fullest
 // of them with 1.2 times the average where lengths are mixed: attention over four coarse
@@ -79,6 +79,9 @@ __global__ __launch_bounds__(kHitThreads) void select_hit_kernel(
 // and of 53 entries for 32 CUs the 11 longest have one to themselves.  In us, longest first throughout / so: six cameras
 // (8 heads of 32, 640 to 1,300 tokens, 50 items an XCD) 262 / 254 a pass, one camera 205 / 203, two stages of six 836 /
 // 822; sets of equal or far more items the same.
+// Sequences of as many tiles share a cut, so that an XCD has whole heads of one of them and not an eighth of each: two
+// stages of six cameras (decoders among them) 825 us a pass by sequences, 807 by such classes, six cameras 258 / 256, eight
+// high-resolution frames of equal length 0.15 to 0.3 %.
 // gated: no item at all.  The items are then not written (and not only counted as none): there
 // is no barrier between the two loops over the entries, so where both wrote one, either could
 // be the last, and an item that is left sends a workgroup to a sequence without keys.
@@ -99,56 +102,42 @@ __device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readla
 // The plan proper: the lengths of the nseq sequences are in s_len (shared, published by a
 // barrier); all threads of a workgroup of at least 2 * kMaxBatch threads call it.
 __device__ __forceinline__ void plan_body(const PlanArgs& p, int nseq, const int* s_len, bool gated) {
-  __shared__ int s_order[2 * kMaxBatch];
-  __shared__ int s_turn[2 * kMaxBatch], s_start[2 * kMaxBatch * 8];
+  // items of the sequences of more query tiles, of those of as many, and of the latter in front of this sequence's
+  __shared__ int s_before[2 * kMaxBatch], s_class[2 * kMaxBatch], s_within[2 * kMaxBatch];
   __shared__ int s_count[8];
   __shared__ int s_cu[2 * kMaxBatch + 1], s_pcu[2 * kMaxBatch + 1];
   const int tid = threadIdx.x;
   // (no integer divisions: the kernel's time is latency, the way of its code to the CU included)
   const int heads = p.heads, cap8 = p.cap8, log_q = 31 - __clz(p.block_q);   // block_q: a power of two
   auto tiles = [&](int f) { return (s_len[f] + p.block_q - 1) >> log_q; };
-  // items of the sequence of that rank that XCD x gets: an eighth, and one more for each of the
-  // n % 8 XCDs from `turn` on; `first` is the number of those that the XCDs in front of it get
+  // XCD x's part of n items: an eighth, and one more for each of the n % 8 XCDs from `turn` on; `first` is the number
+  // of those that the XCDs in front of it get.  With `turn` the items in front of these, modulo 8, XCD x has
+  // (items >> 3) + (x < items % 8) of `items` items dealt so far.
   auto run_of = [&](int n, int turn, int x, int& first) {
     const int rest = n & 7, end = turn + rest;
     first = x * (n >> 3) + max(min(end, x) - turn, 0) + max(min(end - 8, x), 0);
     return (n >> 3) + (((x - turn) & 7) < rest ? 1 : 0);
   };
+  auto dealt = [&](int items, int x) { return (items >> 3) + (x < (items & 7) ? 1 : 0); };
   int4* const items4 = reinterpret_cast<int4*>(p.items);
-  if (tid < nseq) {
-    const int len = s_len[tid];
-    int rank = 0;
+  if (tid < max(nseq, 8)) {
+    const int len = tid < nseq ? s_len[tid] : 0, nt = (len + p.block_q - 1) >> log_q;
+    int before = 0, of_class = 0, within = 0, all = 0;
     for (int j = 0; j < nseq; ++j) {
-      const int lj = s_len[j];
-      rank += (lj > len) || (lj == len && j < tid);
+      const int lj = s_len[j], tj = tiles(j), n = heads * tj;
+      all += n;
+      before += tj > nt ? n : 0;
+      of_class += tj == nt ? n : 0;
+      within += tj == nt && (lj > len || (lj == len && j < tid)) ? n : 0;
     }
-    s_order[rank] = tid;
+    if (tid < nseq) {
+      s_before[tid] = before;
+      s_class[tid] = of_class;
+      s_within[tid] = within;
+    }
+    if (tid < 8) s_count[tid] = gated ? 0 : min(dealt(all, tid), cap8);
   }
-  __syncthreads();
   const int lane = tid & (kWave - 1), wave = tid / kWave, waves = blockDim.x / kWave;
-  if (wave == 0) {
-    int turn = 0;
-    for (int i0 = 0; i0 < nseq; i0 += kWave) {
-      const int i = i0 + lane;
-      const int rest = i < nseq ? (heads * tiles(s_order[i])) & 7 : 0;
-      const int end = wave_scan(rest);
-      if (i < nseq) s_turn[i] = (turn + end - rest) & 7;
-      turn += last_lane(end);
-    }
-  }
-  __syncthreads();
-  for (int x = wave; x < 8; x += waves) {   // XCD x: places of its runs, 64 sequences at a time
-    int pos = 0;
-    for (int i0 = 0; i0 < nseq; i0 += kWave) {
-      const int i = i0 + lane;
-      int first;
-      const int n = i < nseq ? run_of(heads * tiles(s_order[i]), s_turn[i], x, first) : 0;
-      const int end = wave_scan(n);
-      if (i < nseq) s_start[i * 8 + x] = pos + end - n;
-      pos += last_lane(end);
-    }
-    if (lane == 0) s_count[x] = gated ? 0 : min(pos, cap8);
-  }
   if (wave == waves - 1) {
     int pos = 0, ppos = 0;
     for (int i0 = 0; i0 < nseq; i0 += kWave) {
@@ -177,20 +166,18 @@ __device__ __forceinline__ void plan_body(const PlanArgs& p, int nseq, const int
     *p.m_all = s_cu[nseq];
     if (p.m_seen != nullptr) *p.m_seen = s_cu[nseq];
   }
-  for (int u = tid; !gated && u < nseq * 8; u += blockDim.x) {   // one thread per run
-    const int f = s_order[u >> 3], x = u & 7, nt = tiles(f), j0 = s_start[u];
+  for (int u = tid; !gated && u < nseq * 64; u += blockDim.x) {   // eight threads for a sequence's part of a run
+    const int f = u >> 6, x = (u >> 3) & 7, nt = tiles(f), before = s_before[f], own = s_within[f];
     int first;
-    const int n = run_of(heads * nt, s_turn[u >> 3], x, first);
-    int h = (int)(first * __builtin_amdgcn_rcpf((float)max(nt, 1)));   // first / nt, or one off
-    h += (h + 1) * nt <= first ? 1 : h * nt > first ? -1 : 0;
-    int q = first - h * nt;
+    const int n = run_of(s_class[f], before & 7, x, first), at = dealt(before, x) - first;   // of the class; its place
+    const int i1 = min(min(first + n, own + heads * nt), cap8 - at);
     const int turned = s_count[x] > p.round ? p.round : 0;   // entries
-    for (int j = j0; j < min(j0 + n, cap8); ++j) {
-      items4[8 * (j < turned ? turned - 1 - j : j) + x] = make_int4((f << 24) | (h << 19) | q, s_cu[f], s_len[f], s_pcu[f]);
-      if (++q == nt) {
-        q = 0;
-        ++h;
-      }
+    const float rcp = __builtin_amdgcn_rcpf((float)max(nt, 1));
+    for (int i = max(first, own) + (u & 7); i < i1; i += 8) {
+      const int item = i - own, j = at + i;
+      int h = (int)((float)item * rcp);   // item / nt, or one off
+      h += (h + 1) * nt <= item ? 1 : h * nt > item ? -1 : 0;
+      items4[8 * (j < turned ? turned - 1 - j : j) + x] = make_int4((f << 24) | (h << 19) | (item - h * nt), s_cu[f], s_len[f], s_pcu[f]);
     }
   }
   for (int i = tid; i < 8 * cap8; i += blockDim.x)

@@ -1,4 +1,4 @@
-"""The attention's work list cuts the items of every sequence into eight runs, one for each XCD, and
+"""The attention's work list cuts the items of the sequences of as many tiles into eight runs, one for each XCD, and
 deals what does not divide by eight in turn: with 1, 3 or 4 heads and one to three items a head all
 remainders occur, with fewer items than XCDs and with more.  64 frames are 128 sequences, two wavefronts
 of them.  Queues of 32 entries and fewer, and of more, whose first 32 are turned round.  An item that were missing or done for another sequence would show in its frame's rows: every
