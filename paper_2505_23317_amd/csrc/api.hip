@@ -508,8 +508,8 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
     return CFDETR_OK;
   }
   // width 768, few rows: a LayerNorm and the contraction behind it are one launch
-  const bool norm_qkv = bf && ctx->slim_qkv && norm_rows_fit(m_hint, 3 * d, d);
-  const bool norm_ff1 = bf && ctx->slim_ff1 && norm_rows_fit(m_hint, F, d);
+  const bool norm_qkv = bf && ctx->slim_qkv && norm_rows_fit(m_hint, m_cap, 3 * d, d);
+  const bool norm_ff1 = bf && ctx->slim_ff1 && norm_rows_fit(m_hint, m_cap, F, d);
   for (int l = 0; l < c.n_layers; ++l) {
     const char* wqkv = static_cast<const char*>(w.w_qkv) + (size_t)l * 3 * d * d * es;
     const char* wo = static_cast<const char*>(w.w_o) + (size_t)l * d * d * es;
@@ -887,8 +887,8 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
   // the LayerNorm after it and the next layer's q/k/v projection.
   const bool fused = ctx->dtail_packed_layer != 0;
   // width 768, few rows: a LayerNorm and the contraction behind it are one launch
-  const bool norm_qkv = ctx->dslim_qkv && norm_rows_fit(Mq, 3 * d, d), norm_q = ctx->dslim_q && norm_rows_fit(Mq, d, d);
-  const bool norm_ff1 = ctx->dslim_ff1 && norm_rows_fit(Mq, F, d);
+  const bool norm_qkv = ctx->dslim_qkv && norm_rows_fit(Mq, Mq, 3 * d, d), norm_q = ctx->dslim_q && norm_rows_fit(Mq, Mq, d, d);
+  const bool norm_ff1 = ctx->dslim_ff1 && norm_rows_fit(Mq, Mq, F, d);
   const size_t dd = (size_t)d * d * 2, df = (size_t)F * d * 2;
   for (int l = 0; l < L; ++l) {
     const bool last = l + 1 == L;

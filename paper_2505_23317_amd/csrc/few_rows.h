@@ -268,8 +268,20 @@ inline int few_rows_tiles(int m, int N, int K, bool gelu, int cus) {
 // round of them is all there may be (with a second one two launches are faster); eight strips are a round of a workgroup's
 // wavefronts and take 5 us with 32 rows, 6.5 with 64, behind 4 and 8.5 us of launch, rows and LayerNorm. In us, the cuts mt /
 // shares for 1,300 rows: q/k/v 1/4 13.8, 1/6 11.9, 2/9 14.4, 2/12 13.9; N = 3072 1/4 16.3, 1/6 14.1, 2/9 17.5, 2/12 14.8;
-// 2,600 rows: q/k/v 1/2 23.7, 1/3 19.9, 2/4 23.0, 2/6 19.6; N = 3072 1/3 24.4, 2/4 25.1, 2/6 22.4. Beyond four rounds it no
-// longer gains: 3,200 rows in two shares 24.9 and 32.0, and two launches 25.3 and 30.7.
+// 2,600 rows: q/k/v 1/2 23.7, 1/3 19.9, 2/4 23.0, 2/6 19.6; N = 3072 1/3 24.4, 2/4 25.1, 2/6 22.4; N = 1152, 1,200 rows 1/4 9.8
+// (nine strips: two rounds), 1/5 8.5. Beyond four rounds it no longer gains: 3,200 rows in two shares 24.9 and 32.0, and two
+// launches 25.3 and 30.7.
+// Most rows: N = 384 and 768 16,384, 1152 to 1920 8,192, 2304 to 3072 5,440, 4608 some 3,200. Two launches / one near them:
+// N = 384, 16,300 rows 28.3 / 21.2; 768, 8,100 rows 21.1 / 18.4, 16,300 rows 33.6 / 28.9; 1152, 8,100 rows 31.9 / 25.0; 1536 31.2 /
+// 29.1; 1920 38.1 / 34.6; 2304, 5,400 rows 31.7 / 28.0; 3072 38.2 / 34.5; 4608, 2,400 rows 29.7 / 26.2, 3,200 rows 32.9 / 32.8.
+// Fewest: as long as workgroups of 32 rows x 128 columns leave every CU with one at most, two launches are faster, whose weights
+// are all on their way before the first row is looked at. Passes with two / one for that contraction, us, one context over
+// and over, and three in turn, which find their weights in memory: q/k/v, 12 layers, up to 384 rows: 64 rows 407 / 421 and 484 /
+// 527, 288 rows 483 / 488 and 566 / 583, 400 rows 543 / 520 and 617 / 612, 480 rows 535 / 511 and 614 / 608; N = 3072, up to 320
+// rows: 288 rows 483 / 488 and 566 / 582, 324 rows 507 / 497 and 583 / 581, 480 rows 535 / 508 and 614 / 599; N = 1536, up to 640
+// rows: 400 rows 495 / 499 and 554 / 569, 720 rows 547 / 534 and 632 / 626; N = 1152, up to 768 rows: 480 rows 496 / 498 and 566 /
+// 579, 918 rows 570 / 551 and 672 / 664; N = 768, six layers of a decoder, up to 1,280 rows: 600 rows 416 / 427 and 459 / 472, 1,200
+// rows 525 / 521 and 600 / 602, 1,500 rows 603 / 589 and 667 / 663.
 constexpr int kNormWidth = 768, kNormRounds = 4;
 struct NormCut {
   int mt = 0;   // 0: no cut
@@ -283,9 +295,10 @@ inline int norm_units(int rows, int mt, int shares, int group_bits) {
 inline NormCut norm_cut(int rows, int N, int cus) {
   const int strips = N / 32, per_xcd = cus < 8 ? 1 : cus / 8;
   NormCut best;
+  if (few_rows_cut(rows, N, kNormWidth, 1, cus).most <= per_xcd) return best;
   double least = 0;
   for (int mt = 1; mt <= 2; ++mt)
-    for (int want = 1; want <= strips / 8; ++want) {
+    for (int want = 1; want <= (strips + 7) / 8; ++want) {
       const int per = (strips + want - 1) / want, shares = (strips + per - 1) / per, rounds = (per + 7) / 8;
       if (rounds > kNormRounds) continue;
       for (int bits = 0; bits <= 3; ++bits) {

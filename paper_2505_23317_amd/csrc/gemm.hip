@@ -1467,11 +1467,12 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 1 : 2) void gemm_bf16_few_kernel
 // A workgroup has 32 MT complete rows, normalised, in LDS, and a share of the columns; its eight wavefronts take
 // strips of 32 columns, each on its own: no two share weights, so those stream through a ring of 24 registers a
 // lane and skip the LDS, and behind the LayerNorm no wavefront waits for another. The rows of a tile are normalised
-// again for each share (1.5 us for 32 of them), which costs less than the launch and the rows' way through memory.
+// again for each share (1.5 us for 32 of them), which costs less than the launch and the rows' way through memory unless
+// the rows are very few (norm_cut).
 // Bounds: a chain - launch 2.5 us, rows 1.5, LayerNorm, then 2.6 us at least for every eight strips (393 KB of weights
 // at a CU's 64 B/clk, or 64 rows' MFMAs), stores. us, LayerNorm and contraction as two launches / this: q/k/v (N = 2304)
-// 350 rows 9.0 / 7.8, 700 rows 11.2 / 9.1, 1,300 rows 16.3 / 11.9, 2,600 rows 24.1 / 19.6, 5,200 rows 32.9 / 30.4; N = 3072
-// with its activation 350 rows 10.4 / 8.0, 700 rows 15.0 / 9.9, 1,300 rows 18.4 / 14.1, 2,600 rows 26.6 / 22.4, 5,200 rows
+// 450 rows 9.7 / 8.5, 700 rows 11.2 / 9.1, 1,300 rows 16.3 / 11.9, 2,600 rows 24.1 / 19.6, 5,200 rows 32.9 / 30.4; N = 3072
+// with its activation 450 rows 9.8 / 8.7, 700 rows 15.0 / 9.9, 1,300 rows 18.4 / 14.1, 2,600 rows 26.6 / 22.4, 5,200 rows
 // 39.3 / 36.2. With more rows than one round of workgroups holds (norm_cut) it gains nothing: 8,200 rows 49.2 / 57.8
 // and 64.0 / 70.1, 16,063 rows 77.8 / 71.3 and 98.3 / 95.4.
 // ---------------------------------------------------------------------------
@@ -2968,10 +2969,13 @@ hipError_t launch_norm_tile(const NormArgs& p, const NormCut& cut, const EP& ep,
   return hipSuccess;
 }
 
+// The rows that norm_rows_fit and the launch go by.
+int norm_rows(int expected, int m_capacity) { return expected > 0 && expected < m_capacity ? expected : m_capacity; }
+
 template <typename EP>
 hipError_t launch_norm(const float* x, const float* ln_g, const float* ln_b, float eps, const void* packed, int N, const EP& ep,
                        const RowPositions* list, const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s) {
-  const int m = m_host > 0 && m_host < m_capacity ? m_host : m_capacity;
+  const int m = norm_rows(m_host, m_capacity);
   const NormCut cut = norm_cut(m, N, cu_count());
   if (cut.mt == 0 || packed == nullptr) return hipErrorInvalidValue;
   NormArgs p{N, eps, RowPositions{}};
@@ -3319,7 +3323,9 @@ hipError_t launch_gemm_qkv(const void* A, const void* W, const float* bias, int 
   return hipGetLastError();
 }
 
-bool norm_rows_fit(int rows, int N, int d) { return d == kNormWidth && rows > 0 && few_rows_supported(N, d) && norm_cut(rows, N, cu_count()).mt != 0; }
+bool norm_rows_fit(int rows, int m_capacity, int N, int d) {
+  return d == kNormWidth && few_rows_supported(N, d) && norm_cut(norm_rows(rows, m_capacity), N, cu_count()).mt != 0;
+}
 
 hipError_t launch_norm_qkv(const float* x, const float* ln_g, const float* ln_b, float eps, const void* packed, const float* bias, int d,
                            float q_scale, void* qk, void* vt, int vt_ld, const RowPositions& positions, bool list,

@@ -370,11 +370,11 @@ hipError_t launch_gemm_qkv(const void* A, const void* W, const float* bias, int 
                            const int32_t* cu_seqlens, const int32_t* pcu, int B,
                            const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s,
                            const int32_t* vt_pos = nullptr, const void* packed = nullptr);
-// LayerNorm of the fp32 rows x and the contraction behind it, for few rows (norm_rows_fit, by the rows expected), in one
-// launch and with the same bits as launch_layernorm and launch_gemm_qkv / launch_gemm (kBias and kBiasGelu).
+// LayerNorm of the fp32 rows x and the contraction behind it, for few rows (norm_rows_fit, by the rows expected, 0:
+// unknown), in one launch and with the same bits as launch_layernorm and launch_gemm_qkv / launch_gemm (kBias and kBiasGelu).
 // `packed`: launch_slim_pack's.  launch_norm_qkv reads the rows' positions in positions.out (null: it finds them
 // itself), or with `list` finds them and writes them there.
-bool norm_rows_fit(int rows, int N, int d);
+bool norm_rows_fit(int rows, int m_capacity, int N, int d);
 hipError_t launch_norm_qkv(const float* x, const float* ln_g, const float* ln_b, float eps, const void* packed, const float* bias, int d,
                            float q_scale, void* qk, void* vt, int vt_ld, const RowPositions& positions, bool list,
                            const int32_t* m_ptr, int m_host, int m_capacity, hipStream_t s);

@@ -10,8 +10,8 @@ DRIVER = """
 #include <cstdio>
 using namespace cfdetr;
 int main() {
-  for (int N : {768, 1536, 2304, 3072, 640})
-    for (int rows = 1; rows <= 6000; rows += rows < 100 ? 1 : 37)
+  for (int N : {384, 768, 1152, 1536, 1920, 2304, 2688, 3072, 4608})
+    for (int rows = 1; rows <= 20000; rows += rows < 100 ? 1 : rows < 8000 ? 37 : 370)
       for (int cus : {256, 64}) {
         const NormCut c = norm_cut(rows, N, cus);
         std::printf("%d %d %d %d %d %d %d %d\\n", N, rows, cus, c.mt, c.mt ? c.shares : 0, c.mt ? c.per_share : 0,
@@ -56,8 +56,26 @@ def test_every_tile_and_strip_once_and_a_workgroup_a_cu(cuts):
 
 
 @pytest.mark.parametrize("N, rows, mt", [(2304, 1300, 1), (3072, 1300, 1), (3072, 2600, 2), (2304, 5200, 2), (3072, 5200, 2),
-                                         (2304, 8200, 0), (3072, 16063, 0)])
+                                         (2304, 8200, 0), (3072, 16063, 0), (384, 4000, 1), (384, 16300, 2), (768, 4000, 1),
+                                         (768, 16300, 2), (1152, 8100, 2), (1920, 8100, 2), (1920, 9600, 0), (4608, 2400, 2)])
 def test_by_the_figures(cuts, N, rows, mt):
     """Heights at the row counts that the comments at norm_cut and its kernel have figures for (the nearest below)."""
     at = max((r for n, r, cus, *_ in cuts if n == N and cus == 256 and r <= rows))
     assert [c[3] for c in cuts if c[:3] == (N, at, 256)] == [mt]
+
+
+# rows up to which a pass is faster with two launches, and from which with one (one context over and over or three in turn)
+@pytest.mark.parametrize("N, two, one", [(768, 900, 1500), (1152, 612, 918), (1536, 612, 720), (2304, 324, 400), (3072, 288, 330),
+                                         (4608, 64, 210)])
+def test_fewest_rows_by_the_figures(cuts, N, two, one):
+    for n, rows, cus, mt, *_ in cuts:
+        if n == N and cus == 256 and (rows <= two or one <= rows <= 2 * one):
+            assert (mt == 0) == (rows <= two), rows
+
+
+def test_as_few_strips_as_wavefronts(cuts):
+    """No share has more rounds of eight strips than its width needs: N = 1152 at 1,000 rows is five shares of eight strips
+    at most and not four of nine, which would be two rounds."""
+    at = {(n, rows): (shares, per) for n, rows, cus, mt, shares, per, *_ in cuts if cus == 256 and mt}
+    near = min((r for n, r in at if n == 1152 and r >= 1000))
+    assert at[1152, near] == (5, 8)
