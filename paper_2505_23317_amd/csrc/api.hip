@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "few_rows.h"
 #include "kernels.h"
 
 using namespace cfdetr;
@@ -292,8 +293,8 @@ constexpr int kSpreadRows = 15;
 // rows 595 / 562 and 556 / 561, 1,000 to 3,000 rows, whose three contexts the cache holds, 0.5 % lost.  32 to 128
 // workgroups do the same.  Not in encoders of width 256 (one camera 207 / 208.5), nor with more rows, whose attention fills
 // the chip (six cameras, 29 rows a CU, 256.5 / 257.9).  At width 768 where a LayerNorm and the contraction behind it are one
-// launch (norm_rows_fit): three small frames 1,136 / 1,022, and 1,096 with the launches apart, which gain nothing by it
-// (1,030 / 1,139, three contexts in turn each time).
+// launch (norm_rows_fit), with a line of its own (norm_reads_ahead): three small frames 1,136 / 1,022, and 1,096 with the
+// launches apart, which gain nothing by it (1,030 / 1,139, three contexts in turn each time).
 constexpr int kAheadRows = 16;
 
 enum class RunKind { kMerged = 0, kFine = 1, kExact = 2 };
@@ -548,7 +549,7 @@ cfdetr_status run_encoder(cfdetr_ctx* ctx, int nseq, const RunShape& shape, int 
                                           Epilogue::kBias, ctx->qkv, nullptr, bf, m_ptr, m_hint, m_cap,
                                           s));
     ReadAhead ahead;
-    if (norm_qkv && shape.block_q == 128) {
+    if (norm_qkv && shape.block_q == 128 && norm_reads_ahead(m_hint > 0 && m_hint < m_cap ? m_hint : m_cap, ctx->cus)) {
       const size_t dd = (size_t)d * d * 2, df = (size_t)F * d * 2;
       ask_for(ahead, 0, ctx->slim_o + l * dd, dd);
       ask_for(ahead, 1, ctx->slim_ff1 + l * df, df);
@@ -893,7 +894,7 @@ cfdetr_status decode_impl(cfdetr_ctx* ctx, const float* memory, const int32_t* c
   for (int l = 0; l < L; ++l) {
     const bool last = l + 1 == L;
     ReadAhead ahead, behind_cross;
-    if (norm_qkv && dblock_q == 128) {
+    if (norm_qkv && dblock_q == 128 && norm_reads_ahead(Mq, ctx->cus)) {
       ask_for(ahead, 0, ctx->dslim_o + l * dd, dd);
       ask_for(ahead, 1, ctx->dslim_q + l * dd, dd);
       ask_for(behind_cross, 0, ctx->dslim_o2 + l * dd, dd);

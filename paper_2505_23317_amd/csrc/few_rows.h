@@ -318,4 +318,13 @@ inline NormCut norm_cut(int rows, int N, int cus) {
   return best;
 }
 
+// Are the weights behind an attention launch asked for during it (read_ahead, attention.hip), at width 768 with q/k/v behind their
+// LayerNorm in one launch? From 2.5 rows a CU on: with fewer the attention is over before they have come. Passes in us,
+// without / with, one context over and over, and three in turn: 12 layers, F = 3072, 400 rows 516 / 536 and 620 / 624, 576 rows
+// 510 / 541 and 618 / 630, 720 rows 592 / 627 and 738 / 717, 1,200 rows 696 / 691 and 852 / 777, 2,000 rows 1,002 / 970 and 1,047 /
+// 1,005, 5,200 rows 1,755 / 1,656 and 1,758 / 1,662; F = 1536, 576 rows 473 / 492 and 553 / 563, 720 rows 533 / 531 and 642 / 611;
+// decoders of 6 layers, 600 rows 387 / 408 and 447 / 455, 900 rows 454 / 473 and 540 / 520, 1,200 rows 476 / 489 and 581 / 547,
+// 4,800 rows 992 / 1,007 and 1,111 / 1,051: a decoder alone on the chip pays 1.5 to 4 % for the 4 to 6 % of several.
+inline bool norm_reads_ahead(int rows, int cus) { return 2 * rows > 5 * cus; }
+
 }  // namespace cfdetr

@@ -17,19 +17,26 @@ int main() {
         std::printf("%d %d %d %d %d %d %d %d\\n", N, rows, cus, c.mt, c.mt ? c.shares : 0, c.mt ? c.per_share : 0,
                     c.mt ? c.group_bits : 0, c.mt ? norm_units(rows, c.mt, c.shares, c.group_bits) : 0);
       }
+  for (int rows = 1; rows <= 6000; ++rows)
+    for (int cus : {256, 64}) std::printf("ahead %d %d %d\\n", rows, cus, norm_reads_ahead(rows, cus));
 }
 """
 
 
 @pytest.fixture(scope="module")
-def cuts(tmp_path_factory):
+def lines(tmp_path_factory):
     at = tmp_path_factory.mktemp("cut")
     (at / "driver.hip").write_text(DRIVER)
     r = subprocess.run([build._hipcc(), "--offload-arch=gfx950", "-std=c++17", "-I", build.CSRC, str(at / "driver.hip"), "-o",
                         str(at / "driver")], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     out = subprocess.run([str(at / "driver")], capture_output=True, text=True, check=True).stdout
-    return [tuple(map(int, line.split())) for line in out.splitlines()]
+    return [line.split() for line in out.splitlines()]
+
+
+@pytest.fixture(scope="module")
+def cuts(lines):
+    return [tuple(map(int, line)) for line in lines if line[0] != "ahead"]
 
 
 def test_every_tile_and_strip_once_and_a_workgroup_a_cu(cuts):
@@ -79,3 +86,10 @@ def test_as_few_strips_as_wavefronts(cuts):
     at = {(n, rows): (shares, per) for n, rows, cus, mt, shares, per, *_ in cuts if cus == 256 and mt}
     near = min((r for n, r in at if n == 1152 and r >= 1000))
     assert at[1152, near] == (5, 8)
+
+
+def test_weights_are_asked_for_ahead_by_the_figures(lines):
+    """Rows at which a pass is slower, and faster, with the weights behind an attention launch asked for during it."""
+    on = {int(rows): got == "1" for _, rows, cus, got in (v for v in lines if v[0] == "ahead") if cus == "256"}
+    assert not any(on[rows] for rows in (400, 576, 600))
+    assert all(on[rows] for rows in (720, 900, 1200, 2000, 4800, 5200))
