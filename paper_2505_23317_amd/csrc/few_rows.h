@@ -3,10 +3,10 @@
 //
 // With few rows a contraction is latency and not throughput: the launch, one trip to memory
 // for the rows and one for the weights.  A wavefront therefore takes 32 rows (or 64) by 32
-// columns and the whole of K, a workgroup 128 columns, so that there are as many workgroups
-// as the shape yields without cutting a sum; the weights, which no two wavefronts of a
+// columns and the whole of K, a workgroup 128 columns, or 64 where every one then has a CU of its own, so that there are
+// as many workgroups as the shape yields without cutting a sum; the weights, which no two wavefronts of a
 // workgroup share, skip the LDS: packed 1 KB per MFMA operand they stream through a ring of
-// 24 registers a lane, all of them asked for before the first row is looked at.
+// 24 registers a lane, 48 in workgroups of two wavefronts, all of them asked for before the first row is looked at.
 #pragma once
 #include <type_traits>
 
@@ -16,8 +16,8 @@ namespace cfdetr {
 
 // Which tiles a workgroup does.  Every XCD has an L2 of its own, and with few rows a good part
 // of what a launch takes is its operands' way into the eight of them, so an XCD gets a
-// rectangle of tiles: the row tiles are cut in 2^row_bits groups (1, 2, 4 or 8), the 128-column parts
-// in 8 / that.  The grid (few_rows_grid) is a workgroup per part of a group, times eight, by the row tiles of
+// rectangle of tiles: the row tiles are cut in 2^row_bits groups (1, 2, 4 or 8), the column parts (128 or 64
+// columns, or a share of them) in 8 / that.  The grid (few_rows_grid) is a workgroup per part of a group, times eight, by the row tiles of
 // a group; a workgroup has part `part` (or none) of row tiles r, r + step, .. below r_end.  Row tiles change
 // slowest, so that the workgroups for rows that turn out not to be there come last: in between the others
 // they cost CUs their turn (768 x 3072: 1,200 rows 19.8 against 13.8 us, 4,800 rows 42.2 against 32.5).
@@ -242,13 +242,13 @@ inline FewDown few_rows_down(int m, int N, int K, int cus) {
 // its share (41 tiles of 6 parts are 33 at best).  In us, 32 rows / 64 rows / packed tiles (gemm_bf16_packed_kernel),
 // N x K = 768 x 3072: 1,200 rows 13.5 / 15.7 / 24.1, 1,300 rows 20.0 / 15.9 / 24.2, 2,200 rows 22.5 / 19.0 / 24.7, 2,600
 // rows 23.6 / 28.9 / 25.1, 2,700 rows 31.0 / 30.4 / 25.4; 768 x 768: 1,200 rows 5.6 / 7.1 / 9.0, 2,200 rows 8.5 / 7.7 /
-// 9.4, 2,600 rows 9.1 / 12.6 / 9.8, 2,700 rows 11.1 / 12.2 / 10.0; 2304 x 768: 300 rows 5.1 / 6.2 / 8.2, 700 rows
-// 7.7 / 6.8 / 8.3, 800 rows 7.8 / 9.4 / 8.7, 900 rows 10.5 / 10.4 / 8.8.
+// 9.4, 2,600 rows 9.1 / 12.6 / 9.8, 2,700 rows 11.1 / 12.2 / 10.0.  q/k/v of width 384 (1152 x 384), this and tiles with the
+// weights through the LDS: 700 rows 4.0 (32) and 5.9, 1,420 rows 5.2 (64) and 6.4, 2,000 rows 7.1 and 6.9.
+// At width 768 what follows a LayerNorm comes here only as long as no CU gets two workgroups of 32 rows; behind that it is one
+// launch with the LayerNorm (norm_cut) or a packed tile.  2304 x 768, 300 rows: 5.1 / 6.2 / 8.2.
 // Then 64 rows with two workgroups a CU
-//  - where the activation is behind it, which a tile of 64 x 256 does with half as many wavefronts: 3072 x 768 (packed weights
-//    past an XCD's 4 MB of L2, too): 700 rows 10.6 / 10.5 / 12.1, 1,000 rows 11.3 / 11.6 / 12.3, 1,300 rows 14.9 /
-//    12.2 / 14.9, 1,400 rows 17.2 / 15.5 / 14.8; 6144 x 768: 530 rows 13.3 / 12.0 / 17.2; 2304 x 384: 1,420
-//    rows 9.9 / 8.2 / 11.6; even at 2304 x 768, and 1536 x 768, 2,000 rows, 11.3 / 11.2 / 10.9;
+//  - where the activation is behind it, which a tile of 64 x 256 does with half as many wavefronts: 2304 x 384 (feed-forward
+//    widths past the layer kernel's), 1,420 rows 9.9 / 8.2 / 11.6;
 //  - where the packed tiles do not fit (N no multiple of 256; the third figure is then for tiles with the weights through the LDS)
 //    over a long K and the CUs are three quarters full: 384 x 3072: 6,400 rows 31.9 / 31.4 / 28.7, 8,500 rows
 //    42.1 / 31.6 / 36.1, 10,700 rows 46.0 / 34.6 / 39.6, 10,900 rows 51.3 / 44.5 / 39.5.

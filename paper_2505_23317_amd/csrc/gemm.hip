@@ -3047,14 +3047,16 @@ hipError_t launch_direct(const void* A, const void* W, int N, int K, const EP& e
   const long rounds192 = (tiles192 + cus - 1) / cus, rounds192n = (tiles192n + 2 * cus - 1) / (2 * cus);
   const long t128 = 100 * rounds128, t192n = 150 * rounds192n;
   const bool narrow_ok = N % 128 == 0 && tiles128 >= cus;
-  if (packed && few_rows_supported(N, K)) {
-    const int tiles = few_rows_tiles(m, N, K, std::is_same_v<EP, EpiAct<bf16_t, kActGelu>>, (int)cus);
-    if (tiles == 1 && few_rows_narrow(m, N, K, (int)cus)) return launch_few<1, 2>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
-    if (tiles == 1) return launch_few<1, 4>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
-    if (tiles == 2) return launch_few<2, 4>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+  if constexpr (!std::is_same_v<EP, EpiKvLayers>) {   // (whose weights are not packed)
+    if (packed && few_rows_supported(N, K)) {
+      const int tiles = few_rows_tiles(m, N, K, std::is_same_v<EP, EpiAct<bf16_t, kActGelu>>, (int)cus);
+      if (tiles == 1 && few_rows_narrow(m, N, K, (int)cus)) return launch_few<1, 2>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+      if (tiles == 1) return launch_few<1, 4>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+      if (tiles == 2) return launch_few<2, 4>(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, s);
+    }
+    if (packed && N % 256 == 0 && K % 128 == 0)
+      return launch_packed(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, m, s);
   }
-  if (packed && N % 256 == 0 && K % 128 == 0)
-    return launch_packed(a.A, packed, N, K, ep, m_ptr, m_host, m_capacity, m, s);
   // A deeper ring (3 or 4 buffers, also with slabs of 32) measured no faster for these tiles: the
   // latency of the loads is not what bounds their main loops.
   if (N % 256 == 0 && m >= 8192) {

@@ -17,6 +17,13 @@ int main() {
         std::printf("%d %d %d %d %d %d %d %d\\n", N, rows, cus, c.mt, c.mt ? c.shares : 0, c.mt ? c.per_share : 0,
                     c.mt ? c.group_bits : 0, c.mt ? norm_units(rows, c.mt, c.shares, c.group_bits) : 0);
       }
+  for (int N = 384; N <= 6144; N += 384)
+    for (int rows = 1; rows <= 20000; rows += rows < 2000 ? 1 : 37)
+      for (int cus : {256, 64, 304})
+        for (int gelu = 0; gelu < 2; ++gelu)
+          if (few_rows_tiles(rows, N, 768, gelu != 0, cus) && norm_cut(rows, N, cus).mt == 0)
+            std::printf("apart %d %d %d %d\\n", N, rows, few_rows_tiles(rows, N, 768, gelu != 0, cus),
+                        few_rows_cut(rows, N, 768, 1, cus).most <= cus / 8);
   for (int rows = 1; rows <= 6000; ++rows)
     for (int cus : {256, 64}) std::printf("ahead %d %d %d\\n", rows, cus, norm_reads_ahead(rows, cus));
 }
@@ -36,7 +43,7 @@ def lines(tmp_path_factory):
 
 @pytest.fixture(scope="module")
 def cuts(lines):
-    return [tuple(map(int, line)) for line in lines if line[0] != "ahead"]
+    return [tuple(map(int, line)) for line in lines if line[0].isdigit()]
 
 
 def test_every_tile_and_strip_once_and_a_workgroup_a_cu(cuts):
@@ -90,6 +97,14 @@ def test_as_few_strips_as_wavefronts(cuts):
 
 def test_weights_are_asked_for_ahead_by_the_figures(lines):
     """Rows at which a pass is slower, and faster, with the weights behind an attention launch asked for during it."""
-    on = {int(rows): got == "1" for _, rows, cus, got in (v for v in lines if v[0] == "ahead") if cus == "256"}
+    on = {int(rows): got == "1" for k, rows, cus, got, *_ in (v for v in lines if v[0] == "ahead") if cus == "256"}
     assert not any(on[rows] for rows in (400, 576, 600))
     assert all(on[rows] for rows in (720, 900, 1200, 2000, 4800, 5200))
+
+
+def test_few_row_kernel_only_with_a_workgroup_a_cu(lines):
+    """What follows a LayerNorm of width 768 in a launch of its own for few rows takes 32 rows a workgroup, one a CU: the
+    figures at few_rows_tiles name no other form for it."""
+    apart = [tuple(map(int, v[1:])) for v in lines if v[0] == "apart"]
+    assert {n for n, *_ in apart} == set(range(384, 6145, 384))
+    assert all(tiles == 1 and alone for _, _, tiles, alone in apart)
