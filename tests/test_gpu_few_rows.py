@@ -25,12 +25,13 @@ def _coarse(cfg, w, images):
     return y
 
 
-# cells of a frame, frames of the batch: 384 leaves the kernels behind 3,840 rows, 768 behind some 1,300 (first feed-forward
-# matrix) to 2,700 rows
+# cells of a frame, frames of the batch: 384 leaves the kernels behind 3,840 rows, or has no layer kernel (hidden widths past
+# 2,048) and leaves them behind some 1,500 (first feed-forward matrix) to 2,700 rows, 768 behind 320 to 2,700 rows
 @pytest.mark.parametrize("d, heads, ffn, cells, frames", [
     (384, 6, 1536, (1, 31), 60), (384, 6, 768, (5, 13), 40), (384, 6, 384, (29, 31), 3),
     (768, 12, 3072, (3, 11), 60), (768, 12, 1536, (5, 13), 64), (768, 12, 3072, (29, 31), 8),
-    (384, 6, 768, (5, 13), 64), (384, 6, 1536, (29, 31), 5), (768, 12, 3072, (5, 13), 11), (768, 12, 3072, (5, 13), 40)])
+    (384, 6, 768, (5, 13), 64), (384, 6, 1536, (29, 31), 5), (768, 12, 3072, (5, 13), 11), (768, 12, 3072, (5, 13), 40),
+    (384, 6, 2304, (3, 11), 64), (384, 6, 2304, (5, 13), 64), (384, 6, 2688, (29, 31), 4), (384, 6, 2688, (19, 37), 8)])
 def test_encoder_alone_and_in_a_batch(d, heads, ffn, cells, frames):
     import torch
 
@@ -51,7 +52,8 @@ def test_encoder_alone_and_in_a_batch(d, heads, ffn, cells, frames):
 
 # (the last: 64 frames take the attention's items of 256 queries, one frame those of 128)
 @pytest.mark.parametrize("d, heads, ffn, queries",
-                         [(384, 6, 1536, 1), (384, 6, 384, 65), (768, 12, 1536, 97), (768, 12, 1536, 155)])
+                         [(384, 6, 1536, 1), (384, 6, 384, 65), (768, 12, 1536, 97), (768, 12, 1536, 155), (384, 6, 2304, 97),
+                          (384, 6, 2688, 703)])
 def test_decoder_alone_and_in_a_batch(d, heads, ffn, queries):
     import torch
     from paper_2505_23317_amd import cfdetr as K

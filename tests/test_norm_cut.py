@@ -3,6 +3,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_norm_rows as G
 from paper_2505_23317_amd import build
 
 DRIVER = """
@@ -17,6 +18,11 @@ int main() {
         std::printf("%d %d %d %d %d %d %d %d\\n", N, rows, cus, c.mt, c.mt ? c.shares : 0, c.mt ? c.per_share : 0,
                     c.mt ? c.group_bits : 0, c.mt ? norm_units(rows, c.mt, c.shares, c.group_bits) : 0);
       }
+  for (int N : {HIDDEN, 2304})
+    for (int frames : {FRAMES, MOST}) {
+      const NormCut c = norm_cut(CELLS * frames, N, 256);
+      std::printf("gpu %d %d %d %d %d\\n", N, frames, c.mt, c.mt ? c.shares : 0, c.mt ? c.per_share : 0);
+    }
   for (int N = 384; N <= 6144; N += 384)
     for (int rows = 1; rows <= 20000; rows += rows < 2000 ? 1 : 37)
       for (int cus : {256, 64, 304})
@@ -33,7 +39,11 @@ int main() {
 @pytest.fixture(scope="module")
 def lines(tmp_path_factory):
     at = tmp_path_factory.mktemp("cut")
-    (at / "driver.hip").write_text(DRIVER)
+    sizes = {"HIDDEN": G.HIDDEN, "FRAMES": G.FRAMES, "MOST": (G.MOST,), "CELLS": (G.CELLS[0] * G.CELLS[1],)}
+    text = DRIVER
+    for name, values in sizes.items():
+        text = text.replace(name, ", ".join(map(str, values)))
+    (at / "driver.hip").write_text(text)
     r = subprocess.run([build._hipcc(), "--offload-arch=gfx950", "-std=c++17", "-I", build.CSRC, str(at / "driver.hip"), "-o",
                         str(at / "driver")], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
@@ -108,3 +118,17 @@ def test_few_row_kernel_only_with_a_workgroup_a_cu(lines):
     apart = [tuple(map(int, v[1:])) for v in lines if v[0] == "apart"]
     assert {n for n, *_ in apart} == set(range(384, 6145, 384))
     assert all(tiles == 1 and alone for _, _, tiles, alone in apart)
+
+
+def test_what_the_gpu_test_covers(lines):
+    """The batches of test_gpu_norm_rows.py: every one has a launch of the kind under test (the largest at the
+    narrower hidden widths), at both heights and in two to twelve shares, even ones and uneven ones; the batch that they
+    are compared with has none."""
+    cut = {(int(n), int(f)): tuple(map(int, rest)) for k, n, f, *rest in (v for v in lines if v[0] == "gpu")}
+    for ffn in G.HIDDEN:
+        assert cut[ffn, G.MOST][0] == cut[2304, G.MOST][0] == 0
+        assert all(cut[ffn, f][0] or cut[2304, f][0] for f in G.FRAMES if f <= 40 or ffn < 2304)
+        assert {cut[ffn, f][0] for f in G.FRAMES} >= {1, 2}
+    shares = {c[1] for c in cut.values() if c[0]}
+    assert min(shares) == 2 and max(shares) == 12
+    assert any(shares * per != ffn // 32 for ffn in G.HIDDEN[1:] for mt, shares, per in (cut[ffn, f] for f in G.FRAMES) if mt)
