@@ -89,8 +89,8 @@ hipError_t launch_pad_tokens(const int32_t* tok_desc, const int32_t* cu_seqlens,
 // entries of four words (so items holds 32*cap8 words): the attention work item of
 // workgroup w (sequence<<24 | head<<19 | query tile, or -1) followed by the offset,
 // length and padded offset of its sequence, arranged so that every XCD gets an eighth of
-// the items of each sequence, longest sequences first but for the first `round` entries of a longer queue, which
-// are turned round.
+// the items of all sequences of as many query tiles (whole heads of some of these sequences, not an eighth of each),
+// longest sequences first but for the first `round` entries of a longer queue, which are turned round.
 // Also sets queue_heads[0..n_heads_q), the fetch counters of the attention launches
 // that follow (eight per launch), to queue_start = (attention grid) / 8: the entries
 // before that are handed out by workgroup index; or to -1 for a queue with no entries

@@ -79,12 +79,16 @@ __global__ __launch_bounds__(256) void layernorm_kernel(
 }
 
 // The same with four elements per lane and step (16-byte loads, 8- or 16-byte stores), for
-// widths that are a multiple of four.  The grid is what the chip holds at most, and a wavefront goes on to further rows,
+// widths that are a multiple of four.  The grid is kRowGroups workgroups a CU at most, and a wavefront goes on to further rows,
 // the next one on its way while it works: with a workgroup for every four rows of the capacity (52,224, of which 16,063
-// were there) 15.7 us a launch at width 768, so 12.9 (5.7 TB/s; 4 workgroups a CU the same, rows in runs for the
-// XCDs too).
+// were there) 15.7 us a launch at width 768, so 12.9 (5.7 TB/s; rows in runs for the XCDs the same).
 constexpr int kLnMaxQuads = kLnMaxPairs / 2;
-// Workgroups of four wavefronts that a CU holds.
+// Workgroups of four wavefronts a CU.  It holds five at a time (96 registers); the others start as those end.  us a launch
+// with four / five / six / eight, six inputs in turn: width 768, 8,192 rows 7.9 / 7.8 / 8.0 / 7.3, 10,000 rows 8.9 / 8.7 / 8.7 / 8.9,
+// 16,063 rows 13.8 / 13.7 / 14.0 / 14.0, 20,000 rows 16.7 / 16.8 / 17.8 / 16.8; width 1024, 6,500 rows 8.1 / 7.8 / 7.4 / 7.4, 16,063 rows
+// 17.5 / 17.5 / 17.8 / 17.6; width 512, 8,192 rows 6.5 / 6.3 / 6.1 / 6.0, 16,063 rows 9.8 / 9.6 / 9.4 / 9.9; width 192, 8,192 rows 4.5 / 4.2 /
+// 4.4 / 4.4, 20,000 rows 8.4 / 8.2 / 8.7 / 8.0: no number is the best throughout, and with eight a wavefront has one row up to
+// 8,192 of them.
 constexpr int kRowGroups = 8;
 
 __device__ __forceinline__ void store_quad(float* p, float a, float b, float c, float d) {

@@ -1,5 +1,5 @@
-"""The LayerNorm launches of widths without a layer kernel hold 8,192 rows at once on 256 CUs, and a wavefront goes on to
-further ones: a frame's rows have the same bits alone (one row a wavefront at most) and among 8,150 to 24,650 rows, at the
+"""The LayerNorm launches of widths without a layer kernel are wavefronts for 8,192 rows on 256 CUs, and a wavefront goes on
+to further ones: a frame's rows have the same bits alone (one row a wavefront at most) and among 8,150 to 24,650 rows, at the
 first and the last row of one, two and three turns."""
 import numpy as np
 import pytest
