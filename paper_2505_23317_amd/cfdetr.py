@@ -416,12 +416,14 @@ class Encoder:
     @staticmethod
     def _stream() -> int:
         """Address of the current device's current stream.  torch.cuda.current_stream() makes a Python object of it,
-        2.7 us a call, a third of what the smallest call (a selection) took; asked for as a number it is 0.2 us.  It also
-        initialises the GPU and refuses to in a child that was forked behind that, so it stays the way of both."""
+        2.7 us a call, a third of what the smallest call (a selection) took; asked for as a number it is 0.25 us.  It also
+        refuses to in a child that was forked from a process that uses the GPU, so such a child goes that way still (the
+        tensors of a call have initialised the GPU otherwise)."""
         import torch
-        if not torch.cuda.is_initialized():   # (nor is it, to torch, in such a child)
+        c = torch._C
+        if c._cuda_isInBadFork():
             return torch.cuda.current_stream().cuda_stream
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
     def alloc_outputs(self, B: int):
         import torch
